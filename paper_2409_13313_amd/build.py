@@ -4,11 +4,15 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libozimmu.so")
 SOURCES = ["ozimmu_api.hip", "ozimmu_split.hip", "ozimmu_gemm.hip"]
+# ozimmu_resident.hip holds kernels specialised for a slice count: one compilation per count, all of them linked into
+# the object of the chunk GEMM (whoever links that object gets every way to run the schedule)
+RESIDENT_KS = range(3, 17)
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
@@ -16,22 +20,27 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=o
 
 def build(verbose: bool = False) -> str:
     """Compile every source and link the shared library; always recompiles."""
-    objs = []
-    procs = []
-    for src in SOURCES:
-        obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-        cmd = ["hipcc", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    objs = [os.path.join(CSRC, src.replace(".hip", ".o")) for src in SOURCES]
+    core = os.path.join(CSRC, "ozimmu_gemm_core.o")
+    resident = [os.path.join(CSRC, f"ozimmu_resident_k{k}.o") for k in RESIDENT_KS]
+    jobs = [(src, [], core if obj.endswith("ozimmu_gemm.o") else obj) for src, obj in zip(SOURCES, objs)]
+    jobs += [("ozimmu_resident.hip", [f"-DOZ_RES_K={k}"], obj) for k, obj in zip(RESIDENT_KS, resident)]
+
+    def compile_one(job):
+        src, defs, obj = job
+        cmd = ["hipcc", *FLAGS, *defs, "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-        objs.append(obj)
-    for cmd, pr in procs:
-        out, _ = pr.communicate()
-        out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
+        pr = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        out = "\n".join(l for l in pr.stdout.splitlines() if "packed-fp32-ops" not in l)
         if pr.returncode != 0:
             raise RuntimeError(f"hipcc failed: {' '.join(cmd)}\n{out}")
         if verbose and out.strip():
             print(out)
+
+    with ThreadPoolExecutor(max_workers=8) as pool:
+        list(pool.map(compile_one, jobs))
+    subprocess.run(["ld", "-r", "-o", os.path.join(CSRC, "ozimmu_gemm.o"), core, *resident], check=True)
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
     return LIB

@@ -6,6 +6,7 @@
 #include "../../include/ozimmu.h"
 #include "ozimmu_kernels.h"
 #include "ozimmu_layout.h"
+#include "ozimmu_resident.h"
 #include <mutex>
 
 namespace {
@@ -212,8 +213,10 @@ struct Finish {
 };
 
 // Steps (iii) + (iv) (+ (v), see Finish) for the whole schedule of Algorithm 6 (groups g = 2..k+1 ascending, chunks
-// of at most r consecutive s), into D.  Four ways to run it, with bit-identical results (details where each is
+// of at most r consecutive s), into D.  Five ways to run it, with bit-identical results (details where each is
 // decided below):
+//  * resident: one launch, all chunk sums of a tile side by side in registers, D written once -- the default where its
+//    estimate is the lowest (nearly everywhere at 3 to 16 slices and at most 16 chunks);
 //  * the queue: one launch whose work items are the (chunk, tile) pairs, an INT32 block per item, the tile's chunks
 //    added up by the workgroup that completes it -- the default for outputs of more tiles than compute units (and
 //    from QUEUE_MIN_TILES tiles on where the chunk-parallel way has no room) when the workspace holds the blocks;
@@ -246,7 +249,7 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     const int64_t T = output_tiles(m, p);
     const int64_t w = chunks_of(k, r_eff);
 
-    // Fourth way ("queue"), for the tiles [0, tiles) of the band order: one launch whose work items are all
+    // The queue, for the tiles [0, tiles) of the band order: one launch whose work items are all
     // (chunk, tile) pairs, handed out round by round (256 tiles) through a counter; an item leaves its INT32 sums
     // in a block, and the workgroup that stores the last block of a tile adds the tile's chunks up (steps (iv),
     // (v)).  Needs sets x chunks x min(tiles, 256) blocks (the rounds take the sets in turn) and a counter per
@@ -298,21 +301,17 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
         a.sync_zeroed = take_clean();
         return hip_status(ozk::launch_gemm(a, 3, st));
     };
-    // Asked for, or the output has more tiles than compute units (measured against queue for the full rounds +
-    // one of the other ways for a short last round: equal or better with everything in the queue), or at least
-    // QUEUE_MIN_TILES and no room for the chunk-parallel way.  An output of one round of tiles whose blocks fit
-    // goes the chunk-parallel way further down: every compute unit gets items from the first moment, and the one
-    // accumulation kernel at the end costs less than the queue's ramp (k = 8, chunk-parallel against queue:
-    // 2560^3, 100 tiles, 0.53 against 0.58 ms; 3072^3 0.87 against 0.92; 4096^3, 256 tiles, 1.87 against 1.89;
-    // 5120^3, 400 tiles, with the queue for the full round only: 3.60 against 3.43).
+    // An output of one round of tiles whose blocks fit goes the chunk-parallel way rather than through the queue: every
+    // compute unit gets items from the first moment, and the one accumulation kernel at the end costs less than the
+    // queue's ramp (k = 8, chunk-parallel against queue: 2560^3, 100 tiles, 0.53 against 0.58 ms; 3072^3 0.87 against
+    // 0.92; 4096^3, 256 tiles, 1.87 against 1.89; 5120^3, 400 tiles, with the queue for the full round only: 3.60
+    // against 3.43).
     const bool one_round_fits = !per_slice && partial && T <= num_cu && T * w <= CHUNK_PARALLEL_MAX_BLOCKS &&
                                 T * w <= partial_capacity;
-    if (schedule == OZIMMU_SCHEDULE_QUEUE || (schedule == 0 && T >= QUEUE_MIN_TILES && !one_round_fits)) {
-        const int64_t sets = queue_sets(T);
-        if (sets > 0) return launch_queue(T, sets);
-    }
+    const int64_t sets_all = queue_sets(T);
+    if (schedule == OZIMMU_SCHEDULE_QUEUE && sets_all > 0) return launch_queue(T, sets_all);
 
-    // Third way, for outputs of few tiles, or the tiles of a partly filled last round (`cand`, the last ones in band
+    // Chunk-parallel, for outputs of few tiles, or the tiles of a partly filled last round (`cand`, the last ones in band
     // order): ONE launch whose work items are (chunk, inner part, tile), every chunk writing (or, when cut,
     // atomically adding) its INT32 sums to a block of its own per tile, and one kernel that adds the chunks of every
     // element in the order of Algorithm 6.  All chunks of all those tiles run side by side, so a 1024^3 product
@@ -320,6 +319,7 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     const int64_t cand = num_cu > 0 ? (T <= num_cu ? T : T % num_cu) : 0;  // tiles of the last round, if not full or the only one
     int64_t cp_tail = 0;  // tiles that go this way
     int cp_z = 1;
+    double cp_us = 0.0;
     if (!per_slice && partial && cand >= 1 && cand * w <= CHUNK_PARALLEL_MAX_BLOCKS && cand * w <= partial_capacity &&
         schedule != OZIMMU_SCHEDULE_ONE_LAUNCH && schedule != OZIMMU_SCHEDULE_SPLIT_INNER) {
         // (measured on MI355X: a stage 0.58 us; prologue + epilogue of an item 12 us, 19 us when the epilogue adds
@@ -352,18 +352,17 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
         if (schedule == OZIMMU_SCHEDULE_CHUNK_PARALLEL || best < 0.97 * one_launch_us) {
             cp_tail = cand;
             cp_z = best_z;
+            cp_us = best;
         }
     }
-    if (cp_tail == 0 && one_round_fits && schedule == 0 && T >= QUEUE_MIN_TILES) {
-        // (the model preferred the persistent launch to the chunk-parallel way: the queue beats that one)
-        const int64_t sets = queue_sets(T);
-        if (sets > 0) return launch_queue(T, sets);
-    }
+    // (where the model prefers the persistent launch to the chunk-parallel way, the queue beats that one)
+    const bool queue_pays = schedule == 0 && T >= QUEUE_MIN_TILES && sets_all > 0 && !(one_round_fits && cp_tail > 0);
 
     // tiles [0, T - tail) go to the persistent launch, the last `tail` tiles (band order) are cut Z ways
     int64_t tail = 0;
     int Z = 1;
-    if (!per_slice && partial && cp_tail == 0 && schedule != OZIMMU_SCHEDULE_ONE_LAUNCH &&
+    double tail_us = 0.0;
+    if (!per_slice && partial && cp_tail == 0 && !queue_pays && schedule != OZIMMU_SCHEDULE_ONE_LAUNCH &&
         schedule != OZIMMU_SCHEDULE_CHUNK_PARALLEL) {
         const int64_t ncu = num_cu;
         const int64_t zmax = KT / 4;  // every part gets at least one group of 4 stages of the shortest chunk
@@ -389,9 +388,61 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
             if (best_z && (schedule == OZIMMU_SCHEDULE_SPLIT_INNER || best < 0.9 * fused_us)) {
                 tail = cand;
                 Z = (int)best_z;
+                tail_us = best * (double)w;
             }
         }
     }
+
+    // Resident: all chunks of a tile resident in registers (ozimmu_resident.h).  It reads every slice once per tile
+    // where the other ways read it once per slice pair, and it writes nothing but D, so it is the fastest wherever
+    // its tiles (of 32 x 32 to 128 x 128 outputs) fill the chip and their chunk sums fit the registers without
+    // making the tiles so small that the operands' way through LDS becomes the bound.
+    if (schedule == 0 && !per_slice) {
+        const double pairs = (double)k * (k + 1) / 2, rounds = (double)((T - tail - cp_tail + num_cu - 1) / num_cu);
+        // what the ways above take: the queue 0.64 us per stage of 64 inner positions and 17 us per work item of a tile
+        // (measured 96.5 ms at 16384^3, k = 8; 36.7 ms at 4096 x 65536 x 4096, k = 10; 7.4 ms at 8192^3, k = 6)
+        double other_us = queue_pays ? (0.64 * pairs * KT + 17.0 * (double)w) * (double)T / num_cu
+                                     : cp_us + tail_us + rounds * (0.60 * pairs * KT + 50.0 * (double)w);
+        int variant = -1;
+        for (int v = 0; v < ozr::NUM_VARIANTS; ++v) {
+            const double us = ozr::estimate_us(k, r_eff, v, m, n, p, num_cu);
+            if (us > 0.0 && us < other_us) {
+                other_us = us;
+                variant = v;
+            }
+        }
+        if (variant >= 0) {
+            const ozk::GemmArgs g = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
+            ozk::ResidentArgs a{};
+            a.SA = g.SA;
+            a.SB = g.SB;
+            a.PA = g.PA;
+            a.PB = g.PB;
+            a.pstrideA = g.pstrideA;
+            a.pstrideB = g.pstrideB;
+            a.cA = g.cA;
+            a.cB = g.cB;
+            a.strideA = g.strideA;
+            a.strideB = g.strideB;
+            a.KT = KT;
+            a.steps = (int)((n + ozl::TILE_K - 1) / ozl::TILE_K);
+            a.m = m;
+            a.p = p;
+            a.D = D;
+            a.ldd = ldd;
+            a.eA = eA;
+            a.eB = eB;
+            a.beta = beta;
+            a.finish = fin.on ? 1 : 0;
+            a.alpha = fin.alpha;
+            a.cbeta = fin.cbeta;
+            a.Cout = fin.Cout;
+            a.ldco = fin.ldco;
+            return hip_status(ozk::launch_resident(a, k, r_eff, variant, st));
+        }
+    }
+    if (queue_pays) return launch_queue(T, sets_all);
+
     if (T - tail - cp_tail > 0) {
         ozk::GemmArgs a = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
         a.tile_count = (int)(T - tail - cp_tail);

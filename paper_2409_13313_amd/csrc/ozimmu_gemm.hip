@@ -69,6 +69,7 @@
 // of D through the then idle ring (see there).
 #include "ozimmu_kernels.h"
 #include "ozimmu_layout.h"
+#include "ozimmu_resident.h"
 #include <type_traits>
 
 namespace {
@@ -1337,8 +1338,42 @@ hipError_t setup_gemm_kernels()
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm<2, NSTAGES>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm<3, NSTAGES>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm<3, NSTAGES>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    ResidentArgs ra{};
+    ra.setup = 1;
+    for (int k = ozr::MIN_K; k <= ozr::MAX_K; ++k)
+        for (int r : {1, 2, 4, 8, k}) {
+            if (r > k) continue;
+            for (int variant = 0; variant < ozr::NUM_VARIANTS; ++variant) {
+                e = launch_resident(ra, k, r, variant, nullptr);
+                if (e != hipSuccess) return e;
+            }
+        }
+    return hipSuccess;
+}
+
+hipError_t launch_resident(const ResidentArgs& a, int k, int r, int variant, hipStream_t st)
+{
+    static_assert(ozr::MIN_K == 3 && ozr::MAX_K == 16, "one case per slice count below");
+    switch (k) {
+        case 3: return launch_resident_k<3>(a, r, variant, st);
+        case 4: return launch_resident_k<4>(a, r, variant, st);
+        case 5: return launch_resident_k<5>(a, r, variant, st);
+        case 6: return launch_resident_k<6>(a, r, variant, st);
+        case 7: return launch_resident_k<7>(a, r, variant, st);
+        case 8: return launch_resident_k<8>(a, r, variant, st);
+        case 9: return launch_resident_k<9>(a, r, variant, st);
+        case 10: return launch_resident_k<10>(a, r, variant, st);
+        case 11: return launch_resident_k<11>(a, r, variant, st);
+        case 12: return launch_resident_k<12>(a, r, variant, st);
+        case 13: return launch_resident_k<13>(a, r, variant, st);
+        case 14: return launch_resident_k<14>(a, r, variant, st);
+        case 15: return launch_resident_k<15>(a, r, variant, st);
+        case 16: return launch_resident_k<16>(a, r, variant, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_fill_zero_i32(int64_t count, int32_t* x, hipStream_t st)

@@ -121,6 +121,34 @@ hipError_t launch_accumulate_tiles(const TileAccArgs& t, hipStream_t st);
 // blocks Ct[q][tile]; they are added in schedule order, one rounded FP64 addition each.  Uses t.tile_*, m, p, Ct,
 // eA, eB, D, ldd and the finish fields; shift / first are ignored.
 hipError_t launch_accumulate_chunks(const TileAccArgs& t, int k, int r, int beta, hipStream_t st);
+// Steps (iii) to (v) with all chunks of a tile resident in registers (ozimmu_resident.hip).
+struct ResidentArgs {
+    const int8_t* SA;
+    const int8_t* SB;
+    const int32_t* PA;     // prefix row sums of the stored bytes, as in GemmArgs
+    const int32_t* PB;
+    int64_t pstrideA, pstrideB;
+    const int32_t* cA;
+    const int32_t* cB;
+    int64_t strideA, strideB;
+    int KT;                // inner tiles of the packed layout
+    int steps;             // inner tiles that hold anything but padding (<= KT)
+    int64_t m, p;
+    double* D;
+    int64_t ldd;
+    const int32_t* eA;
+    const int32_t* eB;
+    int beta;
+    int finish;
+    double alpha, cbeta;
+    double* Cout;
+    int64_t ldco;
+    int TM, TP;            // filled in by the launcher
+    int setup;             // nothing is launched: the kernel's dynamic LDS limit is raised on the current device
+};
+template <int K>
+hipError_t launch_resident_k(const ResidentArgs& a, int r, int variant, hipStream_t st);
+hipError_t launch_resident(const ResidentArgs& a, int k, int r, int variant, hipStream_t st);
 // Step (v): C <- alpha D + beta C (beta == 0: C not read).
 hipError_t launch_axpby(int64_t m, int64_t p, double alpha, const double* D, int64_t ldd, double beta, double* C,
                         int64_t ldc, hipStream_t st);

@@ -1,0 +1,617 @@
+// Steps (iii) to (v) of the scheme with every chunk of a tile resident in registers.
+//
+// k_gemm (ozimmu_gemm.hip) runs the chunks of a tile one after the other and streams both operands' slices anew for
+// every slice pair: k (k + 1) / 2 reads of an A tile and of a B tile per tile and inner step.  k_resident turns the
+// loops round: for one inner step of 64 it takes ALL k slices of its rows of A and of its columns of B (2 k tiles
+// instead of k (k + 1)) and runs all k (k + 1) / 2 slice pairs on them, each into the INT32 accumulators of its chunk.
+// The w chunk sums of a tile (Algorithm 6) thus grow side by side in the accumulation registers, and when the inner
+// dimension is through they are added up in FP64 in the order of Algorithm 6 - one rounded addition per chunk, as
+// everywhere - and D is written once.  No INT32 blocks, no second pass, no counters between workgroups.
+//
+// What bounds it: the matrix cores, at the clock the chip's power budget allows.  Per MFMA the wave fetches 0.167 KiB of
+// fragments from LDS (k = 8, tiles of 64 x 128; k_gemm 0.25), the compute unit brings in 85 bytes of operands (128), and
+// the launch reads 137 GB from beyond L2 at 16384^3 (281).  All of that is energy that goes into clock instead:
+// 16384^3, k = 8: 1.90 GHz at 91 % busy pipes against 1.68 GHz at 91.5 %, 86.9 against 95.6 ms on one box
+// (3.64 POP/s, 90 % of what a register-only MFMA loop sustains on such bytes).  Small outputs gain more: their tiles
+// need no blocks, no atomic adds and no second kernel, and 64 x 64 tiles spread a 1024^3 product over the whole chip
+// (per call, k_gemm's ways -> this: 1024^3 k = 9 124 -> 72 us, 777 x 1001 x 513 k = 7 122 -> 60 us, 4096^3 k = 8 1.83 ->
+// 1.55 ms, 4096^3 k = 9 with one addition per slice pair 4.02 -> 2.75 ms).
+//
+// Fragments: L = (k + 1) / 2 low slices of both operands stay in registers for a step, the high ones pass through two
+// buffers, so that every fragment is fetched once per step and wave.  A wave holds as many 16 x 16 tiles as w chunk
+// sums leave room for in the 256 accumulation registers (ozimmu_resident.h).
+//
+// This file is compiled once per slice count (OZ_RES_K = k).
+#include "ozimmu_kernels.h"
+#include "ozimmu_layout.h"
+#include "ozimmu_resident.h"
+#include <type_traits>
+#include <utility>
+
+#ifndef OZ_RES_K
+#define OZ_RES_K 8
+#endif
+
+namespace {
+
+using namespace ozl;
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) const v4i* lds_v4i_ptr;
+
+template <int... I, class F>
+__device__ __attribute__((always_inline)) inline void static_for_impl(std::integer_sequence<int, I...>, F&& f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __attribute__((always_inline)) inline void static_for(F&& f)
+{
+    static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
+template <int N>
+__device__ inline void wait_vmcnt()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// (the builtin, not asm: the compiler then knows that its own LDS reads have returned)
+__device__ inline void wait_lds() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+
+using ozr::num_chunks;
+
+// number (in schedule order) of the chunk that holds the pair (s, t)
+constexpr int chunk_of(int s, int t, int r)
+{
+    int w = 0;
+    for (int g = 2; g < s + t; ++g) w += (g - 2) / r + 1;
+    return w + (s - 1) / r;
+}
+
+// chunk number c: s = s0 .. s1 of group g
+struct Range {
+    int g, s0, s1;
+};
+template <int K, int R>
+constexpr Range chunk_range(int c)
+{
+    int n = 0;
+    for (int g = 2; g <= K + 1; ++g)
+        for (int s0 = 1; s0 <= g - 1; s0 += R, ++n)
+            if (n == c) return Range{g, s0, (s0 + R - 1 < g - 1) ? s0 + R - 1 : g - 1};
+    return Range{0, 0, 0};
+}
+
+// The order of one inner step, made at compile time.  With L = (k + 1) / 2 no pair has both slices above L.  Group
+// number gi = 0 .. L - 1 belongs to j = L - gi: first the pairs of low slices whose larger one is j, then those of the
+// high slice h = k + 1 - j (if h > L) with the low slices 1 .. j.  After it slice j is used up for this step: its
+// registers take slice j of the NEXT step at the start of the next group.  The high slices pass through two buffers.
+template <int K, int R, int TA, int TB>
+struct Plan {
+    static constexpr int L = (K + 1) / 2;
+    static constexpr int NP = K * (K + 1) / 2;
+    static constexpr int W = num_chunks(K, R);
+    static constexpr int TT = TA * TB;          // MFMAs of a pair
+    static constexpr int NM = NP * TT;          // MFMAs of a step
+    static constexpr int NF = TA + TB;          // fragments of a slice
+    static constexpr int NC = (2 * NF + 3) / 4;  // copies (of 16 rows) per wave and slice
+
+    int s[NP] = {}, t[NP] = {};
+    int group_at[L + 1] = {};        // first MFMA of a group
+    int nread[L] = {}, read_slice[L][3] = {};  // slices whose fragments are fetched in a group
+    bool read_next[L][3] = {};       // ... for the next step
+    // per MFMA index: fragment fetch (group-local list position) and copy, -1 = none
+    int read_pos[NM] = {}, copy_pos[NM] = {}, group_of[NM] = {};
+
+    constexpr int high(int j) const { return K + 1 - j > L ? K + 1 - j : 0; }
+    constexpr Plan()
+    {
+        int n = 0;
+        for (int gi = 0; gi < L; ++gi) {
+            const int j = L - gi;
+            group_at[gi] = n * TT;
+            s[n] = j, t[n++] = j;
+            for (int q = j - 1; q >= 1; --q) {
+                s[n] = j, t[n++] = q;
+                s[n] = q, t[n++] = j;
+            }
+            const int h = high(j);
+            if (h)
+                for (int q = j; q >= 1; --q) {
+                    s[n] = h, t[n++] = q;
+                    s[n] = q, t[n++] = h;
+                }
+            auto add = [&](int sl, bool next) {
+                read_slice[gi][nread[gi]] = sl;
+                read_next[gi][nread[gi]++] = next;
+            };
+            if (gi == 0) {
+                add(1, false);
+                if (high(L)) add(high(L), false);
+            } else {
+                add(j + 1, true);
+            }
+            if (j >= 2 && high(j - 1)) add(high(j - 1), false);
+        }
+        group_at[L] = NM;
+        for (int q = 0; q < NM; ++q) read_pos[q] = copy_pos[q] = -1;
+        for (int gi = 0; gi < L; ++gi) {
+            const int len = group_at[gi + 1] - group_at[gi];
+            for (int q = group_at[gi]; q < group_at[gi + 1]; ++q) group_of[q] = gi;
+            auto spread = [&](int count, int most) {
+                int sp = len / (count + 2);
+                sp = sp > most ? most : sp;
+                return sp < 1 ? 1 : sp;
+            };
+            const int nr = nread[gi] * NF, nc = nread[(gi + L - 1) % L] * NC;
+            const int spr = spread(nr, TT <= 4 ? 2 : 4), spc = spread(nc, 4);
+            for (int x = 0; x < nr; ++x) read_pos[group_at[gi] + (x * spr < len ? x * spr : len - 1)] = x;
+            for (int x = 0; x < nc; ++x) copy_pos[group_at[gi] + (x * spc + 1 < len ? x * spc + 1 : len - 1)] = x;
+        }
+    }
+};
+
+// Which tile workgroup b takes.  Workgroup b runs on XCD b % 8, and 256 consecutive workgroups run at about the same
+// time; those of one XCD should share operand tiles in its L2, and the XCDs among each other in the memory-side cache.
+// So 256 workgroups in a row ("round") get 256 consecutive places of the order below, XCD x the places 32 x .. 32 x + 31
+// of them: an 8 x 4 patch of tiles, eight patches to a block of 16 x 16.  The order: all whole 16 x 16 blocks (rows of
+// blocks back and forth), then what is left of the tile grid on the right, then below, in bands of 8 rows walked column
+// by column.  A last round that is not full is cut into eight equal ranges.
+__device__ inline void band_order(int lin, int rows, int& r, int& c, int cols)
+{
+    const int width = 8 * cols, band = lin / width, in_band = lin - band * width;
+    const int h = rows - 8 * band < 8 ? rows - 8 * band : 8;
+    r = 8 * band + in_band % h;
+    c = in_band / h;
+}
+__device__ inline void tile_of_block(int b, int TM, int TP, int& tm, int& tp)
+{
+    const int T = TM * TP, x = b & 7, round = b >> 8;
+    int lin;
+    if (T - (round << 8) >= 256) {
+        lin = (round << 8) + x * 32 + ((b >> 3) & 31);
+    } else {
+        const int left = T - (round << 8), base = left >> 3, rem = left & 7;
+        lin = (round << 8) + x * base + (x < rem ? x : rem) + ((b & 255) >> 3);
+    }
+    const int BM = TM / 16, BP = TP / 16, whole = BM * BP * 256;
+    if (lin < whole) {
+        const int q = lin >> 8, u = lin & 255, br = q / BP, bc = q - br * BP;
+        const int patch = u >> 5, mem = u & 31;
+        tm = br * 16 + (patch >> 2) * 8 + (mem & 7);
+        tp = ((br & 1) ? BP - 1 - bc : bc) * 16 + (patch & 3) * 4 + (mem >> 3);
+        return;
+    }
+    lin -= whole;
+    const int wr = TP - BP * 16;       // columns right of the blocks, over all rows
+    if (lin < TM * wr) {
+        band_order(lin, TM, tm, tp, wr);
+        tp += BP * 16;
+    } else {
+        band_order(lin - TM * wr, TM - BM * 16, tm, tp, BP * 16);
+        tm += BM * 16;
+    }
+}
+
+template <int K, int R, int TA, int TB, int D, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
+{
+    using P = Plan<K, R, TA, TB>;
+    static constexpr P plan{};
+    constexpr int L = P::L, W = P::W, NF = P::NF;
+    constexpr int RA = 32 * TA, RB = 32 * TB;               // rows and columns of the workgroup's tile
+    constexpr int SLOT = (RA + RB) * TILE_K;                // one slice of both operands: A rows, then B columns
+    constexpr int SET = K * SLOT;                           // all slices of an inner step
+    extern __shared__ __align__(16) int8_t lds[];
+    int* const lds_exp = reinterpret_cast<int*>(lds + D * SET);  // exponents of the tile's rows, then columns
+
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // workgroup b runs on XCD b % 8
+    int tm, tp;
+    tile_of_block((int)blockIdx.x, a.TM, a.TP, tm, tp);
+    tm = __builtin_amdgcn_readfirstlane(tm);
+    tp = __builtin_amdgcn_readfirstlane(tp);
+    const uint32_t row0 = (uint32_t)tm * RA, col0 = (uint32_t)tp * RB;
+
+    // Operand copies: 16 rows (1 KiB) of a packed tile per instruction.  A slice's 2 TA pieces of A and 2 TB pieces of B
+    // lie one behind the other in its LDS slot, wave w brings pieces w NC .. w NC + NC - 1 (where they do not divide among
+    // four waves the last wave repeats some: the same bytes to the same place).  One M0 per slice: the instruction
+    // offset moves the LDS and the global address alike, so the global base of piece q is taken q KiB lower.
+    constexpr int NC = P::NC;
+    const int piece0 = wave * NC < 2 * NF - NC ? wave * NC : 2 * NF - NC;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+    uint32_t m0_cur = lds_base + (uint32_t)piece0 * 1024u, m0_nxt = m0_cur + (D - 1) * SET;
+    const int64_t rowblk = rowblock_bytes(a.KT);
+    const int8_t* gbase[NC];
+    int64_t gstride[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+        const int pc = piece0 + q;
+        const bool isb = pc >= 2 * TA;
+        uint32_t row = isb ? col0 + (uint32_t)(pc - 2 * TA) * 16u : row0 + (uint32_t)pc * 16u;
+        const uint32_t top = (uint32_t)(isb ? a.pstrideB : a.pstrideA) - 16u;  // (padded rows of the stack)
+        row = row < top ? row : top;  // a tile may reach past the padding: what it reads there is never stored
+        gbase[q] = (isb ? a.SB : a.SA) + (int64_t)(row / TILE_R) * rowblk + (int)(row % TILE_R) * TILE_K - q * 1024;
+        gstride[q] = isb ? a.strideB : a.strideA;
+    }
+
+    // copy number q of slice s into the set at m0; voff = 16 lane + 16 KiB * inner step
+    auto copy = [&](auto S, auto X, uint32_t m0, uint32_t voff) __attribute__((always_inline)) {
+        constexpr int s = decltype(S)::value, q = decltype(X)::value;
+        const int8_t* base = gbase[q] + (int64_t)(s - 1) * gstride[q];
+        if constexpr (q == 0)
+            asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" ::"s"(m0), "n"((s - 1) * SLOT),
+                         "v"(voff), "s"(base)
+                         : "memory", "scc");
+        else
+            asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(voff), "s"(base), "n"(q * 1024) : "memory");
+    };
+    auto copy_slice = [&](auto S, uint32_t m0, uint32_t voff) __attribute__((always_inline)) {
+        static_for<NC>([&](auto X) __attribute__((always_inline)) { copy(S, X, m0, voff); });
+    };
+
+    // Fragment addresses (see k_gemm: one MFMA takes 64 inner bytes, the four lane groups of 16 supply the logical chunks
+    // 0, 3, 1, 2, which keeps the fetches off each other's banks).  ds_read offsets are 16-bit immediates: a second base
+    // serves what lies beyond.
+    constexpr int FAR = 49152;
+    uint32_t fcur[2][2], fnxt[2][2];  // [A, B][near, far]
+    {
+        const int chunk = (0x9c >> (2 * (lane >> 4))) & 3;  // 0, 3, 1, 2
+        const int ra = wm * (16 * TA) + (lane & 15), rb = wn * (16 * TB) + (lane & 15);
+        const uint32_t oa = lds_base + ra * TILE_K + swizzle(ra, chunk) * CHUNK;
+        const uint32_t ob = lds_base + RA * TILE_K + rb * TILE_K + swizzle(rb, chunk) * CHUNK;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            fcur[0][f] = oa + f * FAR;
+            fcur[1][f] = ob + f * FAR;
+            fnxt[0][f] = oa + f * FAR + (D - 1) * SET;
+            fnxt[1][f] = ob + f * FAR + (D - 1) * SET;
+        }
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                if (f == 1 && SET <= 61440) continue;
+                asm volatile("" : "+v"(fcur[o][f]));
+                if (D > 1) asm volatile("" : "+v"(fnxt[o][f]));
+            }
+    }
+    v4i low[L + 1][NF], hi[2][NF];  // fragments: row tiles of A, then column tiles of B
+    auto fetch = [&](auto S, auto X, auto NEXT) __attribute__((always_inline)) {
+        constexpr int s = decltype(S)::value, x = decltype(X)::value;
+        constexpr bool next = decltype(NEXT)::value && D > 1;
+        constexpr bool isb = x >= TA;
+        constexpr int off = (s - 1) * SLOT + (isb ? x - TA : x) * 1024;
+        constexpr int f = off >= 61440 ? 1 : 0;
+        const uint32_t base = next ? fnxt[isb][f] : fcur[isb][f];
+        const v4i v = *(lds_v4i_ptr)(uintptr_t)(base + (off - f * FAR));
+        if constexpr (s <= L)
+            low[s][x] = v;
+        else
+            hi[(s - L - 1) & 1][x] = v;
+    };
+
+    v4i acc[W][TA][TB];
+    const int KT = a.steps;
+
+    const uint32_t lv = (uint32_t)lane * 16u;
+    auto step_off = [&](int kt) { return (uint32_t)(kt < KT - 1 ? kt : KT - 1) * (uint32_t)TILE_BYTES; };
+    // Copies of step 0 - and of step 1 for a ring of two - in the order of the loop, so that its counted waits hold from
+    // the start: what group gi reads, gi = 0 .. L - 1, a low slice for the step after (slice 2 belongs to the last group
+    // and is brought by group 0 of the loop).  Before that, the low slices 2 .. L of step 0 themselves.
+    static_assert(L >= 2, "at least three slices");
+    auto copy_group = [&](auto GI, int step, uint32_t m0_this, uint32_t m0_next) __attribute__((always_inline)) {
+        constexpr int gi = decltype(GI)::value;
+        static_for<plan.nread[gi]>([&](auto X) __attribute__((always_inline)) {
+            constexpr int sl = plan.read_slice[gi][decltype(X)::value];
+            constexpr bool next = plan.read_next[gi][decltype(X)::value];
+            copy_slice(std::integral_constant<int, sl>{}, next ? m0_next : m0_this, lv + step_off(step + (next ? 1 : 0)));
+        });
+    };
+    static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
+        copy_slice(std::integral_constant<int, L - decltype(X)::value>{}, m0_cur, lv);
+    });
+    copy_group(std::integral_constant<int, 0>{}, 0, m0_cur, m0_nxt);
+    // Start values and exponents, their loads behind the first copies (memory operations return in order: whoever waits for
+    // these has the copies as well, and needs them).
+    {
+        const int cA = a.cA[0], cB = a.cB[0];
+        if (t < RA) {
+            const uint32_t gr = row0 + t;
+            lds_exp[t] = (int64_t)gr < a.m ? a.eA[gr] : 0;
+        }
+        if (t < RB) {
+            const uint32_t gc = col0 + t;
+            lds_exp[RA + t] = (int64_t)gc < a.p ? a.eB[gc] : 0;
+        }
+        // The accumulators of a chunk start at -(ra[row] + cb[column]) (see the head of ozimmu_gemm.hip); the inner
+        // positions past the last step carry q = 0, i.e. the offsets themselves, in the stored sums.
+        // (row and column tiles past the padding take any sums: their results are never stored)
+        uint32_t rr[TA], cc[TB];
+#pragma unroll
+        for (int i = 0; i < TA; ++i) {
+            const uint32_t r0 = row0 + wm * (16 * TA) + 16 * i, top = (uint32_t)a.pstrideA - 16u;
+            rr[i] = (r0 < top ? r0 : top) + 4 * (lane >> 4);
+        }
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+            const uint32_t c0 = col0 + wn * (16 * TB) + 16 * j, top = (uint32_t)a.pstrideB - 16u;
+            cc[j] = (c0 < top ? c0 : top) + (lane & 15);
+        }
+        static_for<W>([&](auto C) __attribute__((always_inline)) {
+            constexpr int c = decltype(C)::value;
+            constexpr Range range = chunk_range<K, R>(c);
+            constexpr int s0 = range.s0, s1 = range.s1, t0 = range.g - s1, t1 = range.g - s0;
+            if (cA | cB) {
+                v4i sa[TA];
+                int sb[TB];
+#pragma unroll
+                for (int i = 0; i < TA; ++i) {
+                    sa[i] = *reinterpret_cast<const v4i*>(a.PA + (int64_t)(s1 - 1) * a.pstrideA + rr[i]);
+                    if (s0 > 1) sa[i] -= *reinterpret_cast<const v4i*>(a.PA + (int64_t)(s0 - 2) * a.pstrideA + rr[i]);
+                }
+#pragma unroll
+                for (int j = 0; j < TB; ++j) {
+                    sb[j] = a.PB[(int64_t)(t1 - 1) * a.pstrideB + cc[j]];
+                    if (t0 > 1) sb[j] -= a.PB[(int64_t)(t0 - 2) * a.pstrideB + cc[j]];
+                }
+                const uint32_t fix = (uint32_t)((s1 - s0 + 1) * cA * cB) * (uint32_t)((2 * a.KT - KT) * TILE_K);
+#pragma unroll
+                for (int i = 0; i < TA; ++i)
+#pragma unroll
+                    for (int j = 0; j < TB; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            acc[c][i][j][r] = (int)(fix - (uint32_t)cB * (uint32_t)sa[i][r] - (uint32_t)cA * (uint32_t)sb[j]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < TA; ++i)
+#pragma unroll
+                    for (int j = 0; j < TB; ++j) acc[c][i][j] = (v4i){0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int i = 0; i < TA; ++i)
+#pragma unroll
+                for (int j = 0; j < TB; ++j) asm volatile("" : "+a"(acc[c][i][j]));
+            if constexpr (c % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    wait_vmcnt<P::NC * plan.nread[0]>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
+        constexpr int s = L - decltype(X)::value;
+        static_for<NF>([&](auto F) __attribute__((always_inline)) { fetch(std::integral_constant<int, s>{}, F, std::false_type{}); });
+    });
+    wait_lds();
+    __builtin_amdgcn_s_barrier();  // every wave has the low slices of step 0: their slots are free
+    asm volatile("" ::: "memory");
+    static_for<L - 2>([&](auto GI) __attribute__((always_inline)) {
+        copy_group(std::integral_constant<int, decltype(GI)::value + 1>{}, 0, m0_cur, m0_nxt);
+    });
+    if constexpr (D == 2) {
+        copy_slice(std::integral_constant<int, 2>{}, m0_nxt, lv + step_off(1));
+        static_for<L - 1>([&](auto GI) __attribute__((always_inline)) {
+            copy_group(std::integral_constant<int, decltype(GI)::value>{}, 1, m0_nxt, m0_cur);
+        });
+    }
+
+    uint32_t m0_sum = m0_cur + m0_nxt, fsum[2][2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            fsum[o][f] = fcur[o][f] + fnxt[o][f];
+            if (D == 2) asm volatile("" : "+v"(fsum[o][f]));
+        }
+    if (D == 2) asm volatile("" : "+s"(m0_sum));
+    // where the copies of a step read: what is fetched for this step is followed by step kt + D in its place (v1), what is
+    // fetched for the next one by step kt + 1 + D (v2; past the end: the last step again, never used)
+    uint32_t v1 = lv + step_off(D), v2 = v1;
+    for (int kt = 0; kt < KT; ++kt) {
+        static_for<P::NM>([&](auto Q) __attribute__((always_inline)) {
+            constexpr int q = decltype(Q)::value;
+            constexpr int gi = plan.group_of[q], gp = (gi + L - 1) % L;
+            if constexpr (plan.group_at[gi] == q) {
+                // what this group reads has landed, and every wave has what the group before read
+                wait_lds();
+                wait_vmcnt<P::NC * (D * K - plan.nread[gi] - plan.nread[gp])>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (plan.group_at[0] + 2 == q) {
+                // what the step needs from its second group on, and the next step from its start (in a gap between two
+                // MFMAs: at the end of the loop it would make a bubble of a dozen instructions)
+                v2 = lv + step_off(kt + 1 + D);
+                asm volatile("" : "+v"(v2));
+                if constexpr (D == 2) {
+                    m0_nxt = m0_sum - m0_cur;
+                    asm volatile("" : "+s"(m0_nxt));
+                }
+            }
+            if constexpr (D == 2 && plan.group_at[0] + 3 == q) {
+                fnxt[0][0] = fsum[0][0] - fcur[0][0];
+                fnxt[1][0] = fsum[1][0] - fcur[1][0];
+                asm volatile("" : "+v"(fnxt[0][0]), "+v"(fnxt[1][0]));
+                if constexpr (SET > 61440) {
+                    fnxt[0][1] = fsum[0][1] - fcur[0][1];
+                    fnxt[1][1] = fsum[1][1] - fcur[1][1];
+                    asm volatile("" : "+v"(fnxt[0][1]), "+v"(fnxt[1][1]));
+                }
+            }
+            if constexpr (plan.read_pos[q] >= 0) {
+                constexpr int x = plan.read_pos[q];
+                constexpr int sl = plan.read_slice[gi][x / NF];
+                // (the operand that is needed first comes first: B of a low slice, A of a high one)
+                constexpr int f = sl <= L ? (x % NF + TA) % NF : x % NF;
+                fetch(std::integral_constant<int, sl>{}, std::integral_constant<int, f>{},
+                      std::integral_constant<bool, plan.read_next[gi][x / NF]>{});
+            }
+            if constexpr (plan.copy_pos[q] >= 0) {
+                constexpr int x = plan.copy_pos[q];
+                constexpr int sl = plan.read_slice[gp][x / P::NC];
+                // group 0 replaces what the last group of the step before read for this step
+                constexpr bool next = plan.read_next[gp][x / P::NC] && gi != 0;
+                copy(std::integral_constant<int, sl>{}, std::integral_constant<int, x % P::NC>{}, next ? m0_nxt : m0_cur,
+                     next ? v2 : v1);
+            }
+            constexpr int pr = q / P::TT, m = q % P::TT;
+            constexpr int s = plan.s[pr], u = plan.t[pr];
+            // (back and forth, so that consecutive MFMAs share an operand)
+            constexpr int j = m / TA, i = (j & 1) ? TA - 1 - m % TA : m % TA;
+            constexpr int c = chunk_of(s, u, R);
+            const v4i fa = s <= L ? low[s <= L ? s : 0][i] : hi[(s - L - 1) & 1][i];
+            const v4i fb = u <= L ? low[u <= L ? u : 0][TA + j] : hi[(u - L - 1) & 1][TA + j];
+            acc[c][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, acc[c][i][j], 0, 0, 0);
+            // (an MFMA touches no memory: without a use in the order of the asm statements instruction selection may gather
+            // all fetches and copies of the step in front of all MFMAs)
+            // (with one set of operands it does not, and the use would cost moves of accumulators)
+            if constexpr (D == 2) asm volatile("" ::"a"(acc[c][i][j]));
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        v1 = v2;
+        if constexpr (D == 2) {
+            m0_cur = m0_nxt;
+            fcur[0][0] = fnxt[0][0], fcur[0][1] = fnxt[0][1];
+            fcur[1][0] = fnxt[1][0], fcur[1][1] = fnxt[1][1];
+        }
+    }
+    wait_vmcnt<0>();  // no copy may still be writing LDS when the workgroup ends
+
+    // Steps (iv) and (v): per element the chunk sums in schedule order, one rounded addition each.  Register r of tile
+    // (i, j) in lane l: row 4 (l / 16) + r, column l % 16.
+    int lq = lane >> 4, lc = lane & 15;
+    asm volatile("" : "+v"(lq), "+v"(lc));
+    double* const obase = a.finish ? a.Cout : a.D;
+    const int64_t opitch = a.finish ? a.ldco : a.ldd;
+    const bool with_c = a.finish && a.cbeta != 0.0;
+    int ea[TA][4], eb[TB];
+    int emin = 0x7fffffff, emax = -0x7fffffff;
+#pragma unroll
+    for (int j = 0; j < TB; ++j) eb[j] = lds_exp[RA + wn * (16 * TB) + 16 * j + lc];
+#pragma unroll
+    for (int i = 0; i < TA; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ea[i][r] = lds_exp[wm * (16 * TA) + 16 * i + 4 * lq + r];
+#pragma unroll
+    for (int j = 0; j < TB; ++j)
+#pragma unroll
+        for (int i = 0; i < TA; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int e = ea[i][r] + eb[j];
+                emin = e < emin ? e : emin;
+                emax = e > emax ? e : emax;
+            }
+    // Rounding does not see a common power of two: while every term is a normal number, the sum can be formed on the
+    // integers scaled by 2^(beta (2 - g)) only (a term and its addition are then one fused multiply-add of an exact
+    // product) and scaled by 2^(2 - 2 beta + ea + eb) at the end.  Otherwise term by term.
+    const bool plain_range = emin + 2 - a.beta * (K + 1) >= -1022 && emax + 2 - 2 * a.beta + 40 <= 1023;
+    const bool scaled = __ballot(plain_range) == ~0ull;
+    auto finish_tile = [&](auto SCALED) __attribute__((always_inline)) {
+        const double step = ldexp(1.0, -a.beta);
+#pragma unroll
+        for (int j = 0; j < TB; ++j) {
+            const int64_t col = (int64_t)col0 + wn * (16 * TB) + 16 * j + lc;
+#pragma unroll
+            for (int i = 0; i < TA; ++i) {
+                const int64_t row = (int64_t)row0 + wm * (16 * TA) + 16 * i + 4 * lq;
+                double* const out = obase + row * opitch + col;
+                double cold[4] = {0.0, 0.0, 0.0, 0.0};
+                if (with_c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (col < a.p && row + r < a.m) cold[r] = __builtin_nontemporal_load(out + r * opitch);
+                double d[4];
+                double scale = 1.0;
+                static_for<W>([&](auto C) __attribute__((always_inline)) {
+                    constexpr int c = decltype(C)::value;
+                    constexpr int g = chunk_range<K, R>(c).g;
+                    if constexpr (c > 0)
+                        if constexpr (g != chunk_range<K, R>(c - 1).g) scale *= step;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const double x = (double)acc[c][i][j][r];
+                        if constexpr (decltype(SCALED)::value) {
+                            d[r] = c == 0 ? x : __builtin_fma(x, scale, d[r]);
+                        } else {
+                            const double term = ldexp(x, ea[i][r] + eb[j] + 2 - a.beta * g);
+                            d[r] = c == 0 ? term : d[r] + term;
+                        }
+                    }
+                });
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if constexpr (decltype(SCALED)::value) d[r] = ldexp(d[r], ea[i][r] + eb[j] + 2 - 2 * a.beta);
+                    if (a.finish) {
+                        d[r] = a.alpha * d[r];
+                        if (with_c) d[r] = d[r] + a.cbeta * cold[r];
+                    }
+                    if (col < a.p && row + r < a.m) __builtin_nontemporal_store(d[r], out + r * opitch);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    if (scaled)
+        finish_tile(std::true_type{});
+    else
+        finish_tile(std::false_type{});
+}
+
+template <int K, int R, int V>
+hipError_t launch(const ozk::ResidentArgs& a_in, hipStream_t st)
+{
+    constexpr ozr::Config c = ozr::config(K, R, V);
+    if constexpr (c.ta == 0) {
+        return a_in.setup ? hipSuccess : hipErrorInvalidValue;
+    } else {
+        ozk::ResidentArgs a = a_in;
+        constexpr int RA = 32 * c.ta, RB = 32 * c.tb;
+        a.TM = (int)((a.m + RA - 1) / RA);
+        a.TP = (int)((a.p + RB - 1) / RB);
+        constexpr int smem = ozr::lds_bytes(K, c);
+        static_assert(smem <= 160 * 1024, "LDS of a compute unit");
+        if (a.setup)
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_resident<K, R, c.ta, c.tb, c.depth, c.waves>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        hipLaunchKernelGGL((k_resident<K, R, c.ta, c.tb, c.depth, c.waves>), dim3((unsigned)a.TM * (unsigned)a.TP), dim3(256),
+                           smem, st, a);
+        return hipGetLastError();
+    }
+}
+
+template <int K, int R>
+hipError_t launch_r(const ozk::ResidentArgs& a, int variant, hipStream_t st)
+{
+    switch (variant) {
+        case 0: return launch<K, R, 0>(a, st);
+        case 1: return launch<K, R, 1>(a, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+namespace ozk {
+
+template <>
+hipError_t launch_resident_k<OZ_RES_K>(const ResidentArgs& a, int r, int variant, hipStream_t st)
+{
+    constexpr int K = OZ_RES_K;
+    if (r >= K) return launch_r<K, K>(a, variant, st);
+    if constexpr (K > 8)
+        if (r == 8) return launch_r<K, 8>(a, variant, st);
+    if constexpr (K > 4)
+        if (r == 4) return launch_r<K, 4>(a, variant, st);
+    if (r == 2) return launch_r<K, 2>(a, variant, st);
+    if (r == 1) return launch_r<K, 1>(a, variant, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace ozk

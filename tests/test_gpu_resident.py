@@ -1,0 +1,87 @@
+"""GPU parity of the kernel that keeps all chunk sums of a tile in registers (ozimmu_resident.hip), at the sizes where it can
+go wrong: the edges of its tiles (32 to 128 rows and columns), inner dimensions around the step of 64 and of one or two
+steps, every slice count it is built for, chunks shorter than the groups (long inner dimensions, per-pair
+accumulation), step (v), strided outputs, and exponents at which the scaled summation has to give way to the
+term-by-term one.  Each D is compared bit for bit with the oracle and / or the persistent launch."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2409_13313_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def oz():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: the HIP path has no CPU fallback")
+    from paper_2409_13313_amd import ozimmu
+    return ozimmu
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+@pytest.mark.parametrize("k", range(3, 17))
+@pytest.mark.parametrize("m,n,p", [(1, 1, 1), (31, 63, 33), (65, 64, 63), (129, 65, 97), (64, 129, 257), (257, 300, 128)])
+def test_tile_and_step_edges_match_the_oracle_bit_for_bit(oz, m, n, p, k):
+    A, B = inputs.phi_pair(m, n, p, 1.0, seed=201)
+    D = torch.full((m, p + 1), float("nan"), dtype=torch.float64, device="cuda")
+    oz.dgemm(dev(A), dev(B), k, D=D[:, :p])
+    got = D.cpu().numpy()
+    assert np.array_equal(got[:, :p], oracle.dgemm(A, B, k)) and np.isnan(got[:, p]).all()
+
+
+@pytest.mark.parametrize("m,n,p,k,split,accumulate", [
+    (2040, 1990, 2049, 3, "rn", "grouped"), (2048, 2048, 2048, 4, "rn", "grouped"),    # tiles of 128 x 128
+    (1990, 2047, 2000, 5, "rn", "grouped"), (2000, 1999, 2047, 6, "bitmask", "grouped"),  # 64 x 128, two steps in LDS
+    (1000, 1999, 2047, 7, "rn", "grouped"), (1024, 2050, 2048, 8, "rn", "grouped"),    # 64 x 128, one step in LDS
+    (1030, 8200, 1000, 9, "rn", "grouped"), (1030, 8200, 1000, 12, "rn", "grouped"),   # r = 8: short chunks
+    (2050, 8200, 1990, 14, "rn", "grouped"),                                           # 20 chunks: 32 x 96
+    (1500, 16400, 1500, 8, "rn", "grouped"), (1500, 16400, 1500, 5, "bitmask", "grouped"),  # r = 4
+    (1030, 300, 1000, 7, "bitmask", "per_pair"), (1030, 300, 1000, 9, "bitmask", "per_pair"),  # 28 and 45 chunks
+    (1030, 300, 1000, 3, "rn", "per_pair"), (1030, 300, 1000, 5, "rn", "per_pair"), (1030, 300, 1000, 6, "rn", "per_pair"),
+    (1030, 300, 1000, 10, "rn", "per_pair"), (1030, 300, 1000, 11, "rn", "wide")])
+def test_larger_outputs_match_the_persistent_launch_and_sampled_oracle_entries(oz, m, n, p, k, split, accumulate):
+    A, B = inputs.phi_pair(m, n, p, 1.0, seed=202)
+    dA, dB = dev(A), dev(B)
+    ref = oz.dgemm_variant(dA, dB, k, split, accumulate, schedule="one_launch")
+    got = oz.dgemm_variant(dA, dB, k, split, accumulate)
+    assert torch.equal(got, ref)
+    I, J = inputs.sample_indices(m, 24, seed=3), inputs.sample_indices(p, 24, seed=4)
+    want = oracle.dgemm_variant(np.ascontiguousarray(A[I]), np.ascontiguousarray(B[:, J]), k, split, accumulate)
+    assert np.array_equal(got[torch.from_numpy(I).cuda()][:, torch.from_numpy(J).cuda()].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("k", [4, 8, 9, 13])
+@pytest.mark.parametrize("alpha,beta", [(-1.5, 0.0), (0.75, -0.25)])
+def test_step_v_on_ragged_tiles(oz, k, alpha, beta):
+    m, n, p = 333, 190, 277
+    A, B = inputs.phi_pair(m, n, p, 1.0, seed=203)
+    C0 = np.random.Generator(np.random.PCG64(204)).standard_normal((m, p))
+    C = torch.full((m, p + 3), -7.0, dtype=torch.float64, device="cuda")
+    C[:, :p] = dev(C0)
+    oz.gemm_ex(False, False, alpha, dev(A), dev(B), beta, C[:, :p], k)
+    got = C.cpu().numpy()
+    assert np.array_equal(got[:, :p], oracle.gemm_ex(False, False, alpha, A, B, beta, C0, k)) and (got[:, p:] == -7.0).all()
+
+
+@pytest.mark.parametrize("shift", [-520, -480, 0, 480, 497])
+def test_scales_at_the_ends_of_the_exponent_range(oz, shift):
+    # rows and columns scaled by powers of two (the products by 2^(2 shift - 20) to 2^(2 shift + 20), at most 2^1014, and
+    # the sums stay below 2^1024): some tiles hold terms (or results) that are
+    # subnormal or close to overflow and are summed term by term, the others take the scaled sum; same bits as the
+    # persistent launch, which always sums term by term
+    m, n, p, k = 200, 130, 300, 8
+    A, B = inputs.phi_pair(m, n, p, 0.5, seed=205)
+    rng = np.random.Generator(np.random.PCG64(206))
+    A = np.ldexp(A, (shift + rng.integers(-10, 11, size=(m, 1))).astype(np.int32))
+    B = np.ldexp(B, (shift + rng.integers(-10, 11, size=(1, p))).astype(np.int32))
+    dA, dB = dev(A), dev(B)
+    ref = oz.dgemm_variant(dA, dB, k, schedule="one_launch")
+    got = oz.dgemm(dA, dB, k)
+    assert bool(torch.isfinite(ref).all())
+    assert torch.equal(got, ref)
