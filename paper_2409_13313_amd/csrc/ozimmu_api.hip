@@ -599,7 +599,8 @@ int ozimmu_split_A(int64_t m, int64_t n, const double* A, int64_t lda, int k, in
     if (m == 0 || n == 0) return OZIMMU_OK;
     if (!A || !SA || !eA) return OZIMMU_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(SA) % 256) return OZIMMU_ERR_WORKSPACE;
-    return hip_status(ozk::launch_split_A(m, n, A, lda, k, beta_of(n), 0, rn_offset(beta_of(n)), SA, eA, (hipStream_t)stream));
+    const ozk::SplitIn op = {A, lda, m, n, 0, rn_offset(beta_of(n)), SA, eA};
+    return hip_status(ozk::launch_split(&op, 1, k, beta_of(n), 0, (hipStream_t)stream));
 }
 
 int ozimmu_split_B(int64_t n, int64_t p, const double* B, int64_t ldb, int k, int8_t* SB, int32_t* eB, void* stream)
@@ -609,7 +610,8 @@ int ozimmu_split_B(int64_t n, int64_t p, const double* B, int64_t ldb, int k, in
     if (p == 0 || n == 0) return OZIMMU_OK;
     if (!B || !SB || !eB) return OZIMMU_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(SB) % 256) return OZIMMU_ERR_WORKSPACE;
-    return hip_status(ozk::launch_split_B(n, p, B, ldb, k, beta_of(n), 0, rn_offset(beta_of(n)), SB, eB, (hipStream_t)stream));
+    const ozk::SplitIn op = {B, ldb, p, n, 1, rn_offset(beta_of(n)), SB, eB};
+    return hip_status(ozk::launch_split(&op, 1, k, beta_of(n), 0, (hipStream_t)stream));
 }
 
 int ozimmu_gemm_group(int64_t m, int64_t n, int64_t p, const int8_t* SA, int kA, const int8_t* SB, int kB, int g,
@@ -728,13 +730,10 @@ int ozimmu_gemm_ex(int transA, int transB, int64_t m, int64_t n, int64_t p, doub
     const int64_t blocks = (int64_t)((static_cast<char*>(workspace) + workspace_bytes - ws) / BLOCK_BYTES);
 
     // op(A): one scale per row of op(A).  Stored transposed (n x m), those rows are the columns of the
-    // stored matrix, which is what the column-wise split kernel handles; likewise for op(B).
-    hipError_t e = transA ? ozk::launch_split_B(n, m, A, lda, k, bt, 0, rn_offset(bt), SA, eA, st)
-                          : ozk::launch_split_A(m, n, A, lda, k, bt, 0, rn_offset(bt), SA, eA, st);
-    if (e != hipSuccess) return OZIMMU_ERR_HIP;
-    e = transB ? ozk::launch_split_A(p, n, B, ldb, k, bt, 0, rn_offset(bt), SB, eB, st)
-               : ozk::launch_split_B(n, p, B, ldb, k, bt, 0, rn_offset(bt), SB, eB, st, static_cast<uint32_t*>(scratch),
-                                     ozk::SYNC_WORDS);
+    // stored matrix, which the column-wise split handles; likewise for op(B).
+    const ozk::SplitIn ops[2] = {{A, lda, m, n, transA ? 1 : 0, rn_offset(bt), SA, eA},
+                                 {B, ldb, p, n, transB ? 0 : 1, rn_offset(bt), SB, eB}};
+    const hipError_t e = ozk::launch_split(ops, 2, k, bt, 0, st, static_cast<uint32_t*>(scratch), ozk::SYNC_WORDS);
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
 
     // Step (v) rides on the epilogue of every tile's last chunk.  beta == 0: the running sum lives in C and the
@@ -743,7 +742,7 @@ int ozimmu_gemm_ex(int transA, int transB, int64_t m, int64_t n, int64_t p, doub
     const bool in_place = beta == 0.0;
     const Finish fin = {!(alpha == 1.0 && beta == 0.0), alpha, beta, C, ldc};
     return run_schedule(m, n, p, SA, SB, eA, eB, k, r, false, 0, in_place ? C : Dw, in_place ? ldc : p, fin, partial,
-                        blocks, scratch, ds.num_cu, st, !transB);
+                        blocks, scratch, ds.num_cu, st, true);
 }
 
 int ozimmu_dgemm(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, const double* B, int64_t ldb,
@@ -824,8 +823,8 @@ int ozimmu_split_A_variant(int64_t m, int64_t n, const double* A, int64_t lda, i
     if (m == 0 || n == 0) return OZIMMU_OK;
     if (!A || !SA || !eA) return OZIMMU_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(SA) % 256) return OZIMMU_ERR_WORKSPACE;
-    return hip_status(ozk::launch_split_A(m, n, A, lda, k, beta_of(n), split_mode, split_mode == 0 ? rn_offset(beta_of(n)) : 0, SA, eA,
-                                          (hipStream_t)stream));
+    const ozk::SplitIn op = {A, lda, m, n, 0, split_mode == 0 ? rn_offset(beta_of(n)) : 0, SA, eA};
+    return hip_status(ozk::launch_split(&op, 1, k, beta_of(n), split_mode, (hipStream_t)stream));
 }
 
 int ozimmu_split_B_variant(int64_t n, int64_t p, const double* B, int64_t ldb, int k, int split_mode, int8_t* SB,
@@ -836,8 +835,8 @@ int ozimmu_split_B_variant(int64_t n, int64_t p, const double* B, int64_t ldb, i
     if (p == 0 || n == 0) return OZIMMU_OK;
     if (!B || !SB || !eB) return OZIMMU_ERR_NULL;
     if (reinterpret_cast<uintptr_t>(SB) % 256) return OZIMMU_ERR_WORKSPACE;
-    return hip_status(ozk::launch_split_B(n, p, B, ldb, k, beta_of(n), split_mode, split_mode == 0 ? rn_offset(beta_of(n)) : 0, SB, eB,
-                                          (hipStream_t)stream));
+    const ozk::SplitIn op = {B, ldb, p, n, 1, split_mode == 0 ? rn_offset(beta_of(n)) : 0, SB, eB};
+    return hip_status(ozk::launch_split(&op, 1, k, beta_of(n), split_mode, (hipStream_t)stream));
 }
 
 int ozimmu_init(void)
@@ -921,12 +920,14 @@ int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, co
     hipError_t e = mark(0);
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
     const int offset = (split_mode == OZIMMU_SPLIT_NEAREST && accumulate_mode != OZIMMU_ACCUM_WIDE) ? rn_offset(beta) : 0;
-    e = per_slice ? ozk::launch_split_A_per_slice(m, n, A, lda, k, beta, SA, eA, remA, st)
-                  : ozk::launch_split_A(m, n, A, lda, k, beta, split_mode, offset, SA, eA, st);
-    if (e != hipSuccess) return OZIMMU_ERR_HIP;
-    e = per_slice ? ozk::launch_split_B_per_slice(n, p, B, ldb, k, beta, SB, eB, remB, st)
-                  : ozk::launch_split_B(n, p, B, ldb, k, beta, split_mode, offset, SB, eB, st,
-                                        static_cast<uint32_t*>(scratch), ozk::SYNC_WORDS);
+    if (per_slice) {
+        e = ozk::launch_split_A_per_slice(m, n, A, lda, k, beta, SA, eA, remA, st);
+        if (e != hipSuccess) return OZIMMU_ERR_HIP;
+        e = ozk::launch_split_B_per_slice(n, p, B, ldb, k, beta, SB, eB, remB, st);
+    } else {
+        const ozk::SplitIn ops[2] = {{A, lda, m, n, 0, offset, SA, eA}, {B, ldb, p, n, 1, offset, SB, eB}};
+        e = ozk::launch_split(ops, 2, k, beta, split_mode, st, static_cast<uint32_t*>(scratch), ozk::SYNC_WORDS);
+    }
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
     e = mark(1);
     if (e != hipSuccess) return OZIMMU_ERR_HIP;

@@ -7,17 +7,20 @@
 
 namespace ozk {
 
-// Step (i): row exponents + slices of A.  split_mode 0: round to nearest, ceil exponent (Algorithm 8);
-// 1: bit-mask digits, floor exponent (Algorithm 3).  SA is a whole stack (ozl::stack_bytes): slices, prefix row
-// sums, trailer; `offset` is the stack's offset c (stored byte = slice integer + c; needs |q + c| <= 127).
-hipError_t launch_split_A(int64_t m, int64_t n, const double* A, int64_t lda, int k, int beta, int split_mode,
-                          int offset, int8_t* SA, int32_t* eA, hipStream_t st);
-// Step (ii): column exponents + slices of B (the same applied to B^T).
-// also_zero: optional array of also_zero_count 32-bit words that the first kernel of the split clears on the way
-// (the soft-barrier counters of the GEMM that follows: one launch less per call)
-hipError_t launch_split_B(int64_t n, int64_t p, const double* B, int64_t ldb, int k, int beta, int split_mode,
-                          int offset, int8_t* SB, int32_t* eB, hipStream_t st, uint32_t* also_zero = nullptr,
-                          int also_zero_count = 0);
+// Steps (i) and (ii): exponents and slices of one or two operands (in one launch where that pays).  split_mode 0: round to
+// nearest, ceil exponent (Algorithm 8); 1: bit-mask digits, floor exponent (Algorithm 3).
+struct SplitIn {
+    const double* X;
+    int64_t ld, rows, n;   // rows: scaled vectors (rows of A; by_col: columns of B, their elements ld apart); n: their length
+    int by_col;
+    int offset;            // the stack's offset c (stored byte = slice integer + c; needs |q + c| <= 127)
+    int8_t* S;             // a whole stack (ozl::stack_bytes): slices, prefix row sums, trailer
+    int32_t* e;
+};
+// also_zero: optional array of also_zero_count (at most 512) 32-bit words cleared on the way (the soft-barrier counters of
+// the GEMM that follows: one launch less per call)
+hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st,
+                        uint32_t* also_zero = nullptr, int also_zero_count = 0);
 // Algorithm 5: round-to-nearest slices with one scale per slice.  e holds k arrays of exponents (slice-major);
 // rem is scratch for the remainders: m x inner_padded(n) doubles for A, n x p doubles for B.
 hipError_t launch_split_A_per_slice(int64_t m, int64_t n, const double* A, int64_t lda, int k, int beta, int8_t* SA,

@@ -5,22 +5,20 @@
 //   e      = ceil(log2 max |x|) over a row of A / a column of B (0 if all zero)
 //   slice s (s = 1..k) of x = the integer nearest (ties to even) to
 //            remainder / 2^(e + 1 - s beta), remainder reduced accordingly.
-// How: instead of the printed (x + sigma) - sigma trick the kernels scale once,
-//   y_1 = x * 2^(beta - 1 - e)  (exact, |y_1| <= 2^(beta-1)),
-//   q_s = rint(y_s)             (v_rndne_f64: round half to even),
-//   y_{s+1} = (y_s - q_s) * 2^beta   (both exact),
-// which yields the same integers: y_s is remainder / grid_s at every step.
-// Both kernels are HBM-bound: 8 bytes read (A twice when its row does not stay
-// in cache) and k bytes written per element.
+// How: the kernels scale once,
+//   y = x * 2^(beta - 1 - e)  (exact, |y| <= 2^(beta-1)),
+// and then round the remainder to one grid after the other, 1, 2^-beta, 2^(-2 beta), ... (see digits4).
+// The kernels are HBM-bound: 8 bytes read (16 where a vector does not stay in
+// registers or cache) and k bytes written per element.
 // The bytes stored are q_s + c (c = offset of the stack, see ozimmu_layout.h;
-// inner padding counts as a real zero, padding rows of A are all zero bytes); with them go the prefix sums over the slices
-// of the row sums of the stored bytes, which the GEMM epilogue needs to take the
+// inner padding counts as a real zero; padding rows are not written at all: what they hold only reaches outputs that are
+// never stored); with them go the prefix sums over the slices
+// of the row sums of the stored bytes, which the GEMM needs to take the
 // offsets out again.
 #include "ozimmu_kernels.h"
 #include "ozimmu_layout.h"
 
 namespace {
-
 using namespace ozl;
 
 constexpr int OZIMMU_MAX_SLICES_DEV = 20;  // OZIMMU_MAX_SLICES of the C ABI
@@ -95,174 +93,291 @@ __device__ inline uint32_t slice_word4(double* y, int c, double two_beta, int* s
 }
 
 // ---------------------------------------------------------------------------
-// A: one wave per padded row, four consecutive rows per workgroup (their 64-byte
-// segments are adjacent in a packed tile, so the workgroup's stores fill whole
-// 128-byte lines).  Pass 1 reduces max |a_ij| over the row inside the wave,
-// pass 2 re-reads the row (from L2 / Infinity Cache when it is still there)
-// and writes the k slices.  A lane handles 4 consecutive inner elements per
-// 256-element sweep: the wave reads 2 KiB contiguous per sweep.
+// Rows of A and columns of B in one launch.
+//
+// Rows: a workgroup of 8 waves takes ROWS consecutive vectors (4, 2 or 1); a wave
+// covers 256 / ROWS inner positions of them at a time, a lane 4 consecutive ones,
+// so that a slice goes out in runs of 64 ROWS bytes.  Columns: a workgroup takes
+// COLS of them (16, 8 or 4); a wave covers 1024 / COLS inner positions, a lane 16
+// consecutive ones of one column, which is exactly one 16-byte chunk of the packed
+// tile per slice: nothing has to be transposed, and 16 columns x 64 positions are
+// written in one piece of 1 KiB.  (Reads: 8 COLS contiguous bytes per inner position.)
+// Either way a thread keeps up to 16 elements (rows: DBR) in registers: what a
+// workgroup cannot keep it walks in batches of that size, the last batch of the
+// maximum's walk staying in the registers, the others being read again (from L2 or the
+// memory-side cache when they are still there).
+//
+// Bound by HBM where there is enough of it, by latency below: what matters is loads in flight, so more and smaller
+// workgroups with 16 elements a thread beat fewer with more of the row in registers up to inner dimensions of 8192.
+// Measured against the five launches this took before (one pass over A, fill, column maxima, split of B, prefix sums),
+// both operands, k = 8: 256^2 27.6 -> 8.8 us, 1024^2 (k = 9) 41 -> 16, 2048^2 55 -> 29, 4096^2 194 -> 132;
+// rows alone 16384^2 962 -> 907 us (4.7 TB/s, what a plain copy reaches), 65536 x 4096 (k = 10) 1.86 -> 1.23 ms; columns
+// alone, read twice, 4096^2 108 -> 59, 16384^2 1.52 -> 1.34 ms.
 // ---------------------------------------------------------------------------
-template <bool VEC, bool MASK>
-__global__ __launch_bounds__(256) void k_split_A(int64_t m, int64_t n, const double* __restrict__ A, int64_t lda,
-                                                 int k, int beta, int c, int8_t* __restrict__ SA,
-                                                 int32_t* __restrict__ eA, int32_t* __restrict__ P,
-                                                 int32_t* __restrict__ trailer, int64_t Npad, int64_t Rpad,
-                                                 int64_t slice_stride)
+typedef __attribute__((address_space(1))) const double* global_f64;
+
+struct SplitOp {
+    const double* X;      // rows: vector i at X + i ld; columns: vector j at X + j, its elements ld apart
+    int64_t ld, rows, n;
+    int8_t* S;
+    int32_t* e;
+    int32_t* P;
+    int32_t* trailer;
+    int64_t Rpad, slice_stride;
+    int KT, c;
+    int by_col;
+    int vec;              // rows: 16-byte loads are aligned
+    int blocks;           // workgroups
+};
+
+// Digits of 4 consecutive elements for one slice, packed (digit of element j in byte j); the elements become the
+// remainders.  Nearest, ties to even: adding sig = 1.5 * 2^52 grids rounds to the grid and leaves the digit in the low
+// bits of the sum (the published sequence (a + sigma) - sigma; the digit needs no conversion, the remainder no scaling).
+template <bool MASK>
+__device__ inline uint32_t digits4(double* y, double sig, double grid_inv, double grid)
 {
-    __shared__ int lsum[4][OZIMMU_MAX_SLICES_DEV][64];  // per-lane sums of the stored bytes, per slice
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t R = (int64_t)blockIdx.x * 4 + w;
-    const int64_t KT = Npad / TILE_K;
-    if (blockIdx.x == 0 && threadIdx.x == 0) trailer[0] = c;
-
-    if (R >= m) {  // padding row: zeros in every slice, zero sums
-        for (int64_t l = 4 * lane; l < Npad; l += 256)
-            for (int s = 0; s < k; ++s)
-                *reinterpret_cast<uint32_t*>(SA + s * slice_stride + packed_offset(R, l, KT)) = 0u;
-        if (lane < k) P[(int64_t)lane * Rpad + R] = 0;
-        return;
-    }
-    const double* row = A + R * lda;
-
-    auto load4 = [&](int64_t l, double* v) {
-        if (VEC && l + 3 < n) {
-            double2 a = *reinterpret_cast<const double2*>(row + l);
-            double2 b = *reinterpret_cast<const double2*>(row + l + 2);
-            v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
-        } else {
+    uint32_t q[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = (l + j < n) ? row[l + j] : 0.0;
+    for (int j = 0; j < 4; ++j) {
+        if (MASK) {
+            const double d = __builtin_trunc(y[j] * grid_inv);   // (powers of two: exact)
+            q[j] = (uint32_t)__double_as_longlong(d + 6755399441055744.0);
+            y[j] -= d * grid;
+        } else {
+            const double t = y[j] + sig;
+            q[j] = (uint32_t)__double_as_longlong(t);
+            y[j] -= t - sig;
+        }
+    }
+    // (remainders now, four elements at a time: left to the compiler, the sums of all that a thread holds wait in registers
+    // until after the store, and half as many waves fit)
+    asm volatile("" : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]));
+    return __builtin_amdgcn_perm(q[1], q[0], 0x0c0c0400u) | __builtin_amdgcn_perm(q[3], q[2], 0x04000c0cu);
+}
+// the stored bytes digit + c (no carry between bytes: digit + 128 + c stays below 256), and their sum added to *sum
+__device__ inline uint32_t with_offset(uint32_t w, uint32_t c4, int* sum)
+{
+    w = ((w ^ 0x80808080u) + c4) ^ 0x80808080u;
+    *sum = __builtin_amdgcn_sdot4((int)w, 0x01010101, *sum, false);
+    return w;
+}
+
+template <bool MASK>
+__device__ inline int exponent_of(double mx)
+{
+    return key_to_exp<MASK>(exp_key(abs_bits(mx)));
+}
+
+template <int DB, int ROWS, bool MASK>
+__device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int beta, double (*red)[16], int (*lsum)[16])
+{
+    constexpr int LPR = 64 / ROWS;        // lanes of a row
+    constexpr int TPW = 4 / ROWS;         // inner tiles of 64 a wave covers at a time
+    constexpr int U = DB / 4;
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), nw = blockDim.x >> 6;
+    const int64_t R = block * ROWS + lane / LPR;
+    const int li = (lane % LPR) * 4;
+    const bool ok = R < o.rows;
+    const global_f64 row = (global_f64)o.X + (ok ? R : o.rows - 1) * o.ld;  // (lanes past the edge read along and store nothing)
+    const int groups = o.KT / TPW, per_batch = nw * U, nb = (groups + per_batch - 1) / per_batch;
+    double y[U][4];
+    double mx = 0.0;
+    auto load = [&](int b) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int gq = b * per_batch + u * nw + w;
+            const int64_t l = (int64_t)gq * (64 * TPW) + li;
+            if (o.vec && (int64_t)(gq + 1) * (64 * TPW) <= o.n) {  // (uniform)
+                typedef double f64x2 __attribute__((ext_vector_type(2)));
+                typedef __attribute__((address_space(1))) const f64x2* global_f64x2;
+                const f64x2 p = *(global_f64x2)(row + l), q = *(global_f64x2)(row + l + 2);
+                y[u][0] = p.x, y[u][1] = p.y, y[u][2] = q.x, y[u][3] = q.y;
+            } else if (gq < groups) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double v = row[l + j < o.n ? l + j : o.n - 1];
+                    y[u][j] = l + j < o.n ? v : 0.0;
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) y[u][j] = 0.0;
+            }
         }
     };
-
-    uint64_t mx = 0;
-    for (int64_t l = 4 * lane; l < n; l += 256) {
-        double v[4];
-        load4(l, v);
+    for (int b = nb - 1; b >= 0; --b) {
+        load(b);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint64_t b = abs_bits(v[j]);
-            mx = b > mx ? b : mx;
-        }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) mx = fmax(mx, fabs(y[u][j]));
     }
-    mx = wave_max_u64(mx);
-    const int e = key_to_exp<MASK>(exp_key(mx));
-    if (lane == 0) eA[R] = e;
+#pragma unroll
+    for (int off = LPR / 2; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+    if (lane % LPR == 0) red[w][lane / LPR] = mx;
+    for (int i = t; i < k * ROWS; i += blockDim.x) lsum[i / ROWS][i % ROWS] = 0;
+    __syncthreads();
+    for (int q = 0; q < nw; ++q) mx = fmax(mx, red[q][lane / LPR]);
+    const int e = exponent_of<MASK>(mx);
     const int sc = beta - 1 - e;
-    const double two_beta = (double)(1 << beta);
-    for (int s = 0; s < k; ++s) lsum[w][s][lane] = 0;
-
-    for (int64_t l = 4 * lane; l < Npad; l += 256) {
-        double y[4];
-        load4(l, y);
+    const uint32_t c4 = (uint32_t)o.c * 0x01010101u;
+    const double inv_step = ldexp(1.0, -beta), step = (double)(1 << beta);
+    if (w == 0 && lane % LPR == 0 && ok) o.e[R] = e;
+    for (int b = 0; b < nb; ++b) {
+        if (b > 0) load(b);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) y[j] = ldexp(y[j], sc);
-        int8_t* out = SA + packed_offset(R, l, KT);
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) y[u][j] = ldexp(y[u][j], sc);
+        double sig = 6755399441055744.0, grid_inv = 1.0, grid = 1.0;
+        int8_t* out = o.S + packed_offset(R, (int64_t)(b * per_batch + w) * (64 * TPW) + li, o.KT);
         for (int s = 0; s < k; ++s) {
-            int sm;
-            *reinterpret_cast<uint32_t*>(out) = slice_word4<MASK>(y, c, two_beta, &sm);
-            out += slice_stride;
-            lsum[w][s][lane] += sm;
+            int sum = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (b * per_batch + u * nw + w < groups) {
+                    const uint32_t v = with_offset(digits4<MASK>(y[u], sig, grid_inv, grid), c4, &sum);
+                    if (ok) *reinterpret_cast<uint32_t*>(out + (int64_t)u * nw * (TPW * TILE_BYTES)) = v;
+                }
+            }
+            out += o.slice_stride;
+            sig *= inv_step, grid *= inv_step, grid_inv *= step;
+#pragma unroll
+            for (int off = LPR / 2; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+            if (lane % LPR == 0) atomicAdd(&lsum[s][lane / LPR], sum);
         }
     }
-    int run = 0;
-    for (int s = 0; s < k; ++s) {
-        run += wave_sum_i32(lsum[w][s][lane]);
-        if (lane == 0) P[(int64_t)s * Rpad + R] = run;
+    __syncthreads();
+    if (t < ROWS && block * ROWS + t < o.rows) {
+        int run = 0;
+        for (int s = 0; s < k; ++s) {
+            run += lsum[s][t];
+            o.P[(int64_t)s * o.Rpad + block * ROWS + t] = run;
+        }
     }
 }
 
-// ---------------------------------------------------------------------------
-// A, single pass (rows of at most 1024 * GROUPS padded elements; GROUPS = 4, 8 or 16): one workgroup
-// per padded row keeps the whole row in registers (4 * GROUPS doubles per
-// thread), reduces max |a_ij| through LDS and writes the k slices, so A is read
-// from HBM exactly once.  Thread t holds elements 4t + 1024 g .. + 3.
-// Workgroup b serves XCD b % 8 (hardware dispatch order); the row mapping below
-// gives the four rows of a 4-row group (whose 64-byte segments share 256
-// contiguous bytes of a packed tile) to four workgroups of the same XCD, so the
-// partial lines meet in one L2.
-// ---------------------------------------------------------------------------
-template <int GROUPS, bool VEC, bool MASK>
-__global__ __launch_bounds__(256) void k_split_A_row(int64_t m, int64_t n, const double* __restrict__ A, int64_t lda,
-                                                     int k, int beta, int c, int8_t* __restrict__ SA,
-                                                     int32_t* __restrict__ eA, int32_t* __restrict__ P,
-                                                     int32_t* __restrict__ trailer, int64_t Npad, int64_t Rpad,
-                                                     int64_t slice_stride)
+template <int DB, int COLS, bool MASK>
+__device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int beta, double (*red)[16], int (*lsum)[16])
 {
-    __shared__ uint64_t part[4];
-    __shared__ int wsum[4][OZIMMU_MAX_SLICES_DEV];  // per-wave sums of the stored bytes, per slice
-    const int t = threadIdx.x;
-    // the grid has rows_padded(m) workgroups, a multiple of 256, so b / 8 and b % 8 cover whole groups of 32 rows
-    const int64_t b = blockIdx.x, x = b % 8, j = b / 8;
-    const int64_t R = ((j / 4) * 8 + x) * 4 + (j % 4);
-    const int64_t KT = Npad / TILE_K;
-    if (b == 0 && t == 0) trailer[0] = c;
-
-    if (R >= m) {  // padding row: zeros in every slice, zero sums
-        for (int64_t l = 4 * t; l < Npad; l += 1024)
-            for (int s = 0; s < k; ++s)
-                *reinterpret_cast<uint32_t*>(SA + s * slice_stride + packed_offset(R, l, KT)) = 0u;
-        if (t < k) P[(int64_t)t * Rpad + R] = 0;
-        return;
-    }
-    const double* row = A + R * lda;
-    double v[GROUPS][4];
-    uint64_t mx = 0;
+    constexpr int TPW = 16 / COLS;        // inner tiles of 64 a wave covers at a time
+    constexpr int U = DB / 16;
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), nw = blockDim.x >> 6;
+    const int cl = lane % COLS, lb = lane / COLS;
+    const int64_t R = block * COLS + cl;  // column = packed row
+    const bool ok = R < o.rows;
+    const int64_t col = ok ? R : o.rows - 1;  // (lanes past the edge read along and store nothing)
+    const int groups = o.KT / TPW, per_batch = nw * U, nb = (groups + per_batch - 1) / per_batch;
+    double y[U][16];
+    double mx = 0.0;
+    auto load = [&](int b) {
 #pragma unroll
-    for (int g = 0; g < GROUPS; ++g) {
-        const int64_t l = 4 * t + 1024 * g;
-        if (VEC && l + 3 < n) {
-            double2 a = *reinterpret_cast<const double2*>(row + l);
-            double2 d = *reinterpret_cast<const double2*>(row + l + 2);
-            v[g][0] = a.x; v[g][1] = a.y; v[g][2] = d.x; v[g][3] = d.y;
-        } else {
+        for (int u = 0; u < U; ++u) {
+            const int gq = b * per_batch + u * nw + w;
+            const int64_t l = (int64_t)gq * (64 * TPW) + lb * 16;
+            if ((int64_t)(gq + 1) * (64 * TPW) <= o.n) {      // (uniform)
+                // (one running pointer, opaque to the optimiser: sixteen addresses at once cost a third of the registers)
+                global_f64 p = (global_f64)o.X + l * o.ld + col;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[g][q] = (l + q < n) ? row[l + q] : 0.0;
-        }
-    }
+                for (int i = 0; i < 16; ++i) {
+                    y[u][i] = *p;
+                    p += o.ld;
+                    asm volatile("" : "+v"(p));
+                }
+            } else if (gq < groups) {
+                global_f64 p = (global_f64)o.X + col;
 #pragma unroll
-    for (int g = 0; g < GROUPS; ++g)
+                for (int i = 0; i < 16; ++i) {
+                    const int64_t li = l + i < o.n ? l + i : o.n - 1;
+                    const double v = p[li * o.ld];
+                    y[u][i] = l + i < o.n ? v : 0.0;
+                }
+            } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint64_t ab = abs_bits(v[g][q]);
-            mx = ab > mx ? ab : mx;
-        }
-    mx = wave_max_u64(mx);
-    if ((t & 63) == 0) part[t >> 6] = mx;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < 4; ++w) mx = part[w] > mx ? part[w] : mx;
-    const int e = key_to_exp<MASK>(exp_key(mx));
-    if (t == 0) eA[R] = e;
-    const int sc = beta - 1 - e;
-    const double two_beta = (double)(1 << beta);
-#pragma unroll
-    for (int g = 0; g < GROUPS; ++g)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[g][q] = ldexp(v[g][q], sc);
-    // slice after slice over the whole row (the remainders stay in v), so that one sum per slice is reduced
-    for (int s = 0; s < k; ++s) {
-        int tsum = 0;
-#pragma unroll
-        for (int g = 0; g < GROUPS; ++g) {
-            const int64_t l = 4 * t + 1024 * g;
-            if (l < Npad) {
-                int sm;
-                *reinterpret_cast<uint32_t*>(SA + s * slice_stride + packed_offset(R, l, KT)) =
-                    slice_word4<MASK>(v[g], c, two_beta, &sm);
-                tsum += sm;
+                for (int i = 0; i < 16; ++i) y[u][i] = 0.0;
             }
         }
-        tsum = wave_sum_i32(tsum);
-        if ((t & 63) == 0) wsum[t >> 6][s] = tsum;
+    };
+    for (int b = nb - 1; b >= 0; --b) {
+        load(b);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mx = fmax(mx, fabs(y[u][i]));
+    }
+#pragma unroll
+    for (int off = COLS; off < 64; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+    if (lane < COLS) red[w][lane] = mx;
+    for (int i = t; i < k * COLS; i += blockDim.x) lsum[i / COLS][i % COLS] = 0;
+    __syncthreads();
+    for (int q = 0; q < nw; ++q) mx = fmax(mx, red[q][cl]);
+    const int e = exponent_of<MASK>(mx);
+    const int sc = beta - 1 - e;
+    const uint32_t c4 = (uint32_t)o.c * 0x01010101u;
+    const double inv_step = ldexp(1.0, -beta), step = (double)(1 << beta);
+    if (w == 0 && lane < COLS && ok) o.e[R] = e;
+    for (int b = 0; b < nb; ++b) {
+        if (b > 0) load(b);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) y[u][i] = ldexp(y[u][i], sc);
+        double sig = 6755399441055744.0, grid_inv = 1.0, grid = 1.0;
+        int8_t* out = o.S + packed_offset(R, (int64_t)(b * per_batch + w) * (64 * TPW) + lb * 16, o.KT);
+        for (int s = 0; s < k; ++s) {
+            int sum = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (b * per_batch + u * nw + w < groups) {
+                    uint4 v;
+                    v.x = with_offset(digits4<MASK>(y[u], sig, grid_inv, grid), c4, &sum);
+                    v.y = with_offset(digits4<MASK>(y[u] + 4, sig, grid_inv, grid), c4, &sum);
+                    v.z = with_offset(digits4<MASK>(y[u] + 8, sig, grid_inv, grid), c4, &sum);
+                    v.w = with_offset(digits4<MASK>(y[u] + 12, sig, grid_inv, grid), c4, &sum);
+                    if (ok) *reinterpret_cast<uint4*>(out + (int64_t)u * nw * (TPW * TILE_BYTES)) = v;
+                }
+            }
+            out += o.slice_stride;
+            sig *= inv_step, grid *= inv_step, grid_inv *= step;
+#pragma unroll
+            for (int off = COLS; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+            if (lane < COLS) atomicAdd(&lsum[s][lane], sum);
+        }
     }
     __syncthreads();
-    if (t == 0) {
+    if (t < COLS && block * COLS + t < o.rows) {
         int run = 0;
         for (int s = 0; s < k; ++s) {
-            run += wsum[0][s] + wsum[1][s] + wsum[2][s] + wsum[3][s];
-            P[(int64_t)s * Rpad + R] = run;
+            run += lsum[s][t];
+            o.P[(int64_t)s * o.Rpad + block * COLS + t] = run;
         }
+    }
+}
+
+constexpr int SPLIT_WAVES = 8;
+template <int DBR, int ROWS, int COLS, bool MASK>
+__global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : 3) void k_split_both(SplitOp a, SplitOp b, int k, int beta, uint32_t* zero, int zero_count)
+{
+    __shared__ double red[SPLIT_WAVES][16];
+    __shared__ int lsum[OZIMMU_MAX_SLICES_DEV][16];  // sums of the stored bytes per slice and vector
+    const bool second = (int)blockIdx.x >= a.blocks;
+    // (field by field: a reference to one of the two would have the fields loaded into vector registers)
+    SplitOp o;
+    o.X = second ? b.X : a.X, o.ld = second ? b.ld : a.ld, o.rows = second ? b.rows : a.rows, o.n = second ? b.n : a.n;
+    o.S = second ? b.S : a.S, o.e = second ? b.e : a.e, o.P = second ? b.P : a.P, o.trailer = second ? b.trailer : a.trailer;
+    o.Rpad = second ? b.Rpad : a.Rpad, o.slice_stride = second ? b.slice_stride : a.slice_stride;
+    o.KT = second ? b.KT : a.KT, o.c = second ? b.c : a.c, o.by_col = second ? b.by_col : a.by_col;
+    o.vec = second ? b.vec : a.vec;
+    int block = second ? (int)blockIdx.x - a.blocks : (int)blockIdx.x;
+    if (block == 0 && threadIdx.x == 0) o.trailer[0] = o.c;
+    if (blockIdx.x == 0 && (int)threadIdx.x < zero_count) zero[threadIdx.x] = 0u;
+    // (the grid holds whole sets of 32 workgroups per operand: four neighbours share memory lines and run on one XCD)
+    block = (block >> 5) * 32 + (block & 7) * 4 + ((block >> 3) & 3);
+    if (o.by_col) {
+        if ((int64_t)block * COLS >= o.rows) return;
+        split_cols<16, COLS, MASK>(o, block, k, beta, red, lsum);
+    } else {
+        if ((int64_t)block * ROWS >= o.rows) return;
+        split_rows<DBR, ROWS, MASK>(o, block, k, beta, red, lsum);
     }
 }
 
@@ -309,14 +424,12 @@ inline int colmax_rows(int64_t n, int64_t p)
     return lch;
 }
 
-// two fills in one launch: x[0, cx) = vx and y[0, cy) = vy, then z[0, cz) = 0 (any count may be 0)
-__global__ void k_fill3_u32(int64_t cx, uint32_t* x, uint32_t vx, int64_t cy, uint32_t* y, uint32_t vy, int64_t cz,
-                            uint32_t* z)
+// two fills in one launch: x[0, cx) = vx and y[0, cy) = vy
+__global__ void k_fill2_u32(int64_t cx, uint32_t* x, uint32_t vx, int64_t cy, uint32_t* y, uint32_t vy)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < cx) x[i] = vx;
     if (i < cy) y[i] = vy;
-    if (i < cz) z[i] = 0u;
 }
 
 __global__ void k_fill_u32(int64_t count, uint32_t* x, uint32_t v)
@@ -609,83 +722,133 @@ __global__ void k_set_i32(int32_t* x, int32_t v) { x[0] = v; }
 }  // namespace
 namespace ozk {
 
-hipError_t launch_split_A(int64_t m, int64_t n, const double* A, int64_t lda, int k, int beta, int split_mode,
-                          int offset, int8_t* SA, int32_t* eA, hipStream_t st)
+// The columns of an operand with the inner dimension cut across workgroups: for few long columns, which would otherwise
+// leave most of the chip idle (128 columns of 65536, k = 8: 87 against 198 us).
+static hipError_t launch_split_cols_cut(const SplitIn& i, int k, int beta, int split_mode, hipStream_t st)
 {
-    const int64_t Rpad = ozl::rows_padded(m), Npad = ozl::inner_padded(n);
-    const int64_t stride = ozl::slice_bytes(m, n);
-    int32_t* P = reinterpret_cast<int32_t*>(SA + ozl::sums_offset(m, n, k));
-    int32_t* trailer = reinterpret_cast<int32_t*>(SA + ozl::trailer_offset(m, n, k));
-    const bool vec = (reinterpret_cast<uintptr_t>(A) % 16 == 0) && (lda % 2 == 0);
-    const bool mask = split_mode != 0;
-    if (Npad <= 16384) {  // the row fits the registers of one workgroup: single pass over A
-        dim3 grid((unsigned)Rpad), block(256);
-#define OZ_LAUNCH_ROW(G, V, M)                                                                                    \
-    hipLaunchKernelGGL((k_split_A_row<G, V, M>), grid, block, 0, st, m, n, A, lda, k, beta, offset, SA, eA, P, trailer, \
-                       Npad, Rpad, stride)
-#define OZ_PICK_ROW(G)                         \
-    do {                                       \
-        if (vec && !mask) OZ_LAUNCH_ROW(G, true, false);       \
-        else if (!vec && !mask) OZ_LAUNCH_ROW(G, false, false); \
-        else if (vec) OZ_LAUNCH_ROW(G, true, true);             \
-        else OZ_LAUNCH_ROW(G, false, true);                     \
-    } while (0)
-        if (Npad <= 4096)
-            OZ_PICK_ROW(4);
-        else if (Npad <= 8192)
-            OZ_PICK_ROW(8);
-        else
-            OZ_PICK_ROW(16);
-#undef OZ_PICK_ROW
-#undef OZ_LAUNCH_ROW
-        return hipGetLastError();
-    }
-    dim3 grid((unsigned)(Rpad / 4)), block(256);
-#define OZ_LAUNCH_A(V, M)                                                                                          \
-    hipLaunchKernelGGL((k_split_A<V, M>), grid, block, 0, st, m, n, A, lda, k, beta, offset, SA, eA, P, trailer, Npad, \
-                       Rpad, stride)
-    if (vec && !mask)
-        OZ_LAUNCH_A(true, false);
-    else if (!vec && !mask)
-        OZ_LAUNCH_A(false, false);
-    else if (vec)
-        OZ_LAUNCH_A(true, true);
-    else
-        OZ_LAUNCH_A(false, true);
-#undef OZ_LAUNCH_A
-    return hipGetLastError();
-}
-
-hipError_t launch_split_B(int64_t n, int64_t p, const double* B, int64_t ldb, int k, int beta, int split_mode,
-                          int offset, int8_t* SB, int32_t* eB, hipStream_t st, uint32_t* also_zero,
-                          int also_zero_count)
-{
+    const int64_t n = i.n, p = i.rows;
     const int64_t Rpad = ozl::rows_padded(p), Npad = ozl::inner_padded(n);
     const int64_t stride = ozl::slice_bytes(p, n);
-    int32_t* P = reinterpret_cast<int32_t*>(SB + ozl::sums_offset(p, n, k));
-    int32_t* trailer = reinterpret_cast<int32_t*>(SB + ozl::trailer_offset(p, n, k));
-    const int64_t nsums = (int64_t)k * Rpad;
-    const int64_t nfill = nsums > p ? (nsums > also_zero_count ? nsums : also_zero_count)
-                                    : (p > also_zero_count ? p : also_zero_count);
-    hipLaunchKernelGGL(k_fill3_u32, dim3((unsigned)((nfill + 255) / 256)), dim3(256), 0, st, p,
-                       reinterpret_cast<uint32_t*>(eB), RAW_KEY_TAG, nsums, reinterpret_cast<uint32_t*>(P), 0u,
-                       also_zero ? also_zero_count : 0, also_zero);
+    int32_t* P = reinterpret_cast<int32_t*>(i.S + ozl::sums_offset(p, n, k));
+    int32_t* trailer = reinterpret_cast<int32_t*>(i.S + ozl::trailer_offset(p, n, k));
+    const int64_t nsums = (int64_t)k * Rpad, nfill = nsums > p ? nsums : p;
+    hipLaunchKernelGGL(k_fill2_u32, dim3((unsigned)((nfill + 255) / 256)), dim3(256), 0, st, p,
+                       reinterpret_cast<uint32_t*>(i.e), RAW_KEY_TAG, nsums, reinterpret_cast<uint32_t*>(P), 0u);
     const int lch = colmax_rows(n, p);
     dim3 gmax((unsigned)((n + lch - 1) / lch), (unsigned)((p + 63) / 64));
-    hipLaunchKernelGGL(k_colmax_B, gmax, dim3(256), 0, st, n, p, B, ldb, reinterpret_cast<uint32_t*>(eB), lch,
+    hipLaunchKernelGGL(k_colmax_B, gmax, dim3(256), 0, st, n, p, i.X, i.ld, reinterpret_cast<uint32_t*>(i.e), lch,
                        RAW_KEY_TAG);
     // a workgroup takes 4 consecutive blocks of 128 inner rows once there are enough blocks to fill the chip anyway
     const int64_t blocks = Npad / 128;
     const int per_wg = blocks >= 32 ? 4 : 1;
     dim3 grid((unsigned)((blocks + per_wg - 1) / per_wg), (unsigned)(Rpad / 64));
     if (split_mode == 0) {
-        hipLaunchKernelGGL(k_split_B<false>, grid, dim3(256), 0, st, n, p, B, ldb, k, beta, offset, SB, eB, P, trailer,
+        hipLaunchKernelGGL(k_split_B<false>, grid, dim3(256), 0, st, n, p, i.X, i.ld, k, beta, i.offset, i.S, i.e, P, trailer,
                            Npad, Rpad, stride, per_wg);
     } else {
-        hipLaunchKernelGGL(k_split_B<true>, grid, dim3(256), 0, st, n, p, B, ldb, k, beta, offset, SB, eB, P, trailer,
+        hipLaunchKernelGGL(k_split_B<true>, grid, dim3(256), 0, st, n, p, i.X, i.ld, k, beta, i.offset, i.S, i.e, P, trailer,
                            Npad, Rpad, stride, per_wg);
     }
     hipLaunchKernelGGL(k_prefix_sums, dim3((unsigned)((Rpad + 255) / 256)), dim3(256), 0, st, Rpad, k, P);
+    return hipGetLastError();
+}
+
+static SplitOp make_op(const SplitIn& i, int k)
+{
+    SplitOp o{};
+    o.X = i.X;
+    o.ld = i.ld;
+    o.rows = i.rows;
+    o.n = i.n;
+    o.S = i.S;
+    o.e = i.e;
+    o.P = reinterpret_cast<int32_t*>(i.S + ozl::sums_offset(i.rows, i.n, k));
+    o.trailer = reinterpret_cast<int32_t*>(i.S + ozl::trailer_offset(i.rows, i.n, k));
+    o.Rpad = ozl::rows_padded(i.rows);
+    o.slice_stride = ozl::slice_bytes(i.rows, i.n);
+    o.KT = (int)(ozl::inner_padded(i.n) / ozl::TILE_K);
+    o.c = i.offset;
+    o.by_col = i.by_col;
+    o.vec = reinterpret_cast<uintptr_t>(i.X) % 16 == 0 && i.ld % 2 == 0;
+    return o;
+}
+
+hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,
+                        int also_zero_count)
+{
+    SplitOp op[2]{};
+    int used = 0, rows = 0, cols = 0;
+    for (int q = 0; q < count; ++q) {
+        const SplitIn& i = ops[q];
+        if (i.by_col) {
+            // A workgroup streams its columns at some 30 bytes per ns, 16 + k bytes per element, four columns at least;
+            // the other way costs about 60 us of launches and merging and moves 2.9 TB/s.
+            const double own_us = (double)i.n * 4 * (16 + k) / 30e3;
+            const double cut_us = 60.0 + (double)i.n * (double)i.rows * (16 + k) / 2.9e6;
+            if (own_us > cut_us) {
+                const hipError_t e = launch_split_cols_cut(i, k, beta, split_mode, st);
+                if (e != hipSuccess) return e;
+                continue;
+            }
+        }
+        SplitOp o = make_op(i, k);
+        // As many workgroups as it takes to fill the chip, else runs of memory as long as possible: 16 columns from 256
+        // workgroups on (4096 columns of 4096: 59 us with 16, 67 with 8, 71 with 4; 1024 columns: 41, 26, 21), rows by two
+        // where a row keeps 8 waves busy (4096 rows of 4096: 49 us, by four 58; 1024 rows of 1024: 9.0 and 7.9), one by one
+        // where there are few (256 rows of 16384: 21 us, by two 24).
+        if (i.by_col) {
+            const int c = i.rows >= 4096 ? 16 : i.rows >= 2048 ? 8 : 4;
+            if (cols == 0 || c < cols) cols = c;
+        } else {
+            const int r = i.n < 2048 ? 4 : (i.n > 8192 && i.rows <= 512) ? 1 : 2;
+            if (rows == 0 || r < rows) rows = r;
+        }
+        op[used++] = o;
+    }
+    if (used == 0) {
+        if (also_zero_count > 0)
+            hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)((also_zero_count + 255) / 256)), dim3(256), 0, st, also_zero_count,
+                               also_zero, 0u);
+        return hipGetLastError();
+    }
+    const int64_t n = op[0].n;
+    if (rows == 0) rows = n < 2048 ? 4 : 2;
+    if (cols == 0) cols = 16;
+    // whole sets of 32 workgroups per operand (see k_split_both)
+    for (int q = 0; q < used; ++q) {
+        const int per = op[q].by_col ? cols : rows;
+        op[q].blocks = (int)(((op[q].rows + per - 1) / per + 31) / 32 * 32);
+    }
+    const dim3 grid((unsigned)(op[0].blocks + op[1].blocks)), block(64 * SPLIT_WAVES);
+    // (beyond 8192 inner positions a row is kept in 64 registers a thread: 16384^2 907 us, with 16 of them 993)
+#define OZ_SPLIT(D, R, C)                                                                                             \
+    do {                                                                                                             \
+        if (split_mode == 0)                                                                                         \
+            hipLaunchKernelGGL((k_split_both<D, R, C, false>), grid, block, 0, st, op[0], op[1], k, beta, also_zero, \
+                               also_zero_count);                                                                     \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_split_both<D, R, C, true>), grid, block, 0, st, op[0], op[1], k, beta, also_zero,  \
+                               also_zero_count);                                                                     \
+    } while (0)
+#define OZ_SPLIT_COLS(D, R)             \
+    do {                                \
+        if (cols == 16)                 \
+            OZ_SPLIT(D, R, 16);         \
+        else if (cols == 8)             \
+            OZ_SPLIT(D, R, 8);          \
+        else                            \
+            OZ_SPLIT(D, R, 4);          \
+    } while (0)
+    if (n > 8192 && rows == 1)
+        OZ_SPLIT_COLS(64, 1);
+    else if (n > 8192)
+        OZ_SPLIT_COLS(64, 2);
+    else if (rows == 2)
+        OZ_SPLIT_COLS(16, 2);
+    else
+        OZ_SPLIT_COLS(16, 4);
+#undef OZ_SPLIT_COLS
+#undef OZ_SPLIT
     return hipGetLastError();
 }
 

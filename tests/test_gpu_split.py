@@ -1,0 +1,66 @@
+"""GPU parity of the split kernels at the sizes where they can go wrong: the batches a workgroup walks when a vector does not
+fit its registers (8 waves of 64 lanes with 16 or 64 elements each), the number of vectors per workgroup (1, 2, 4 rows;
+4, 8, 16 columns), remainders of all of these, alignment, and the few long columns that are cut across workgroups.
+Slices and exponents bit for bit against the oracle; the sums behind the slices through a product."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2409_13313_amd import inputs
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def oz():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: the HIP path has no CPU fallback")
+    from paper_2409_13313_amd import ozimmu
+    return ozimmu
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+# (vectors, length): 4 rows / 2 rows / 1 row a workgroup; one batch and several; lengths around 64, 256, 512 and 8192
+SHAPES = [(1, 1), (3, 63), (5, 64), (33, 255), (130, 513), (7, 2047), (6, 2049), (9, 4100), (5, 8192), (3, 8193), (2, 16390),
+          (515, 8200), (2050, 130), (4100, 70), (3, 70000)]
+
+
+@pytest.mark.parametrize("split", ["rn", "bitmask"])
+@pytest.mark.parametrize("rows,n", SHAPES)
+def test_rows_and_columns_match_the_oracle_bit_for_bit(oz, rows, n, split):
+    k = 5 if rows * n > 100000 else 9
+    A, _ = inputs.phi_pair(rows, n, 1, 2.0, seed=301)
+    A[0, : n // 2] = 0.0                       # (a vector whose largest element sits in its last batch)
+    pad = n % 3                                # rows with and without the alignment for 16-byte loads
+    Ap = torch.zeros((rows, n + pad), dtype=torch.float64, device="cuda")
+    Ap[:, :n] = dev(A)
+    beta, _ = oracle.params(n)
+    want, we = oracle.split_rows(A, k, beta, form="int" if split == "rn" else "bitmask")
+    S, e = oz.split_A(Ap[:, :n], k, split)
+    assert np.array_equal(e.cpu().numpy(), we)
+    assert np.array_equal(oz.export_slices(rows, n, k, S).cpu().numpy(), want)
+    Bp = torch.zeros((n, rows + pad), dtype=torch.float64, device="cuda")
+    Bp[:, :rows] = dev(A.T)
+    S, e = oz.split_B(Bp[:, :rows], k, split)
+    assert np.array_equal(e.cpu().numpy(), we)
+    assert np.array_equal(oz.export_slices(rows, n, k, S).cpu().numpy(), want)
+    few = np.ascontiguousarray(A[:2])          # the same vectors as rows and as columns of one call
+    got = oz.dgemm_variant(Ap[:, :n], dev(few.T), k, split).cpu().numpy()
+    assert np.array_equal(got, oracle.dgemm_variant(A, few.T, k, split))
+    got = oz.dgemm_variant(dev(few), Bp[:, :rows], k, split).cpu().numpy()
+    assert np.array_equal(got, oracle.dgemm_variant(few, A.T, k, split))
+
+
+@pytest.mark.parametrize("transA,transB", [(True, True), (True, False), (False, True)])
+def test_both_operands_by_columns_or_by_rows(oz, transA, transB):
+    # operand pairs of one kind, with different numbers of vectors (the smaller choice of columns / rows a workgroup serves both)
+    m, n, p, k = 2100, 600, 40, 6
+    A, B = inputs.phi_pair(m, n, p, 1.0, seed=302)
+    a, b = (np.ascontiguousarray(A.T) if transA else A), (np.ascontiguousarray(B.T) if transB else B)
+    C = torch.full((m, p), float("nan"), dtype=torch.float64, device="cuda")
+    oz.gemm_ex(transA, transB, 1.0, dev(a), dev(b), 0.0, C, k)
+    assert np.array_equal(C.cpu().numpy(), oracle.dgemm(A, B, k))
