@@ -87,7 +87,14 @@ constexpr Range chunk_range(int c)
 // number gi = 0 .. L - 1 belongs to j = L - gi: first the pairs of low slices whose larger one is j, then those of the
 // high slice h = k + 1 - j (if h > L) with the low slices 1 .. j.  After it slice j is used up for this step: its
 // registers take slice j of the NEXT step at the start of the next group.  The high slices pass through two buffers.
-template <int K, int R, int TA, int TB>
+//
+// Groups are gathered into intervals, each opened by a barrier: what an interval reads from LDS has landed before it, and
+// the copies that replace what an interval has read go out in the one after.  Few of them, because a barrier costs some
+// 80 ns (with one per group, one workgroup on a compute unit, 1024^3, k = 9: 1.76 us a step for 1.37 us of MFMAs): two for a ring
+// of two steps, where a copy has a whole step to arrive; three for a ring of one - first group, second group, the rest -
+// which leaves every copy some 2000 cycles; five beyond 13 slices,
+// where the rest has grown too long (8192^3, k = 16: 40.0 ms with three, 38.4 with five; k = 12 23.7 and 24.3).
+template <int K, int R, int TA, int TB, int D>
 struct Plan {
     static constexpr int L = (K + 1) / 2;
     static constexpr int NP = K * (K + 1) / 2;
@@ -96,13 +103,18 @@ struct Plan {
     static constexpr int NM = NP * TT;          // MFMAs of a step
     static constexpr int NF = TA + TB;          // fragments of a slice
     static constexpr int NC = (2 * NF + 3) / 4;  // copies (of 16 rows) per wave and slice
+    static constexpr int NI = D == 2 ? 2 : (L < 3 ? L : (K > 13 ? 5 : 3));
 
     int s[NP] = {}, t[NP] = {};
     int group_at[L + 1] = {};        // first MFMA of a group
     int nread[L] = {}, read_slice[L][3] = {};  // slices whose fragments are fetched in a group
     bool read_next[L][3] = {};       // ... for the next step
-    // per MFMA index: fragment fetch (group-local list position) and copy, -1 = none
-    int read_pos[NM] = {}, copy_pos[NM] = {}, group_of[NM] = {};
+    int first_group[NI + 1] = {};    // groups of an interval
+    int nslot[NI] = {}, slot_slice[NI][K] = {};  // the same by interval
+    bool slot_next[NI][K] = {};
+    // per MFMA index: group, interval, fragment fetch (group-local list position) and copy (interval-local), -1 = none
+    int read_pos[NM] = {}, copy_pos[NM] = {}, group_of[NM] = {}, interval_of[NM] = {};
+    bool opens[NM] = {};             // first MFMA of an interval
 
     constexpr int high(int j) const { return K + 1 - j > L ? K + 1 - j : 0; }
     constexpr Plan()
@@ -135,19 +147,39 @@ struct Plan {
             if (j >= 2 && high(j - 1)) add(high(j - 1), false);
         }
         group_at[L] = NM;
+        if (D == 2) {
+            // two intervals of about equal length
+            int g = 1;
+            while (g < L - 1 && 2 * group_at[g] < NM) ++g;
+            first_group[1] = L == 1 ? 1 : g;
+        } else {
+            for (int v = 1; v < NI; ++v) first_group[v] = v;
+        }
+        first_group[NI] = L;
+        for (int v = 0; v < NI; ++v)
+            for (int gi = first_group[v]; gi < first_group[v + 1]; ++gi)
+                for (int x = 0; x < nread[gi]; ++x) {
+                    slot_slice[v][nslot[v]] = read_slice[gi][x];
+                    slot_next[v][nslot[v]++] = read_next[gi][x];
+                }
         for (int q = 0; q < NM; ++q) read_pos[q] = copy_pos[q] = -1;
+        auto spread = [](int len, int count, int most) {
+            int sp = len / (count + 2);
+            sp = sp > most ? most : sp;
+            return sp < 1 ? 1 : sp;
+        };
         for (int gi = 0; gi < L; ++gi) {
             const int len = group_at[gi + 1] - group_at[gi];
             for (int q = group_at[gi]; q < group_at[gi + 1]; ++q) group_of[q] = gi;
-            auto spread = [&](int count, int most) {
-                int sp = len / (count + 2);
-                sp = sp > most ? most : sp;
-                return sp < 1 ? 1 : sp;
-            };
-            const int nr = nread[gi] * NF, nc = nread[(gi + L - 1) % L] * NC;
-            const int spr = spread(nr, TT <= 4 ? 2 : 4), spc = spread(nc, 4);
+            const int nr = nread[gi] * NF, spr = spread(len, nr, TT <= 4 ? 2 : 4);
             for (int x = 0; x < nr; ++x) read_pos[group_at[gi] + (x * spr < len ? x * spr : len - 1)] = x;
-            for (int x = 0; x < nc; ++x) copy_pos[group_at[gi] + (x * spc + 1 < len ? x * spc + 1 : len - 1)] = x;
+        }
+        for (int v = 0; v < NI; ++v) {
+            const int at = group_at[first_group[v]], len = group_at[first_group[v + 1]] - at;
+            opens[at] = true;
+            for (int q = at; q < at + len; ++q) interval_of[q] = v;
+            const int nc = nslot[(v + NI - 1) % NI] * NC, spc = spread(len, nc, 4);
+            for (int x = 0; x < nc; ++x) copy_pos[at + (x * spc + 1 < len ? x * spc + 1 : len - 1)] = x;
         }
     }
 };
@@ -197,9 +229,9 @@ __device__ inline void tile_of_block(int b, int TM, int TP, int& tm, int& tp)
 template <int K, int R, int TA, int TB, int D, int WAVES>
 __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
 {
-    using P = Plan<K, R, TA, TB>;
+    using P = Plan<K, R, TA, TB, D>;
     static constexpr P plan{};
-    constexpr int L = P::L, W = P::W, NF = P::NF;
+    constexpr int L = P::L, W = P::W, NF = P::NF, NI = P::NI;
     constexpr int RA = 32 * TA, RB = 32 * TB;               // rows and columns of the workgroup's tile
     constexpr int SLOT = (RA + RB) * TILE_K;                // one slice of both operands: A rows, then B columns
     constexpr int SET = K * SLOT;                           // all slices of an inner step
@@ -300,36 +332,18 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
 
     const uint32_t lv = (uint32_t)lane * 16u;
     auto step_off = [&](int kt) { return (uint32_t)(kt < KT - 1 ? kt : KT - 1) * (uint32_t)TILE_BYTES; };
-    // Copies of step 0 - and of step 1 for a ring of two - in the order of the loop, so that its counted waits hold from
-    // the start: what group gi reads, gi = 0 .. L - 1, a low slice for the step after (slice 2 belongs to the last group
-    // and is brought by group 0 of the loop).  Before that, the low slices 2 .. L of step 0 themselves.
     static_assert(L >= 2, "at least three slices");
-    auto copy_group = [&](auto GI, int step, uint32_t m0_this, uint32_t m0_next) __attribute__((always_inline)) {
-        constexpr int gi = decltype(GI)::value;
-        static_for<plan.nread[gi]>([&](auto X) __attribute__((always_inline)) {
-            constexpr int sl = plan.read_slice[gi][decltype(X)::value];
-            constexpr bool next = plan.read_next[gi][decltype(X)::value];
-            copy_slice(std::integral_constant<int, sl>{}, next ? m0_next : m0_this, lv + step_off(step + (next ? 1 : 0)));
-        });
-    };
-    static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
-        copy_slice(std::integral_constant<int, L - decltype(X)::value>{}, m0_cur, lv);
-    });
-    copy_group(std::integral_constant<int, 0>{}, 0, m0_cur, m0_nxt);
-    // Start values and exponents, their loads behind the first copies (memory operations return in order: whoever waits for
-    // these has the copies as well, and needs them).
+    // What the compiler loads itself goes out first - scale exponents and the prefix sums of the stored bytes for the start
+    // values -, then the first copies; all of it is on its way before anything is waited for.  (With the loads behind the
+    // copies and a branch on the offsets, three latencies in a row: 6.5 us from the first instruction to the loop at 4096^3,
+    // k = 8; now 3.8 us, 2.8 us on an idle chip.)
+    const int cA = a.cA[0], cB = a.cB[0];
+    int exp_row = 0, exp_col = 0;
+    v4i pa[K][TA];
+    int pb[K][TB];
+    if (t < RA && row0 + t < a.m) exp_row = a.eA[row0 + t];
+    if (t < RB && col0 + t < a.p) exp_col = a.eB[col0 + t];
     {
-        const int cA = a.cA[0], cB = a.cB[0];
-        if (t < RA) {
-            const uint32_t gr = row0 + t;
-            lds_exp[t] = (int64_t)gr < a.m ? a.eA[gr] : 0;
-        }
-        if (t < RB) {
-            const uint32_t gc = col0 + t;
-            lds_exp[RA + t] = (int64_t)gc < a.p ? a.eB[gc] : 0;
-        }
-        // The accumulators of a chunk start at -(ra[row] + cb[column]) (see the head of ozimmu_gemm.hip); the inner
-        // positions past the last step carry q = 0, i.e. the offsets themselves, in the stored sums.
         // (row and column tiles past the padding take any sums: their results are never stored)
         uint32_t rr[TA], cc[TB];
 #pragma unroll
@@ -342,45 +356,55 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
             const uint32_t c0 = col0 + wn * (16 * TB) + 16 * j, top = (uint32_t)a.pstrideB - 16u;
             cc[j] = (c0 < top ? c0 : top) + (lane & 15);
         }
-        static_for<W>([&](auto C) __attribute__((always_inline)) {
-            constexpr int c = decltype(C)::value;
-            constexpr Range range = chunk_range<K, R>(c);
-            constexpr int s0 = range.s0, s1 = range.s1, t0 = range.g - s1, t1 = range.g - s0;
-            if (cA | cB) {
-                v4i sa[TA];
-                int sb[TB];
 #pragma unroll
-                for (int i = 0; i < TA; ++i) {
-                    sa[i] = *reinterpret_cast<const v4i*>(a.PA + (int64_t)(s1 - 1) * a.pstrideA + rr[i]);
-                    if (s0 > 1) sa[i] -= *reinterpret_cast<const v4i*>(a.PA + (int64_t)(s0 - 2) * a.pstrideA + rr[i]);
-                }
+        for (int q = 0; q < K; ++q) {
 #pragma unroll
-                for (int j = 0; j < TB; ++j) {
-                    sb[j] = a.PB[(int64_t)(t1 - 1) * a.pstrideB + cc[j]];
-                    if (t0 > 1) sb[j] -= a.PB[(int64_t)(t0 - 2) * a.pstrideB + cc[j]];
-                }
-                const uint32_t fix = (uint32_t)((s1 - s0 + 1) * cA * cB) * (uint32_t)((2 * a.KT - KT) * TILE_K);
+            for (int i = 0; i < TA; ++i) pa[q][i] = *reinterpret_cast<const v4i*>(a.PA + (int64_t)q * a.pstrideA + rr[i]);
 #pragma unroll
-                for (int i = 0; i < TA; ++i)
-#pragma unroll
-                    for (int j = 0; j < TB; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            acc[c][i][j][r] = (int)(fix - (uint32_t)cB * (uint32_t)sa[i][r] - (uint32_t)cA * (uint32_t)sb[j]);
-            } else {
-#pragma unroll
-                for (int i = 0; i < TA; ++i)
-#pragma unroll
-                    for (int j = 0; j < TB; ++j) acc[c][i][j] = (v4i){0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int i = 0; i < TA; ++i)
-#pragma unroll
-                for (int j = 0; j < TB; ++j) asm volatile("" : "+a"(acc[c][i][j]));
-            if constexpr (c % 8 == 7) __builtin_amdgcn_sched_barrier(0);
-        });
+            for (int j = 0; j < TB; ++j) pb[q][j] = a.PB[(int64_t)q * a.pstrideB + cc[j]];
+        }
     }
-    wait_vmcnt<P::NC * plan.nread[0]>();
+    // Copies of the first steps in the order of the loop, so that its counted waits hold from the start: what interval v
+    // reads in `step` (a low slice for the step after).  Before that, the low slices 2 .. L of step 0 themselves.
+    auto copy_interval = [&](auto V, auto STEP) __attribute__((always_inline)) {
+        constexpr int v = decltype(V)::value;
+        static_for<plan.nslot[v]>([&](auto X) __attribute__((always_inline)) {
+            constexpr int x = decltype(X)::value, data = decltype(STEP)::value + (plan.slot_next[v][x] ? 1 : 0);
+            copy_slice(std::integral_constant<int, plan.slot_slice[v][x]>{}, (data & 1) ? m0_nxt : m0_cur, lv + step_off(data));
+        });
+    };
+    constexpr std::integral_constant<int, 0> step0{};
+    static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
+        copy_slice(std::integral_constant<int, L - decltype(X)::value>{}, m0_cur, lv);
+    });
+    static_for<D == 2 ? NI : 1>([&](auto V) __attribute__((always_inline)) { copy_interval(V, step0); });
+    if (t < RA) lds_exp[t] = exp_row;
+    if (t < RB) lds_exp[RA + t] = exp_col;
+    // The accumulators of a chunk start at -(ra[row] + cb[column]) (see the head of ozimmu_gemm.hip); the inner positions
+    // past the last step carry q = 0, i.e. the offsets themselves, in the stored sums.
+    static_for<W>([&](auto C) __attribute__((always_inline)) {
+        constexpr int c = decltype(C)::value;
+        constexpr Range range = chunk_range<K, R>(c);
+        constexpr int s0 = range.s0, s1 = range.s1, t0 = range.g - s1, t1 = range.g - s0;
+        const uint32_t fix = (uint32_t)((s1 - s0 + 1) * cA * cB) * (uint32_t)((2 * a.KT - KT) * TILE_K);
+        uint32_t cb[TB];
+#pragma unroll
+        for (int j = 0; j < TB; ++j) cb[j] = fix - (uint32_t)cA * (uint32_t)(pb[t1 - 1][j] - (t0 > 1 ? pb[t0 > 1 ? t0 - 2 : 0][j] : 0));
+#pragma unroll
+        for (int i = 0; i < TA; ++i) {
+            uint32_t ra[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                ra[r] = (uint32_t)cB * (uint32_t)(pa[s1 - 1][i][r] - (s0 > 1 ? pa[s0 > 1 ? s0 - 2 : 0][i][r] : 0));
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[c][i][j][r] = (int)(cb[j] - ra[r]);
+                asm volatile("" : "+a"(acc[c][i][j]));
+            }
+        }
+    });
+    wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
@@ -390,15 +414,12 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
     wait_lds();
     __builtin_amdgcn_s_barrier();  // every wave has the low slices of step 0: their slots are free
     asm volatile("" ::: "memory");
-    static_for<L - 2>([&](auto GI) __attribute__((always_inline)) {
-        copy_group(std::integral_constant<int, decltype(GI)::value + 1>{}, 0, m0_cur, m0_nxt);
-    });
-    if constexpr (D == 2) {
-        copy_slice(std::integral_constant<int, 2>{}, m0_nxt, lv + step_off(1));
-        static_for<L - 1>([&](auto GI) __attribute__((always_inline)) {
-            copy_group(std::integral_constant<int, decltype(GI)::value>{}, 1, m0_nxt, m0_cur);
+    if constexpr (D == 2)
+        static_for<NI - 1>([&](auto V) __attribute__((always_inline)) { copy_interval(V, std::integral_constant<int, 1>{}); });
+    else if constexpr (NI > 2)
+        static_for<NI - 2>([&](auto V) __attribute__((always_inline)) {
+            copy_interval(std::integral_constant<int, decltype(V)::value + 1>{}, step0);
         });
-    }
 
     uint32_t m0_sum = m0_cur + m0_nxt, fsum[2][2];
 #pragma unroll
@@ -411,15 +432,16 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
     if (D == 2) asm volatile("" : "+s"(m0_sum));
     // where the copies of a step read: what is fetched for this step is followed by step kt + D in its place (v1), what is
     // fetched for the next one by step kt + 1 + D (v2; past the end: the last step again, never used)
-    uint32_t v1 = lv + step_off(D), v2 = v1;
+    // (v0: v1 of the step before, for what the last interval of that step read for itself)
+    uint32_t v0 = lv + step_off(D - 1), v1 = lv + step_off(D), v2 = v1;
     for (int kt = 0; kt < KT; ++kt) {
         static_for<P::NM>([&](auto Q) __attribute__((always_inline)) {
             constexpr int q = decltype(Q)::value;
-            constexpr int gi = plan.group_of[q], gp = (gi + L - 1) % L;
-            if constexpr (plan.group_at[gi] == q) {
-                // what this group reads has landed, and every wave has what the group before read
+            constexpr int gi = plan.group_of[q], v = plan.interval_of[q], vp = (v + NI - 1) % NI;
+            if constexpr (plan.opens[q]) {
+                // what this interval reads has landed, and every wave has what the interval before read
                 wait_lds();
-                wait_vmcnt<P::NC * (D * K - plan.nread[gi] - plan.nread[gp])>();
+                wait_vmcnt<P::NC * (D * K - plan.nslot[v] - plan.nslot[vp])>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_sched_barrier(0);
@@ -429,10 +451,6 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
                 // MFMAs: at the end of the loop it would make a bubble of a dozen instructions)
                 v2 = lv + step_off(kt + 1 + D);
                 asm volatile("" : "+v"(v2));
-                if constexpr (D == 2) {
-                    m0_nxt = m0_sum - m0_cur;
-                    asm volatile("" : "+s"(m0_nxt));
-                }
             }
             if constexpr (D == 2 && plan.group_at[0] + 3 == q) {
                 fnxt[0][0] = fsum[0][0] - fcur[0][0];
@@ -453,12 +471,13 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
                       std::integral_constant<bool, plan.read_next[gi][x / NF]>{});
             }
             if constexpr (plan.copy_pos[q] >= 0) {
-                constexpr int x = plan.copy_pos[q];
-                constexpr int sl = plan.read_slice[gp][x / P::NC];
-                // group 0 replaces what the last group of the step before read for this step
-                constexpr bool next = plan.read_next[gp][x / P::NC] && gi != 0;
-                copy(std::integral_constant<int, sl>{}, std::integral_constant<int, x % P::NC>{}, next ? m0_nxt : m0_cur,
-                     next ? v2 : v1);
+                constexpr int x = plan.copy_pos[q], y = x / P::NC;
+                constexpr int sl = plan.slot_slice[vp][y];
+                // the first interval replaces what the last one of the step before read
+                constexpr bool next = plan.slot_next[vp][y];
+                constexpr int ahead = (next ? 1 : 0) - (v == 0 ? 1 : 0);  // -1, 0, 1: v0, v1, v2
+                copy(std::integral_constant<int, sl>{}, std::integral_constant<int, x % P::NC>{}, ahead == 0 ? m0_cur : m0_nxt,
+                     ahead < 0 ? v0 : ahead == 0 ? v1 : v2);
             }
             constexpr int pr = q / P::TT, m = q % P::TT;
             constexpr int s = plan.s[pr], u = plan.t[pr];
@@ -474,9 +493,11 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
             if constexpr (D == 2) asm volatile("" ::"a"(acc[c][i][j]));
             __builtin_amdgcn_sched_barrier(0);
         });
+        v0 = v1;
         v1 = v2;
         if constexpr (D == 2) {
             m0_cur = m0_nxt;
+            m0_nxt = m0_sum - m0_cur;
             fcur[0][0] = fnxt[0][0], fcur[0][1] = fnxt[0][1];
             fcur[1][0] = fnxt[1][0], fcur[1][1] = fnxt[1][1];
         }
@@ -513,50 +534,61 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
     // product) and scaled by 2^(2 - 2 beta + ea + eb) at the end.  Otherwise term by term.
     const bool plain_range = emin + 2 - a.beta * (K + 1) >= -1022 && emax + 2 - 2 * a.beta + 40 <= 1023;
     const bool scaled = __ballot(plain_range) == ~0ull;
+    // Four 16 x 16 tiles at a time: sixteen independent chains of additions per lane keep the FP64 unit busy.
     auto finish_tile = [&](auto SCALED) __attribute__((always_inline)) {
+        constexpr int TT = TA * TB, BATCH = TT < 4 ? TT : 4;
         const double step = ldexp(1.0, -a.beta);
+        static_for<(TT + BATCH - 1) / BATCH>([&](auto Q) __attribute__((always_inline)) {
+            constexpr int first = decltype(Q)::value * BATCH, n = TT - first < BATCH ? TT - first : BATCH;
+            double cold[n][4], d[n][4];
+            if (with_c)
 #pragma unroll
-        for (int j = 0; j < TB; ++j) {
-            const int64_t col = (int64_t)col0 + wn * (16 * TB) + 16 * j + lc;
-#pragma unroll
-            for (int i = 0; i < TA; ++i) {
-                const int64_t row = (int64_t)row0 + wm * (16 * TA) + 16 * i + 4 * lq;
-                double* const out = obase + row * opitch + col;
-                double cold[4] = {0.0, 0.0, 0.0, 0.0};
-                if (with_c)
+                for (int x = 0; x < n; ++x) {
+                    const int i = (first + x) % TA, j = (first + x) / TA;
+                    const int64_t col = (int64_t)col0 + wn * (16 * TB) + 16 * j + lc;
+                    const int64_t row = (int64_t)row0 + wm * (16 * TA) + 16 * i + 4 * lq;
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        if (col < a.p && row + r < a.m) cold[r] = __builtin_nontemporal_load(out + r * opitch);
-                double d[4];
-                double scale = 1.0;
-                static_for<W>([&](auto C) __attribute__((always_inline)) {
-                    constexpr int c = decltype(C)::value;
-                    constexpr int g = chunk_range<K, R>(c).g;
-                    if constexpr (c > 0)
-                        if constexpr (g != chunk_range<K, R>(c - 1).g) scale *= step;
+                        cold[x][r] = (col < a.p && row + r < a.m) ? __builtin_nontemporal_load(obase + (row + r) * opitch + col) : 0.0;
+                }
+            double scale = 1.0;
+            static_for<W>([&](auto C) __attribute__((always_inline)) {
+                constexpr int c = decltype(C)::value;
+                constexpr int g = chunk_range<K, R>(c).g;
+                if constexpr (c > 0)
+                    if constexpr (g != chunk_range<K, R>(c - 1).g) scale *= step;
+#pragma unroll
+                for (int x = 0; x < n; ++x) {
+                    const int i = (first + x) % TA, j = (first + x) / TA;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const double x = (double)acc[c][i][j][r];
+                        const double v = (double)acc[c][i][j][r];
                         if constexpr (decltype(SCALED)::value) {
-                            d[r] = c == 0 ? x : __builtin_fma(x, scale, d[r]);
+                            d[x][r] = c == 0 ? v : __builtin_fma(v, scale, d[x][r]);
                         } else {
-                            const double term = ldexp(x, ea[i][r] + eb[j] + 2 - a.beta * g);
-                            d[r] = c == 0 ? term : d[r] + term;
+                            const double term = ldexp(v, ea[i][r] + eb[j] + 2 - a.beta * g);
+                            d[x][r] = c == 0 ? term : d[x][r] + term;
                         }
                     }
-                });
+                }
+            });
+#pragma unroll
+            for (int x = 0; x < n; ++x) {
+                const int i = (first + x) % TA, j = (first + x) / TA;
+                const int64_t col = (int64_t)col0 + wn * (16 * TB) + 16 * j + lc;
+                const int64_t row = (int64_t)row0 + wm * (16 * TA) + 16 * i + 4 * lq;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    if constexpr (decltype(SCALED)::value) d[r] = ldexp(d[r], ea[i][r] + eb[j] + 2 - 2 * a.beta);
+                    if constexpr (decltype(SCALED)::value) d[x][r] = ldexp(d[x][r], ea[i][r] + eb[j] + 2 - 2 * a.beta);
                     if (a.finish) {
-                        d[r] = a.alpha * d[r];
-                        if (with_c) d[r] = d[r] + a.cbeta * cold[r];
+                        d[x][r] = a.alpha * d[x][r];
+                        if (with_c) d[x][r] = d[x][r] + a.cbeta * cold[x][r];
                     }
-                    if (col < a.p && row + r < a.m) __builtin_nontemporal_store(d[r], out + r * opitch);
+                    if (col < a.p && row + r < a.m) __builtin_nontemporal_store(d[x][r], obase + (row + r) * opitch + col);
                 }
-                __builtin_amdgcn_sched_barrier(0);
             }
-        }
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
     if (scaled)
         finish_tile(std::true_type{});
