@@ -22,36 +22,46 @@ struct Config {
 };
 constexpr int lds_bytes(int k, const Config& c) { return c.depth * k * (c.ta + c.tb) * 2048 + 128 * (c.ta + c.tb); }
 
-// variant 0: the largest tile whose chunk sums fit the 256 accumulation registers; 1: a small one for outputs that
-// the large one would not spread over the chip
+// variant 0: the largest tile whose chunk sums fit the 256 accumulation registers; the others: smaller ones for outputs that
+// the large one would not spread evenly over the chip
 constexpr Config config(int k, int r, int variant)
 {
     const int w = num_chunks(k, r);
     Config c{0, 0, 1, 1};
-    if (variant == 0) {
-        if (w <= 4) c.ta = 4, c.tb = 4;
-        else if (w <= 8) c.ta = 2, c.tb = 4;
-        else if (w <= 16) c.ta = 2, c.tb = 2;
-        else if (w <= 21) c.ta = 1, c.tb = 3;
-        else if (w <= 32) c.ta = 1, c.tb = 2;
-        else if (w <= 64) c.ta = 1, c.tb = 1;
-    } else {
-        if (w <= 8) c.ta = 2, c.tb = 2, c.waves = 2;
+    int area = 0;  // 16 x 16 tiles of a wave in the largest tile
+    if (w <= 4) c.ta = 4, c.tb = 4;
+    else if (w <= 8) c.ta = 2, c.tb = 4;
+    else if (w <= 16) c.ta = 2, c.tb = 2;
+    else if (w <= 21) c.ta = 1, c.tb = 3;
+    else if (w <= 32) c.ta = 1, c.tb = 2;
+    else if (w <= 64) c.ta = 1, c.tb = 1;
+    else return c;
+    area = c.ta * c.tb;
+    if (variant > 0) {
+        const int ta = variant == 1 || variant == 2 ? 2 : 1, tb = variant == 1 ? 2 : variant == 2 || variant == 3 ? 3 : variant == 4 ? 2 : 1;
+        c.ta = 0;
+        if (w * ta * tb > 64 || (ta * tb >= area && !(w > 8 && ta * tb == 6))) return c;
+        c.ta = ta, c.tb = tb;
+        // two workgroups on a compute unit where the registers (accumulators; fragments of the low slices and of two high
+        // ones, and about 25 more) and the LDS allow it
+        const int frag = 4 * (ta + tb) * ((k + 1) / 2 + 2);
+        if (w * ta * tb <= 32 && frag + 25 <= 128 && 2 * k * (ta + tb) * 2048 <= 158 * 1024) c.waves = 2;
     }
-    if (c.ta == 0) return c;
     c.depth = 2;
     if (c.waves * lds_bytes(k, c) > 160 * 1024) c.depth = 1;
     if (lds_bytes(k, c) > 160 * 1024) c.ta = 0;
     return c;
 }
 
-constexpr int NUM_VARIANTS = 2;
+constexpr int NUM_VARIANTS = 6;
 
 // Estimate of the kernel's time in microseconds on a chip of num_cu compute units; -1 where it cannot run.
-// Measured on MI355X: an MFMA of the main loop takes 7.3 ns plus 0.022 ns for every byte of operands that the
-// compute unit brings in per MFMA (60 bytes at k = 16, 85 at k = 8 with tiles of 64 x 128, 152 at w = 20 with tiles of 32 x 96:
-// 8.8, 9.0 and 11.2 ns), and a round of tiles 2 us plus 0.8 us per 16 x 16 tile of a wave for its start values and for
-// writing D (8 us at k = 8, 16 us at k = 4); two workgroups on a compute unit cover part of that for each other.
+// Measured on MI355X: an inner step of a workgroup that has its compute unit to itself takes 7.5 ns per MFMA of a wave plus
+// 0.1 to 0.2 us (k = 8, tiles of 64 x 64: 1.16 us, 32 x 32: 0.5 us; 64 x 128: 2.4 us; k = 4, 128 x 128: 1.42 us), one of two workgroups
+// that share it 8.4 ns per MFMA of both plus 0.2 us.  A round of tiles adds start values, the first operands and the
+// writing of D: 4 us plus 0.4 us per 16 x 16 tile of a wave.  Calls of milliseconds run at the clock the power budget leaves,
+// and what an MFMA costs then grows with the bytes of operands that the compute unit brings in for it: 7.3 ns plus 0.022 ns
+// per byte (60 bytes at k = 16, 85 at k = 8 with tiles of 64 x 128, 152 at w = 20 with tiles of 32 x 96: 8.8, 9.0, 11.2 ns).
 inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64_t p, int num_cu)
 {
     if (k < MIN_K || k > MAX_K || (r < k && r != 8 && r != 4 && r != 2 && r != 1)) return -1.0;
@@ -62,12 +72,18 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     if (tiles >= ((int64_t)1 << 23) || steps >= ((int64_t)1 << 17)) return -1.0;  // grid size; 32-bit operand offsets
     const double mfmas = 0.5 * k * (k + 1) * c.ta * c.tb;
     const double copied = 4096.0 * ((2 * (c.ta + c.tb) + 3) / 4) * k;   // bytes per step
-    const double step_us = mfmas * (0.0073 + 2.2e-5 * copied / (4.0 * mfmas));
-    const double round_us = c.waves == 2 ? 7.0 : 2.0 + 0.8 * c.ta * c.tb;
+    const double round_us = 4.0 + 0.4 * c.ta * c.tb;
     const int64_t slots = (int64_t)num_cu * c.waves, full = tiles / slots, left = tiles % slots;
-    double us = (double)full * (steps * step_us * c.waves + round_us);
-    if (left > 0) us += steps * step_us * (left > num_cu ? c.waves : 1) + round_us;
-    return us;
+    auto total = [&](double alone_us, double all_us) {
+        double us = (double)full * ((double)steps * all_us + round_us);
+        if (left > 0) us += (double)steps * (left > num_cu ? all_us : alone_us) + round_us;
+        return us;
+    };
+    const double alone_us = 0.0075 * mfmas + 0.15;
+    const double us = total(alone_us, c.waves == 2 ? 0.0168 * mfmas + 0.2 : alone_us);
+    if (us < 1500.0) return us;
+    const double hot_us = mfmas * (0.0073 + 2.2e-5 * copied / (4.0 * mfmas));
+    return total(hot_us, hot_us * c.waves);
 }
 
 }  // namespace ozr

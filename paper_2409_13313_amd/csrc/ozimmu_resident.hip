@@ -112,8 +112,9 @@ struct Plan {
     int first_group[NI + 1] = {};    // groups of an interval
     int nslot[NI] = {}, slot_slice[NI][K] = {};  // the same by interval
     bool slot_next[NI][K] = {};
-    // per MFMA index: group, interval, fragment fetch (group-local list position) and copy (interval-local), -1 = none
-    int read_pos[NM] = {}, copy_pos[NM] = {}, group_of[NM] = {}, interval_of[NM] = {};
+    // per MFMA index: group, interval, the fragment fetches (read_at .. read_at + reads - 1 of the group's list) and the copies
+    // (of the interval's list) that go out before it
+    int read_at[NM] = {}, reads[NM] = {}, copy_at[NM] = {}, copies[NM] = {}, group_of[NM] = {}, interval_of[NM] = {};
     bool opens[NM] = {};             // first MFMA of an interval
 
     constexpr int high(int j) const { return K + 1 - j > L ? K + 1 - j : 0; }
@@ -162,7 +163,6 @@ struct Plan {
                     slot_slice[v][nslot[v]] = read_slice[gi][x];
                     slot_next[v][nslot[v]++] = read_next[gi][x];
                 }
-        for (int q = 0; q < NM; ++q) read_pos[q] = copy_pos[q] = -1;
         auto spread = [](int len, int count, int most) {
             int sp = len / (count + 2);
             sp = sp > most ? most : sp;
@@ -172,14 +172,20 @@ struct Plan {
             const int len = group_at[gi + 1] - group_at[gi];
             for (int q = group_at[gi]; q < group_at[gi + 1]; ++q) group_of[q] = gi;
             const int nr = nread[gi] * NF, spr = spread(len, nr, TT <= 4 ? 2 : 4);
-            for (int x = 0; x < nr; ++x) read_pos[group_at[gi] + (x * spr < len ? x * spr : len - 1)] = x;
+            for (int x = 0; x < nr; ++x) {
+                const int q = group_at[gi] + (x * spr < len ? x * spr : len - 1);
+                if (reads[q]++ == 0) read_at[q] = x;
+            }
         }
         for (int v = 0; v < NI; ++v) {
             const int at = group_at[first_group[v]], len = group_at[first_group[v + 1]] - at;
             opens[at] = true;
             for (int q = at; q < at + len; ++q) interval_of[q] = v;
             const int nc = nslot[(v + NI - 1) % NI] * NC, spc = spread(len, nc, 4);
-            for (int x = 0; x < nc; ++x) copy_pos[at + (x * spc + 1 < len ? x * spc + 1 : len - 1)] = x;
+            for (int x = 0; x < nc; ++x) {
+                const int q = at + (x * spc + 1 < len ? x * spc + 1 : len - 1);
+                if (copies[q]++ == 0) copy_at[q] = x;
+            }
         }
     }
 };
@@ -462,23 +468,23 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
                     asm volatile("" : "+v"(fnxt[0][1]), "+v"(fnxt[1][1]));
                 }
             }
-            if constexpr (plan.read_pos[q] >= 0) {
-                constexpr int x = plan.read_pos[q];
+            static_for<plan.reads[q]>([&](auto X) __attribute__((always_inline)) {
+                constexpr int x = plan.read_at[q] + decltype(X)::value;
                 constexpr int sl = plan.read_slice[gi][x / NF];
                 // (the operand that is needed first comes first: B of a low slice, A of a high one)
                 constexpr int f = sl <= L ? (x % NF + TA) % NF : x % NF;
                 fetch(std::integral_constant<int, sl>{}, std::integral_constant<int, f>{},
                       std::integral_constant<bool, plan.read_next[gi][x / NF]>{});
-            }
-            if constexpr (plan.copy_pos[q] >= 0) {
-                constexpr int x = plan.copy_pos[q], y = x / P::NC;
+            });
+            static_for<plan.copies[q]>([&](auto X) __attribute__((always_inline)) {
+                constexpr int x = plan.copy_at[q] + decltype(X)::value, y = x / P::NC;
                 constexpr int sl = plan.slot_slice[vp][y];
                 // the first interval replaces what the last one of the step before read
                 constexpr bool next = plan.slot_next[vp][y];
                 constexpr int ahead = (next ? 1 : 0) - (v == 0 ? 1 : 0);  // -1, 0, 1: v0, v1, v2
                 copy(std::integral_constant<int, sl>{}, std::integral_constant<int, x % P::NC>{}, ahead == 0 ? m0_cur : m0_nxt,
                      ahead < 0 ? v0 : ahead == 0 ? v1 : v2);
-            }
+            });
             constexpr int pr = q / P::TT, m = q % P::TT;
             constexpr int s = plan.s[pr], u = plan.t[pr];
             // (back and forth, so that consecutive MFMAs share an operand)
@@ -624,6 +630,10 @@ hipError_t launch_r(const ozk::ResidentArgs& a, int variant, hipStream_t st)
     switch (variant) {
         case 0: return launch<K, R, 0>(a, st);
         case 1: return launch<K, R, 1>(a, st);
+        case 2: return launch<K, R, 2>(a, st);
+        case 3: return launch<K, R, 3>(a, st);
+        case 4: return launch<K, R, 4>(a, st);
+        case 5: return launch<K, R, 5>(a, st);
         default: return hipErrorInvalidValue;
     }
 }
