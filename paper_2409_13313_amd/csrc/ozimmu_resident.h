@@ -58,10 +58,13 @@ constexpr int NUM_VARIANTS = 6;
 // Estimate of the kernel's time in microseconds on a chip of num_cu compute units; -1 where it cannot run.
 // Measured on MI355X: an inner step of a workgroup that has its compute unit to itself takes 7.5 ns per MFMA of a wave plus
 // 0.1 to 0.2 us (k = 8, tiles of 64 x 64: 1.16 us, 32 x 32: 0.5 us; 64 x 128: 2.4 us; k = 4, 128 x 128: 1.42 us), one of two workgroups
-// that share it 8.4 ns per MFMA of both plus 0.2 us.  A round of tiles adds start values, the first operands and the
-// writing of D: 4 us plus 0.4 us per 16 x 16 tile of a wave.  Calls of milliseconds run at the clock the power budget leaves,
-// and what an MFMA costs then grows with the bytes of operands that the compute unit brings in for it: 7.3 ns plus 0.022 ns
-// per byte (60 bytes at k = 16, 85 at k = 8 with tiles of 64 x 128, 152 at w = 20 with tiles of 32 x 96: 8.8, 9.0, 11.2 ns).
+// that share it 8.4 ns per MFMA of both plus 0.2 us; with several rounds of tiles the former becomes 0.27 us.  A round of
+// tiles adds start values, the first operands and the writing of D: 4 us plus 0.4 us per 16 x 16 tile of a wave.  Calls of
+// milliseconds run at the clock the power budget leaves, and what an MFMA costs then grows with the bytes that are moved
+// for it (4096^3: k = 9, 64 x 96 against 64 x 64 with half the fetches more, 1.85 and 1.91 ms; k = 10, 2.25 and 2.28;
+// k = 5, two workgroups of 64 x 96 against one of 96 x 96, 0.75 and 0.80): 6.8 ns plus 0.02 ns per byte of operands that the
+// compute unit brings in plus 5 ns per KiB of fragments that a wave fetches from LDS (k = 16, 64 x 64: 60 bytes, 0.12 KiB, 8.8 ns;
+// k = 8, 64 x 128: 85, 0.17, 9.0; w = 20, 32 x 96: 152, 0.30, 11.2).
 inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64_t p, int num_cu)
 {
     if (k < MIN_K || k > MAX_K || (r < k && r != 8 && r != 4 && r != 2 && r != 1)) return -1.0;
@@ -71,7 +74,8 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     const int64_t tiles = ((m + 32 * c.ta - 1) / (32 * c.ta)) * ((p + 32 * c.tb - 1) / (32 * c.tb));
     if (tiles >= ((int64_t)1 << 23) || steps >= ((int64_t)1 << 17)) return -1.0;  // grid size; 32-bit operand offsets
     const double mfmas = 0.5 * k * (k + 1) * c.ta * c.tb;
-    const double copied = 4096.0 * ((2 * (c.ta + c.tb) + 3) / 4) * k;   // bytes per step
+    const double copied = 2048.0 * (c.ta + c.tb) * k / (4.0 * mfmas);        // bytes brought in per MFMA
+    const double fetched = (double)(c.ta + c.tb) * k / mfmas;                 // KiB fetched from LDS per MFMA and wave
     const double round_us = 4.0 + 0.4 * c.ta * c.tb;
     const int64_t slots = (int64_t)num_cu * c.waves, full = tiles / slots, left = tiles % slots;
     auto total = [&](double alone_us, double all_us) {
@@ -80,9 +84,9 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
         return us;
     };
     const double alone_us = 0.0075 * mfmas + 0.15;
-    const double us = total(alone_us, c.waves == 2 ? 0.0168 * mfmas + 0.2 : alone_us);
+    const double us = total(alone_us, c.waves == 2 ? 0.0168 * mfmas + 0.2 : alone_us + 0.12);
     if (us < 1500.0) return us;
-    const double hot_us = mfmas * (0.0073 + 2.2e-5 * copied / (4.0 * mfmas));
+    const double hot_us = mfmas * (0.0068 + 2.0e-5 * copied + 0.005 * fetched);
     return total(hot_us, hot_us * c.waves);
 }
 
