@@ -22,9 +22,9 @@ if ROOT not in sys.path:
 PEAK_INT8_TOPS = 5000.0      # MI355X dense INT8 MFMA peak, 5.0 POP/s
 PEAK_HBM_GBS = 8000.0
 # Bytes per launch of the GEMM kernel at the L2 / fabric boundary, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
-# runs of this script, each scaled by the same counter on a plain copy (profiles/k_gemm_16384_k8_traffic.md).
+# runs of this script, each scaled by the same counter on a plain copy (profiles/gemm_16384_k8_traffic.md).
 # Counters cannot be read from inside this process: the figure exists for the shapes profiled, else null.
-MEASURED_TRAFFIC_BYTES = {(16384, 16384, 16384, 8): 281.0e9 + 10.74e9}
+MEASURED_TRAFFIC_BYTES = {(16384, 16384, 16384, 8): 143.4e9 + 2.15e9}
 
 
 def log(*a):
@@ -174,8 +174,8 @@ def main() -> int:
         "phases_ms": {"split_A_and_B": round(split_ms, 4), "chunk_gemm_with_fused_accumulation": round(gemm_ms, 4)},
         "int8_mfma_utilisation_pct": round(100.0 * gemm_tops / PEAK_INT8_TOPS, 2),
         "roofline": {
-            "kernel": "k_gemm<3,4> (persistent INT8 MFMA kernel, queue schedule: every chunk GEMM of the schedule is "
-                      "a work item; the workgroup that completes a tile adds its chunks up in FP64; one launch per step)",
+            "kernel": "k_resident (INT8 MFMA kernel: all chunk sums of a tile grow in registers while the inner dimension is "
+                      "walked once, then are added up in FP64; one launch per step; shapes of very many chunks: k_gemm<3,4>)",
             "bound": "mfma",
             "achieved": round(gemm_tops, 2),
             "peak": PEAK_INT8_TOPS,
@@ -186,7 +186,7 @@ def main() -> int:
             "ops_per_launch": int_ops,
             "traffic": MEASURED_TRAFFIC_BYTES.get((m, n, p, k)),
             "traffic_note": ("FETCH_SIZE + WRITE_SIZE of one launch, rocprofv3 --pmc, copy-calibrated "
-                             "(profiles/k_gemm_16384_k8_traffic.md)" if (m, n, p, k) in MEASURED_TRAFFIC_BYTES else
+                             "(profiles/gemm_16384_k8_traffic.md)" if (m, n, p, k) in MEASURED_TRAFFIC_BYTES else
                              "null: no rocprofv3 --pmc run of this shape is on file (hardware counters cannot be "
                              "read from inside the benchmark process)"),
             "algorithmic_bytes": float(pairs) * (m * n + n * p) + 8.0 * m * p,

@@ -87,8 +87,8 @@ size_t ozimmu_slices_bytes(int64_t rows, int64_t n, int k);
 size_t ozimmu_workspace_bytes(int64_t m, int64_t n, int64_t p, int k);
 
 /* The least ozimmu_dgemm accepts (one block per output tile, at most 128): with less than
- * ozimmu_workspace_bytes the call gives the same D, but small outputs cannot take the chunk-parallel
- * schedule (see OZIMMU_SCHEDULE_CHUNK_PARALLEL below).  Monotone in m, n, p and k.  Host. */
+ * ozimmu_workspace_bytes the call gives the same D, but calls that need blocks cannot take the chunk-parallel
+ * or the queue schedule (see OZIMMU_SCHEDULE_CHUNK_PARALLEL below).  Monotone in m, n, p and k.  Host. */
 size_t ozimmu_workspace_bytes_min(int64_t m, int64_t n, int64_t p, int k);
 
 /* D <- A B with k slices: steps (i)-(iv) of the scheme (Section 1) as
@@ -96,7 +96,7 @@ size_t ozimmu_workspace_bytes_min(int64_t m, int64_t n, int64_t p, int k);
  *   A, B, D      device, FP64, row-major (see above); D is overwritten.
  *   k            number of slices, 1..OZIMMU_MAX_SLICES.
  *   workspace    device, 256-byte aligned, >= ozimmu_workspace_bytes_min(m,n,p,k) bytes
- *                (ozimmu_workspace_bytes(m,n,p,k) to let small outputs run their fastest schedule).
+ *                (ozimmu_workspace_bytes(m,n,p,k) to let every shape run its fastest schedule).
  * m, n or p equal to 0 is valid: nothing is computed, and for n == 0 (m, p > 0)
  * D is set to +0. */
 int ozimmu_dgemm(int64_t m, int64_t n, int64_t p,
@@ -135,9 +135,13 @@ int ozimmu_dgemm_profiled(int64_t m, int64_t n, int64_t p,
 enum { OZIMMU_SPLIT_NEAREST = 0, OZIMMU_SPLIT_BITMASK = 1, OZIMMU_SPLIT_NEAREST_PER_SLICE = 2 };
 enum { OZIMMU_ACCUM_GROUPED = 0, OZIMMU_ACCUM_PER_PAIR = 1, OZIMMU_ACCUM_WIDE = 2 };
 /* How the schedule is run; OR one of these into accumulate_mode (default: the library chooses).  The result
- * does not depend on it, bit for bit.
+ * does not depend on it, bit for bit.  Without a flag, for 3 to 16 slices with one scale per row and column, the
+ * library usually takes a way that has no flag: all chunk sums of a tile (32 x 32 to 128 x 128 outputs) grow side by
+ * side in registers while the inner dimension is walked once, and D is written once.  It needs no blocks, so any workspace
+ * that is accepted will do.  The ways below serve the rest - other slice counts, a scale per slice, schedules of so
+ * many chunks (long inner dimensions) that the tiles would become too small - and whoever asks for them.
  *   OZIMMU_SCHEDULE_ONE_LAUNCH   the whole schedule in one persistent kernel with the FP64 accumulation
- *                                fused into the GEMM epilogue (what large outputs get when the workspace
+ *                                fused into the GEMM epilogue (what such large outputs get when the workspace
  *                                has no room for the blocks of the queue);
  *   OZIMMU_SCHEDULE_SPLIT_INNER  for the tiles (256 x 256) that would leave most compute units idle -- an
  *                                output of at most 128 tiles, or the last, partly filled round of at most
@@ -160,8 +164,9 @@ enum { OZIMMU_ACCUM_GROUPED = 0, OZIMMU_ACCUM_PER_PAIR = 1, OZIMMU_ACCUM_WIDE = 
  *                                (256 tiles, all their chunks, longest chunks first) through a counter; an item
  *                                leaves its INT32 sums in a block, and the workgroup that completes a tile's last
  *                                block adds the tile's chunks up in the order of Algorithm 6.  The blocks are
- *                                recycled every few rounds.  The default for outputs of more tiles than compute
- *                                units; ignored where the workspace has no room for it. */
+ *                                recycled every few rounds.  Chosen for outputs of more tiles than compute units
+ *                                whose chunks are too many for registers; ignored where the workspace has no room
+ *                                for it. */
 enum { OZIMMU_SCHEDULE_ONE_LAUNCH = 0x100, OZIMMU_SCHEDULE_SPLIT_INNER = 0x200, OZIMMU_SCHEDULE_CHUNK_PARALLEL = 0x400,
        OZIMMU_SCHEDULE_QUEUE = 0x800 };
 int ozimmu_dgemm_variant(int64_t m, int64_t n, int64_t p,

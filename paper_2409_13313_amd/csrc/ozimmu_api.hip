@@ -400,7 +400,10 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     if (schedule == 0 && !per_slice) {
         const double pairs = (double)k * (k + 1) / 2, rounds = (double)((T - tail - cp_tail + num_cu - 1) / num_cu);
         // what the ways above take: the queue 0.64 us per stage of 64 inner positions and 17 us per work item of a tile
-        // (measured 96.5 ms at 16384^3, k = 8; 36.7 ms at 4096 x 65536 x 4096, k = 10; 7.4 ms at 8192^3, k = 6)
+        // (measured 96.5 ms at 16384^3, k = 8; 36.7 ms at 4096 x 65536 x 4096, k = 10; 7.4 ms at 8192^3, k = 6).  Both
+        // sides at some shapes, whole calls, queue or chunk-parallel against the chosen resident variant: 4096^3 k = 3
+        // 0.46 / 0.36 ms, k = 8 1.78 / 1.48, k = 16 5.91 / 4.87; 1024 x 16384 x 1024 k = 8 0.61 / 0.54;
+        // 2048 x 65536 x 2048 k = 6 (12 chunks) 5.08 / 4.96; 4096 x 65536 x 4096 k = 10 (30 chunks) 39.7 / 40.3
         double other_us = queue_pays ? (0.64 * pairs * KT + 17.0 * (double)w) * (double)T / num_cu
                                      : cp_us + tail_us + rounds * (0.60 * pairs * KT + 50.0 * (double)w);
         int variant = -1;

@@ -1,4 +1,9 @@
-// Steps (iii) and (iv) of the scheme on the gfx950 matrix cores.
+// Steps (iii) and (iv) of the scheme on the gfx950 matrix cores, one chunk after the other.
+//
+// (Most calls take k_resident, ozimmu_resident.hip, which keeps all chunks of a tile in registers.  What is here serves
+// slice counts outside 3 .. 16, slices with one scale each, schedules of so many chunks that k_resident's tiles would be
+// too small - 4096 x 65536 x 4096, k = 10, 30 chunks: the queue 39.7 ms, k_resident 40.3 to 42.3 -, the forced schedules
+// and the phase-level entry points.)
 //
 // k_gemm computes, for one chunk of one group g (Algorithm 6 of the paper),
 //     C'' = sum_{s = s0..s1} A''_s B''_{g-s}          (INT8 x INT8 -> INT32, exact)
@@ -16,7 +21,7 @@
 // a.nchunks > 0 one MODE 3 launch covers ALL chunks of the schedule at once: a work
 // item is (chunk, part, tile), every chunk has a block per tile of its own, and a
 // separate kernel adds the chunks up in FP64 in the order of Algorithm 6.  With
-// a.queue_sets > 0 as well (the "queue" schedule, the default for larger outputs)
+// a.queue_sets > 0 as well (the "queue" schedule, for larger outputs)
 // the items are (chunk, tile), handed out round by round, the blocks are recycled,
 // and the workgroup that completes a tile adds its chunks up itself (accumulate_tile:
 // steps (iv) and (v) inside the launch); see the item loop of k_gemm.

@@ -2,7 +2,8 @@
 //
 // A slice stack holds k slices of a matrix with `rows` scaled vectors (rows of
 // A, or columns of B) of inner length n.  Rows are padded to a multiple of
-// TILE_R, the inner index to a multiple of KPAD, padding is zero.  One slice is
+// TILE_R, the inner index to a multiple of KPAD; inner padding is zero, padding
+// rows and their row sums are not written (their results are never stored).  One slice is
 // stored tile-major: tile (rt, kt) = TILE_R rows x TILE_K inner bytes is one
 // contiguous 16 KiB block, tiles of one row block are consecutive in kt, so a
 // workgroup streaming along the inner dimension reads consecutive blocks and
@@ -19,8 +20,8 @@
 //
 // Stored bytes are OFFSET-ENCODED: a stack carries one offset c and the byte of
 // an element is q + c, q being the slice integer of the method (inner padding
-// is q = 0 like any zero; padding ROWS may hold anything that is consistent
-// with their row sums: their results are never stored).  Round-to-nearest
+// is q = 0 like any zero; padding ROWS hold whatever the memory held: every kernel
+// computes on them and stores none of it).  Round-to-nearest
 // slices obey |q| <= 2^(beta-1) and are stored with c = 2^(beta-1) - 1 (63 for
 // beta = 7: bytes in [-1, 127], practically all non-negative); other slices
 // with c = 0.  Why: the matrix cores draw measurably less power on operands of

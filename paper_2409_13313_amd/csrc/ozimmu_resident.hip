@@ -14,8 +14,14 @@
 // 16384^3, k = 8: 1.90 GHz at 91 % busy pipes against 1.68 GHz at 91.5 %, 86.9 against 95.6 ms on one box
 // (3.64 POP/s, 90 % of what a register-only MFMA loop sustains on such bytes).  Small outputs gain more: their tiles
 // need no blocks, no atomic adds and no second kernel, and 64 x 64 tiles spread a 1024^3 product over the whole chip
-// (per call, k_gemm's ways -> this: 1024^3 k = 9 124 -> 72 us, 777 x 1001 x 513 k = 7 122 -> 60 us, 4096^3 k = 8 1.83 ->
-// 1.55 ms, 4096^3 k = 9 with one addition per slice pair 4.02 -> 2.75 ms).
+// (whole calls, k_gemm's ways and a split of three to seven launches -> this behind a split of one: 1024^3 k = 9
+// 126 -> 43 us, 777 x 1001 x 513 k = 7 122 -> 29 us, 4096^3 k = 8 1.86 -> 1.50 ms, 4096^3 k = 9 with one addition per slice
+// pair 4.13 -> 2.61 ms).
+//
+// Tried without gain: the MFMAs of a pair with A held and B changing (0.7 % slower at 16384^3, 1 % at 4096^3); chunk sums
+// beyond the 256 accumulation registers in ordinary ones, for tiles a third larger (k = 6 96 x 128, k = 8 96 x 96, k = 12
+// 64 x 96: 5 % slower, 1 % slower, equal at 8192^3, 21 % slower at 4096^3 k = 8: moves between the register files in the
+// loop).
 //
 // Fragments: L = (k + 1) / 2 low slices of both operands stay in registers for a step, the high ones pass through two
 // buffers, so that every fragment is fetched once per step and wave.  A wave holds as many 16 x 16 tiles as w chunk

@@ -547,7 +547,7 @@ __global__ __launch_bounds__(256) void k_split_B(int64_t n, int64_t p, const dou
 }
 
 // ---------------------------------------------------------------------------
-// Algorithm 5 (one scale per slice), A: one wave per padded row as in k_split_A.
+// Algorithm 5 (one scale per slice), A: one wave per padded row.
 // The scale of slice s+1 comes from the largest remainder after slice s, so the
 // row is walked k times; what is left of it lives in `rem` (row pitch Npad) and
 // every lane re-reads only the elements it wrote itself.  With
