@@ -63,8 +63,10 @@ constexpr int NUM_VARIANTS = 6;
 // milliseconds run at the clock the power budget leaves, and what an MFMA costs then grows with the bytes that are moved
 // for it (4096^3: k = 9, 64 x 96 against 64 x 64 with half the fetches more, 1.85 and 1.91 ms; k = 10, 2.25 and 2.28;
 // k = 5, two workgroups of 64 x 96 against one of 96 x 96, 0.75 and 0.80): 6.8 ns plus 0.02 ns per byte of operands that the
-// compute unit brings in plus 5 ns per KiB of fragments that a wave fetches from LDS (k = 16, 64 x 64: 60 bytes, 0.12 KiB, 8.8 ns;
-// k = 8, 64 x 128: 85, 0.17, 9.0; w = 20, 32 x 96: 152, 0.30, 11.2).
+// compute unit brings in plus 5 ns per KiB of fragments that a wave fetches from LDS (k = 16, 64 x 64: 60 bytes, 0.12 KiB,
+// 8.8 ns; k = 8, 64 x 128: 85, 0.17, 9.0; w = 20, 32 x 96: 152, 0.30, 11.2).  Two workgroups on a compute unit fill each
+// other's barriers: 0.6 ns less (k = 5, two of 64 x 96 against one of 64 x 128: 5.44 and 5.94 ms at 8192^3, 44.0 and 46.4 at
+// 16384^3; k = 8, two of 64 x 64 against one of 64 x 128: 11.84 and 11.44 at 8192^3, and the estimate keeps the latter).
 inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64_t p, int num_cu)
 {
     if (k < MIN_K || k > MAX_K || (r < k && r != 8 && r != 4 && r != 2 && r != 1)) return -1.0;
@@ -86,7 +88,7 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     const double alone_us = 0.0075 * mfmas + 0.15;
     const double us = total(alone_us, c.waves == 2 ? 0.0168 * mfmas + 0.2 : alone_us + 0.12);
     if (us < 1500.0) return us;
-    const double hot_us = mfmas * (0.0068 + 2.0e-5 * copied + 0.005 * fetched);
+    const double hot_us = mfmas * ((c.waves == 2 ? 0.0062 : 0.0068) + 2.0e-5 * copied + 0.005 * fetched);
     return total(hot_us, hot_us * c.waves);
 }
 
