@@ -62,7 +62,7 @@ constexpr int NUM_VARIANTS = 6;
 // tiles adds start values, the first operands and the writing of D: 4 us plus 0.4 us per 16 x 16 tile of a wave.  Calls of
 // milliseconds run at the clock the power budget leaves, and what an MFMA costs then grows with the bytes that are moved
 // for it (4096^3: k = 9, 64 x 96 against 64 x 64 with half the fetches more, 1.85 and 1.91 ms; k = 10, 2.25 and 2.28;
-// k = 5, two workgroups of 64 x 96 against one of 96 x 96, 0.75 and 0.80): 6.8 ns plus 0.02 ns per byte of operands that the
+// k = 5, two workgroups of 64 x 96 against one of 64 x 128, 0.75 and 0.80): 6.8 ns plus 0.02 ns per byte of operands that the
 // compute unit brings in plus 5 ns per KiB of fragments that a wave fetches from LDS (k = 16, 64 x 64: 60 bytes, 0.12 KiB,
 // 8.8 ns; k = 8, 64 x 128: 85, 0.17, 9.0; w = 20, 32 x 96: 152, 0.30, 11.2).  Two workgroups on a compute unit fill each
 // other's barriers: 0.6 ns less (k = 5, two of 64 x 96 against one of 64 x 128: 5.44 and 5.94 ms at 8192^3, 44.0 and 46.4 at
