@@ -115,6 +115,8 @@ __device__ inline uint32_t slice_word4(double* y, int c, double two_beta, int* s
 // alone, read twice, 4096^2 108 -> 59, 16384^2 1.52 -> 1.34 ms.
 // ---------------------------------------------------------------------------
 typedef __attribute__((address_space(1))) const double* global_f64;
+typedef double f64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
+typedef __attribute__((address_space(1))) const f64x2_a8* global_f64x2;
 
 struct SplitOp {
     const double* X;      // rows: vector i at X + i ld; columns: vector j at X + j, its elements ld apart
@@ -126,23 +128,24 @@ struct SplitOp {
     int64_t Rpad, slice_stride;
     int KT, c;
     int by_col;
-    int vec;              // rows: 16-byte loads are aligned
     int blocks;           // workgroups
 };
 
 // Digits of 4 consecutive elements for one slice, packed (digit of element j in byte j); the elements become the
 // remainders.  Nearest, ties to even: adding sig = 1.5 * 2^52 grids rounds to the grid and leaves the digit in the low
 // bits of the sum (the published sequence (a + sigma) - sigma; the digit needs no conversion, the remainder no scaling).
+// Truncation: the remainder is scaled to the next grid (step = 2^beta; exact), which stays 1 (scaling the digit instead of
+// the remainder costs an operation more: 12 rows of 768, k = 16, 10.0 instead of 8.6 us).
 template <bool MASK>
-__device__ inline uint32_t digits4(double* y, double sig, double grid_inv, double grid)
+__device__ inline uint32_t digits4(double* y, double sig, double step)
 {
     uint32_t q[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         if (MASK) {
-            const double d = __builtin_trunc(y[j] * grid_inv);   // (powers of two: exact)
+            const double d = __builtin_trunc(y[j]);
             q[j] = (uint32_t)__double_as_longlong(d + 6755399441055744.0);
-            y[j] -= d * grid;
+            y[j] = (y[j] - d) * step;
         } else {
             const double t = y[j] + sig;
             q[j] = (uint32_t)__double_as_longlong(t);
@@ -187,16 +190,17 @@ __device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int be
         for (int u = 0; u < U; ++u) {
             const int gq = b * per_batch + u * nw + w;
             const int64_t l = (int64_t)gq * (64 * TPW) + li;
-            if (o.vec && (int64_t)(gq + 1) * (64 * TPW) <= o.n) {  // (uniform)
-                typedef double f64x2 __attribute__((ext_vector_type(2)));
-                typedef __attribute__((address_space(1))) const f64x2* global_f64x2;
-                const f64x2 p = *(global_f64x2)(row + l), q = *(global_f64x2)(row + l + 2);
+            if ((int64_t)(gq + 1) * (64 * TPW) <= o.n) {  // (uniform)
+                // (16-byte loads want 4-byte alignment only: any row and leading dimension will do.  An odd one with 8-byte loads,
+                // each with its own bounds: 6 rows of 2036013, k = 1, 1316 instead of 424 us, 22 of 1813697, k = 8, 2084 and 1213)
+                const f64x2_a8 p = *(global_f64x2)(row + l), q = *(global_f64x2)(row + l + 2);
                 y[u][0] = p.x, y[u][1] = p.y, y[u][2] = q.x, y[u][3] = q.y;
-            } else if (gq < groups) {
+            } else if ((int64_t)gq * (64 * TPW) < o.n) {  // (uniform; what lies wholly in the padding is not loaded)
+                const int left = (int)(o.n - (int64_t)gq * (64 * TPW));
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const double v = row[l + j < o.n ? l + j : o.n - 1];
-                    y[u][j] = l + j < o.n ? v : 0.0;
+                    y[u][j] = 0.0;
+                    if (li + j < left) y[u][j] = row[l + j];
                 }
             } else {
 #pragma unroll
@@ -228,19 +232,19 @@ __device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int be
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) y[u][j] = ldexp(y[u][j], sc);
-        double sig = 6755399441055744.0, grid_inv = 1.0, grid = 1.0;
+        double sig = 6755399441055744.0;
         int8_t* out = o.S + packed_offset(R, (int64_t)(b * per_batch + w) * (64 * TPW) + li, o.KT);
         for (int s = 0; s < k; ++s) {
             int sum = 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (b * per_batch + u * nw + w < groups) {
-                    const uint32_t v = with_offset(digits4<MASK>(y[u], sig, grid_inv, grid), c4, &sum);
+                    const uint32_t v = with_offset(digits4<MASK>(y[u], sig, step), c4, &sum);
                     if (ok) *reinterpret_cast<uint32_t*>(out + (int64_t)u * nw * (TPW * TILE_BYTES)) = v;
                 }
             }
             out += o.slice_stride;
-            sig *= inv_step, grid *= inv_step, grid_inv *= step;
+            sig *= inv_step;
 #pragma unroll
             for (int off = LPR / 2; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
             if (lane % LPR == 0) atomicAdd(&lsum[s][lane / LPR], sum);
@@ -283,13 +287,15 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
                     p += o.ld;
                     asm volatile("" : "+v"(p));
                 }
-            } else if (gq < groups) {
-                global_f64 p = (global_f64)o.X + col;
+            } else if ((int64_t)gq * (64 * TPW) < o.n) {      // (uniform; what lies wholly in the padding is not loaded)
+                const int left = (int)(o.n - (int64_t)gq * (64 * TPW));
+                global_f64 p = (global_f64)o.X + l * o.ld + col;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int64_t li = l + i < o.n ? l + i : o.n - 1;
-                    const double v = p[li * o.ld];
-                    y[u][i] = l + i < o.n ? v : 0.0;
+                    y[u][i] = 0.0;
+                    if (lb * 16 + i < left) y[u][i] = *p;
+                    p += o.ld;
+                    asm volatile("" : "+v"(p));
                 }
             } else {
 #pragma unroll
@@ -321,7 +327,7 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int i = 0; i < 16; ++i) y[u][i] = ldexp(y[u][i], sc);
-        double sig = 6755399441055744.0, grid_inv = 1.0, grid = 1.0;
+        double sig = 6755399441055744.0;
         int8_t* out = o.S + packed_offset(R, (int64_t)(b * per_batch + w) * (64 * TPW) + lb * 16, o.KT);
         for (int s = 0; s < k; ++s) {
             int sum = 0;
@@ -329,15 +335,15 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
             for (int u = 0; u < U; ++u) {
                 if (b * per_batch + u * nw + w < groups) {
                     uint4 v;
-                    v.x = with_offset(digits4<MASK>(y[u], sig, grid_inv, grid), c4, &sum);
-                    v.y = with_offset(digits4<MASK>(y[u] + 4, sig, grid_inv, grid), c4, &sum);
-                    v.z = with_offset(digits4<MASK>(y[u] + 8, sig, grid_inv, grid), c4, &sum);
-                    v.w = with_offset(digits4<MASK>(y[u] + 12, sig, grid_inv, grid), c4, &sum);
+                    v.x = with_offset(digits4<MASK>(y[u], sig, step), c4, &sum);
+                    v.y = with_offset(digits4<MASK>(y[u] + 4, sig, step), c4, &sum);
+                    v.z = with_offset(digits4<MASK>(y[u] + 8, sig, step), c4, &sum);
+                    v.w = with_offset(digits4<MASK>(y[u] + 12, sig, step), c4, &sum);
                     if (ok) *reinterpret_cast<uint4*>(out + (int64_t)u * nw * (TPW * TILE_BYTES)) = v;
                 }
             }
             out += o.slice_stride;
-            sig *= inv_step, grid *= inv_step, grid_inv *= step;
+            sig *= inv_step;
 #pragma unroll
             for (int off = COLS; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
             if (lane < COLS) atomicAdd(&lsum[s][lane], sum);
@@ -366,7 +372,6 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : 3) void k_split_b
     o.S = second ? b.S : a.S, o.e = second ? b.e : a.e, o.P = second ? b.P : a.P, o.trailer = second ? b.trailer : a.trailer;
     o.Rpad = second ? b.Rpad : a.Rpad, o.slice_stride = second ? b.slice_stride : a.slice_stride;
     o.KT = second ? b.KT : a.KT, o.c = second ? b.c : a.c, o.by_col = second ? b.by_col : a.by_col;
-    o.vec = second ? b.vec : a.vec;
     int block = second ? (int)blockIdx.x - a.blocks : (int)blockIdx.x;
     if (block == 0 && threadIdx.x == 0) o.trailer[0] = o.c;
     if (blockIdx.x == 0 && (int)threadIdx.x < zero_count) zero[threadIdx.x] = 0u;
@@ -769,7 +774,6 @@ static SplitOp make_op(const SplitIn& i, int k)
     o.KT = (int)(ozl::inner_padded(i.n) / ozl::TILE_K);
     o.c = i.offset;
     o.by_col = i.by_col;
-    o.vec = reinterpret_cast<uintptr_t>(i.X) % 16 == 0 && i.ld % 2 == 0;
     return o;
 }
 

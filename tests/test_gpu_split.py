@@ -26,7 +26,8 @@ def dev(x):
 
 # (vectors, length): 4 rows / 2 rows / 1 row a workgroup; one batch and several; lengths around 64, 256, 512 and 8192
 SHAPES = [(1, 1), (3, 63), (5, 64), (33, 255), (130, 513), (7, 2047), (6, 2049), (9, 4100), (5, 8192), (3, 8193), (2, 16390),
-          (515, 8200), (2050, 130), (4100, 70), (3, 70000)]
+          (515, 8200), (2050, 130), (4100, 70), (3, 70000),
+          (300, 257), (300, 5001)]
 
 
 @pytest.mark.parametrize("split", ["rn", "bitmask"])
