@@ -128,6 +128,7 @@ struct SplitOp {
     int64_t Rpad, slice_stride;
     int KT, c;
     int by_col;
+    int per;              // vectors per workgroup: rows 1, 2 or 4, columns 4, 8 or 16
     int blocks;           // workgroups
 };
 
@@ -360,8 +361,11 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
 }
 
 constexpr int SPLIT_WAVES = 8;
-template <int DBR, int ROWS, int COLS, bool MASK>
-__global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : 3) void k_split_both(SplitOp a, SplitOp b, int k, int beta, uint32_t* zero, int zero_count)
+// DBR: elements of a row a thread holds (columns: 16); COLS: the launch may have columns.  Vectors per workgroup are each
+// operand's own: both sides of a product may be columns (A transposed), one of many vectors and one of few.
+// (With 64 elements a thread one kernel for both numbers of rows would spill: ROWS is fixed there.)
+template <int DBR, int ROWS, bool COLS, bool MASK>
+__global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : DBR == 32 ? 4 : 2) void k_split_both(SplitOp a, SplitOp b, int k, int beta, uint32_t* zero, int zero_count)
 {
     __shared__ double red[SPLIT_WAVES][16];
     __shared__ int lsum[OZIMMU_MAX_SLICES_DEV][16];  // sums of the stored bytes per slice and vector
@@ -372,17 +376,31 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : 3) void k_split_b
     o.S = second ? b.S : a.S, o.e = second ? b.e : a.e, o.P = second ? b.P : a.P, o.trailer = second ? b.trailer : a.trailer;
     o.Rpad = second ? b.Rpad : a.Rpad, o.slice_stride = second ? b.slice_stride : a.slice_stride;
     o.KT = second ? b.KT : a.KT, o.c = second ? b.c : a.c, o.by_col = second ? b.by_col : a.by_col;
+    o.per = second ? b.per : a.per;
     int block = second ? (int)blockIdx.x - a.blocks : (int)blockIdx.x;
     if (block == 0 && threadIdx.x == 0) o.trailer[0] = o.c;
     if (blockIdx.x == 0 && (int)threadIdx.x < zero_count) zero[threadIdx.x] = 0u;
     // (the grid holds whole sets of 32 workgroups per operand: four neighbours share memory lines and run on one XCD)
     block = (block >> 5) * 32 + (block & 7) * 4 + ((block >> 3) & 3);
-    if (o.by_col) {
-        if ((int64_t)block * COLS >= o.rows) return;
-        split_cols<16, COLS, MASK>(o, block, k, beta, red, lsum);
+    if ((int64_t)block * o.per >= o.rows) return;
+    if (COLS && o.by_col) {
+        if (o.per == 16)
+            split_cols<16, 16, MASK>(o, block, k, beta, red, lsum);
+        else if (o.per == 8)
+            split_cols<16, 8, MASK>(o, block, k, beta, red, lsum);
+        else
+            split_cols<16, 4, MASK>(o, block, k, beta, red, lsum);
     } else {
-        if ((int64_t)block * ROWS >= o.rows) return;
-        split_rows<DBR, ROWS, MASK>(o, block, k, beta, red, lsum);
+        if constexpr (ROWS > 0) {
+            split_rows<DBR, ROWS, MASK>(o, block, k, beta, red, lsum);
+        } else {
+            if (DBR == 16 && o.per == 4)
+                split_rows<DBR, 4, MASK>(o, block, k, beta, red, lsum);
+            else if (o.per == 2)
+                split_rows<DBR, 2, MASK>(o, block, k, beta, red, lsum);
+            else
+                split_rows<DBR, 1, MASK>(o, block, k, beta, red, lsum);
+        }
     }
 }
 
@@ -777,37 +795,55 @@ static SplitOp make_op(const SplitIn& i, int k)
     return o;
 }
 
+// Columns a workgroup of k_split_both takes (16, 8 or 4), or 0 where they are better cut along the inner dimension
+// (launch_split_cols_cut).  By microseconds of each form, fitted to 64 to 8192 columns of 4096 to 2^18, k = 1, 4, 8 and 16, each
+// form forced, the operand in no cache; taking the fastest by this estimate costs 1 % on average against the fastest
+// measured, 18 % at worst.
+//  * Whole, 16 + k bytes an element (read twice): a compute unit moves 25, 20, 19 bytes per ns with 16, 8, 4 columns a
+//    workgroup, however many workgroups it holds (24 with 4 where what an XCD's workgroups read stays in its L2 for the second
+//    time), all of them 4.4, 3.9, 2.9 per ps (k = 8, us with 16, 8, 4: 4096 columns of 4096 97, 108, 124; 2017 of 16384 254,
+//    214, 240; 1024 of 4096 54, 42, 37; one workgroup too many for the compute units: 2117 of 80064, k = 2, 878, 1141, 1315).
+//  * Cut: four launches and their merging, 60 + 2.4 k us; 6 bytes per ps where the operand stays in the memory-side cache for the
+//    second time, else 4.1; padding columns are written too.  Against the best whole, k = 8: 64 columns of 16384 90 and 72 us,
+//    500 of 65536 219 and 354, 1024 of 65536 434 and 513, 2017 of 65536 824 and 711, 8192 of 16384 807 and 713.
+// Up to 256 inner positions, where a wave does not share a tile of 64 with others, 16 (1024 columns of 64: 6.4 us, with 4 7.6).
+static int columns_per_workgroup(int64_t n, int64_t columns, int k)
+{
+    if (n <= 256) return 16;
+    const double in_l2 = 128.0 * (double)n * (double)((columns + 127) / 128);  // bytes an XCD reads: 16 columns a memory line, 8 XCDs
+    const double cut_bytes = (double)n * (16.0 * (double)columns + (double)k * (double)ozl::rows_padded(columns));
+    double least = 60.0 + 2.4 * k + cut_bytes / (8.0 * (double)n * (double)columns <= 2.7e8 ? 6e6 : 4.1e6);
+    int best = 0;
+    for (int c = 16; c >= 4; c /= 2) {
+        const double unit = c == 16 ? 25e3 : c == 8 ? 20e3 : in_l2 <= 3.3e6 ? 24e3 : 19e3;  // bytes per us of a compute unit
+        const double chip = c == 16 ? 4.4e6 : c == 8 ? 3.9e6 : 2.9e6;
+        const double rounds = (double)(((columns + c - 1) / c + 255) / 256), bytes = (double)n * (16 + k);
+        const double one_us = bytes * c * rounds / unit, all_us = bytes * (double)columns / chip;
+        const double us = 6.0 + (one_us > all_us ? one_us : all_us);
+        if (us < least) {
+            least = us;
+            best = c;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,
                         int also_zero_count)
 {
     SplitOp op[2]{};
-    int used = 0, rows = 0, cols = 0;
+    int used = 0;
+    bool columns = false;
     for (int q = 0; q < count; ++q) {
-        const SplitIn& i = ops[q];
-        if (i.by_col) {
-            // A workgroup streams its columns at some 30 bytes per ns, 16 + k bytes per element, four columns at least;
-            // the other way costs about 60 us of launches and merging and moves 2.9 TB/s.
-            const double own_us = (double)i.n * 4 * (16 + k) / 30e3;
-            const double cut_us = 60.0 + (double)i.n * (double)i.rows * (16 + k) / 2.9e6;
-            if (own_us > cut_us) {
-                const hipError_t e = launch_split_cols_cut(i, k, beta, split_mode, st);
-                if (e != hipSuccess) return e;
-                continue;
-            }
+        const int per = ops[q].by_col ? columns_per_workgroup(ops[q].n, ops[q].rows, k) : 0;
+        if (ops[q].by_col && per == 0) {
+            const hipError_t e = launch_split_cols_cut(ops[q], k, beta, split_mode, st);
+            if (e != hipSuccess) return e;
+            continue;
         }
-        SplitOp o = make_op(i, k);
-        // As many workgroups as it takes to fill the chip, else runs of memory as long as possible: 16 columns from 256
-        // workgroups on (4096 columns of 4096: 59 us with 16, 67 with 8, 71 with 4; 1024 columns: 41, 26, 21), rows by two
-        // where a row keeps 8 waves busy (4096 rows of 4096: 49 us, by four 58; 1024 rows of 1024: 9.0 and 7.9), one by one
-        // where there are few (256 rows of 16384: 21 us, by two 24).
-        if (i.by_col) {
-            const int c = i.rows >= 4096 ? 16 : i.rows >= 2048 ? 8 : 4;
-            if (cols == 0 || c < cols) cols = c;
-        } else {
-            const int r = i.n < 2048 ? 4 : (i.n > 8192 && i.rows <= 512) ? 1 : 2;
-            if (rows == 0 || r < rows) rows = r;
-        }
-        op[used++] = o;
+        columns = columns || ops[q].by_col;
+        op[used] = make_op(ops[q], k);
+        op[used++].per = per;
     }
     if (used == 0) {
         if (also_zero_count > 0)
@@ -816,43 +852,64 @@ hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int spli
         return hipGetLastError();
     }
     const int64_t n = op[0].n;
-    if (rows == 0) rows = n < 2048 ? 4 : 2;
-    if (cols == 0) cols = 16;
-    // whole sets of 32 workgroups per operand (see k_split_both)
-    for (int q = 0; q < used; ++q) {
-        const int per = op[q].by_col ? cols : rows;
-        op[q].blocks = (int)(((op[q].rows + per - 1) / per + 31) / 32 * 32);
+    int waves = 4, dbr = 16;
+    if (columns) {
+        // (the 4 tiles of an inner dimension of up to 256 keep four waves busy: 262144 columns of 64, k = 8, 178 us, with
+        // eight 216)
+        if (n > 256) waves = SPLIT_WAVES;
+        // Rows beside columns: by two where a row keeps 8 waves busy (4096 rows of 4096: 49 us, by four 58; 1024 rows of
+        // 1024: 9.0 and 7.9), one by one where there are few (256 rows of 16384: 21 us, by two 24).  Beyond 8192 inner
+        // positions a row is kept in 64 registers a thread (16384^2 907 us, with 16 of them 993).
+        for (int q = 0; q < used; ++q) {
+            if (op[q].by_col) continue;
+            op[q].per = n < 2048 ? 4 : (n > 8192 && op[q].rows <= 512) ? 1 : 2;
+            if (n > 8192) dbr = 64;
+        }
+    } else {
+        // Rows alone, up to 16384 inner positions: a workgroup of as few waves and registers as hold its rows, so that several
+        // share a compute unit - all eight waves where there are few rows, for the time of one (16 rows of 2048, k = 16: 9.3 us,
+        // with four waves 10.4).  One row a workgroup from 2048 positions on; more, whose longer pieces of a packed tile are whole
+        // memory lines, where the slices leave the caches (us, by one and by two: 4096 rows of 4096 k = 8 47.8 and 48.3, k = 16
+        // 129 and 90; 2048 of 8192 k = 1 24.0 and 25.2, k = 16 127 and 91; 2048 of 12288 k = 1 34.8 and 45.1; 4096 of 16384
+        // k = 16 447 and 380; a row of just over 8192 wastes the wide form's registers: 16384 of 9216 k = 8 540 and 568).
+        // Beyond, one by one where there are few, as beside columns.
+        for (int q = 0; q < used; ++q) {
+            const bool few = op[q].rows <= (n > 16384 ? 512 : 256);
+            const double slices = (double)k * (double)op[q].rows * (double)n;
+            const bool one = n > 16384 ? few : n > 10240 ? slices <= 200e6 : n > 8192 || slices <= 150e6;
+            op[q].per = n <= 1024 ? 4 : n > 2048 ? (one ? 1 : 2) : few ? 1 : one ? 2 : 4;
+            if (few ? n > 256 : op[q].per * n > 64 * 16 * 4) waves = SPLIT_WAVES;
+            const int hold = n <= 4096 || (one && n <= 8192) ? 16 : n <= 8192 || (one && n <= 16384) ? 32 : 64;
+            dbr = hold > dbr ? hold : dbr;
+        }
     }
-    const dim3 grid((unsigned)(op[0].blocks + op[1].blocks)), block(64 * SPLIT_WAVES);
-    // (beyond 8192 inner positions a row is kept in 64 registers a thread: 16384^2 907 us, with 16 of them 993)
-#define OZ_SPLIT(D, R, C)                                                                                             \
-    do {                                                                                                             \
-        if (split_mode == 0)                                                                                         \
-            hipLaunchKernelGGL((k_split_both<D, R, C, false>), grid, block, 0, st, op[0], op[1], k, beta, also_zero, \
-                               also_zero_count);                                                                     \
-        else                                                                                                         \
-            hipLaunchKernelGGL((k_split_both<D, R, C, true>), grid, block, 0, st, op[0], op[1], k, beta, also_zero,  \
-                               also_zero_count);                                                                     \
-    } while (0)
-#define OZ_SPLIT_COLS(D, R)             \
-    do {                                \
-        if (cols == 16)                 \
-            OZ_SPLIT(D, R, 16);         \
-        else if (cols == 8)             \
-            OZ_SPLIT(D, R, 8);          \
-        else                            \
-            OZ_SPLIT(D, R, 4);          \
-    } while (0)
-    if (n > 8192 && rows == 1)
-        OZ_SPLIT_COLS(64, 1);
-    else if (n > 8192)
-        OZ_SPLIT_COLS(64, 2);
-    else if (rows == 2)
-        OZ_SPLIT_COLS(16, 2);
+    if (dbr == 64) {  // one number of rows a launch
+        int rows = 2;
+        for (int q = 0; q < used; ++q) rows = !op[q].by_col && op[q].per < rows ? op[q].per : rows;
+        for (int q = 0; q < used; ++q) op[q].per = op[q].by_col ? op[q].per : rows;
+        dbr += rows;
+    }
+    // whole sets of 32 workgroups per operand (see k_split_both)
+    for (int q = 0; q < used; ++q) op[q].blocks = (int)(((op[q].rows + op[q].per - 1) / op[q].per + 31) / 32 * 32);
+    const dim3 grid((unsigned)(op[0].blocks + op[1].blocks)), block(64 * waves);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, op[0], op[1], k, beta, also_zero, also_zero_count);
+    };
+    const bool mask = split_mode != 0;
+    if (columns && dbr == 16)
+        mask ? launch(k_split_both<16, 0, true, true>) : launch(k_split_both<16, 0, true, false>);
+    else if (columns && dbr == 65)
+        mask ? launch(k_split_both<64, 1, true, true>) : launch(k_split_both<64, 1, true, false>);
+    else if (columns)
+        mask ? launch(k_split_both<64, 2, true, true>) : launch(k_split_both<64, 2, true, false>);
+    else if (dbr == 16)
+        mask ? launch(k_split_both<16, 0, false, true>) : launch(k_split_both<16, 0, false, false>);
+    else if (dbr == 32)
+        mask ? launch(k_split_both<32, 0, false, true>) : launch(k_split_both<32, 0, false, false>);
+    else if (dbr == 65)
+        mask ? launch(k_split_both<64, 1, false, true>) : launch(k_split_both<64, 1, false, false>);
     else
-        OZ_SPLIT_COLS(16, 4);
-#undef OZ_SPLIT_COLS
-#undef OZ_SPLIT
+        mask ? launch(k_split_both<64, 2, false, true>) : launch(k_split_both<64, 2, false, false>);
     return hipGetLastError();
 }
 

@@ -27,7 +27,7 @@ def dev(x):
 # (vectors, length): 4 rows / 2 rows / 1 row a workgroup; one batch and several; lengths around 64, 256, 512 and 8192
 SHAPES = [(1, 1), (3, 63), (5, 64), (33, 255), (130, 513), (7, 2047), (6, 2049), (9, 4100), (5, 8192), (3, 8193), (2, 16390),
           (515, 8200), (2050, 130), (4100, 70), (3, 70000),
-          (300, 257), (300, 5001)]
+          (300, 257), (300, 1030), (300, 2100), (200, 1100), (300, 5001), (270, 8194), (260, 10300), (520, 16390)]
 
 
 @pytest.mark.parametrize("split", ["rn", "bitmask"])
@@ -65,3 +65,40 @@ def test_both_operands_by_columns_or_by_rows(oz, transA, transB):
     C = torch.full((m, p), float("nan"), dtype=torch.float64, device="cuda")
     oz.gemm_ex(transA, transB, 1.0, dev(a), dev(b), 0.0, C, k)
     assert np.array_equal(C.cpu().numpy(), oracle.dgemm(A, B, k))
+
+
+# (vectors, length, k): the forms that only large operands take - rows whose slices leave the caches (four, two a workgroup, 32
+# and 64 elements a thread), columns by 16, 8 and 4 a workgroup, one more than fills the compute units
+@pytest.mark.parametrize("rows,n,k", [(13000, 1300, 9), (8010, 2100, 9), (2110, 8100, 9), (1710, 10300, 12), (4353, 4700, 5),
+                                      (2117, 6000, 4), (1030, 5000, 6), (4100, 200, 4), (20001, 3, 8)])
+@pytest.mark.parametrize("split", ["rn", "bitmask"])
+def test_large_operands_match_the_oracle_on_sampled_vectors(oz, rows, n, k, split):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(303)
+    A = torch.rand((rows, n), dtype=torch.float64, device="cuda", generator=gen) - 0.5
+    A *= torch.exp(torch.randn((rows, n), dtype=torch.float64, device="cuda", generator=gen))
+    beta, _ = oracle.params(n)
+    pick = np.unique(np.concatenate([[0, 1, rows - 1, rows - 2], inputs.sample_indices(rows, 12, seed=7)]))
+    at = torch.from_numpy(pick).cuda()
+    want, we = oracle.split_rows(A[at].cpu().numpy(), k, beta, form="int" if split == "rn" else "bitmask")
+    for S, e in (oz.split_A(A, k, split), oz.split_B(A.T.contiguous(), k, split)):
+        got = oz.export_slices(rows, n, k, S)
+        assert np.array_equal(e[at].cpu().numpy(), we)
+        assert np.array_equal(got[:, at].cpu().numpy(), want)
+        del got
+
+
+@pytest.mark.parametrize("columns,n,k,cut", [(60, 16384, 8, False), (60, 65536, 1, True), (500, 65536, 8, True),
+                                             (1000, 65536, 8, True), (700, 200000, 1, True), (4000, 16384, 8, False),
+                                             (1000, 4096, 8, False), (2100, 80000, 2, True), (20000, 10, 1, False)])
+def test_long_columns_are_cut_where_that_is_faster(oz, columns, n, k, cut):
+    # measured 1.2 to 2.7 times faster than taking them whole (and the other way round).  Which way a call takes shows in the
+    # padding of the stack: only the cut way writes it
+    B = torch.ones((n, columns), dtype=torch.float64, device="cuda")
+    S = torch.full((oz.slices_bytes(columns, n, k),), 0x5A, dtype=torch.int8, device="cuda")
+    e = torch.empty(columns, dtype=torch.int32, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    assert oz._lib.ozimmu_split_B(n, columns, B.data_ptr(), columns, k, S.data_ptr(), e.data_ptr(), st) == 0
+    row_block = -(-n // 256) * 256 * 256                      # bytes of 256 packed rows; row r of a tile at 64 r
+    at = (-(-columns // 256) - 1) * row_block + 255 * 64
+    assert bool((S[at:at + 64] != 0x5A).any()) == cut
