@@ -279,6 +279,20 @@ int ozimmu_gemm_group_accumulate(int64_t m, int64_t n, int64_t p,
                                  const int32_t *eA, const int32_t *eB, int first,
                                  double *D, int64_t ldd, void *scratch, void *stream);
 
+/* The way of running the schedule that keeps all chunk sums of a tile in registers (see ozimmu_dgemm_variant), with tile
+ * number `tile` (0 .. OZIMMU_RESIDENT_TILES - 1) instead of the library's choice; the result is the same, bit for bit.
+ * Debug / test helpers.
+ *   ozimmu_resident_tile  rows and columns of that tile (either may be NULL) for inner dimension n, k slices and an
+ *                         accumulate mode; OZIMMU_ERR_SLICES where there is no such kernel.  Host, pure.
+ *   ozimmu_dgemm_resident arguments as for ozimmu_dgemm_variant (no schedule flag, one scale per row and column);
+ *                         OZIMMU_ERR_SLICES where there is no such kernel. */
+#define OZIMMU_RESIDENT_TILES 6
+int ozimmu_resident_tile(int64_t n, int k, int accumulate_mode, int tile, int *rows, int *cols);
+int ozimmu_dgemm_resident(int64_t m, int64_t n, int64_t p,
+                          const double *A, int64_t lda, const double *B, int64_t ldb,
+                          double *D, int64_t ldd, int k, int split_mode, int accumulate_mode, int tile,
+                          void *workspace, size_t workspace_bytes, void *stream);
+
 /* Unpack a packed slice stack into the canonical order out[s][row][l]
  * (int8, k x rows x n, dense): for A that is A''_s[i][l]; for B it is
  * B''_s[l][j] stored at out[s][j][l].  Debug / test helper. */

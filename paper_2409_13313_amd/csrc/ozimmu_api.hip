@@ -80,9 +80,16 @@ int64_t r_wide_of(int64_t n, int beta)
     return r;
 }
 
+// most products of a chunk, by accumulate mode
+int64_t r_of_mode(int64_t n, int accumulate_mode)
+{
+    if (accumulate_mode == OZIMMU_ACCUM_PER_PAIR) return 1;
+    return accumulate_mode == OZIMMU_ACCUM_WIDE ? r_wide_of(n, beta_of(n)) : r_of(n, beta_of(n));
+}
+
 int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, const double* B, int64_t ldb,
                double* D, int64_t ldd, int k, int split_mode, int accumulate_mode, void* workspace,
-               size_t workspace_bytes, void* stream, void* const* events);
+               size_t workspace_bytes, void* stream, void* const* events, int resident_tile = -1);
 
 // The split-inner way of running the schedule (see run_schedule) works on at most this many 256 x 256 tiles
 // at a time: outputs that small as a whole, or the last, partly filled round of tiles of a larger output
@@ -230,11 +237,12 @@ struct Finish {
 //    with its inner range cut into Z parts on Z workgroups per tile, which add their partial sums to zeroed
 //    per-tile INT32 blocks with integer atomics, then the accumulation kernel over those tiles, which also clears
 //    the blocks again.
-// schedule: 0 = choose, or one of the OZIMMU_SCHEDULE_* flags (honoured when possible).
+// schedule: 0 = choose, or one of the OZIMMU_SCHEDULE_* flags (honoured when possible).  resident_tile >= 0: the resident
+// way with that tile (the caller has checked that there is one).
 int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t* SB, const int32_t* eA,
                  const int32_t* eB, int k, int64_t r, bool per_slice, int schedule, double* D, int64_t ldd,
                  const Finish& fin, int32_t* partial, int64_t partial_capacity, void* scratch, int num_cu, hipStream_t st,
-                 bool sync_clean = false)
+                 bool sync_clean = false, int resident_tile = -1)
 {
     // sync_clean: the caller has already zeroed the soft-barrier counters in `scratch` (the first GEMM launch
     // then need not; later ones of the same call find them used and do)
@@ -248,6 +256,37 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     const int KT = (int)(ozl::inner_padded(n) / ozl::TILE_K);
     const int64_t T = output_tiles(m, p);
     const int64_t w = chunks_of(k, r_eff);
+
+    auto launch_resident = [&](int variant) -> int {
+        const ozk::GemmArgs g = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
+        ozk::ResidentArgs a{};
+        a.SA = g.SA;
+        a.SB = g.SB;
+        a.PA = g.PA;
+        a.PB = g.PB;
+        a.pstrideA = g.pstrideA;
+        a.pstrideB = g.pstrideB;
+        a.cA = g.cA;
+        a.cB = g.cB;
+        a.strideA = g.strideA;
+        a.strideB = g.strideB;
+        a.KT = KT;
+        a.steps = (int)((n + ozl::TILE_K - 1) / ozl::TILE_K);
+        a.m = m;
+        a.p = p;
+        a.D = D;
+        a.ldd = ldd;
+        a.eA = eA;
+        a.eB = eB;
+        a.beta = beta;
+        a.finish = fin.on ? 1 : 0;
+        a.alpha = fin.alpha;
+        a.cbeta = fin.cbeta;
+        a.Cout = fin.Cout;
+        a.ldco = fin.ldco;
+        return hip_status(ozk::launch_resident(a, k, r_eff, variant, st));
+    };
+    if (resident_tile >= 0) return launch_resident(resident_tile);
 
     // The queue, for the tiles [0, tiles) of the band order: one launch whose work items are all
     // (chunk, tile) pairs, handed out round by round (256 tiles) through a counter; an item leaves its INT32 sums
@@ -414,35 +453,7 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
                 variant = v;
             }
         }
-        if (variant >= 0) {
-            const ozk::GemmArgs g = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
-            ozk::ResidentArgs a{};
-            a.SA = g.SA;
-            a.SB = g.SB;
-            a.PA = g.PA;
-            a.PB = g.PB;
-            a.pstrideA = g.pstrideA;
-            a.pstrideB = g.pstrideB;
-            a.cA = g.cA;
-            a.cB = g.cB;
-            a.strideA = g.strideA;
-            a.strideB = g.strideB;
-            a.KT = KT;
-            a.steps = (int)((n + ozl::TILE_K - 1) / ozl::TILE_K);
-            a.m = m;
-            a.p = p;
-            a.D = D;
-            a.ldd = ldd;
-            a.eA = eA;
-            a.eB = eB;
-            a.beta = beta;
-            a.finish = fin.on ? 1 : 0;
-            a.alpha = fin.alpha;
-            a.cbeta = fin.cbeta;
-            a.Cout = fin.Cout;
-            a.ldco = fin.ldco;
-            return hip_status(ozk::launch_resident(a, k, r_eff, variant, st));
-        }
+        if (variant >= 0) return launch_resident(variant);
     }
     if (queue_pays) return launch_queue(T, sets_all);
 
@@ -818,6 +829,33 @@ int ozimmu_dgemm_variant(int64_t m, int64_t n, int64_t p, const double* A, int64
                       stream, nullptr);
 }
 
+int ozimmu_resident_tile(int64_t n, int k, int accumulate_mode, int tile, int* rows, int* cols)
+{
+    if (n < 1 || n > MAX_INNER) return OZIMMU_ERR_DIM;
+    if (accumulate_mode < OZIMMU_ACCUM_GROUPED || accumulate_mode > OZIMMU_ACCUM_WIDE) return OZIMMU_ERR_SLICES;
+    if (k < 1 || k > OZIMMU_MAX_SLICES || tile < 0 || tile >= ozr::NUM_VARIANTS) return OZIMMU_ERR_SLICES;
+    const int64_t r = r_of_mode(n, accumulate_mode);
+    const ozr::Config c = ozr::config_for(k, (int)(r < k ? r : k), tile);
+    if (c.ta == 0) return OZIMMU_ERR_SLICES;
+    if (rows) *rows = 32 * c.ta;
+    if (cols) *cols = 32 * c.tb;
+    return OZIMMU_OK;
+}
+
+int ozimmu_dgemm_resident(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, const double* B, int64_t ldb,
+                          double* D, int64_t ldd, int k, int split_mode, int accumulate_mode, int tile, void* workspace,
+                          size_t workspace_bytes, void* stream)
+{
+    if (split_mode != OZIMMU_SPLIT_NEAREST && split_mode != OZIMMU_SPLIT_BITMASK) return OZIMMU_ERR_SLICES;
+    if (accumulate_mode == OZIMMU_ACCUM_WIDE && split_mode != OZIMMU_SPLIT_NEAREST) return OZIMMU_ERR_SLICES;
+    int rows = 0, cols = 0;
+    const int st = ozimmu_resident_tile(n, k, accumulate_mode, tile, &rows, &cols);
+    if (st != OZIMMU_OK) return st;
+    if (m < 0 || p < 0 || m > MAX_OUTER || p > MAX_OUTER || !ozr::in_range(m, n, p, rows, cols)) return OZIMMU_ERR_DIM;
+    return dgemm_impl(m, n, p, A, lda, B, ldb, D, ldd, k, split_mode, accumulate_mode, workspace, workspace_bytes, stream,
+                      nullptr, tile);
+}
+
 int ozimmu_split_A_variant(int64_t m, int64_t n, const double* A, int64_t lda, int k, int split_mode, int8_t* SA,
                            int32_t* eA, void* stream)
 {
@@ -874,7 +912,7 @@ namespace {
 
 int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, const double* B, int64_t ldb,
                double* D, int64_t ldd, int k, int split_mode, int accumulate_mode, void* workspace,
-               size_t workspace_bytes, void* stream, void* const* events)
+               size_t workspace_bytes, void* stream, void* const* events, int resident_tile)
 {
     if (m < 0 || n < 0 || p < 0 || m > MAX_OUTER || p > MAX_OUTER || n > MAX_INNER) return OZIMMU_ERR_DIM;
     if (lda < n || ldb < p || ldd < p || lda > MAX_LD || ldb > MAX_LD || ldd > MAX_LD) return OZIMMU_ERR_DIM;
@@ -900,9 +938,7 @@ int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, co
     const int beta = beta_of(n);
     const bool per_slice = split_mode == OZIMMU_SPLIT_NEAREST_PER_SLICE;
     const int64_t ne = per_slice ? k : 1;  // exponent arrays per operand
-    const int64_t r = accumulate_mode == OZIMMU_ACCUM_PER_PAIR
-                          ? 1
-                          : (accumulate_mode == OZIMMU_ACCUM_WIDE ? r_wide_of(n, beta) : r_of(n, beta));
+    const int64_t r = r_of_mode(n, accumulate_mode);
     char* ws = static_cast<char*>(workspace);
     void* scratch = ws;
     ws += align256(OZIMMU_SCRATCH_BYTES);
@@ -944,7 +980,7 @@ int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, co
         capacity = (int64_t)((static_cast<char*>(workspace) + workspace_bytes - reinterpret_cast<char*>(partial)) /
                              BLOCK_BYTES);
     const int rc = run_schedule(m, n, p, SA, SB, eA, eB, k, r, per_slice, schedule, D, ldd, no_finish, partial,
-                                capacity, scratch, ds.num_cu, st, !per_slice);
+                                capacity, scratch, ds.num_cu, st, !per_slice, resident_tile);
     if (rc != OZIMMU_OK) return rc;
     return hip_status(mark(2));
 }

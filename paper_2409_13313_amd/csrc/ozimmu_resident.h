@@ -55,6 +55,18 @@ constexpr Config config(int k, int r, int variant)
 
 constexpr int NUM_VARIANTS = 6;
 
+// config() of what the kernel is built for; ta == 0 for anything else
+constexpr Config config_for(int k, int r, int variant)
+{
+    if (k < MIN_K || k > MAX_K || (r < k && r != 8 && r != 4 && r != 2 && r != 1)) return Config{0, 0, 1, 1};
+    return config(k, r < k ? r : k, variant);
+}
+// grid size; 32-bit operand offsets
+constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
+{
+    return ((m + rows - 1) / rows) * ((p + cols - 1) / cols) < ((int64_t)1 << 23) && (n + 63) / 64 < ((int64_t)1 << 17);
+}
+
 // Estimate of the kernel's time in microseconds on a chip of num_cu compute units; -1 where it cannot run.
 // Measured on MI355X: an inner step of a workgroup that has its compute unit to itself takes 7.5 ns per MFMA of a wave plus
 // 0.1 to 0.2 us (k = 8, tiles of 64 x 64: 1.16 us, 32 x 32: 0.5 us; 64 x 128: 2.4 us; k = 4, 128 x 128: 1.42 us), one of two workgroups
@@ -69,12 +81,10 @@ constexpr int NUM_VARIANTS = 6;
 // 16384^3; k = 8, two of 64 x 64 against one of 64 x 128: 11.84 and 11.44 at 8192^3, and the estimate keeps the latter).
 inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64_t p, int num_cu)
 {
-    if (k < MIN_K || k > MAX_K || (r < k && r != 8 && r != 4 && r != 2 && r != 1)) return -1.0;
-    const Config c = config(k, r < k ? r : k, variant);
-    if (c.ta == 0 || num_cu < 1) return -1.0;
+    const Config c = config_for(k, r, variant);
+    if (c.ta == 0 || num_cu < 1 || !in_range(m, n, p, 32 * c.ta, 32 * c.tb)) return -1.0;
     const int64_t steps = (n + 63) / 64;
     const int64_t tiles = ((m + 32 * c.ta - 1) / (32 * c.ta)) * ((p + 32 * c.tb - 1) / (32 * c.tb));
-    if (tiles >= ((int64_t)1 << 23) || steps >= ((int64_t)1 << 17)) return -1.0;  // grid size; 32-bit operand offsets
     const double mfmas = 0.5 * k * (k + 1) * c.ta * c.tb;
     const double copied = 2048.0 * (c.ta + c.tb) * k / (4.0 * mfmas);        // bytes brought in per MFMA
     const double fetched = (double)(c.ta + c.tb) * k / mfmas;                 // KiB fetched from LDS per MFMA and wave

@@ -77,6 +77,10 @@ _lib.ozimmu_init.argtypes = []
 _lib.ozimmu_init.restype = _int
 _lib.ozimmu_dgemm_static.argtypes = [_i64, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _i64, _int, _vp]
 _lib.ozimmu_dgemm_static.restype = _int
+_lib.ozimmu_resident_tile.argtypes = [_i64, _int, _int, _int, ctypes.POINTER(_int), ctypes.POINTER(_int)]
+_lib.ozimmu_resident_tile.restype = _int
+_lib.ozimmu_dgemm_resident.argtypes = [_i64, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _i64, _int, _int, _int, _int, _vp, _sz, _vp]
+_lib.ozimmu_dgemm_resident.restype = _int
 _lib.ozimmu_export_slices.argtypes = [_i64, _i64, _int, _vp, _vp, _vp]
 _lib.ozimmu_export_slices.restype = _int
 
@@ -85,11 +89,13 @@ EXPORTS = ["ozimmu_status_string", "ozimmu_params", "ozimmu_num_chunks", "ozimmu
            "ozimmu_r_wide", "ozimmu_split_A_variant", "ozimmu_split_B_variant", "ozimmu_split_A", "ozimmu_split_B", "ozimmu_gemm_group",
            "ozimmu_accumulate", "ozimmu_gemm_group_accumulate", "ozimmu_export_slices",
            "ozimmu_workspace_bytes_variant", "ozimmu_remainder_bytes", "ozimmu_split_A_per_slice",
-           "ozimmu_split_B_per_slice", "ozimmu_init", "ozimmu_dgemm_static", "ozimmu_workspace_bytes_min"]
+           "ozimmu_split_B_per_slice", "ozimmu_init", "ozimmu_dgemm_static", "ozimmu_workspace_bytes_min",
+           "ozimmu_resident_tile", "ozimmu_dgemm_resident"]
 
 
 SPLIT_MODES = {"rn": 0, "bitmask": 1, "per_slice": 2}
 ACCUMULATE_MODES = {"grouped": 0, "per_pair": 1, "wide": 2}
+RESIDENT_TILES = 6
 SCHEDULES = {"auto": 0, "one_launch": 0x100, "split_inner": 0x200, "chunk_parallel": 0x400, "queue": 0x800}
 
 
@@ -211,6 +217,32 @@ def dgemm_variant(A: torch.Tensor, B: torch.Tensor, k: int, split: str = "rn", a
                                      SPLIT_MODES[split], ACCUMULATE_MODES[accumulate] | SCHEDULES[schedule],
                                      workspace.data_ptr(),
                                      workspace.numel(), _stream()))
+    return D
+
+
+def resident_tile(n: int, k: int, accumulate: str, tile: int) -> Optional[Tuple[int, int]]:
+    """Rows and columns of resident tile number `tile`, None where there is no such kernel."""
+    rows, cols = _int(0), _int(0)
+    if _lib.ozimmu_resident_tile(n, k, ACCUMULATE_MODES[accumulate], tile, ctypes.byref(rows), ctypes.byref(cols)) != 0:
+        return None
+    return rows.value, cols.value
+
+
+def dgemm_resident(A: torch.Tensor, B: torch.Tensor, k: int, tile: int, split: str = "rn", accumulate: str = "grouped",
+                   D: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """dgemm_variant with all chunk sums in registers and the given tile (debug / test helper)."""
+    _dev(A, torch.float64), _dev(B, torch.float64)
+    m, n = A.shape
+    n2, p = B.shape
+    if n != n2:
+        raise ValueError("inner dimensions differ")
+    if D is None:
+        D = torch.empty((m, p), dtype=torch.float64, device=A.device)
+    if workspace is None:
+        workspace = alloc_workspace(m, n, p, k, A.device, split)
+    _check(_lib.ozimmu_dgemm_resident(m, n, p, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), D.data_ptr(), _ld(D), k,
+                                      SPLIT_MODES[split], ACCUMULATE_MODES[accumulate], tile, workspace.data_ptr(),
+                                      workspace.numel(), _stream()))
     return D
 
 

@@ -74,6 +74,21 @@ int main()
     EXPECT(ozimmu_dgemm_variant(4, 4, 4, fd, 4, fd, 4, fd, 4, 8, 2, OZIMMU_ACCUM_GROUPED, fake, 1 << 30, nullptr),
            OZIMMU_ERR_SLICES);
     EXPECT(ozimmu_dgemm_variant(4, 4, 4, fd, 4, fd, 4, fd, 4, 8, 0, 0x300, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    for (int k = 0; k <= 21; ++k)
+        for (int tile = -1; tile <= OZIMMU_RESIDENT_TILES; ++tile)
+            for (int64_t n : {(int64_t)0, (int64_t)1, (int64_t)8200, (int64_t)40000, inner_max, inner_max + 1}) {
+                int rows = 0, cols = 0;
+                const int st = ozimmu_resident_tile(n, k, OZIMMU_ACCUM_GROUPED, tile, &rows, &cols);
+                EXPECT(st == OZIMMU_OK ? (rows >= 32 && rows <= 128 && cols >= 32 && cols <= 128) : rows == 0, 1);
+                EXPECT(st != OZIMMU_OK || (k >= 3 && k <= 16 && tile >= 0 && tile < OZIMMU_RESIDENT_TILES && n >= 1 && n <= inner_max), 1);
+            }
+    EXPECT(ozimmu_resident_tile(64, 8, 3, 0, nullptr, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_resident_tile(64, 8, 0, 0, nullptr, nullptr), OZIMMU_OK);
+    EXPECT(ozimmu_dgemm_resident(4, 4, 4, fd, 4, fd, 4, fd, 4, 2, 0, 0, 0, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_dgemm_resident(4, 4, 4, fd, 4, fd, 4, fd, 4, 8, 2, 1, 0, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_dgemm_resident(4, inner_max, 4, fd, inner_max, fd, 4, fd, 4, 8, 0, 1, 0, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
+    EXPECT(ozimmu_dgemm_resident(4, 4, 4, fd, 3, fd, 4, fd, 4, 8, 0, 0, 0, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
+    EXPECT(ozimmu_dgemm_resident(4, 4, 4, fd, 4, fd, 4, fd, 4, 8, 0, 0, 0, fake, 16, nullptr), OZIMMU_ERR_WORKSPACE);
     EXPECT(ozimmu_gemm_ex(0, 0, 4, 4, 4, 1.0, fd, 3, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
     EXPECT(ozimmu_gemm_ex(1, 0, 5, 4, 4, 1.0, fd, 4, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
     EXPECT(ozimmu_gemm_ex(0, 1, 4, 5, 4, 1.0, fd, 5, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);

@@ -1,8 +1,8 @@
-"""GPU parity of the kernel that keeps all chunk sums of a tile in registers (ozimmu_resident.hip), at the sizes where it can
-go wrong: the edges of its tiles (32 to 128 rows and columns), inner dimensions around the step of 64 and of one or two
-steps, every slice count it is built for, chunks shorter than the groups (long inner dimensions, per-pair
-accumulation), step (v), strided outputs, and exponents at which the scaled summation has to give way to the
-term-by-term one.  Each D is compared bit for bit with the oracle and / or the persistent launch."""
+"""GPU parity of the kernel that keeps all chunk sums of a tile in registers (ozimmu_resident.hip): every one of its instances
+(slice count x chunk length x tile) forced, and the library's own choice at the sizes where it can go wrong: the edges of its
+tiles (32 to 128 rows and columns), inner dimensions around the step of 64, chunks shorter than the groups (long inner
+dimensions, per-pair accumulation), step (v), strided outputs, and exponents at which the scaled summation has to give way to
+the term-by-term one.  Each D is compared bit for bit with the oracle and / or the persistent launch."""
 import numpy as np
 import pytest
 
@@ -35,14 +35,52 @@ def test_tile_and_step_edges_match_the_oracle_bit_for_bit(oz, m, n, p, k):
     assert np.array_equal(got[:, :p], oracle.dgemm(A, B, k)) and np.isnan(got[:, p]).all()
 
 
+# Chunk lengths r by the inner dimensions and the accumulate mode that give them; inner dimensions of one step, an odd and an
+# even number of steps
+CHUNKS = {"whole groups": ("grouped", (60, 130, 257)), "8": ("grouped", (8200, 8260)), "4": ("grouped", (16400, 16500)),
+          "2": ("grouped", (32800, 32900)), "1": ("per_pair", (64, 129, 250))}
+
+
+@pytest.mark.parametrize("k,chunk", [(k, c) for c in CHUNKS for k in range(3, 17) if not (c in "842" and k <= int(c))])
+def test_every_tile_of_every_instance(oz, k, chunk):
+    # the compile-time order of fetches, copies and counted waits is another one for every instance
+    accumulate, inner = CHUNKS[chunk]
+    m, p, tiles = 293, 261, 0
+    for n in inner:
+        A, B = inputs.phi_pair(m, n, p, 1.0, seed=207)
+        dA, dB = dev(A), dev(B)
+        ref = oz.dgemm_variant(dA, dB, k, "rn", accumulate, schedule="one_launch")
+        rows, cols = np.array([0, 31, 130, m - 1]), np.array([0, 33, 128, p - 1])
+        want = oracle.dgemm_variant(np.ascontiguousarray(A[rows]), np.ascontiguousarray(B[:, cols]), k, "rn", accumulate)
+        assert np.array_equal(ref.cpu().numpy()[np.ix_(rows, cols)], want)
+        for tile in range(oz.RESIDENT_TILES):
+            if oz.resident_tile(n, k, accumulate, tile) is None:
+                continue
+            tiles += 1
+            D = torch.full((m, p + 1), float("nan"), dtype=torch.float64, device="cuda")
+            oz.dgemm_resident(dA, dB, k, tile, "rn", accumulate, D=D[:, :p])
+            assert torch.equal(D[:, :p], ref) and bool(torch.isnan(D[:, p]).all()), (n, tile)
+    assert tiles > 0 or (accumulate == "per_pair" and k > 10) or (chunk == "2" and k > 15)   # more than 64 chunk sums
+
+
+def test_no_tile_where_the_kernel_has_none(oz):
+    A = torch.zeros((40, 40), dtype=torch.float64, device="cuda")
+    for k, tile, split, accumulate in ((2, 0, "rn", "grouped"), (17, 0, "rn", "grouped"), (8, 6, "rn", "grouped"),
+                                       (8, -1, "rn", "grouped"), (11, 0, "rn", "per_pair"), (8, 0, "per_slice", "per_pair"),
+                                       (8, 0, "bitmask", "wide")):
+        with pytest.raises(oz.OzimmuError) as err:
+            oz.dgemm_resident(A, A, k, tile, split, accumulate, workspace=oz.alloc_workspace(40, 40, 40, 20))
+        assert err.value.status == -3
+
+
 @pytest.mark.parametrize("m,n,p,k,split,accumulate", [
-    (2040, 1990, 2049, 3, "rn", "grouped"), (2048, 2048, 2048, 4, "rn", "grouped"),    # tiles of 128 x 128
-    (1990, 2047, 2000, 5, "rn", "grouped"), (2000, 1999, 2047, 6, "bitmask", "grouped"),  # 64 x 128, two steps in LDS
-    (1000, 1999, 2047, 7, "rn", "grouped"), (1024, 2050, 2048, 8, "rn", "grouped"),    # 64 x 128, one step in LDS
-    (1030, 8200, 1000, 9, "rn", "grouped"), (1030, 8200, 1000, 12, "rn", "grouped"),   # r = 8: short chunks
-    (2050, 8200, 1990, 14, "rn", "grouped"),                                           # 20 chunks: 32 x 96
-    (1500, 16400, 1500, 8, "rn", "grouped"), (1500, 16400, 1500, 5, "bitmask", "grouped"),  # r = 4
-    (1030, 300, 1000, 7, "bitmask", "per_pair"), (1030, 300, 1000, 9, "bitmask", "per_pair"),  # 28 and 45 chunks
+    (2040, 1990, 2049, 3, "rn", "grouped"), (2048, 2048, 2048, 4, "rn", "grouped"),
+    (1990, 2047, 2000, 5, "rn", "grouped"), (2000, 1999, 2047, 6, "bitmask", "grouped"),
+    (1000, 1999, 2047, 7, "rn", "grouped"), (1024, 2050, 2048, 8, "rn", "grouped"),
+    (1030, 8200, 1000, 9, "rn", "grouped"), (1030, 8200, 1000, 12, "rn", "grouped"),
+    (2050, 8200, 1990, 14, "rn", "grouped"),
+    (1500, 16400, 1500, 8, "rn", "grouped"), (1500, 16400, 1500, 5, "bitmask", "grouped"),
+    (1030, 300, 1000, 7, "bitmask", "per_pair"), (1030, 300, 1000, 9, "bitmask", "per_pair"),
     (1030, 300, 1000, 3, "rn", "per_pair"), (1030, 300, 1000, 5, "rn", "per_pair"), (1030, 300, 1000, 6, "rn", "per_pair"),
     (1030, 300, 1000, 10, "rn", "per_pair"), (1030, 300, 1000, 11, "rn", "wide")])
 def test_larger_outputs_match_the_persistent_launch_and_sampled_oracle_entries(oz, m, n, p, k, split, accumulate):
