@@ -492,7 +492,7 @@ __global__ void k_prefix_sums(int64_t Rpad, int k, int32_t* P)
 constexpr int SBATCH = 4;
 constexpr int PITCH = 33;  // dwords per column row in LDS (32 data + 1 pad)
 
-template <bool MASK>
+template <bool MASK, bool KEEP>
 __global__ __launch_bounds__(256) void k_split_B(int64_t n, int64_t p, const double* __restrict__ B, int64_t ldb,
                                                  int k, int beta, int c, int8_t* __restrict__ SB,
                                                  int32_t* eB, int32_t* __restrict__ P,
@@ -554,11 +554,15 @@ __global__ __launch_bounds__(256) void k_split_B(int64_t n, int64_t p, const dou
                     const uint32_t* src = &tile[s][jr * PITCH + oc * 4];
                     uint4 v = make_uint4(src[0], src[1], src[2], src[3]);
                     int8_t* dst = SB + (int64_t)(sb + s) * slice_stride + packed_offset(j0 + jr, l0 + oc * CHUNK, KT);
-                    // whole 128-byte lines that nobody reads before the GEMM: non-temporal (4 % on this kernel; the
-                    // 64-byte row segments of the A kernels need the L2 to merge them and stay temporal)
+                    // Whole 128-byte lines.  KEEP: the memory-side cache holds the slices until the products read them, whose
+                    // steps otherwise wait on memory (41 x 25165 x 94, k = 6, 32 x 32 tiles: 159 us and 105); where they
+                    // are too many, non-temporal, 4 % faster here (1024 columns of 65536, k = 8).
                     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
                     const u32x4 vv = {v.x, v.y, v.z, v.w};
-                    __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(dst));
+                    if constexpr (KEEP)
+                        *reinterpret_cast<u32x4*>(dst) = vv;
+                    else
+                        __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(dst));
                 }
             }
             __syncthreads();
@@ -765,13 +769,15 @@ static hipError_t launch_split_cols_cut(const SplitIn& i, int k, int beta, int s
     const int64_t blocks = Npad / 128;
     const int per_wg = blocks >= 32 ? 4 : 1;
     dim3 grid((unsigned)((blocks + per_wg - 1) / per_wg), (unsigned)(Rpad / 64));
-    if (split_mode == 0) {
-        hipLaunchKernelGGL(k_split_B<false>, grid, dim3(256), 0, st, n, p, i.X, i.ld, k, beta, i.offset, i.S, i.e, P, trailer,
-                           Npad, Rpad, stride, per_wg);
-    } else {
-        hipLaunchKernelGGL(k_split_B<true>, grid, dim3(256), 0, st, n, p, i.X, i.ld, k, beta, i.offset, i.S, i.e, P, trailer,
-                           Npad, Rpad, stride, per_wg);
-    }
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, n, p, i.X, i.ld, k, beta, i.offset, i.S, i.e, P, trailer, Npad, Rpad,
+                           stride, per_wg);
+    };
+    const bool mask = split_mode != 0, keep = (double)Npad * (8.0 * (double)p + (double)k * (double)Rpad) <= 200e6;
+    if (keep)
+        mask ? launch(k_split_B<true, true>) : launch(k_split_B<false, true>);
+    else
+        mask ? launch(k_split_B<true, false>) : launch(k_split_B<false, false>);
     hipLaunchKernelGGL(k_prefix_sums, dim3((unsigned)((Rpad + 255) / 256)), dim3(256), 0, st, Rpad, k, P);
     return hipGetLastError();
 }
@@ -797,26 +803,25 @@ static SplitOp make_op(const SplitIn& i, int k)
 
 // Columns a workgroup of k_split_both takes (16, 8 or 4), or 0 where they are better cut along the inner dimension
 // (launch_split_cols_cut).  By microseconds of each form, fitted to 64 to 8192 columns of 4096 to 2^18, k = 1, 4, 8 and 16, each
-// form forced, the operand in no cache; taking the fastest by this estimate costs 1 % on average against the fastest
-// measured, 18 % at worst.
+// form forced, operands beyond 64 MB in no cache (smaller ones are usually still there from whatever made them).
 //  * Whole, 16 + k bytes an element (read twice): a compute unit moves 25, 20, 19 bytes per ns with 16, 8, 4 columns a
-//    workgroup, however many workgroups it holds (24 with 4 where what an XCD's workgroups read stays in its L2 for the second
-//    time), all of them 4.4, 3.9, 2.9 per ps (k = 8, us with 16, 8, 4: 4096 columns of 4096 97, 108, 124; 2017 of 16384 254,
-//    214, 240; 1024 of 4096 54, 42, 37; one workgroup too many for the compute units: 2117 of 80064, k = 2, 878, 1141, 1315).
-//  * Cut: four launches and their merging, 60 + 2.4 k us; 6 bytes per ps where the operand stays in the memory-side cache for the
+//    workgroup, however many workgroups it holds (32 with 4 of an operand in the caches), all of them 4.4, 3.9, 2.9 (4.2)
+//    per ps (k = 8, us with 16, 8, 4: 4096 columns of 4096 97, 108, 124; 2017 of 16384 254, 214, 240; 1024 of 4096 54, 42, 37;
+//    one workgroup too many for the compute units: 2117 of 80064, k = 2, 878, 1141, 1315).
+//  * Cut: four launches and their merging, 65 + 2.4 k us; 6 bytes per ps where the operand stays in the memory-side cache for the
 //    second time, else 4.1; padding columns are written too.  Against the best whole, k = 8: 64 columns of 16384 90 and 72 us,
 //    500 of 65536 219 and 354, 1024 of 65536 434 and 513, 2017 of 65536 824 and 711, 8192 of 16384 807 and 713.
 // Up to 256 inner positions, where a wave does not share a tile of 64 with others, 16 (1024 columns of 64: 6.4 us, with 4 7.6).
 static int columns_per_workgroup(int64_t n, int64_t columns, int k)
 {
     if (n <= 256) return 16;
-    const double in_l2 = 128.0 * (double)n * (double)((columns + 127) / 128);  // bytes an XCD reads: 16 columns a memory line, 8 XCDs
+    const bool small = 8.0 * (double)n * (double)columns <= 64e6;
     const double cut_bytes = (double)n * (16.0 * (double)columns + (double)k * (double)ozl::rows_padded(columns));
-    double least = 60.0 + 2.4 * k + cut_bytes / (8.0 * (double)n * (double)columns <= 2.7e8 ? 6e6 : 4.1e6);
+    double least = 65.0 + 2.4 * k + cut_bytes / (8.0 * (double)n * (double)columns <= 2.7e8 ? 6e6 : 4.1e6);
     int best = 0;
     for (int c = 16; c >= 4; c /= 2) {
-        const double unit = c == 16 ? 25e3 : c == 8 ? 20e3 : in_l2 <= 3.3e6 ? 24e3 : 19e3;  // bytes per us of a compute unit
-        const double chip = c == 16 ? 4.4e6 : c == 8 ? 3.9e6 : 2.9e6;
+        const double unit = c == 16 ? 25e3 : c == 8 ? 20e3 : small ? 32e3 : 19e3;  // bytes per us of a compute unit
+        const double chip = c == 16 ? 4.4e6 : c == 8 ? 3.9e6 : small ? 4.2e6 : 2.9e6;
         const double rounds = (double)(((columns + c - 1) / c + 255) / 256), bytes = (double)n * (16 + k);
         const double one_us = bytes * c * rounds / unit, all_us = bytes * (double)columns / chip;
         const double us = 6.0 + (one_us > all_us ? one_us : all_us);

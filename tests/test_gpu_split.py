@@ -90,7 +90,8 @@ def test_large_operands_match_the_oracle_on_sampled_vectors(oz, rows, n, k, spli
 
 @pytest.mark.parametrize("columns,n,k,cut", [(60, 16384, 8, False), (60, 65536, 1, True), (500, 65536, 8, True),
                                              (1000, 65536, 8, True), (700, 200000, 1, True), (4000, 16384, 8, False),
-                                             (1000, 4096, 8, False), (2100, 80000, 2, True), (20000, 10, 1, False)])
+                                             (1000, 4096, 8, False), (2100, 80000, 2, True), (20000, 10, 1, False),
+                                             (60, 24000, 1, False), (200, 20000, 8, False)])
 def test_long_columns_are_cut_where_that_is_faster(oz, columns, n, k, cut):
     # measured 1.2 to 2.7 times faster than taking them whole (and the other way round).  Which way a call takes shows in the
     # padding of the stack: only the cut way writes it
