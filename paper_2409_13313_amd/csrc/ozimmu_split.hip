@@ -773,7 +773,7 @@ static hipError_t launch_split_cols_cut(const SplitIn& i, int k, int beta, int s
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, n, p, i.X, i.ld, k, beta, i.offset, i.S, i.e, P, trailer, Npad, Rpad,
                            stride, per_wg);
     };
-    const bool mask = split_mode != 0, keep = (double)Npad * (8.0 * (double)p + (double)k * (double)Rpad) <= 200e6;
+    const bool mask = split_mode != 0, keep = (8.0 + k) * (double)n * (double)p <= 260e6;
     if (keep)
         mask ? launch(k_split_B<true, true>) : launch(k_split_B<false, true>);
     else
@@ -802,53 +802,93 @@ static SplitOp make_op(const SplitIn& i, int k)
 }
 
 // Columns a workgroup of k_split_both takes (16, 8 or 4), or 0 where they are better cut along the inner dimension
-// (launch_split_cols_cut).  By microseconds of each form, fitted to 64 to 8192 columns of 4096 to 2^18, k = 1, 4, 8 and 16, each
-// form forced, operands beyond 64 MB in no cache (smaller ones are usually still there from whatever made them).
-//  * Whole, 16 + k bytes an element (read twice): a compute unit moves 25, 20, 19 bytes per ns with 16, 8, 4 columns a
-//    workgroup, however many workgroups it holds (32 with 4 of an operand in the caches), all of them 4.4, 3.9, 2.9 (4.2)
+// (launch_split_cols_cut); 0 for rows.  By the least sum of microseconds over the operands of a call, which share a launch unless
+// they are cut.  Fitted to 64 to 8192 columns of 4096 to 2^18, k = 1, 4, 8 and 16, each form forced, operands beyond 64 MB in
+// no cache (smaller ones are usually still there from whatever made them, unless both together are beyond 128 MB).
+//  * Whole, 16 + k bytes an element (read twice): a compute unit moves 25, 20, 16.5 bytes per ns with 16, 8, 4 columns a
+//    workgroup, however many workgroups it holds (26 with 4 of an operand in the caches), all of them 4.4, 3.9, 2.9 (4.2)
 //    per ps (k = 8, us with 16, 8, 4: 4096 columns of 4096 97, 108, 124; 2017 of 16384 254, 214, 240; 1024 of 4096 54, 42, 37;
 //    one workgroup too many for the compute units: 2117 of 80064, k = 2, 878, 1141, 1315).
 //  * Cut: four launches and their merging, 65 + 2.4 k us; 6 bytes per ps where the operand stays in the memory-side cache for the
 //    second time, else 4.1; padding columns are written too.  Against the best whole, k = 8: 64 columns of 16384 90 and 72 us,
 //    500 of 65536 219 and 354, 1024 of 65536 434 and 513, 2017 of 65536 824 and 711, 8192 of 16384 807 and 713.
+//  * Rows beside or instead: 8 + k bytes an element (16 + k beyond 16384 positions) at 4.5 per ps, a row at 25 per ns.
 // Up to 256 inner positions, where a wave does not share a tile of 64 with others, 16 (1024 columns of 64: 6.4 us, with 4 7.6).
-static int columns_per_workgroup(int64_t n, int64_t columns, int k)
+static void choose_columns(const SplitIn* ops, int count, int k, int* per)
 {
-    if (n <= 256) return 16;
-    const bool small = 8.0 * (double)n * (double)columns <= 64e6;
-    const double cut_bytes = (double)n * (16.0 * (double)columns + (double)k * (double)ozl::rows_padded(columns));
-    double least = 65.0 + 2.4 * k + cut_bytes / (8.0 * (double)n * (double)columns <= 2.7e8 ? 6e6 : 4.1e6);
-    int best = 0;
-    for (int c = 16; c >= 4; c /= 2) {
-        const double unit = c == 16 ? 25e3 : c == 8 ? 20e3 : small ? 32e3 : 19e3;  // bytes per us of a compute unit
-        const double chip = c == 16 ? 4.4e6 : c == 8 ? 3.9e6 : small ? 4.2e6 : 2.9e6;
-        const double rounds = (double)(((columns + c - 1) / c + 255) / 256), bytes = (double)n * (16 + k);
-        const double one_us = bytes * c * rounds / unit, all_us = bytes * (double)columns / chip;
-        const double us = 6.0 + (one_us > all_us ? one_us : all_us);
-        if (us < least) {
+    constexpr int FORMS = 4, columns_of[FORMS] = {16, 8, 4, 0};
+    for (int q = 0; q < count; ++q) per[q] = ops[q].by_col && ops[q].n <= 256 ? 16 : 0;
+    if (ops[0].n <= 256) return;
+    const double n = (double)ops[0].n, both = (double)ops[0].rows + (count == 2 ? (double)ops[1].rows : 0.0);
+    const int forms0 = ops[0].by_col ? FORMS : 1, forms1 = count == 2 && ops[1].by_col ? FORMS : 1;
+    double least = -1.0;
+    for (int form = 0; form < forms0 * forms1; ++form) {
+        const int f[2] = {form % forms0, form / forms0};
+        double cut_us = 0.0, all_us = 0.0, longest_us = 0.0, rows_us = 0.0, groups = 0.0, group_us = 0.0;  // of the launch they share
+        bool shared = false;
+        for (int q = 0; q < count; ++q) {
+            const double vectors = (double)ops[q].rows;
+            const int c = columns_of[f[q]];
+            if (!ops[q].by_col) {
+                const double row_us = n * (16 + k) / 25e3;
+                rows_us = n * vectors * (n > 16384 ? 16 + k : 8 + k) / 4.5e6;
+                all_us += rows_us;
+                longest_us = longest_us > row_us ? longest_us : row_us;
+                shared = true;
+            } else if (c == 0) {
+                const double bytes = n * (16.0 * vectors + (double)k * (double)ozl::rows_padded(ops[q].rows));
+                cut_us += 65.0 + 2.4 * k + bytes / (8.0 * n * vectors <= 2.7e8 ? 6e6 : 4.1e6);
+            } else {
+                const bool cached = 8.0 * n * vectors <= 64e6 && 8.0 * n * both <= 128e6;
+                const double w = (double)((ops[q].rows + c - 1) / c);
+                const double us = n * (16 + k) * c / (c == 16 ? 25e3 : c == 8 ? 20e3 : cached ? 26e3 : 16.5e3);
+                all_us += n * vectors * (16 + k) / (c == 16 ? 4.4e6 : c == 8 ? 3.9e6 : cached ? 4.2e6 : 2.9e6);
+                groups += w, group_us += w * us;
+                longest_us = longest_us > us ? longest_us : us;
+                shared = true;
+            }
+        }
+        double us = cut_us;
+        if (shared) {
+            // (short workgroups share compute units, long ones each bind one's rate)
+            const double rounds = n > 4096.0 ? (double)(((int64_t)groups + 255) / 256) : groups / 256.0;
+            double own_us = groups > 0.0 ? rounds * group_us / groups : 0.0;
+            own_us = own_us > all_us ? own_us : all_us;
+            // (a long workgroup of columns has less of the memory while rows take most of it: 39 columns of 189760 beside 1024
+            // rows, k = 4, 1167 us, cut 816)
+            const double slowed_us = longest_us + 0.25 * rows_us;
+            own_us = own_us > slowed_us ? own_us : slowed_us;
+            us += 6.0 + own_us;
+        }
+        if (least < 0.0 || us < least) {
             least = us;
-            best = c;
+            for (int q = 0; q < count; ++q) per[q] = ops[q].by_col ? columns_of[f[q]] : 0;
         }
     }
-    return best;
 }
 
 hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,
                         int also_zero_count)
 {
     SplitOp op[2]{};
-    int used = 0;
+    int used = 0, per[2] = {0, 0};
     bool columns = false;
+    choose_columns(ops, count, k, per);
     for (int q = 0; q < count; ++q) {
-        const int per = ops[q].by_col ? columns_per_workgroup(ops[q].n, ops[q].rows, k) : 0;
-        if (ops[q].by_col && per == 0) {
+        if (ops[q].by_col && per[q] == 0) {
             const hipError_t e = launch_split_cols_cut(ops[q], k, beta, split_mode, st);
             if (e != hipSuccess) return e;
             continue;
         }
         columns = columns || ops[q].by_col;
         op[used] = make_op(ops[q], k);
-        op[used++].per = per;
+        op[used++].per = per[q];
+    }
+    // columns first: their workgroups are the longer ones
+    if (used == 2 && op[1].by_col && !op[0].by_col) {
+        const SplitOp rows = op[0];
+        op[0] = op[1];
+        op[1] = rows;
     }
     if (used == 0) {
         if (also_zero_count > 0)
