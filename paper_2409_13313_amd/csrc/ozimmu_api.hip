@@ -7,6 +7,7 @@
 #include "ozimmu_kernels.h"
 #include "ozimmu_layout.h"
 #include "ozimmu_resident.h"
+#include <cmath>
 #include <mutex>
 
 namespace {
@@ -442,9 +443,17 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
         // (measured 96.5 ms at 16384^3, k = 8; 36.7 ms at 4096 x 65536 x 4096, k = 10; 7.4 ms at 8192^3, k = 6).  Both
         // sides at some shapes, whole calls, queue or chunk-parallel against the chosen resident variant: 4096^3 k = 3
         // 0.46 / 0.36 ms, k = 8 1.78 / 1.48, k = 16 5.91 / 4.87; 1024 x 16384 x 1024 k = 8 0.61 / 0.54;
-        // 2048 x 65536 x 2048 k = 6 (12 chunks) 5.08 / 4.96; 4096 x 65536 x 4096 k = 10 (30 chunks) 39.7 / 40.3
+        // 2048 x 65536 x 2048 k = 6 (12 chunks) 5.08 / 4.96; 4096 x 65536 x 4096 k = 10 (30 chunks) 39.7 / 40.3.
+        // Beyond 16384 inner positions the chunk-parallel way takes longer than its estimate (by 1.04 at 20000, 1.15 at 40000, 1.2
+        // to 1.35 at 80000, less with few chunks).  The split-inner way takes 2.0 to 2.3 times its own from 140000 on, where it wins
+        // (23 x 309890 x 14, k = 3, 561 us, k_resident 1588; 7 x 196852 x 184, k = 10, 2970 and 2896), and more before (474 x
+        // 37065 x 351, k = 3, 308 and 179).
         double other_us = queue_pays ? (0.64 * pairs * KT + 17.0 * (double)w) * (double)T / num_cu
-                                     : cp_us + tail_us + rounds * (0.60 * pairs * KT + 50.0 * (double)w);
+                                     : cp_us + 1.9 * tail_us + rounds * (0.60 * pairs * KT + 50.0 * (double)w);
+        if (!queue_pays && n > 16384) {
+            const double slower = 0.02 + 0.004 * (double)w;
+            other_us *= 1.0 + (slower < 0.08 ? slower : 0.08) * log2((double)n / 16384.0);
+        }
         int variant = -1;
         for (int v = 0; v < ozr::NUM_VARIANTS; ++v) {
             const double us = ozr::estimate_us(k, r_eff, v, m, n, p, num_cu);

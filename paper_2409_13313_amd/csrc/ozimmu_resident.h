@@ -1,6 +1,7 @@
 // Which tile the kernel with resident chunk sums (ozimmu_resident.hip) uses for which schedule: shared by the kernel and
 // by the host code that chooses between the ways to run a schedule.
 #pragma once
+#include "ozimmu_layout.h"
 #include <cstdint>
 
 namespace ozr {
@@ -79,6 +80,14 @@ constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
 // 8.8 ns; k = 8, 64 x 128: 85, 0.17, 9.0; w = 20, 32 x 96: 152, 0.30, 11.2).  Two workgroups on a compute unit fill each
 // other's barriers: 0.6 ns less (k = 5, two of 64 x 96 against one of 64 x 128: 5.44 and 5.94 ms at 8192^3, 44.0 and 46.4 at
 // 16384^3; k = 8, two of 64 x 64 against one of 64 x 128: 11.84 and 11.44 at 8192^3, and the estimate keeps the latter).
+// (The first of the two prices is used up to 1500 us: they differ there by 10 % for 64 x 128, k = 8, less for smaller tiles.)
+//
+// A step of few MFMAs waits for its operands instead.  How long depends on where they come from: the memory-side cache
+// ("near") while it holds the operands and their slices (256 MiB), else memory ("far").  And on the ring: a copy has two thirds of a step to
+// arrive with one step in LDS, one and a half with two (us a step, near / far: one, 40 KiB 0.6 / 0.9, 48 KiB 0.7 / 1.03, two
+// intervals (k <= 4) 0.93 / 1.36; two, 12 KiB 0.2 / 0.33, 24 KiB 0.25 / 0.42, 48 KiB 0.68 / 0.76).  Without this the choice fell on
+// tiles that were latency bound: 1473 x 13248 x 872, k = 4, 64 x 96 tiles 296 us (estimated 130), the chunk-parallel way
+// 206; 1042 x 30250 x 1180, k = 4, whole call 1030 us, now 790; 615 x 31277 x 496, k = 7, 684, now 530.
 inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64_t p, int num_cu)
 {
     const Config c = config_for(k, r, variant);
@@ -86,20 +95,36 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     const int64_t steps = (n + 63) / 64;
     const int64_t tiles = ((m + 32 * c.ta - 1) / (32 * c.ta)) * ((p + 32 * c.tb - 1) / (32 * c.tb));
     const double mfmas = 0.5 * k * (k + 1) * c.ta * c.tb;
-    const double copied = 2048.0 * (c.ta + c.tb) * k / (4.0 * mfmas);        // bytes brought in per MFMA
-    const double fetched = (double)(c.ta + c.tb) * k / mfmas;                 // KiB fetched from LDS per MFMA and wave
-    const double round_us = 4.0 + 0.4 * c.ta * c.tb;
+    const double kib = 2.0 * k * (c.ta + c.tb);                               // operands of a step
+    const double copied = 1024.0 * kib / (4.0 * mfmas);                      // bytes brought in per MFMA
+    const double fetched = 0.5 * kib / mfmas;                                 // KiB fetched from LDS per MFMA and wave
+    // (rows of D that begin inside a piece of 64 bytes leave pieces to be merged: 4224 x 384 x 1611, k = 4, 128 x 128
+    // tiles 54 us, 1608 columns 37)
+    const double odd_us = p % 8 != 0 && c.ta * c.tb == 16 ? 0.6 : 0.0;
+    const double round_us = 4.0 + (0.4 + odd_us) * c.ta * c.tb;
     const int64_t slots = (int64_t)num_cu * c.waves, full = tiles / slots, left = tiles % slots;
     auto total = [&](double alone_us, double all_us) {
         double us = (double)full * ((double)steps * all_us + round_us);
         if (left > 0) us += (double)steps * (left > num_cu ? all_us : alone_us) + round_us;
         return us;
     };
-    const double alone_us = 0.0075 * mfmas + 0.15;
-    const double us = total(alone_us, c.waves == 2 ? 0.0168 * mfmas + 0.2 : alone_us + 0.12);
+    // how much of the operands comes from memory
+    const double bytes = (8.0 * (double)(m + p) + (double)k * (double)(ozl::rows_padded(m) + ozl::rows_padded(p))) * (double)n;
+    const double far = bytes < 240e6 ? 0.0 : bytes > 320e6 ? 1.0 : (bytes - 240e6) / 80e6;
+    auto at_least = [](double us, double least) { return us > least ? us : least; };
+    double wait_us;                                                           // least time of a step, its operands' way
+    if (c.depth == 1)
+        wait_us = (0.05 + 0.0135 * kib + far * (0.40 - 0.002 * kib)) * (k <= 4 ? 1.5 : 1.0);
+    else
+        wait_us = (1.0 - far) * (0.15 + 0.0035 * kib) + far * at_least(0.24 + 0.0075 * kib, kib / 62.0);
+    double wait2_us = wait_us;                                                // the same with all places taken
+    if (far == 1.0 && n > 12000 && (c.waves == 2 || c.depth == 2)) wait2_us = at_least(wait_us, kib / (c.waves == 2 ? 34.0 : 58.0));
+    if (far == 1.0 && c.waves == 2 && c.depth == 1 && k <= 4) wait2_us = at_least(wait2_us, 1.5);
+    const double us = total(at_least(0.0075 * mfmas + 0.15, wait_us),
+                            at_least(c.waves == 2 ? 0.0168 * mfmas + 0.2 : 0.0075 * mfmas + 0.27, wait2_us));
     if (us < 1500.0) return us;
     const double hot_us = mfmas * ((c.waves == 2 ? 0.0062 : 0.0068) + 2.0e-5 * copied + 0.005 * fetched);
-    return total(hot_us, hot_us * c.waves);
+    return total(at_least(hot_us, wait_us), at_least(hot_us * c.waves, wait2_us));
 }
 
 }  // namespace ozr
