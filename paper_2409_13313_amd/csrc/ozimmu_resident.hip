@@ -264,7 +264,10 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
     // Operand copies: 16 rows (1 KiB) of a packed tile per instruction.  A slice's 2 TA pieces of A and 2 TB pieces of B
     // lie one behind the other in its LDS slot, wave w brings pieces w NC .. w NC + NC - 1 (where they do not divide among
     // four waves the last wave repeats some: the same bytes to the same place).  One M0 per slice: the instruction
-    // offset moves the LDS and the global address alike, so the global base of piece q is taken q KiB lower.
+    // offset moves the LDS and the global address alike, so the global base of piece q is taken q KiB lower.  (M0 is a
+    // reserved register, no allocation puts a value there; that nothing else in the kernel names it is tested on the
+    // assembly of every instance.  As an operand of the other copies it costs moves in two loops, k = 6, w = 8, 64 x 128 and
+    // k = 16, 64 x 64.)
     constexpr int NC = P::NC;
     const int piece0 = wave * NC < 2 * NF - NC ? wave * NC : 2 * NF - NC;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
 
     // Fragment addresses (see k_gemm: one MFMA takes 64 inner bytes, the four lane groups of 16 supply the logical chunks
     // 0, 3, 1, 2, which keeps the fetches off each other's banks).  ds_read offsets are 16-bit immediates: a second base
-    // serves what lies beyond.
+    // serves what lies beyond (k = 16 with 64 x 64 tiles, 128 KiB a set, reaches past both: an addition per fetch there).
     constexpr int FAR = 49152;
     uint32_t fcur[2][2], fnxt[2][2];  // [A, B][near, far]
     {

@@ -1,0 +1,61 @@
+"""Code-generation checks of the kernel with resident chunk sums, every instance of it (CPU only: hipcc cross-compiles).
+
+Its copies into LDS are inline assembly that the compiler does not follow: M0 holds their LDS address, and hand-written
+`s_waitcnt vmcnt(N)` count the copies in flight.  The first copy of a slice sets M0
+and the others rely on it, so nothing else in the whole kernel may name it; and the loop holds neither spills (whose reloads
+bring waits of their own) nor moves to and from accumulation registers nor a `vmcnt` wait of the compiler's."""
+import os
+import re
+import shutil
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = os.path.join(ROOT, "paper_2409_13313_amd", "csrc", "ozimmu_resident.hip")
+FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=off",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
+INSTANCE = re.compile(r"^(_ZN12_GLOBAL__N_110k_residentILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)EEEv\w+):(.*?)s_endpgm", re.S | re.M)
+
+pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+
+
+def assembly(out, k):
+    pr = subprocess.run(["hipcc", *FLAGS, f"-DOZ_RES_K={k}", "--cuda-device-only", "-S", SRC, "-o", out],
+                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert pr.returncode == 0, pr.stdout[-3000:]
+    return open(out).read()
+
+
+def test_every_instance(tmp_path):
+    with ThreadPoolExecutor(8) as pool:
+        texts = list(pool.map(lambda k: assembly(str(tmp_path / f"k{k}.s"), k), range(3, 17)))
+    seen = 0
+    for text in texts:
+        for m in INSTANCE.finditer(text):
+            name, (k, r, ta, tb, depth, waves) = m.group(1), map(int, m.groups()[1:7])
+            what = (k, r, 32 * ta, 32 * tb)
+            lines = m.group(8).split("\n")
+            mfma = [i for i, line in enumerate(lines) if "v_mfma_i32_16x16x64_i8" in line]
+            assert len(mfma) == k * (k + 1) // 2 * ta * tb, what
+            by_hand = False
+            m0 = 0
+            for i, line in enumerate(lines):
+                if "#ASMSTART" in line or "#ASMEND" in line:
+                    by_hand = "#ASMSTART" in line
+                    continue
+                code = line.split(";")[0]
+                if re.search(r"\bm0\b", code):
+                    assert by_hand and code.strip().startswith("s_add_u32 m0,"), (what, line)
+                    m0 += 1
+                if mfma[0] <= i <= mfma[-1]:
+                    assert by_hand or "vmcnt" not in code, (what, line)
+                    assert not re.search(r"v_accvgpr|scratch_|buffer_", code), (what, line)
+            assert m0 >= k, what
+            at = text.index(".name:           " + name)
+            about = text[text.rindex("- .agpr_count", 0, at):text.find("- .agpr_count", at)]
+            for key in ("private_segment_fixed_size", "vgpr_spill_count", "sgpr_spill_count"):
+                assert re.search(r"\.%s:\s+(\d+)" % key, about).group(1) == "0", (what, key)
+            seen += 1
+    assert seen == 196
