@@ -65,13 +65,6 @@ __device__ inline uint64_t wave_max_u64(uint64_t v)
     return v;
 }
 
-__device__ inline int wave_sum_i32(int v)
-{
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 // One slice of 4 consecutive inner elements: digits of y[], remainders updated in place, the 4 stored
 // bytes (digit + c, c = the stack's offset) packed into a dword.  Returns the dword; *sum receives the sum
 // of the 4 stored bytes.  Inner padding (l >= n) enters as y = 0 like a real zero and is stored as c.
@@ -461,11 +454,10 @@ __global__ void k_fill_u32(int64_t count, uint32_t* x, uint32_t v)
     if (i < count) x[i] = v;
 }
 
-template <bool MASK>
 __global__ void k_decode_keys(int64_t count, int32_t* e)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) e[i] = key_to_exp<MASK>((uint32_t)e[i]);
+    if (i < count) e[i] = key_to_exp<false>((uint32_t)e[i]);
 }
 
 // per-slice sums of a stack (k arrays of Rpad entries) -> prefix sums over the slices, in place
@@ -992,7 +984,7 @@ hipError_t launch_split_B_per_slice(int64_t n, int64_t p, const double* B, int64
         hipLaunchKernelGGL(k_split_B_ps, grid, dim3(256), 0, st, n, p, s == 0 ? B : rem, s == 0 ? ldb : p, beta,
                            SB + (int64_t)s * stride, keys + (int64_t)s * p,
                            s + 1 < k ? keys + (int64_t)(s + 1) * p : nullptr, rem, Npad);
-    hipLaunchKernelGGL(k_decode_keys<false>, dim3((unsigned)((nk + 255) / 256)), dim3(256), 0, st, nk, eB);
+    hipLaunchKernelGGL(k_decode_keys, dim3((unsigned)((nk + 255) / 256)), dim3(256), 0, st, nk, eB);
     return hipGetLastError();
 }
 
