@@ -149,6 +149,7 @@ def main() -> int:
     flops = 2.0 * m * n * p
     value = flops / (wall_ms * 1e-3) / 1e12
     int_ops = flops * pairs
+    resident = 3 <= k <= 16 and n <= 2 ** 15   # (longer inner dimensions have more chunks than fit the registers)
     gemm_tops = int_ops / (gemm_ms * 1e-3) / 1e12
     split_bytes = 8.0 * (m * n + n * p) + float(k) * (m * n + n * p)
     log(f"k={k}: {wall_ms:.2f} ms/step  -> {value:.1f} TFLOP/s effective; split {split_ms:.2f} ms "
@@ -189,7 +190,8 @@ def main() -> int:
                              "(profiles/gemm_16384_k8_traffic.md)" if (m, n, p, k) in MEASURED_TRAFFIC_BYTES else
                              "null: no rocprofv3 --pmc run of this shape is on file (hardware counters cannot be "
                              "read from inside the benchmark process)"),
-            "algorithmic_bytes": float(pairs) * (m * n + n * p) + 8.0 * m * p,
+            # every slice read once where all chunks of a tile stay in registers, else anew for every slice pair
+            "algorithmic_bytes": float(k if resident else pairs) * (m * n + n * p) + 8.0 * m * p,
         },
         "split_hbm": {"algorithmic_GBps": round(split_bytes / split_ms / 1e6, 1), "peak_GBps": PEAK_HBM_GBS,
                       "frac": round(split_bytes / split_ms / 1e6 / PEAK_HBM_GBS, 4)},
