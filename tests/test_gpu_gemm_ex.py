@@ -86,7 +86,7 @@ def test_gemm_ex_empty_inner_dimension_scales_c(oz):
 
 
 def test_gemm_ex_large_output_with_a_cut_tail_round(oz):
-    # 272 tiles: one full round in the persistent launch, 16 tiles cut along the inner dimension; transposed
+    # 272 tiles of 256 x 256 (for the persistent launch one full round and 16 tiles more; k_resident takes it); transposed
     # operands and step (v) on top.  Rows / columns from every band of 256 (every tile, so also the cut tail
     # round) are recomputed by the oracle.
     m, n, p, k = 4352, 520, 4096, 4

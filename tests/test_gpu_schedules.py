@@ -107,7 +107,7 @@ def test_chunk_parallel_with_strided_output_reused_workspace_and_step_v(oz):
         oz.dgemm_variant(dev(A), dev(B), k, "rn", "grouped", D=Dbig[:, :p], workspace=ws, schedule="chunk_parallel")
     got = Dbig.cpu().numpy()
     assert np.array_equal(got[:, :p], want) and (got[:, p:] == -1.0).all()
-    # the GEMM-routine form takes the same way by default at this size: step (v) in the accumulation kernel
+    # the GEMM-routine form, by the way the library chooses
     C0 = np.random.Generator(np.random.PCG64(96)).standard_normal((m, p))
     for alpha, beta in ((-1.5, 0.0), (0.75, -0.25)):
         C = dev(C0)
@@ -210,8 +210,37 @@ def test_queue_schedule_matches_the_persistent_launch_and_sampled_oracle_entries
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("m,n,p,k,way", [
+    (4096, 300, 8192, 17, "queue"),            # 512 tiles: two full rounds of the queue, no tail
+    (300, 520, 270, 17, "chunk_parallel"),     # 4 ragged tiles
+    (700, 2100, 300, 20, "chunk_parallel")])
+def test_step_v_in_the_last_addition_of_the_ways_with_blocks(oz, m, n, p, k, way):
+    # slice counts beyond those k_resident is built for: the default is one of the ways that leave their INT32 sums in blocks of
+    # the workspace, and step (v) rides on the pass that adds the blocks up
+    A, B = inputs.phi_pair(m, n, p, 0.5, seed=99)
+    dA, dB = dev(A), dev(B)
+    ref = oz.dgemm_variant(dA, dB, k, "rn", "grouped", schedule="one_launch")
+    ws = oz.alloc_workspace(m, n, p, k)
+    ws.fill_(0x5A)
+    assert torch.equal(oz.dgemm(dA, dB, k, workspace=ws), ref)
+    assert not bool((blocks_of(ws, oz, m, n, p, k) == 0x5A).all())
+    forced = torch.empty_like(ref)
+    ws2 = queue_workspace(oz, m, n, p, k) if way == "queue" else ws
+    oz.dgemm_variant(dA, dB, k, "rn", "grouped", D=forced, workspace=ws2, schedule=way)
+    assert torch.equal(forced, ref)
+    C0 = torch.from_numpy(np.random.Generator(np.random.PCG64(100)).standard_normal((m, p))).cuda()
+    for alpha, beta in ((-1.5, 0.0), (0.75, -0.25)):
+        C = C0.clone()
+        ws.fill_(0x5A)
+        oz.gemm_ex(False, False, alpha, dA, dB, beta, C, k, workspace=ws)
+        assert not bool((blocks_of(ws, oz, m, n, p, k) == 0x5A).all())
+        t1 = alpha * ref
+        want = t1 if beta == 0.0 else t1 + beta * C0
+        assert torch.equal(C, want)
+
+
 def test_default_schedule_of_a_large_output_is_bit_identical_with_step_v(oz):
-    # 1056 tiles: the default is the queue (full rounds) here; step (v) rides on its tile accumulation
+    # 1056 tiles of 256 x 256: step (v) rides on the last additions of whichever way the library takes (k_resident)
     m, n, p, k = 8192, 300, 8448, 4
     A, B = inputs.phi_pair(m, n, p, 0.5, seed=99)
     dA, dB = dev(A), dev(B)
@@ -226,30 +255,37 @@ def test_default_schedule_of_a_large_output_is_bit_identical_with_step_v(oz):
         assert torch.equal(C, want)
 
 
-def test_default_schedule_repeated_calls_give_the_same_bits(oz):
-    # 592 tiles in three rounds on recycled blocks: every call of a run must reproduce the persistent launch's D
+@pytest.mark.parametrize("schedule", ["auto", "queue"])
+def test_default_schedule_repeated_calls_give_the_same_bits(oz, schedule):
+    # the queue: 592 tiles in three rounds on recycled blocks, and every call of a run must reproduce the persistent launch's D
     # (the blocks written by one XCD are read by another; a stale value would show as a difference here)
     m, n, p, k = 4096, 256, 9472, 8
     A, B = inputs.phi_pair(m, n, p, 1.0, seed=101)
     dA, dB = dev(A), dev(B)
     ref = oz.dgemm_variant(dA, dB, k, "rn", "grouped", schedule="one_launch")
-    ws = oz.alloc_workspace(m, n, p, k)
+    ws = queue_workspace(oz, m, n, p, k) if schedule == "queue" else oz.alloc_workspace(m, n, p, k)
     D = torch.empty_like(ref)
     for rep in range(25):
         D.fill_(float("nan"))
-        oz.dgemm(dA, dB, k, D=D, workspace=ws)
+        oz.dgemm_variant(dA, dB, k, "rn", "grouped", D=D, workspace=ws, schedule=schedule)
         assert torch.equal(D, ref), f"call {rep}"
 
 
 @pytest.mark.parametrize("split,accumulate", [("bitmask", "grouped"), ("rn", "wide"), ("bitmask", "per_pair")])
-def test_default_schedule_of_a_large_output_with_the_comparison_variants(oz, split, accumulate):
-    # 272 tiles: the queue by default where its blocks fit (one per chunk: per-pair accumulation has 15 of them at
-    # k = 5), else the persistent launch; either way the bits of the forced persistent launch and of the oracle
+@pytest.mark.parametrize("schedule", ["auto", "queue"])
+def test_default_schedule_of_a_large_output_with_the_comparison_variants(oz, split, accumulate, schedule):
+    # 272 tiles, by the library's choice (k_resident) and as a queue (a block per chunk: per-pair accumulation has 15 of them at
+    # k = 5): the bits of the forced persistent launch and of the oracle
     m, n, p, k = 4096, 300, 4352, 5
     A, B = inputs.phi_pair(m, n, p, 2.0, seed=102)
     dA, dB = dev(A), dev(B)
     ref = oz.dgemm_variant(dA, dB, k, split, accumulate, schedule="one_launch")
-    got = oz.dgemm_variant(dA, dB, k, split, accumulate)
+    got = torch.empty_like(ref)
+    blocks = 3 * k * (k + 1) // 2 * 256 + 2
+    ws = None
+    if schedule == "queue":
+        ws = torch.empty(oz.workspace_bytes_min(m, n, p, k) + blocks * 4 * 256 * 256, dtype=torch.uint8, device="cuda")
+    oz.dgemm_variant(dA, dB, k, split, accumulate, D=got, workspace=ws, schedule=schedule)
     assert torch.equal(got, ref)
     I = inputs.sample_indices(m, 32, seed=5)
     J = inputs.sample_indices(p, 32, seed=6)
