@@ -11,8 +11,8 @@
 // What bounds it: the matrix cores, at the clock the chip's power budget allows.  Per MFMA the wave fetches 0.167 KiB of
 // fragments from LDS (k = 8, tiles of 64 x 128; k_gemm 0.25), the compute unit brings in 85 bytes of operands (128), and
 // the launch reads 137 GB from beyond L2 at 16384^3 (281).  All of that is energy that goes into clock instead:
-// 16384^3, k = 8: 1.90 GHz at 91 % busy pipes against 1.68 GHz at 91.5 %, 86.9 against 95.6 ms on one box
-// (3.64 POP/s, 90 % of what a register-only MFMA loop sustains on such bytes).  Small outputs gain more: their tiles
+// 16384^3, k = 8: 1.86 GHz at 92 % busy pipes against 1.68 GHz at 91.5 %, 86.9 against 95.6 ms on one box
+// (3.5 to 3.7 POP/s, 86 to 90 % of what a register-only MFMA loop sustains on such bytes).  Small outputs gain more: their tiles
 // need no blocks, no atomic adds and no second kernel, and 64 x 64 tiles spread a 1024^3 product over the whole chip
 // (whole calls, k_gemm's ways and a split of three to seven launches -> this behind a split of one: 1024^3 k = 9
 // 126 -> 43 us, 777 x 1001 x 513 k = 7 122 -> 29 us, 4096^3 k = 8 1.86 -> 1.50 ms, 4096^3 k = 9 with one addition per slice

@@ -88,7 +88,7 @@ __device__ inline uint32_t slice_word4(double* y, int c, double two_beta, int* s
 // ---------------------------------------------------------------------------
 // Rows of A and columns of B in one launch.
 //
-// Rows: a workgroup of 8 waves takes ROWS consecutive vectors (4, 2 or 1); a wave
+// Rows: a workgroup of 8 waves (4 for short ones alone) takes ROWS consecutive vectors (4, 2 or 1); a wave
 // covers 256 / ROWS inner positions of them at a time, a lane 4 consecutive ones,
 // so that a slice goes out in runs of 64 ROWS bytes.  Columns: a workgroup takes
 // COLS of them (16, 8 or 4); a wave covers 1024 / COLS inner positions, a lane 16
