@@ -876,8 +876,9 @@ hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int spli
         op[used] = make_op(ops[q], k);
         op[used++].per = per[q];
     }
-    // columns first: their workgroups are the longer ones
-    if (used == 2 && op[1].by_col && !op[0].by_col) {
+    // Columns first beyond 1024 inner positions: their workgroups are the longer ones (1537 x 2051 x 1283, k = 9, a call 174.1 us,
+    // columns first 170.0; up to there they are not: 777 x 1001 x 513, k = 7, 29.5 and 30.1)
+    if (used == 2 && op[1].by_col && !op[0].by_col && op[0].n > 1024) {
         const SplitOp rows = op[0];
         op[0] = op[1];
         op[1] = rows;
