@@ -287,7 +287,7 @@ int ozimmu_gemm_group_accumulate(int64_t m, int64_t n, int64_t p,
  *                         accumulate mode; OZIMMU_ERR_SLICES where there is no such kernel.  Host, pure.
  *   ozimmu_dgemm_resident arguments as for ozimmu_dgemm_variant (no schedule flag, one scale per row and column);
  *                         OZIMMU_ERR_SLICES where there is no such kernel. */
-#define OZIMMU_RESIDENT_TILES 6
+#define OZIMMU_RESIDENT_TILES 7
 int ozimmu_resident_tile(int64_t n, int k, int accumulate_mode, int tile, int *rows, int *cols);
 int ozimmu_dgemm_resident(int64_t m, int64_t n, int64_t p,
                           const double *A, int64_t lda, const double *B, int64_t ldb,

@@ -23,25 +23,37 @@ struct Config {
 };
 constexpr int lds_bytes(int k, const Config& c) { return c.depth * k * (c.ta + c.tb) * 2048 + 128 * (c.ta + c.tb); }
 
+constexpr int ACC_TILES = 64;    // tiles of 16 x 16 that the accumulation registers of a wave hold
+constexpr int NUM_VARIANTS = 7, EXTENDED = 6;  // the last one is k_extended, the others k_resident
+
 // variant 0: the largest tile whose chunk sums fit the 256 accumulation registers; the others: smaller ones for outputs that
-// the large one would not spread evenly over the chip
+// the large one would not spread evenly over the chip; EXTENDED: the next larger tile whose chunk sums fit the ordinary registers
+// too, beside fragments (those of the low slices and of two high ones) and about 24 more.  Shapes in the order of what they move per MFMA;
+// others that fit (96 x 96, 64 x 160, 32 x 128) were no faster.
 constexpr Config config(int k, int r, int variant)
 {
     const int w = num_chunks(k, r);
     Config c{0, 0, 1, 1};
-    int area = 0;  // 16 x 16 tiles of a wave in the largest tile
     if (w <= 4) c.ta = 4, c.tb = 4;
     else if (w <= 8) c.ta = 2, c.tb = 4;
     else if (w <= 16) c.ta = 2, c.tb = 2;
     else if (w <= 21) c.ta = 1, c.tb = 3;
     else if (w <= 32) c.ta = 1, c.tb = 2;
-    else if (w <= 64) c.ta = 1, c.tb = 1;
-    else return c;
-    area = c.ta * c.tb;
-    if (variant > 0) {
+    else if (w <= ACC_TILES) c.ta = 1, c.tb = 1;
+    const int area = c.ta * c.tb;  // 16 x 16 tiles of a wave in the largest tile
+    if (variant == EXTENDED) {
+        constexpr int shapes[8][2] = {{4, 4}, {3, 4}, {2, 4}, {2, 3}, {2, 2}, {1, 3}, {1, 2}, {1, 1}};
+        c.ta = 0;
+        for (int x = 0; x < 8 && c.ta == 0; ++x) {
+            const int ta = shapes[x][0], tb = shapes[x][1];
+            const int more = 4 * (w * ta * tb - ACC_TILES), frag = 4 * (ta + tb) * ((k + 1) / 2 + 2);
+            if (ta == 3 && k < 5) continue;  // (no faster: few MFMAs a step, 96 x 128 outputs to write)
+            if (ta * tb > area && (more > 0 ? more : 0) + frag + 24 <= 256) c.ta = ta, c.tb = tb;
+        }
+    } else if (variant > 0) {
         const int ta = variant == 1 || variant == 2 ? 2 : 1, tb = variant == 1 ? 2 : variant == 2 || variant == 3 ? 3 : variant == 4 ? 2 : 1;
         c.ta = 0;
-        if (w * ta * tb > 64 || (ta * tb >= area && !(w > 8 && ta * tb == 6))) return c;
+        if (w * ta * tb > ACC_TILES || (ta * tb >= area && !(w > 8 && ta * tb == 6))) return c;
         c.ta = ta, c.tb = tb;
         // two workgroups on a compute unit where the registers (accumulators; fragments of the low slices and of two high
         // ones, and about 25 more) and the LDS allow it
@@ -53,8 +65,6 @@ constexpr Config config(int k, int r, int variant)
     if (lds_bytes(k, c) > 160 * 1024) c.ta = 0;
     return c;
 }
-
-constexpr int NUM_VARIANTS = 6;
 
 // config() of what the kernel is built for; ta == 0 for anything else
 constexpr Config config_for(int k, int r, int variant)
@@ -71,7 +81,8 @@ constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
 // Estimate of the kernel's time in microseconds on a chip of num_cu compute units; -1 where it cannot run.
 // Measured on MI355X: an inner step of a workgroup that has its compute unit to itself takes 7.5 ns per MFMA of a wave plus
 // 0.1 to 0.2 us (k = 8, tiles of 64 x 64: 1.16 us, 32 x 32: 0.5 us; 64 x 128: 2.4 us; k = 4, 128 x 128: 1.42 us), one of two workgroups
-// that share it 8.4 ns per MFMA of both plus 0.2 us; with several rounds of tiles the former becomes 0.27 us.  A round of
+// that share it 8.4 ns per MFMA of both plus 0.2 us; with several rounds of tiles the former becomes 0.27 us (32 x 32: 0.2; w = 45
+// 0.52 us a step, 32 x 64 0.95).  A round of
 // tiles adds start values, the first operands and the writing of D: 4 us plus 0.4 us per 16 x 16 tile of a wave.  Calls of
 // milliseconds run at the clock the power budget leaves, and what an MFMA costs then grows with the bytes that are moved
 // for it (4096^3: k = 9, 64 x 96 against 64 x 64 with half the fetches more, 1.85 and 1.91 ms; k = 10, 2.25 and 2.28;
@@ -100,8 +111,10 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     const double fetched = 0.5 * kib / mfmas;                                 // KiB fetched from LDS per MFMA and wave
     // (rows of D that begin inside a piece of 64 bytes leave pieces to be merged: 4224 x 384 x 1611, k = 4, 128 x 128
     // tiles 54 us, 1608 columns 37)
-    const double odd_us = p % 8 != 0 && c.ta * c.tb == 16 ? 0.6 : 0.0;
-    const double round_us = 4.0 + (0.4 + odd_us) * c.ta * c.tb;
+    const double odd_us = p % 8 == 0 ? 0.0 : c.ta * c.tb == 16 ? 0.6 : variant == EXTENDED ? 0.3 : 0.0;
+    // (k_extended has more start values to form and more sums to add up: 448 x 359 x 4480, k = 7, one addition per pair, 32 x 96
+    // 39 us behind the split, three rounds of 5.4 us of steps)
+    const double round_us = 4.0 + (variant == EXTENDED ? 2.0 + 0.08 * c.ta * c.tb : 0.0) + (0.4 + odd_us) * c.ta * c.tb;
     const int64_t slots = (int64_t)num_cu * c.waves, full = tiles / slots, left = tiles % slots;
     auto total = [&](double alone_us, double all_us) {
         double us = (double)full * ((double)steps * all_us + round_us);
@@ -120,8 +133,9 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     double wait2_us = wait_us;                                                // the same with all places taken
     if (far == 1.0 && n > 12000 && (c.waves == 2 || c.depth == 2)) wait2_us = at_least(wait_us, kib / (c.waves == 2 ? 34.0 : 58.0));
     if (far == 1.0 && c.waves == 2 && c.depth == 1 && k <= 4) wait2_us = at_least(wait2_us, 1.5);
+    const double barrier_us = c.ta * c.tb == 1 ? 0.2 : 0.27;
     const double us = total(at_least(0.0075 * mfmas + 0.15, wait_us),
-                            at_least(c.waves == 2 ? 0.0168 * mfmas + 0.2 : 0.0075 * mfmas + 0.27, wait2_us));
+                            at_least(c.waves == 2 ? 0.0168 * mfmas + 0.2 : 0.0075 * mfmas + barrier_us, wait2_us));
     if (us < 1500.0) return us;
     const double hot_us = mfmas * ((c.waves == 2 ? 0.0062 : 0.0068) + 2.0e-5 * copied + 0.005 * fetched);
     return total(at_least(hot_us, wait_us), at_least(hot_us * c.waves, wait2_us));

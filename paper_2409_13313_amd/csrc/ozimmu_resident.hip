@@ -18,10 +18,17 @@
 // 126 -> 43 us, 777 x 1001 x 513 k = 7 122 -> 29 us, 4096^3 k = 8 1.86 -> 1.50 ms, 4096^3 k = 9 with one addition per slice
 // pair 4.13 -> 2.61 ms).
 //
-// Tried without gain: the MFMAs of a pair with A held and B changing (0.7 % slower at 16384^3, 1 % at 4096^3); chunk sums
-// beyond the 256 accumulation registers in ordinary ones, for tiles a third larger (k = 6 96 x 128, k = 8 96 x 96, k = 12
-// 64 x 96: 5 % slower, 1 % slower, equal at 8192^3, 21 % slower at 4096^3 k = 8: moves between the register files in the
-// loop).
+// Tried without gain: the MFMAs of a pair with A held and B changing (0.7 % slower at 16384^3, 1 % at 4096^3).
+//
+// k_extended is the same kernel with chunk sums in ordinary registers too, where the 64 tiles of 16 x 16 of the accumulation
+// registers are too few for the next larger tile.  Its MFMAs are asm statements that read and write their sums in place: left to
+// the compiler, sums of a full register file wander, and the moves that takes sit in the loop (64 x 96 at k = 12, 96 x 128 at k = 6:
+// equal and 5 % slower than the smaller tile that way).  A larger tile moves fewer bytes per MFMA, from beyond L2, into LDS and out of
+// it: 128 x 128 instead of two workgroups of 64 x 96 at k = 5, 4096^3 708 -> 658 us and 8192^3 5.62 -> 4.90 ms; 64 x 128 instead of 64 x 96 at
+// k = 9 and 10, 1.84 -> 1.75 and 2.16 -> 2.06 ms at 4096^3, 14.5 -> 13.9 ms at 8192^3, k = 9.  One addition per slice pair, whose k (k + 1) / 2 sums
+// leave small tiles only and whose bound is the way of the operands through LDS, gains most: 4096^3, k = 9, 32 x 64 instead of 32 x 32,
+// 2.54 -> 2.25 ms, and k = 11 to 13, which had no resident tile at all, 5.95, 7.09, 8.32 -> 3.39, 3.77, 4.20 ms.
+// No gain: 96 x 96 and 64 x 160 at k = 7 and 8 (0 to 0.5 % at 8192^3 and 16384^3, 3 to 5 % slower where 4096 is no multiple of them).
 //
 // Fragments: L = (k + 1) / 2 low slices of both operands stay in registers for a step, the high ones pass through two
 // buffers, so that every fragment is fetched once per step and wave.  A wave holds as many 16 x 16 tiles as w chunk
@@ -102,6 +109,7 @@ constexpr Range chunk_range(int c)
 // where the rest has grown too long (8192^3, k = 16: 40.0 ms with three, 38.4 with five; k = 12 23.7 and 24.3).
 template <int K, int R, int TA, int TB, int D>
 struct Plan {
+    static constexpr int k = K, r = R, ta = TA, tb = TB, depth = D;
     static constexpr int L = (K + 1) / 2;
     static constexpr int NP = K * (K + 1) / 2;
     static constexpr int W = num_chunks(K, R);
@@ -238,11 +246,12 @@ __device__ inline void tile_of_block(int b, int TM, int TP, int& tm, int& tp)
     }
 }
 
-template <int K, int R, int TA, int TB, int D, int WAVES>
-__global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
+// A workgroup's tile.  IN_PLACE: k_extended (see the head).
+template <class P, bool IN_PLACE>
+__device__ __attribute__((always_inline)) inline void run_tile(const ozk::ResidentArgs& a)
 {
-    using P = Plan<K, R, TA, TB, D>;
     static constexpr P plan{};
+    constexpr int K = P::k, R = P::r, TA = P::ta, TB = P::tb, D = P::depth;
     constexpr int L = P::L, W = P::W, NF = P::NF, NI = P::NI;
     constexpr int RA = 32 * TA, RB = 32 * TB;               // rows and columns of the workgroup's tile
     constexpr int SLOT = (RA + RB) * TILE_K;                // one slice of both operands: A rows, then B columns
@@ -343,6 +352,8 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
     };
 
     v4i acc[W][TA][TB];
+    // what the accumulation registers do not hold lies in ordinary ones (k_extended)
+    constexpr auto ordinary = [](int c, int i, int j) { return (c * TB + j) * TA + i >= ozr::ACC_TILES; };
     const int KT = a.steps;
 
     const uint32_t lv = (uint32_t)lane * 16u;
@@ -405,19 +416,22 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
         uint32_t cb[TB];
 #pragma unroll
         for (int j = 0; j < TB; ++j) cb[j] = fix - (uint32_t)cA * (uint32_t)(pb[t1 - 1][j] - (t0 > 1 ? pb[t0 > 1 ? t0 - 2 : 0][j] : 0));
-#pragma unroll
-        for (int i = 0; i < TA; ++i) {
+        static_for<TA>([&](auto I) __attribute__((always_inline)) {
+            constexpr int i = decltype(I)::value;
             uint32_t ra[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 ra[r] = (uint32_t)cB * (uint32_t)(pa[s1 - 1][i][r] - (s0 > 1 ? pa[s0 > 1 ? s0 - 2 : 0][i][r] : 0));
-#pragma unroll
-            for (int j = 0; j < TB; ++j) {
+            static_for<TB>([&](auto J) __attribute__((always_inline)) {
+                constexpr int j = decltype(J)::value;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[c][i][j][r] = (int)(cb[j] - ra[r]);
-                asm volatile("" : "+a"(acc[c][i][j]));
-            }
-        }
+                if constexpr (ordinary(c, i, j))
+                    asm volatile("" : "+v"(acc[c][i][j]));
+                else
+                    asm volatile("" : "+a"(acc[c][i][j]));
+            });
+        });
     });
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
@@ -501,11 +515,17 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
             constexpr int c = chunk_of(s, u, R);
             const v4i fa = s <= L ? low[s <= L ? s : 0][i] : hi[(s - L - 1) & 1][i];
             const v4i fb = u <= L ? low[u <= L ? u : 0][TA + j] : hi[(u - L - 1) & 1][TA + j];
-            acc[c][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, acc[c][i][j], 0, 0, 0);
+            // (in place: the compiler sees no matrix instruction; the wait states that its result asks for come after the loop)
+            if constexpr (!IN_PLACE)
+                acc[c][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, acc[c][i][j], 0, 0, 0);
+            else if constexpr (ordinary(c, i, j))
+                asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(acc[c][i][j]) : "v"(fa), "v"(fb));
+            else
+                asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc[c][i][j]) : "v"(fa), "v"(fb));
             // (an MFMA touches no memory: without a use in the order of the asm statements instruction selection may gather
             // all fetches and copies of the step in front of all MFMAs)
             // (with one set of operands it does not, and the use would cost moves of accumulators)
-            if constexpr (D == 2) asm volatile("" ::"a"(acc[c][i][j]));
+            if constexpr (D == 2 && !IN_PLACE) asm volatile("" ::"a"(acc[c][i][j]));
             __builtin_amdgcn_sched_barrier(0);
         });
         v0 = v1;
@@ -518,6 +538,7 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
         }
     }
     wait_vmcnt<0>();  // no copy may still be writing LDS when the workgroup ends
+    if constexpr (IN_PLACE) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 
     // Steps (iv) and (v): per element the chunk sums in schedule order, one rounded addition each.  Register r of tile
     // (i, j) in lane l: row 4 (l / 16) + r, column l % 16.
@@ -611,6 +632,17 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
         finish_tile(std::false_type{});
 }
 
+template <int K, int R, int TA, int TB, int D, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
+{
+    run_tile<Plan<K, R, TA, TB, D>, false>(a);
+}
+template <int K, int R, int TA, int TB, int D>
+__global__ __launch_bounds__(256, 1) void k_extended(ozk::ResidentArgs a)
+{
+    run_tile<Plan<K, R, TA, TB, D>, true>(a);
+}
+
 template <int K, int R, int V>
 hipError_t launch(const ozk::ResidentArgs& a_in, hipStream_t st)
 {
@@ -624,12 +656,14 @@ hipError_t launch(const ozk::ResidentArgs& a_in, hipStream_t st)
         a.TP = (int)((a.p + RB - 1) / RB);
         constexpr int smem = ozr::lds_bytes(K, c);
         static_assert(smem <= 160 * 1024, "LDS of a compute unit");
-        if (a.setup)
-            return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_resident<K, R, c.ta, c.tb, c.depth, c.waves>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        hipLaunchKernelGGL((k_resident<K, R, c.ta, c.tb, c.depth, c.waves>), dim3((unsigned)a.TM * (unsigned)a.TP), dim3(256),
-                           smem, st, a);
-        return hipGetLastError();
+        const void* kernel;
+        if constexpr (V == ozr::EXTENDED)
+            kernel = reinterpret_cast<const void*>(&k_extended<K, R, c.ta, c.tb, c.depth>);
+        else
+            kernel = reinterpret_cast<const void*>(&k_resident<K, R, c.ta, c.tb, c.depth, c.waves>);
+        if (a.setup) return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        void* args[] = {&a};
+        return hipLaunchKernel(kernel, dim3((unsigned)a.TM * (unsigned)a.TP), dim3(256), args, smem, st);
     }
 }
 
@@ -643,6 +677,7 @@ hipError_t launch_r(const ozk::ResidentArgs& a, int variant, hipStream_t st)
         case 3: return launch<K, R, 3>(a, st);
         case 4: return launch<K, R, 4>(a, st);
         case 5: return launch<K, R, 5>(a, st);
+        case ozr::EXTENDED: return launch<K, R, ozr::EXTENDED>(a, st);
         default: return hipErrorInvalidValue;
     }
 }
