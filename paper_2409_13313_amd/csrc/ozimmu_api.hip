@@ -285,6 +285,8 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
         a.cbeta = fin.cbeta;
         a.Cout = fin.Cout;
         a.ldco = fin.ldco;
+        const double* const out = fin.on ? fin.Cout : D;
+        a.keep = (reinterpret_cast<uintptr_t>(out) % 64 != 0 || (fin.on ? fin.ldco : ldd) % 8 != 0) && ozr::merge_rows(k, n);
         return hip_status(ozk::launch_resident(a, k, r_eff, variant, st));
     };
     if (resident_tile >= 0) return launch_resident(resident_tile);

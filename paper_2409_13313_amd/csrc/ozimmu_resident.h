@@ -78,6 +78,14 @@ constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
     return ((m + rows - 1) / rows) * ((p + cols - 1) / cols) < ((int64_t)1 << 23) && (n + 63) / 64 < ((int64_t)1 << 17);
 }
 
+// Rows of the output that do not begin on 64 bytes leave pieces of lines at every tile's edge.  Streamed past L2 (non-temporal
+// stores, 1 to 2 % faster for whole lines: 3000 x 64 x 3000, k = 4, 29.3 us, kept in L2 29.9) they are merged in memory, at a quarter of its
+// rate; kept in L2 until the neighbouring tile has written the rest they are not: 6272 x 56 x 2842, k = 3, 98 -> 48 us,
+// 3439 x 62 x 3552 into rows of 3553, k = 6, 74 -> 49, 2633 x 83 x 5709, k = 8, 113 -> 87.  Where the output is a small part of the work,
+// what that evicts costs as much (pairs times inner steps at 3000 x 3003: 576, k = 8, n = 1024, 238.5 -> 234.4 us; 672,
+// k = 6, n = 2048, 286.8 -> 276.5; 1152, k = 8, n = 2048, 443.8 -> 447.6; 1248, k = 12, n = 1024, 450 -> 454).
+constexpr bool merge_rows(int k, int64_t n) { return (int64_t)k * (k + 1) / 2 * ((n + 63) / 64) <= 700; }
+
 // Estimate of the kernel's time in microseconds on a chip of num_cu compute units; -1 where it cannot run.
 // Measured on MI355X: an inner step of a workgroup that has its compute unit to itself takes 7.5 ns per MFMA of a wave plus
 // 0.1 to 0.2 us (k = 8, tiles of 64 x 64: 1.16 us, 32 x 32: 0.5 us; 64 x 128: 2.4 us; k = 4, 128 x 128: 1.42 us), one of two workgroups
@@ -109,9 +117,9 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     const double kib = 2.0 * k * (c.ta + c.tb);                               // operands of a step
     const double copied = 1024.0 * kib / (4.0 * mfmas);                      // bytes brought in per MFMA
     const double fetched = 0.5 * kib / mfmas;                                 // KiB fetched from LDS per MFMA and wave
-    // (rows of D that begin inside a piece of 64 bytes leave pieces to be merged: 4224 x 384 x 1611, k = 4, 128 x 128
-    // tiles 54 us, 1608 columns 37)
-    const double odd_us = p % 8 == 0 ? 0.0 : c.ta * c.tb == 16 ? 0.6 : variant == EXTENDED ? 0.3 : 0.0;
+    // (rows of D that begin inside a piece of 64 bytes leave pieces to be merged, in memory: 4224 x 4608 x 1611, k = 4, 128 x 128
+    // tiles 296 us, 1608 columns 280)
+    const double odd_us = p % 8 == 0 || merge_rows(k, n) ? 0.0 : c.ta * c.tb == 16 ? 0.6 : variant == EXTENDED ? 0.3 : 0.0;
     // (k_extended has more start values to form and more sums to add up: 448 x 359 x 4480, k = 7, one addition per pair, 32 x 96
     // 39 us behind the split, three rounds of 5.4 us of steps)
     const double round_us = 4.0 + (variant == EXTENDED ? 2.0 + 0.08 * c.ta * c.tb : 0.0) + (0.4 + odd_us) * c.ta * c.tb;

@@ -571,7 +571,8 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     const bool plain_range = emin + 2 - a.beta * (K + 1) >= -1022 && emax + 2 - 2 * a.beta + 40 <= 1023;
     const bool scaled = __ballot(plain_range) == ~0ull;
     // Four 16 x 16 tiles at a time: sixteen independent chains of additions per lane keep the FP64 unit busy.
-    auto finish_tile = [&](auto SCALED) __attribute__((always_inline)) {
+    // KEEP: stores that stay in L2 until its lines are whole (see ozr::merge_rows) instead of streaming past it.
+    auto finish_tile = [&](auto SCALED, auto KEEP) __attribute__((always_inline)) {
         constexpr int TT = TA * TB, BATCH = TT < 4 ? TT : 4;
         const double step = ldexp(1.0, -a.beta);
         static_for<(TT + BATCH - 1) / BATCH>([&](auto Q) __attribute__((always_inline)) {
@@ -620,16 +621,24 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
                         d[x][r] = a.alpha * d[x][r];
                         if (with_c) d[x][r] = d[x][r] + a.cbeta * cold[x][r];
                     }
-                    if (col < a.p && row + r < a.m) __builtin_nontemporal_store(d[x][r], obase + (row + r) * opitch + col);
+                    if (col < a.p && row + r < a.m) {
+                        double* const out = obase + (row + r) * opitch + col;
+                        if constexpr (decltype(KEEP)::value)
+                            *out = d[x][r];
+                        else
+                            __builtin_nontemporal_store(d[x][r], out);
+                    }
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    if (scaled)
-        finish_tile(std::true_type{});
+    if (!scaled)
+        finish_tile(std::false_type{}, std::false_type{});
+    else if (a.keep)
+        finish_tile(std::true_type{}, std::true_type{});
     else
-        finish_tile(std::false_type{});
+        finish_tile(std::true_type{}, std::false_type{});
 }
 
 template <int K, int R, int TA, int TB, int D, int WAVES>
