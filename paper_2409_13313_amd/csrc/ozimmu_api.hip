@@ -285,6 +285,7 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
         a.cbeta = fin.cbeta;
         a.Cout = fin.Cout;
         a.ldco = fin.ldco;
+        a.per_slice = per_slice ? 1 : 0;
         const double* const out = fin.on ? fin.Cout : D;
         a.keep = (reinterpret_cast<uintptr_t>(out) % 64 != 0 || (fin.on ? fin.ldco : ldd) % 8 != 0) && ozr::merge_rows(k, n);
         return hip_status(ozk::launch_resident(a, k, r_eff, variant, st));
@@ -439,7 +440,7 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     // where the other ways read it once per slice pair, and it writes nothing but D, so it is the fastest wherever
     // its tiles (of 32 x 32 to 128 x 128 outputs) fill the chip and their chunk sums fit the registers without
     // making the tiles so small that the operands' way through LDS becomes the bound.
-    if (schedule == 0 && !per_slice) {
+    if (schedule == 0) {
         const double pairs = (double)k * (k + 1) / 2, rounds = (double)((T - tail - cp_tail + num_cu - 1) / num_cu);
         // what the ways above take: the queue 0.64 us per stage of 64 inner positions and 17 us per work item of a tile
         // (measured 96.5 ms at 16384^3, k = 8; 36.7 ms at 4096 x 65536 x 4096, k = 10; 7.4 ms at 8192^3, k = 6).  Both

@@ -146,6 +146,7 @@ struct ResidentArgs {
     double alpha, cbeta;
     double* Cout;
     int64_t ldco;
+    int per_slice;         // one scale per slice (r must be 1): eA, eB hold an array of m, p exponents per slice
     int keep;              // rows of the output are merged in L2 (ozr::merge_rows)
     int TM, TP;            // filled in by the launcher
     int setup;             // nothing is launched: the kernel's dynamic LDS limit is raised on the current device

@@ -540,6 +540,20 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     wait_vmcnt<0>();  // no copy may still be writing LDS when the workgroup ends
     if constexpr (IN_PLACE) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 
+    // One scale per slice (Algorithm 5; a chunk is then one pair): the exponents of all slices of the tile's rows, then columns,
+    // take the place of the operands.
+    int* const slice_exp = reinterpret_cast<int*>(lds);
+    if constexpr (R == 1)
+        if (a.per_slice) {
+            __syncthreads();
+            for (int x = t; x < K * (RA + RB); x += 256) {
+                const int s = x / (RA + RB), y = x - s * (RA + RB);
+                const int64_t at = y < RA ? (int64_t)row0 + y : (int64_t)col0 + (y - RA), end = y < RA ? a.m : a.p;
+                slice_exp[x] = at < end ? (y < RA ? a.eA : a.eB)[s * end + at] : 0;
+            }
+            __syncthreads();
+        }
+
     // Steps (iv) and (v): per element the chunk sums in schedule order, one rounded addition each.  Register r of tile
     // (i, j) in lane l: row 4 (l / 16) + r, column l % 16.
     int lq = lane >> 4, lc = lane & 15;
@@ -572,7 +586,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     const bool scaled = __ballot(plain_range) == ~0ull;
     // Four 16 x 16 tiles at a time: sixteen independent chains of additions per lane keep the FP64 unit busy.
     // KEEP: stores that stay in L2 until its lines are whole (see ozr::merge_rows) instead of streaming past it.
-    auto finish_tile = [&](auto SCALED, auto KEEP) __attribute__((always_inline)) {
+    auto finish_tile = [&](auto SCALED, auto KEEP, auto PER_SLICE) __attribute__((always_inline)) {
         constexpr int TT = TA * TB, BATCH = TT < 4 ? TT : 4;
         const double step = ldexp(1.0, -a.beta);
         static_for<(TT + BATCH - 1) / BATCH>([&](auto Q) __attribute__((always_inline)) {
@@ -591,7 +605,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
             double scale = 1.0;
             static_for<W>([&](auto C) __attribute__((always_inline)) {
                 constexpr int c = decltype(C)::value;
-                constexpr int g = chunk_range<K, R>(c).g;
+                constexpr int g = chunk_range<K, R>(c).g, s = chunk_range<K, R>(c).s0;
                 if constexpr (c > 0)
                     if constexpr (g != chunk_range<K, R>(c - 1).g) scale *= step;
 #pragma unroll
@@ -602,6 +616,11 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
                         const double v = (double)acc[c][i][j][r];
                         if constexpr (decltype(SCALED)::value) {
                             d[x][r] = c == 0 ? v : __builtin_fma(v, scale, d[x][r]);
+                        } else if constexpr (decltype(PER_SLICE)::value) {
+                            const int es = slice_exp[(s - 1) * (RA + RB) + wm * (16 * TA) + 16 * i + 4 * lq + r];
+                            const int et = slice_exp[(g - s - 1) * (RA + RB) + RA + wn * (16 * TB) + 16 * j + lc];
+                            const double term = ldexp(v, es + et + 2 - 2 * a.beta);
+                            d[x][r] = c == 0 ? term : d[x][r] + term;
                         } else {
                             const double term = ldexp(v, ea[i][r] + eb[j] + 2 - a.beta * g);
                             d[x][r] = c == 0 ? term : d[x][r] + term;
@@ -633,12 +652,19 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
             __builtin_amdgcn_sched_barrier(0);
         });
     };
+    constexpr std::false_type no{};
+    constexpr std::true_type yes{};
+    if constexpr (R == 1)
+        if (a.per_slice) {
+            finish_tile(no, yes, yes);
+            return;
+        }
     if (!scaled)
-        finish_tile(std::false_type{}, std::false_type{});
+        finish_tile(no, no, no);
     else if (a.keep)
-        finish_tile(std::true_type{}, std::true_type{});
+        finish_tile(yes, yes, no);
     else
-        finish_tile(std::true_type{}, std::false_type{});
+        finish_tile(yes, no, no);
 }
 
 template <int K, int R, int TA, int TB, int D, int WAVES>
