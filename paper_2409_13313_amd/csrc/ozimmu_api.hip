@@ -113,6 +113,8 @@ constexpr int64_t QUEUE_SETS = 3;
 constexpr int64_t QUEUE_MIN_TILES = 96;
 constexpr int64_t QUEUE_XCD_WORDS = 8 * 40;  // per-XCD ticket batches of the queue (see k_gemm)
 constexpr int64_t BLOCK_BYTES = 4 * 256 * 256;
+// Room for the sums of tiles whose inner dimension is cut (ozr::estimate_us with parts): asked for where that may pay.
+constexpr int64_t CUT_MAX_TILES = 16, CUT_MIN_INNER = 1024, CUT_BLOCKS = 128;
 inline int64_t chunks_of(int k, int64_t r)
 {
     int64_t w = 0;
@@ -137,6 +139,7 @@ inline int64_t partial_blocks(int64_t m, int64_t n, int64_t p, int k)
     const int64_t w = chunks_of(k, r_of(n, beta_of(n)));
     const int64_t items = (T <= 256 ? T : T % 256) * w;
     int64_t blocks = (items <= CHUNK_PARALLEL_MAX_BLOCKS && items > base) ? items : base;
+    if (T <= CUT_MAX_TILES && n >= CUT_MIN_INNER && blocks < CUT_BLOCKS) blocks = CUT_BLOCKS;
     if (T >= QUEUE_MIN_TILES && w * 256 * BLOCK_BYTES < ((int64_t)1 << 31) && T * w < ((int64_t)1 << 30)) {
         const int64_t rounds = (T + 255) / 256;
         const int64_t queue = (rounds < QUEUE_SETS ? rounds : QUEUE_SETS) * w * (T < 256 ? T : 256) +
@@ -258,7 +261,7 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     const int64_t T = output_tiles(m, p);
     const int64_t w = chunks_of(k, r_eff);
 
-    auto launch_resident = [&](int variant) -> int {
+    auto launch_resident = [&](int variant, int parts = 1) -> int {
         const ozk::GemmArgs g = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
         ozk::ResidentArgs a{};
         a.SA = g.SA;
@@ -286,9 +289,17 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
         a.Cout = fin.Cout;
         a.ldco = fin.ldco;
         a.per_slice = per_slice ? 1 : 0;
-        const double* const out = fin.on ? fin.Cout : D;
+        a.parts = parts;
+        a.blocks = partial;
+        double* const out = fin.on ? fin.Cout : D;
         a.keep = (reinterpret_cast<uintptr_t>(out) % 64 != 0 || (fin.on ? fin.ldco : ldd) % 8 != 0) && ozr::merge_rows(k, n);
-        return hip_status(ozk::launch_resident(a, k, r_eff, variant, st));
+        const hipError_t e = ozk::launch_resident(a, k, r_eff, variant, st);
+        if (e != hipSuccess || parts == 1) return hip_status(e);
+        const ozr::Config c = ozr::config_for(k, r_eff, variant);
+        const ozk::AddPartsArgs add = {partial, k,      r_eff,     beta,     parts, c.ta, c.tb,
+                                       m,       p,      eA,        eB,       a.finish, fin.alpha, fin.cbeta,
+                                       out,     fin.on ? fin.ldco : ldd};
+        return hip_status(ozk::launch_add_parts(add, st));
     };
     if (resident_tile >= 0) return launch_resident(resident_tile);
 
@@ -457,15 +468,34 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
             const double slower = 0.02 + 0.004 * (double)w;
             other_us *= 1.0 + (slower < 0.08 ? slower : 0.08) * log2((double)n / 16384.0);
         }
-        int variant = -1;
+        int variant = -1, parts = 1;
         for (int v = 0; v < ozr::NUM_VARIANTS; ++v) {
+            if (per_slice && !ozr::per_slice_tile(k, v)) continue;
             const double us = ozr::estimate_us(k, r_eff, v, m, n, p, num_cu);
-            if (us > 0.0 && us < other_us) {
+            if (us < 0.0) continue;
+            if (us < other_us) {
                 other_us = us;
                 variant = v;
+                parts = 1;
+            }
+            // Tiles that leave half of the chip idle or more, cut along the inner dimension (below 16 us there is nothing to gain,
+            // and the estimates themselves take time)
+            if (us < 16.0) continue;
+            const ozr::Config c = ozr::config_for(k, r_eff, v);
+            const int64_t tiles = ((m + 32 * c.ta - 1) / (32 * c.ta)) * ((p + 32 * c.tb - 1) / (32 * c.tb));
+            const int64_t room = partial ? partial_capacity * BLOCK_BYTES : 0, steps = (n + ozl::TILE_K - 1) / ozl::TILE_K;
+            for (int z = 2; ozr::may_cut(v, c) && z <= 64 && tiles * z <= (int64_t)num_cu * c.waves && 2 * z <= steps &&
+                            ozr::sums_bytes(k, r_eff, c, tiles * z) <= room;
+                 z += z < 4 ? 1 : z / 2) {
+                const double cut_us = ozr::estimate_us(k, r_eff, v, m, n, p, num_cu, z);
+                if (cut_us + 1.0 < other_us) {
+                    other_us = cut_us;
+                    variant = v;
+                    parts = z;
+                }
             }
         }
-        if (variant >= 0) return launch_resident(variant);
+        if (variant >= 0) return launch_resident(variant, parts);
     }
     if (queue_pays) return launch_queue(T, sets_all);
 

@@ -1187,6 +1187,58 @@ __global__ __launch_bounds__(256) void k_accumulate_tiles(ozk::TileAccArgs t)
     }
 }
 
+// Steps (iv) and (v) where the inner dimension of k_resident's tiles was cut among a.parts workgroups: per element the sums of
+// the parts (integers, any order), then the chunks in schedule order.  A workgroup takes one 16 x 16 tile of a wave, ZG waves share
+// its parts, four of them then have one of the four accumulator registers each.  Bound by the latency of the loads (16 bytes a
+// lane, BATCH of them in flight): the sums come from the memory-side cache.
+template <int ZG>
+__global__ __launch_bounds__(64 * ZG) void k_add_parts(ozk::AddPartsArgs a, int w, int TM, int TP)
+{
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    constexpr int BATCH = ZG == 4 ? 8 : 4;
+    __shared__ v4u sums[ZG][BATCH][64];
+    const int t = threadIdx.x, lane = t & 63, zg = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int TT = a.ta * a.tb, wave = blockIdx.x & 3, ij = (int)(blockIdx.x >> 2) % TT, tile = (int)(blockIdx.x >> 2) / TT;
+    int tm, tp;
+    ozr::tile_of_block(tile, TM, TP, tm, tp);
+    const int64_t part = (int64_t)w * TT * 1024;
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(a.blocks) + tile * a.parts * part + ij * 1024 + (wave * 64 + lane) * 4;
+    const int64_t row = (int64_t)(2 * tm + (wave >> 1)) * 16 * a.ta + 16 * (ij % a.ta) + 4 * (lane >> 4) + zg;
+    const int64_t col = (int64_t)(2 * tp + (wave & 1)) * 16 * a.tb + 16 * (ij / a.ta) + (lane & 15);
+    const bool mine = zg < 4 && row < a.m && col < a.p;
+    const int e = mine ? a.eA[row] + a.eB[col] + 2 : 0;
+    const bool with_c = a.finish && a.cbeta != 0.0;
+    const double cold = mine && with_c ? a.out[row * a.ldo + col] : 0.0;
+    double d = 0.0;
+    int g = 2, s0 = 1;
+    for (int c0 = 0; c0 < w; c0 += BATCH) {
+        v4u s[BATCH] = {};
+        for (int z = zg; z < a.parts; z += ZG)
+#pragma unroll
+            for (int b = 0; b < BATCH; ++b)
+                if (c0 + b < w) s[b] += *reinterpret_cast<const v4u*>(src + z * part + (int64_t)(c0 + b) * TT * 1024);
+        __syncthreads();  // the batch before has been added up
+#pragma unroll
+        for (int b = 0; b < BATCH; ++b) sums[zg][b][lane] = s[b];
+        __syncthreads();
+        if (zg < 4)
+            for (int b = 0; b < BATCH && c0 + b < w; ++b) {
+                uint32_t v = 0;
+#pragma unroll
+                for (int q = 0; q < ZG; ++q) v += reinterpret_cast<const uint32_t*>(&sums[q][b][lane])[zg];
+                const double term = ldexp((double)(int)v, e - a.beta * g);
+                d = c0 + b == 0 ? term : d + term;
+                s0 += a.r;
+                if (s0 > g - 1) ++g, s0 = 1;
+            }
+    }
+    if (a.finish) {
+        d = a.alpha * d;
+        if (with_c) d = d + a.cbeta * cold;
+    }
+    if (mine) a.out[row * a.ldo + col] = d;
+}
+
 // Step (iv) over all chunks of the schedule for a range of tiles: chunk q's INT32 sums lie in lane-major blocks
 // Ct[q * tile_count + tile]; D = fl(...fl(fl(T_1 + T_2) + T_3)...) in schedule order (g ascending, chunks of r
 // ascending), T_q = 2^(2 - beta g) diag(2^eA) FP64(C''_q) diag(2^eB), the first addend taken as it is.
@@ -1420,6 +1472,18 @@ hipError_t launch_accumulate_chunks(const TileAccArgs& t_in, int k, int r, int b
     t.TM = (int)(ozl::rows_padded(t.m) / ozl::TILE_R);
     t.TP = (int)(ozl::rows_padded(t.p) / ozl::TILE_R);
     hipLaunchKernelGGL(k_accumulate_chunks, dim3((unsigned)t.tile_count * 32u), dim3(256), 0, st, t, k, r, beta);
+    return hipGetLastError();
+}
+
+hipError_t launch_add_parts(const AddPartsArgs& a, hipStream_t st)
+{
+    const int w = ozr::num_chunks(a.k, a.r < a.k ? a.r : a.k);
+    const int TM = (int)((a.m + 32 * a.ta - 1) / (32 * a.ta)), TP = (int)((a.p + 32 * a.tb - 1) / (32 * a.tb));
+    const dim3 grid((unsigned)(TM * TP * a.ta * a.tb * 4));
+    if (ozr::z_groups(a.parts) == 4)
+        hipLaunchKernelGGL(k_add_parts<4>, grid, dim3(256), 0, st, a, w, TM, TP);
+    else
+        hipLaunchKernelGGL(k_add_parts<16>, grid, dim3(1024), 0, st, a, w, TM, TP);
     return hipGetLastError();
 }
 

@@ -146,6 +146,8 @@ struct ResidentArgs {
     double alpha, cbeta;
     double* Cout;
     int64_t ldco;
+    int parts;             // > 1: the inner dimension of a tile is cut among that many workgroups, which leave their sums in
+    int32_t* blocks;       // `blocks` (ozr::sums_bytes) for launch_add_parts
     int per_slice;         // one scale per slice (r must be 1): eA, eB hold an array of m, p exponents per slice
     int keep;              // rows of the output are merged in L2 (ozr::merge_rows)
     int TM, TP;            // filled in by the launcher
@@ -154,6 +156,19 @@ struct ResidentArgs {
 template <int K>
 hipError_t launch_resident_k(const ResidentArgs& a, int r, int variant, hipStream_t st);
 hipError_t launch_resident(const ResidentArgs& a, int k, int r, int variant, hipStream_t st);
+// Steps (iv) and (v) of a launch with parts > 1.
+struct AddPartsArgs {
+    const int32_t* blocks;
+    int k, r, beta, parts, ta, tb;
+    int64_t m, p;
+    const int32_t* eA;
+    const int32_t* eB;
+    int finish;
+    double alpha, cbeta;
+    double* out;           // D, or Cout where finish is set
+    int64_t ldo;
+};
+hipError_t launch_add_parts(const AddPartsArgs& a, hipStream_t st);
 // Step (v): C <- alpha D + beta C (beta == 0: C not read).
 hipError_t launch_axpby(int64_t m, int64_t p, double alpha, const double* D, int64_t ldd, double beta, double* C,
                         int64_t ldc, hipStream_t st);

@@ -72,6 +72,9 @@ constexpr Config config_for(int k, int r, int variant)
     if (k < MIN_K || k > MAX_K || (r < k && r != 8 && r != 4 && r != 2 && r != 1)) return Config{0, 0, 1, 1};
     return config(k, r < k ? r : k, variant);
 }
+// Tiles for slices with one scale each (r = 1): k_extended only where there is no other (with a third way to add its sums up the
+// compiler reads some of them before the wait states behind the loop).
+constexpr bool per_slice_tile(int k, int variant) { return variant != EXTENDED || config(k, 1, 0).ta == 0; }
 // grid size; 32-bit operand offsets
 constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
 {
@@ -85,6 +88,23 @@ constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
 // what that evicts costs as much (pairs times inner steps at 3000 x 3003: 576, k = 8, n = 1024, 238.5 -> 234.4 us; 672,
 // k = 6, n = 2048, 286.8 -> 276.5; 1152, k = 8, n = 2048, 443.8 -> 447.6; 1248, k = 12, n = 1024, 450 -> 454).
 constexpr bool merge_rows(int k, int64_t n) { return (int64_t)k * (k + 1) / 2 * ((n + 63) / 64) <= 700; }
+
+// Tiles whose inner dimension may be cut among workgroups (k_cut): the smallest, which leave the fewest sums to exchange (at 15
+// shapes of 41 to 1000 rows and columns one of these two was the best or within 4 % of it).
+constexpr bool may_cut(int variant, const Config& c) { return variant != EXTENDED && c.ta * c.tb >= 1 && c.ta * c.tb <= 2; }
+// Bytes of the chunk sums of `tiles` tiles (k_add_parts).
+inline int64_t sums_bytes(int k, int r, const Config& c, int64_t tiles)
+{
+    return tiles * num_chunks(k, r < k ? r : k) * c.ta * c.tb * 4096;
+}
+// z_groups of k_add_parts: threads that share the parts of an element
+constexpr int z_groups(int parts) { return parts > 8 ? 16 : 4; }
+inline double add_parts_us(int k, int r, const Config& c, int64_t tiles, int parts)
+{
+    const int zg = z_groups(parts), batch = zg == 4 ? 8 : 4;
+    const double trips = (double)((parts + zg - 1) / zg) * ((num_chunks(k, r < k ? r : k) + batch - 1) / batch);
+    return 5.0 + 1.0 * trips + (double)sums_bytes(k, r, c, tiles) / 2.5e6;
+}
 
 // Estimate of the kernel's time in microseconds on a chip of num_cu compute units; -1 where it cannot run.
 // Measured on MI355X: an inner step of a workgroup that has its compute unit to itself takes 7.5 ns per MFMA of a wave plus
@@ -107,12 +127,14 @@ constexpr bool merge_rows(int k, int64_t n) { return (int64_t)k * (k + 1) / 2 * 
 // intervals (k <= 4) 0.93 / 1.36; two, 12 KiB 0.2 / 0.33, 24 KiB 0.25 / 0.42, 48 KiB 0.68 / 0.76).  Without this the choice fell on
 // tiles that were latency bound: 1473 x 13248 x 872, k = 4, 64 x 96 tiles 296 us (estimated 130), the chunk-parallel way
 // 206; 1042 x 30250 x 1180, k = 4, whole call 1030 us, now 790; 615 x 31277 x 496, k = 7, 684, now 530.
-inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64_t p, int num_cu)
+//
+// parts > 1: the inner dimension of every tile cut among that many workgroups (one round of them), whose sums k_add_parts adds up.
+inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64_t p, int num_cu, int parts = 1)
 {
     const Config c = config_for(k, r, variant);
     if (c.ta == 0 || num_cu < 1 || !in_range(m, n, p, 32 * c.ta, 32 * c.tb)) return -1.0;
-    const int64_t steps = (n + 63) / 64;
-    const int64_t tiles = ((m + 32 * c.ta - 1) / (32 * c.ta)) * ((p + 32 * c.tb - 1) / (32 * c.tb));
+    const int64_t steps = ((n + 63) / 64 + parts - 1) / parts;
+    const int64_t tiles = parts * ((m + 32 * c.ta - 1) / (32 * c.ta)) * ((p + 32 * c.tb - 1) / (32 * c.tb));
     const double mfmas = 0.5 * k * (k + 1) * c.ta * c.tb;
     const double kib = 2.0 * k * (c.ta + c.tb);                               // operands of a step
     const double copied = 1024.0 * kib / (4.0 * mfmas);                      // bytes brought in per MFMA
@@ -144,9 +166,52 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     const double barrier_us = c.ta * c.tb == 1 ? 0.2 : 0.27;
     const double us = total(at_least(0.0075 * mfmas + 0.15, wait_us),
                             at_least(c.waves == 2 ? 0.0168 * mfmas + 0.2 : 0.0075 * mfmas + barrier_us, wait2_us));
+    if (parts > 1) return us + add_parts_us(k, r, c, tiles, parts);
     if (us < 1500.0) return us;
     const double hot_us = mfmas * ((c.waves == 2 ? 0.0062 : 0.0068) + 2.0e-5 * copied + 0.005 * fetched);
     return total(at_least(hot_us, wait_us), at_least(hot_us * c.waves, wait2_us));
+}
+
+// Which tile workgroup b takes.  Workgroup b runs on XCD b % 8, and 256 consecutive workgroups run at about the same
+// time; those of one XCD should share operand tiles in its L2, and the XCDs among each other in the memory-side cache.
+// So 256 workgroups in a row ("round") get 256 consecutive places of the order below, XCD x the places 32 x .. 32 x + 31
+// of them: an 8 x 4 patch of tiles, eight patches to a block of 16 x 16.  The order: all whole 16 x 16 blocks (rows of
+// blocks back and forth), then what is left of the tile grid on the right, then below, in bands of 8 rows walked column
+// by column.  A last round that is not full is cut into eight equal ranges.
+__host__ __device__ inline void band_order(int lin, int rows, int& r, int& c, int cols)
+{
+    const int width = 8 * cols, band = lin / width, in_band = lin - band * width;
+    const int h = rows - 8 * band < 8 ? rows - 8 * band : 8;
+    r = 8 * band + in_band % h;
+    c = in_band / h;
+}
+__host__ __device__ inline void tile_of_block(int b, int TM, int TP, int& tm, int& tp)
+{
+    const int T = TM * TP, x = b & 7, round = b >> 8;
+    int lin;
+    if (T - (round << 8) >= 256) {
+        lin = (round << 8) + x * 32 + ((b >> 3) & 31);
+    } else {
+        const int left = T - (round << 8), base = left >> 3, rem = left & 7;
+        lin = (round << 8) + x * base + (x < rem ? x : rem) + ((b & 255) >> 3);
+    }
+    const int BM = TM / 16, BP = TP / 16, whole = BM * BP * 256;
+    if (lin < whole) {
+        const int q = lin >> 8, u = lin & 255, br = q / BP, bc = q - br * BP;
+        const int patch = u >> 5, mem = u & 31;
+        tm = br * 16 + (patch >> 2) * 8 + (mem & 7);
+        tp = ((br & 1) ? BP - 1 - bc : bc) * 16 + (patch & 3) * 4 + (mem >> 3);
+        return;
+    }
+    lin -= whole;
+    const int wr = TP - BP * 16;       // columns right of the blocks, over all rows
+    if (lin < TM * wr) {
+        band_order(lin, TM, tm, tp, wr);
+        tp += BP * 16;
+    } else {
+        band_order(lin - TM * wr, TM - BM * 16, tm, tp, BP * 16);
+        tm += BM * 16;
+    }
 }
 
 }  // namespace ozr

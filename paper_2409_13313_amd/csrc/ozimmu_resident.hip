@@ -204,50 +204,8 @@ struct Plan {
     }
 };
 
-// Which tile workgroup b takes.  Workgroup b runs on XCD b % 8, and 256 consecutive workgroups run at about the same
-// time; those of one XCD should share operand tiles in its L2, and the XCDs among each other in the memory-side cache.
-// So 256 workgroups in a row ("round") get 256 consecutive places of the order below, XCD x the places 32 x .. 32 x + 31
-// of them: an 8 x 4 patch of tiles, eight patches to a block of 16 x 16.  The order: all whole 16 x 16 blocks (rows of
-// blocks back and forth), then what is left of the tile grid on the right, then below, in bands of 8 rows walked column
-// by column.  A last round that is not full is cut into eight equal ranges.
-__device__ inline void band_order(int lin, int rows, int& r, int& c, int cols)
-{
-    const int width = 8 * cols, band = lin / width, in_band = lin - band * width;
-    const int h = rows - 8 * band < 8 ? rows - 8 * band : 8;
-    r = 8 * band + in_band % h;
-    c = in_band / h;
-}
-__device__ inline void tile_of_block(int b, int TM, int TP, int& tm, int& tp)
-{
-    const int T = TM * TP, x = b & 7, round = b >> 8;
-    int lin;
-    if (T - (round << 8) >= 256) {
-        lin = (round << 8) + x * 32 + ((b >> 3) & 31);
-    } else {
-        const int left = T - (round << 8), base = left >> 3, rem = left & 7;
-        lin = (round << 8) + x * base + (x < rem ? x : rem) + ((b & 255) >> 3);
-    }
-    const int BM = TM / 16, BP = TP / 16, whole = BM * BP * 256;
-    if (lin < whole) {
-        const int q = lin >> 8, u = lin & 255, br = q / BP, bc = q - br * BP;
-        const int patch = u >> 5, mem = u & 31;
-        tm = br * 16 + (patch >> 2) * 8 + (mem & 7);
-        tp = ((br & 1) ? BP - 1 - bc : bc) * 16 + (patch & 3) * 4 + (mem >> 3);
-        return;
-    }
-    lin -= whole;
-    const int wr = TP - BP * 16;       // columns right of the blocks, over all rows
-    if (lin < TM * wr) {
-        band_order(lin, TM, tm, tp, wr);
-        tp += BP * 16;
-    } else {
-        band_order(lin - TM * wr, TM - BM * 16, tm, tp, BP * 16);
-        tm += BM * 16;
-    }
-}
-
-// A workgroup's tile.  IN_PLACE: k_extended (see the head).
-template <class P, bool IN_PLACE>
+// A workgroup's tile.  IN_PLACE: k_extended (see the head).  CUT: k_cut, a part of a tile's inner dimension.
+template <class P, bool IN_PLACE, bool CUT>
 __device__ __attribute__((always_inline)) inline void run_tile(const ozk::ResidentArgs& a)
 {
     static constexpr P plan{};
@@ -264,8 +222,14 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     const int wm = wave >> 1, wn = wave & 1;
 
     // workgroup b runs on XCD b % 8
-    int tm, tp;
-    tile_of_block((int)blockIdx.x, a.TM, a.TP, tm, tp);
+    int tm, tp, block = (int)blockIdx.x, part = 0;
+    if constexpr (CUT) {
+        // (no padding to whole sets of XCDs: workgroups that end at once have others put two to a compute unit while some stay
+        // idle, 659 x 11776 x 206, k = 6, 84 tiles in three parts, 115 instead of 91 us)
+        part = block / (a.TM * a.TP);
+        block -= part * a.TM * a.TP;
+    }
+    ozr::tile_of_block(block, a.TM, a.TP, tm, tp);
     tm = __builtin_amdgcn_readfirstlane(tm);
     tp = __builtin_amdgcn_readfirstlane(tp);
     const uint32_t row0 = (uint32_t)tm * RA, col0 = (uint32_t)tp * RB;
@@ -278,6 +242,9 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     // assembly of every instance.  As an operand of the other copies it costs moves in two loops, k = 6, w = 8, 64 x 128 and
     // k = 16, 64 x 64.)
     constexpr int NC = P::NC;
+    // inner steps of this part
+    const int kt0 = CUT ? (int)((int64_t)a.steps * part / a.parts) : 0;
+    const int KT = CUT ? (int)((int64_t)a.steps * (part + 1) / a.parts) - kt0 : a.steps;
     const int piece0 = wave * NC < 2 * NF - NC ? wave * NC : 2 * NF - NC;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
     uint32_t m0_cur = lds_base + (uint32_t)piece0 * 1024u, m0_nxt = m0_cur + (D - 1) * SET;
@@ -291,7 +258,8 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
         uint32_t row = isb ? col0 + (uint32_t)(pc - 2 * TA) * 16u : row0 + (uint32_t)pc * 16u;
         const uint32_t top = (uint32_t)(isb ? a.pstrideB : a.pstrideA) - 16u;  // (padded rows of the stack)
         row = row < top ? row : top;  // a tile may reach past the padding: what it reads there is never stored
-        gbase[q] = (isb ? a.SB : a.SA) + (int64_t)(row / TILE_R) * rowblk + (int)(row % TILE_R) * TILE_K - q * 1024;
+        gbase[q] = (isb ? a.SB : a.SA) + (int64_t)(row / TILE_R) * rowblk + (int)(row % TILE_R) * TILE_K - q * 1024 +
+                   (int64_t)kt0 * TILE_BYTES;
         gstride[q] = isb ? a.strideB : a.strideA;
     }
 
@@ -354,7 +322,6 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     v4i acc[W][TA][TB];
     // what the accumulation registers do not hold lies in ordinary ones (k_extended)
     constexpr auto ordinary = [](int c, int i, int j) { return (c * TB + j) * TA + i >= ozr::ACC_TILES; };
-    const int KT = a.steps;
 
     const uint32_t lv = (uint32_t)lane * 16u;
     auto step_off = [&](int kt) { return (uint32_t)(kt < KT - 1 ? kt : KT - 1) * (uint32_t)TILE_BYTES; };
@@ -363,7 +330,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     // values -, then the first copies; all of it is on its way before anything is waited for.  (With the loads behind the
     // copies and a branch on the offsets, three latencies in a row: 6.5 us from the first instruction to the loop at 4096^3,
     // k = 8; now 3.8 us, 2.8 us on an idle chip.)
-    const int cA = a.cA[0], cB = a.cB[0];
+    const int cA = !CUT || part == 0 ? a.cA[0] : 0, cB = !CUT || part == 0 ? a.cB[0] : 0;  // (start values: the first part's)
     int exp_row = 0, exp_col = 0;
     v4i pa[K][TA];
     int pb[K][TB];
@@ -412,7 +379,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
         constexpr int c = decltype(C)::value;
         constexpr Range range = chunk_range<K, R>(c);
         constexpr int s0 = range.s0, s1 = range.s1, t0 = range.g - s1, t1 = range.g - s0;
-        const uint32_t fix = (uint32_t)((s1 - s0 + 1) * cA * cB) * (uint32_t)((2 * a.KT - KT) * TILE_K);
+        const uint32_t fix = (uint32_t)((s1 - s0 + 1) * cA * cB) * (uint32_t)((2 * a.KT - a.steps) * TILE_K);
         uint32_t cb[TB];
 #pragma unroll
         for (int j = 0; j < TB; ++j) cb[j] = fix - (uint32_t)cA * (uint32_t)(pb[t1 - 1][j] - (t0 > 1 ? pb[t0 > 1 ? t0 - 2 : 0][j] : 0));
@@ -540,10 +507,21 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     wait_vmcnt<0>();  // no copy may still be writing LDS when the workgroup ends
     if constexpr (IN_PLACE) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 
+    if constexpr (CUT) {
+        // the part's sums as they lie in the registers, 16 bytes a lane (k_add_parts reads them back)
+        constexpr int TT = TA * TB;
+        int32_t* const out = a.blocks + ((int64_t)(block * a.parts + part) * (W * TT) * 256 + t) * 4;
+        static_for<W * TT>([&](auto X) __attribute__((always_inline)) {
+            constexpr int x = decltype(X)::value, c = x / TT, i = x % TT % TA, j = x % TT / TA;
+            *reinterpret_cast<v4i*>(out + x * 1024) = acc[c][i][j];
+        });
+        return;
+    }
     // One scale per slice (Algorithm 5; a chunk is then one pair): the exponents of all slices of the tile's rows, then columns,
     // take the place of the operands.
+    constexpr bool PER_SLICE = R == 1 && ozr::per_slice_tile(K, IN_PLACE ? ozr::EXTENDED : 0);
     int* const slice_exp = reinterpret_cast<int*>(lds);
-    if constexpr (R == 1)
+    if constexpr (PER_SLICE)
         if (a.per_slice) {
             __syncthreads();
             for (int x = t; x < K * (RA + RB); x += 256) {
@@ -654,7 +632,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     };
     constexpr std::false_type no{};
     constexpr std::true_type yes{};
-    if constexpr (R == 1)
+    if constexpr (PER_SLICE)
         if (a.per_slice) {
             finish_tile(no, yes, yes);
             return;
@@ -670,12 +648,21 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
 template <int K, int R, int TA, int TB, int D, int WAVES>
 __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, R, TA, TB, D>, false>(a);
+    run_tile<Plan<K, R, TA, TB, D>, false, false>(a);
+}
+// Few tiles of a long inner dimension would leave most of the chip idle: each is cut among a.parts workgroups, whose INT32 sums
+// k_add_parts (ozimmu_gemm.hip) adds up.  A kernel of its own: with both ends in one the compiler spills chunk sums.  What bounds it
+// is the latency of a step and of the sums' way (whole calls, k = 8: 47 x 11948 x 48 119 -> 62 us, 43 of it the split; 256 x 8192 x 256
+// 83 -> 63; 67 x 25614 x 69, k = 4, 148 -> 96).
+template <int K, int R, int TA, int TB, int D, int WAVES>
+__global__ __launch_bounds__(256, WAVES) void k_cut(ozk::ResidentArgs a)
+{
+    run_tile<Plan<K, R, TA, TB, D>, false, true>(a);
 }
 template <int K, int R, int TA, int TB, int D>
 __global__ __launch_bounds__(256, 1) void k_extended(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, R, TA, TB, D>, true>(a);
+    run_tile<Plan<K, R, TA, TB, D>, true, false>(a);
 }
 
 template <int K, int R, int V>
@@ -689,6 +676,7 @@ hipError_t launch(const ozk::ResidentArgs& a_in, hipStream_t st)
         constexpr int RA = 32 * c.ta, RB = 32 * c.tb;
         a.TM = (int)((a.m + RA - 1) / RA);
         a.TP = (int)((a.p + RB - 1) / RB);
+        const unsigned tiles = (unsigned)a.TM * (unsigned)a.TP;
         constexpr int smem = ozr::lds_bytes(K, c);
         static_assert(smem <= 160 * 1024, "LDS of a compute unit");
         const void* kernel;
@@ -696,9 +684,19 @@ hipError_t launch(const ozk::ResidentArgs& a_in, hipStream_t st)
             kernel = reinterpret_cast<const void*>(&k_extended<K, R, c.ta, c.tb, c.depth>);
         else
             kernel = reinterpret_cast<const void*>(&k_resident<K, R, c.ta, c.tb, c.depth, c.waves>);
+        if constexpr (ozr::may_cut(V, c)) {
+            const void* cut = reinterpret_cast<const void*>(&k_cut<K, R, c.ta, c.tb, c.depth, c.waves>);
+            if (a.setup) {
+                const hipError_t e = hipFuncSetAttribute(cut, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+                if (e != hipSuccess) return e;
+            }
+            if (a.parts > 1) kernel = cut;
+        } else if (a.parts > 1) {
+            return hipErrorInvalidValue;
+        }
         if (a.setup) return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         void* args[] = {&a};
-        return hipLaunchKernel(kernel, dim3((unsigned)a.TM * (unsigned)a.TP), dim3(256), args, smem, st);
+        return hipLaunchKernel(kernel, dim3(a.parts > 1 ? tiles * (unsigned)a.parts : tiles), dim3(256), args, smem, st);
     }
 }
 
