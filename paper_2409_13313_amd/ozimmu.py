@@ -110,8 +110,13 @@ def _check(status: int) -> None:
         raise OzimmuError(status)
 
 
+# The current stream's handle without a Stream object around it, and every tensor looked at once: a call of a small product takes
+# as long on the host as on the GPU (64^3: 12.9 us a call, of which 6.4 the library and its launches, 2.8 the Stream object).
+_current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _dev(t: torch.Tensor, dtype) -> torch.Tensor:
@@ -127,6 +132,16 @@ def _ld(t: torch.Tensor) -> int:
     if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
         raise ValueError("expected a 2-D tensor with unit stride along rows")
     return t.stride(0) if t.shape[0] > 1 else max(t.shape[1], t.stride(0), 1)
+
+
+def _matrix(t: torch.Tensor) -> Tuple[int, int, int]:
+    """Rows, columns and leading dimension of an FP64 matrix on the GPU (_dev and _ld in one)."""
+    if not (t.is_cuda and t.dtype is torch.float64 and t.dim() == 2):
+        _dev(t, torch.float64), _ld(t)
+    (rows, cols), (ld, unit) = t.shape, t.stride()
+    if cols > 1 and unit != 1:
+        _ld(t)
+    return rows, cols, ld if rows > 1 else max(cols, ld, 1)
 
 
 def status_string(status: int) -> str:
@@ -158,26 +173,30 @@ def workspace_bytes_min(m: int, n: int, p: int, k: int) -> int:
 def alloc_workspace(m: int, n: int, p: int, k, device="cuda", split: str = "rn") -> torch.Tensor:
     """Workspace for calls with k slices; k may be a sequence of slice counts the workspace is to serve
     (the requirement is not monotone in k, so the largest k alone would not do)."""
-    ks = [k] if isinstance(k, int) else list(k)
-    nbytes = max(int(_lib.ozimmu_workspace_bytes_variant(m, n, p, kk, SPLIT_MODES[split])) for kk in ks)
+    if isinstance(k, int):
+        nbytes = _lib.ozimmu_workspace_bytes_variant(m, n, p, k, SPLIT_MODES[split])
+    else:
+        nbytes = max(_lib.ozimmu_workspace_bytes_variant(m, n, p, kk, SPLIT_MODES[split]) for kk in k)
     return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
 
 
 def dgemm(A: torch.Tensor, B: torch.Tensor, k: int, D: Optional[torch.Tensor] = None,
           workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """D = A B emulated with k INT8 slices on the matrix cores."""
-    _dev(A, torch.float64), _dev(B, torch.float64)
-    m, n = A.shape
-    n2, p = B.shape
+    m, n, lda = _matrix(A)
+    n2, p, ldb = _matrix(B)
     if n != n2:
         raise ValueError("inner dimensions differ")
     if D is None:
-        D = torch.empty((m, p), dtype=torch.float64, device=A.device)
-    _dev(D, torch.float64)
+        D, ldd = A.new_empty((m, p)), max(p, 1)
+    else:
+        ldd = _matrix(D)[2]
     if workspace is None:
         workspace = alloc_workspace(m, n, p, k, A.device)
-    _check(_lib.ozimmu_dgemm(m, n, p, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), D.data_ptr(), _ld(D), k,
-                             workspace.data_ptr(), workspace.numel(), _stream()))
+    status = _lib.ozimmu_dgemm(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), ldd, k,
+                               workspace.data_ptr(), workspace.numel(), _stream())
+    if status:
+        raise OzimmuError(status)
     return D
 
 
@@ -204,16 +223,15 @@ def dgemm_variant(A: torch.Tensor, B: torch.Tensor, k: int, split: str = "rn", a
                   schedule: str = "auto") -> torch.Tensor:
     """D = A B in one of the variants of Section 4 (see ozimmu_dgemm_variant in the header); schedule
     "one_launch" / "split_inner" forces how the schedule is run (same bits either way)."""
-    _dev(A, torch.float64), _dev(B, torch.float64)
-    m, n = A.shape
-    n2, p = B.shape
+    m, n, lda = _matrix(A)
+    n2, p, ldb = _matrix(B)
     if n != n2:
         raise ValueError("inner dimensions differ")
     if D is None:
-        D = torch.empty((m, p), dtype=torch.float64, device=A.device)
+        D = A.new_empty((m, p))
     if workspace is None:
         workspace = alloc_workspace(m, n, p, k, A.device, split)
-    _check(_lib.ozimmu_dgemm_variant(m, n, p, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), D.data_ptr(), _ld(D), k,
+    _check(_lib.ozimmu_dgemm_variant(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), _ld(D), k,
                                      SPLIT_MODES[split], ACCUMULATE_MODES[accumulate] | SCHEDULES[schedule],
                                      workspace.data_ptr(),
                                      workspace.numel(), _stream()))
@@ -249,16 +267,20 @@ def dgemm_resident(A: torch.Tensor, B: torch.Tensor, k: int, tile: int, split: s
 def gemm_ex(transA: bool, transB: bool, alpha: float, A: torch.Tensor, B: torch.Tensor, beta: float,
             C: torch.Tensor, k: int, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """C <- alpha * op(A) op(B) + beta * C in place (product emulated with k slices)."""
-    _dev(A, torch.float64), _dev(B, torch.float64), _dev(C, torch.float64)
-    m, n = (A.shape[1], A.shape[0]) if transA else A.shape
-    n2, p = (B.shape[1], B.shape[0]) if transB else B.shape
-    if n != n2 or tuple(C.shape) != (m, p):
+    m, n, lda = _matrix(A)
+    n2, p, ldb = _matrix(B)
+    rows, cols, ldc = _matrix(C)
+    if transA:
+        m, n = n, m
+    if transB:
+        n2, p = p, n2
+    if n != n2 or rows != m or cols != p:
         raise ValueError("shapes do not match")
     if workspace is None:
         workspace = torch.empty(max(int(_lib.ozimmu_workspace_bytes_ex(m, n, p, k)), 256), dtype=torch.uint8,
                                 device=A.device)
-    _check(_lib.ozimmu_gemm_ex(1 if transA else 0, 1 if transB else 0, m, n, p, alpha, A.data_ptr(), _ld(A),
-                               B.data_ptr(), _ld(B), beta, C.data_ptr(), _ld(C), k, workspace.data_ptr(),
+    _check(_lib.ozimmu_gemm_ex(1 if transA else 0, 1 if transB else 0, m, n, p, alpha, A.data_ptr(), lda,
+                               B.data_ptr(), ldb, beta, C.data_ptr(), ldc, k, workspace.data_ptr(),
                                workspace.numel(), _stream()))
     return C
 
@@ -351,13 +373,12 @@ STATIC_WORKSPACE_BYTES = 64 << 20
 
 def dgemm_static(A: torch.Tensor, B: torch.Tensor, k: int, D: torch.Tensor) -> torch.Tensor:
     """dgemm on the library's static workspace: the call allocates nothing (D is the caller's)."""
-    _dev(A, torch.float64), _dev(B, torch.float64), _dev(D, torch.float64)
-    m, n = A.shape
-    n2, p = B.shape
-    if n != n2 or tuple(D.shape) != (m, p):
+    m, n, lda = _matrix(A)
+    n2, p, ldb = _matrix(B)
+    rows, cols, ldd = _matrix(D)
+    if n != n2 or rows != m or cols != p:
         raise ValueError("shapes do not match")
-    _check(_lib.ozimmu_dgemm_static(m, n, p, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), D.data_ptr(), _ld(D), k,
-                                    _stream()))
+    _check(_lib.ozimmu_dgemm_static(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), ldd, k, _stream()))
     return D
 
 
