@@ -40,7 +40,7 @@ int device_state(DeviceState* out)
     std::lock_guard<std::mutex> lock(g_state_mutex);
     DeviceState& s = g_state[dev];
     if (!s.ready) {
-        if (ozk::setup_gemm_kernels() != hipSuccess) return OZIMMU_ERR_HIP;
+        if (ozk::setup_gemm_kernels() != hipSuccess || ozk::setup_small() != hipSuccess) return OZIMMU_ERR_HIP;
         int ncu = 0;
         if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
             return OZIMMU_ERR_HIP;
@@ -594,6 +594,27 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     return OZIMMU_OK;
 }
 
+// The whole call in one launch (k_small) for small outputs of a short inner dimension.
+inline bool overlap(const double* x, int64_t rows, int64_t cols, int64_t ldx, const double* y, int64_t ysize)
+{
+    const uintptr_t x0 = reinterpret_cast<uintptr_t>(x), y0 = reinterpret_cast<uintptr_t>(y);
+    return x0 < y0 + 8 * (uintptr_t)ysize && y0 < x0 + 8 * (uintptr_t)((rows - 1) * ldx + cols);
+}
+// One round of its workgroups, two to a compute unit where LDS holds their slices (us a call in a graph, two launches and one, k = 8:
+// 64^3 9.6 and 5.6, 128^3 10.1 and 6.5, 256^3 11.5 and 8.7, 320 x 256 x 320, 400 workgroups, 12.2 and 11.2, 400 x 256 x 400, 625, 12.4 and
+// 16.1; 512 x 64 x 512, 1024, 10.1 and 10.7; k = 14: 256^3 16.3 and 12.2).
+inline bool small_way(const ozk::SmallArgs& a, int k, int64_t r, int num_cu)
+{
+    if (a.n > ozk::SMALL_MAX_INNER || k < ozk::SMALL_MIN_K || k > ozk::SMALL_MAX_K || r < k) return false;
+    const ozk::SmallArgs::Op &A = a.op[0], &B = a.op[1];
+    const int64_t room = 2 * (2 * k * a.steps * 1024 + 2048) <= 160 * 1024 ? 2 : 1;
+    if (((A.rows + 15) / 16) * ((B.rows + 15) / 16) > room * num_cu) return false;
+    // the operands are read while the output is written
+    const int64_t size = (A.rows - 1) * a.ldo + B.rows;
+    return !overlap(A.X, A.by_col ? a.n : A.rows, A.by_col ? A.rows : a.n, A.ld, a.out, size) &&
+           !overlap(B.X, B.by_col ? a.n : B.rows, B.by_col ? B.rows : a.n, B.ld, a.out, size);
+}
+
 }  // namespace
 
 extern "C" {
@@ -769,6 +790,11 @@ int ozimmu_gemm_ex(int transA, int transB, int64_t m, int64_t n, int64_t p, doub
     if (drc != OZIMMU_OK) return drc;
     const int bt = beta_of(n);
     const int64_t r = r_of(n, bt);
+    if (n <= ozk::SMALL_MAX_INNER) {
+        const ozk::SmallArgs a = {{{A, lda, m, transA ? 1 : 0}, {B, ldb, p, transB ? 0 : 1}}, (int)n, (int)((n + 63) / 64), bt,
+                                  !(alpha == 1.0 && beta == 0.0), alpha, beta, C, ldc};
+        if (small_way(a, k, r, ds.num_cu)) return hip_status(ozk::launch_small(a, k, st));
+    }
     char* ws = static_cast<char*>(workspace);
     void* scratch = ws;
     ws += align256(OZIMMU_SCRATCH_BYTES);
@@ -979,6 +1005,10 @@ int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, co
     accumulate_mode &= 0xff;
     const int beta = beta_of(n);
     const bool per_slice = split_mode == OZIMMU_SPLIT_NEAREST_PER_SLICE;
+    if (split_mode == OZIMMU_SPLIT_NEAREST && schedule == 0 && resident_tile < 0 && !events && n <= ozk::SMALL_MAX_INNER) {
+        const ozk::SmallArgs a = {{{A, lda, m, 0}, {B, ldb, p, 1}}, (int)n, (int)((n + 63) / 64), beta, 0, 1.0, 0.0, D, ldd};
+        if (small_way(a, k, r_of_mode(n, accumulate_mode), ds.num_cu)) return hip_status(ozk::launch_small(a, k, st));
+    }
     const int64_t ne = per_slice ? k : 1;  // exponent arrays per operand
     const int64_t r = r_of_mode(n, accumulate_mode);
     char* ws = static_cast<char*>(workspace);

@@ -156,6 +156,22 @@ struct ResidentArgs {
 template <int K>
 hipError_t launch_resident_k(const ResidentArgs& a, int r, int variant, hipStream_t st);
 hipError_t launch_resident(const ResidentArgs& a, int k, int r, int variant, hipStream_t st);
+// Steps (i) to (v) in one launch (k_small, ozimmu_split.hip): round-to-nearest slices, chunks of whole groups, n <= 256.
+constexpr int SMALL_MIN_K = 3, SMALL_MAX_K = 16, SMALL_MAX_INNER = 256;
+struct SmallArgs {
+    struct Op {
+        const double* X;
+        int64_t ld, rows;  // rows: scaled vectors
+        int by_col;
+    } op[2];
+    int n, steps, beta;    // steps = inner steps of 64
+    int finish;
+    double alpha, cbeta;
+    double* out;           // must not overlap the operands
+    int64_t ldo;
+};
+hipError_t launch_small(const SmallArgs& a, int k, hipStream_t st);
+hipError_t setup_small();  // of the current device
 // Steps (iv) and (v) of a launch with parts > 1.
 struct AddPartsArgs {
     const int32_t* blocks;

@@ -718,6 +718,136 @@ __global__ __launch_bounds__(256) void k_split_B_ps(int64_t n, int64_t p, const 
     }
 }
 
+// ---------------------------------------------------------------------------
+// The whole call (steps (i) to (v)) in one launch, for small outputs of an inner dimension of at most 256.
+//
+// A workgroup has one 16 x 16 tile of the output: it splits the 16 rows and 16 columns itself, into LDS (the packed layout's
+// swizzle, signed digits without offset), each wave multiplies one inner step of 64 into its k chunk sums (r >= k there: a chunk is a
+// group), and the sums of the waves meet in LDS, where each thread adds up one element.  Every vector is split again
+// by all the tiles in its row or column; what it saves is what such a call consists of: a launch and the wait between two
+// dependent ones (k = 8: 64^3 9.6 us for two launches, 5.6 for this one, 256^3 11.5 and 8.7).  What bounds it is one latency after the other:
+// operands, maxima, digits (a thread makes those of 32 elements), fragments, sums.
+// ---------------------------------------------------------------------------
+template <int K>
+__global__ __launch_bounds__(256) void k_small(ozk::SmallArgs a)
+{
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) int8_t lds[];
+    __shared__ double red[2][4][16];
+    __shared__ int lds_exp[2][16];
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int steps = a.steps, slice = steps * 1024;  // bytes of a slice of one operand's 16 vectors
+    const int64_t row0 = (int64_t)blockIdx.y * 16, col0 = (int64_t)blockIdx.x * 16;
+
+    // thread (vector v, place q) holds the positions 64 j + 4 q + 0 .. 3 of step j: neighbouring threads read neighbouring memory
+    double y[2][4][4];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        const ozk::SmallArgs::Op& op = a.op[o];
+        const int v = op.by_col ? (t & 15) : (t >> 4), q = op.by_col ? (t >> 4) : (t & 15);
+        int64_t R = (o == 0 ? row0 : col0) + v;
+        R = R < op.rows ? R : op.rows - 1;  // (vectors past the edge read along, their results are not stored)
+        const global_f64 x = (global_f64)op.X + (op.by_col ? R : R * op.ld);
+        const int64_t pitch = op.by_col ? op.ld : 1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int l = 64 * j + 4 * q;
+            if (!op.by_col && l + 4 <= a.n) {
+                const f64x2_a8 p = *(global_f64x2)(x + l), r = *(global_f64x2)(x + l + 2);
+                y[o][j][0] = p.x, y[o][j][1] = p.y, y[o][j][2] = r.x, y[o][j][3] = r.y;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    y[o][j][i] = 0.0;
+                    if (l + i < a.n) y[o][j][i] = x[(l + i) * pitch];
+                }
+            }
+        }
+    }
+    double mx[2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        mx[o] = 0.0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx[o] = fmax(mx[o], fabs(y[o][j][i]));
+        if (a.op[o].by_col) {
+            mx[o] = fmax(mx[o], __shfl_xor(mx[o], 16, 64));
+            mx[o] = fmax(mx[o], __shfl_xor(mx[o], 32, 64));
+            if (lane < 16) red[o][w][lane] = mx[o];
+        } else {
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) mx[o] = fmax(mx[o], __shfl_xor(mx[o], off, 64));
+        }
+    }
+    __syncthreads();
+    const double inv_step = ldexp(1.0, -a.beta);
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+        const bool by_col = a.op[o].by_col;
+        const int v = by_col ? (t & 15) : (t >> 4), q = by_col ? (t >> 4) : (t & 15);
+        if (by_col)
+#pragma unroll
+            for (int z = 0; z < 4; ++z) mx[o] = fmax(mx[o], red[o][z][v]);
+        const int e = exponent_of<false>(mx[o]), sc = a.beta - 1 - e;
+        if (q == 0) lds_exp[o][v] = e;
+        int8_t* out = lds + o * K * slice + v * TILE_K + swizzle(v, q >> 2) * CHUNK + 4 * (q & 3);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j >= steps) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[o][j][i] = ldexp(y[o][j][i], sc);
+            double sig = 6755399441055744.0;
+#pragma unroll
+            for (int s = 0; s < K; ++s) {
+                *reinterpret_cast<uint32_t*>(out + s * slice + j * 1024) = digits4<false>(y[o][j], sig, 1.0);
+                sig *= inv_step;
+            }
+        }
+    }
+    __syncthreads();
+    v4i acc[K] = {};
+    if (w < steps) {
+        const int chunk = (0x9c >> (2 * (lane >> 4))) & 3;  // 0, 3, 1, 2: see k_resident
+        const int8_t* in = lds + w * 1024 + (lane & 15) * TILE_K + swizzle(lane & 15, chunk) * CHUNK;
+        v4i f[2][K];
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            f[0][s] = *reinterpret_cast<const v4i*>(in + s * slice);
+            f[1][s] = *reinterpret_cast<const v4i*>(in + (K + s) * slice);
+        }
+#pragma unroll
+        for (int g = 0; g < K; ++g)
+#pragma unroll
+            for (int s = 0; s <= g; ++s) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[0][s], f[1][g - s], acc[g], 0, 0, 0);
+    }
+    __syncthreads();  // every wave has its fragments: their place takes the sums
+    if (w < steps)
+#pragma unroll
+        for (int g = 0; g < K; ++g) *reinterpret_cast<v4i*>(lds + (w * K + g) * 1024 + lane * 16) = acc[g];
+    __syncthreads();
+    // register w of the accumulators: row 4 (lane / 16) + w, column lane % 16
+    const int i = 4 * (lane >> 4) + w, j = lane & 15;
+    const int e = lds_exp[0][i] + lds_exp[1][j] + 2;
+    double d = 0.0;
+#pragma unroll
+    for (int g = 0; g < K; ++g) {
+        int v = 0;
+        for (int z = 0; z < steps; ++z) v += *reinterpret_cast<const int*>(lds + (z * K + g) * 1024 + lane * 16 + 4 * w);
+        const double term = ldexp((double)v, e - a.beta * (g + 2));
+        d = g == 0 ? term : d + term;
+    }
+    if (row0 + i < a.op[0].rows && col0 + j < a.op[1].rows) {
+        double* const out = a.out + (row0 + i) * a.ldo + col0 + j;
+        if (a.finish) {
+            d = a.alpha * d;
+            if (a.cbeta != 0.0) d = d + a.cbeta * *out;
+        }
+        *out = d;
+    }
+}
+
 // Unpack: one thread per output byte, out[s][row][l].
 __global__ __launch_bounds__(256) void k_export(int64_t rows, int64_t n, int k, const int8_t* __restrict__ packed,
                                                 const int32_t* __restrict__ trailer, int8_t* __restrict__ out,
@@ -987,6 +1117,29 @@ hipError_t launch_split_B_per_slice(int64_t n, int64_t p, const double* B, int64
                            s + 1 < k ? keys + (int64_t)(s + 1) * p : nullptr, rem, Npad);
     hipLaunchKernelGGL(k_decode_keys, dim3((unsigned)((nk + 255) / 256)), dim3(256), 0, st, nk, eB);
     return hipGetLastError();
+}
+
+template <int K>
+static hipError_t launch_small_k(const SmallArgs* a, int k, hipStream_t st)
+{
+    if constexpr (K <= SMALL_MAX_K) {
+        if (k != K) return launch_small_k<K + 1>(a, k, st);
+        const void* kernel = reinterpret_cast<const void*>(&k_small<K>);
+        if (!a) return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * K * 4 * 1024);
+        void* args[] = {const_cast<SmallArgs*>(a)};
+        const dim3 grid((unsigned)((a->op[1].rows + 15) / 16), (unsigned)((a->op[0].rows + 15) / 16));
+        return hipLaunchKernel(kernel, grid, dim3(256), args, 2 * K * a->steps * 1024, st);
+    }
+    return hipErrorInvalidValue;
+}
+hipError_t launch_small(const SmallArgs& a, int k, hipStream_t st) { return launch_small_k<SMALL_MIN_K>(&a, k, st); }
+hipError_t setup_small()
+{
+    for (int k = SMALL_MIN_K; k <= SMALL_MAX_K; ++k) {
+        const hipError_t e = launch_small_k<SMALL_MIN_K>(nullptr, k, nullptr);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_export(int64_t rows, int64_t n, int k, const int8_t* packed, int8_t* out, hipStream_t st)
