@@ -177,6 +177,12 @@ int check_gemm_args(int64_t m, int64_t n, int64_t p, const void* SA, int kA, con
 // from |q| <= 2^(beta-1).
 inline int rn_offset(int beta) { return (1 << (beta - 1)) - 1; }
 
+// Products so short that the offsets do not matter (a compute unit at work for 100 us or so does not reach the power limit).
+inline bool short_product(int64_t m, int64_t n, int64_t p, int k)
+{
+    return (double)m * (double)n * (double)p * k * (k + 1) <= 3.2e11;
+}
+
 // single chunk (s0 > 0): g, s = s0..s1; full schedule (s0 == 0): g = g_lo..g_hi, chunks of r.
 // SA / SB are whole stacks of kA / kB slices (slices, prefix row sums, trailer).
 ozk::GemmArgs make_args(int64_t m, int64_t n, int64_t p, const int8_t* SA, int kA, const int8_t* SB, int kB, int g_lo,
@@ -815,7 +821,8 @@ int ozimmu_gemm_ex(int transA, int transB, int64_t m, int64_t n, int64_t p, doub
     // stored matrix, which the column-wise split handles; likewise for op(B).
     const ozk::SplitIn ops[2] = {{A, lda, m, n, transA ? 1 : 0, rn_offset(bt), SA, eA},
                                  {B, ldb, p, n, transB ? 0 : 1, rn_offset(bt), SB, eB}};
-    const hipError_t e = ozk::launch_split(ops, 2, k, bt, 0, st, static_cast<uint32_t*>(scratch), ozk::SYNC_WORDS);
+    const hipError_t e = ozk::launch_split(ops, 2, k, bt, 0, st, static_cast<uint32_t*>(scratch), ozk::SYNC_WORDS,
+                                           short_product(m, n, p, k) ? partial : nullptr, (size_t)(blocks * BLOCK_BYTES));
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
 
     // Step (v) rides on the epilogue of every tile's last chunk.  beta == 0: the running sum lives in C and the
@@ -1037,7 +1044,9 @@ int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, co
         e = ozk::launch_split_B_per_slice(n, p, B, ldb, k, beta, SB, eB, remB, st);
     } else {
         const ozk::SplitIn ops[2] = {{A, lda, m, n, 0, offset, SA, eA}, {B, ldb, p, n, 1, offset, SB, eB}};
-        e = ozk::launch_split(ops, 2, k, beta, split_mode, st, static_cast<uint32_t*>(scratch), ozk::SYNC_WORDS);
+        char* const room = reinterpret_cast<char*>(SB) + ozimmu_slices_bytes(p, n, k);
+        e = ozk::launch_split(ops, 2, k, beta, split_mode, st, static_cast<uint32_t*>(scratch), ozk::SYNC_WORDS,
+                              short_product(m, n, p, k) ? room : nullptr, static_cast<char*>(workspace) + workspace_bytes - room);
     }
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
     e = mark(1);

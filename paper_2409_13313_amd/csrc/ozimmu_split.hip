@@ -353,6 +353,149 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
     }
 }
 
+// ---------------------------------------------------------------------------
+// Few long vectors in two launches: the inner dimension cut among workgroups.
+//
+// k_split_both's workgroups own whole vectors, which leaves most of the chip idle here, each working through one latency after
+// the other (48 columns and 47 rows of 11948, k = 8: 40 us).  k_cut_maxima takes the maxima of pieces (as 16-bit keys; no atomics,
+// nothing to clear), k_cut_split reduces those of its vectors and splits its piece.  Stored without offset: there are no sums of bytes
+// to collect.  (That costs clock in long products, and is used where the product is short: launch_split.)
+// A piece: 8 waves of 64 positions of 16 columns, or 8 waves of 4 x 64 positions of 4 rows.
+// ---------------------------------------------------------------------------
+constexpr int CUT_COLS = 16, CUT_ROWS = 4, CUT_WAVES = 8;
+__host__ __device__ inline int cut_vectors(int by_col) { return by_col ? CUT_COLS : CUT_ROWS; }
+__host__ __device__ inline int cut_inner(int by_col) { return by_col ? CUT_WAVES * 64 : CUT_WAVES * 256; }
+
+struct CutOp {
+    const double* X;
+    int64_t ld, rows, n;
+    int8_t* S;
+    int32_t* e;
+    int32_t* trailer;
+    uint16_t* keys;       // [piece][vector]
+    int64_t slice_stride;
+    int KT, by_col, groups, pieces;
+};
+
+// 16 elements a thread: columns, column lane % 16, positions 16 (lane / 16) + 0 .. 15 of a tile of 64; rows, row lane / 16, positions
+// 4 (lane % 16) + 0 .. 3 of four tiles.
+__device__ inline void cut_load(const CutOp& o, int group, int piece, double (*y)[4])
+{
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (o.by_col) {
+        int64_t R = (int64_t)group * CUT_COLS + (lane & 15);
+        R = R < o.rows ? R : o.rows - 1;
+        const int64_t l = (int64_t)piece * (CUT_WAVES * 64) + w * 64 + (lane >> 4) * 16;
+        global_f64 p = (global_f64)o.X + l * o.ld + R;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            y[i / 4][i % 4] = 0.0;
+            if (l + i < o.n) y[i / 4][i % 4] = *p;
+            p += o.ld;
+        }
+    } else {
+        int64_t R = (int64_t)group * CUT_ROWS + (lane >> 4);
+        R = R < o.rows ? R : o.rows - 1;
+        const global_f64 row = (global_f64)o.X + R * o.ld;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t l = (int64_t)piece * (CUT_WAVES * 256) + (u * CUT_WAVES + w) * 64 + (lane & 15) * 4;
+            if (l + 4 <= o.n) {
+                const f64x2_a8 p = *(global_f64x2)(row + l), q = *(global_f64x2)(row + l + 2);
+                y[u][0] = p.x, y[u][1] = p.y, y[u][2] = q.x, y[u][3] = q.y;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    y[u][j] = 0.0;
+                    if (l + j < o.n) y[u][j] = row[l + j];
+                }
+            }
+        }
+    }
+}
+// the largest of the workgroup's values per vector, in every thread of that vector
+template <class T>
+__device__ inline T cut_max(T v, bool by_col, T (*red)[16])
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 0; off < 4; ++off) {
+        if (by_col && off >= 2) break;
+        const T x = __shfl_xor(v, by_col ? 16 << off : 1 << off, 64);
+        v = x > v ? x : v;
+    }
+    const int at = by_col ? lane & 15 : lane >> 4;
+    if (by_col ? lane < 16 : (lane & 15) == 0) red[w][at] = v;
+    __syncthreads();
+    for (int q = 0; q < CUT_WAVES; ++q) v = red[q][at] > v ? red[q][at] : v;
+    return v;
+}
+
+__global__ __launch_bounds__(64 * CUT_WAVES) void k_cut_maxima(CutOp a, CutOp b)
+{
+    __shared__ double red[CUT_WAVES][16];
+    const int first = a.groups * a.pieces, second = (int)blockIdx.x >= first, block = (int)blockIdx.x - (second ? first : 0);
+    const CutOp o = second ? b : a;
+    const int group = block % o.groups, piece = block / o.groups, lane = threadIdx.x & 63;
+    double y[4][4], mx = 0.0;
+    cut_load(o, group, piece, y);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) mx = fmax(mx, fabs(y[i / 4][i % 4]));
+    mx = cut_max(mx, o.by_col, red);
+    const int64_t R = (int64_t)group * cut_vectors(o.by_col) + (o.by_col ? lane & 15 : lane >> 4);
+    if (threadIdx.x < 64 && (o.by_col ? lane < 16 : (lane & 15) == 0) && R < o.rows)
+        o.keys[piece * o.rows + R] = (uint16_t)exp_key(abs_bits(mx));
+}
+
+template <bool MASK>
+__global__ __launch_bounds__(64 * CUT_WAVES) void k_cut_split(CutOp a, CutOp b, int k, int beta, uint32_t* zero, int zero_count)
+{
+    __shared__ int red[CUT_WAVES][16];
+    const int first = a.groups * a.pieces, second = (int)blockIdx.x >= first, block = (int)blockIdx.x - (second ? first : 0);
+    const CutOp o = second ? b : a;
+    const int group = block % o.groups, piece = block / o.groups;
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (block == 0 && t == 0) o.trailer[0] = 0;
+    if (blockIdx.x == 0 && t < zero_count) zero[t] = 0u;
+    double y[4][4];
+    cut_load(o, group, piece, y);
+    // (threads of a vector: 4 lanes or 16 of each wave)
+    const int64_t R = (int64_t)group * cut_vectors(o.by_col) + (o.by_col ? lane & 15 : lane >> 4);
+    const bool ok = R < o.rows;
+    const int share = o.by_col ? w * 4 + (lane >> 4) : w * 16 + (lane & 15), shares = CUT_WAVES * (o.by_col ? 4 : 16);
+    int key = 0;
+    for (int z = share; z < o.pieces; z += shares) {
+        const int x = o.keys[z * o.rows + (ok ? R : o.rows - 1)];
+        key = x > key ? x : key;
+    }
+    key = cut_max(key, o.by_col, red);
+    const int e = key_to_exp<MASK>((uint32_t)key), sc = beta - 1 - e;
+    if (piece == 0 && share == 0 && ok) o.e[R] = e;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y[i / 4][i % 4] = ldexp(y[i / 4][i % 4], sc);
+    const double inv_step = ldexp(1.0, -beta), step = (double)(1 << beta);
+    double sig = 6755399441055744.0;
+    const int64_t l0 = (int64_t)piece * cut_inner(o.by_col) + w * 64 + (o.by_col ? (lane >> 4) * 16 : (lane & 15) * 4);
+    int8_t* out = o.S + packed_offset(R, l0, o.KT);
+    for (int s = 0; s < k; ++s) {
+        uint32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = digits4<MASK>(y[u], sig, step);
+        if (ok) {
+            if (o.by_col) {
+                if (l0 < (int64_t)o.KT * TILE_K) *reinterpret_cast<uint4*>(out) = make_uint4(v[0], v[1], v[2], v[3]);
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (l0 + u * (CUT_WAVES * 64) < (int64_t)o.KT * TILE_K)
+                        *reinterpret_cast<uint32_t*>(out + (int64_t)u * CUT_WAVES * TILE_BYTES) = v[u];
+            }
+        }
+        out += o.slice_stride;
+        sig *= inv_step;
+    }
+}
+
 constexpr int SPLIT_WAVES = 8;
 // DBR: elements of a row a thread holds (columns: 16); COLS: the launch may have columns.  Vectors per workgroup are each
 // operand's own: both sides of a product may be columns (A transposed), one of many vectors and one of few.
@@ -936,11 +1079,11 @@ static SplitOp make_op(const SplitIn& i, int k)
 //    500 of 65536 219 and 354, 1024 of 65536 434 and 513, 2017 of 65536 824 and 711, 8192 of 16384 807 and 713.
 //  * Rows beside or instead: 8 + k bytes an element (16 + k beyond 16384 positions) at 4.5 per ps, a row at 25 per ns.
 // Up to 256 inner positions, where a wave does not share a tile of 64 with others, 16 (1024 columns of 64: 6.4 us, with 4 7.6).
-static void choose_columns(const SplitIn* ops, int count, int k, int* per)
+static double choose_columns(const SplitIn* ops, int count, int k, int* per)
 {
     constexpr int FORMS = 4, columns_of[FORMS] = {16, 8, 4, 0};
     for (int q = 0; q < count; ++q) per[q] = ops[q].by_col && ops[q].n <= 256 ? 16 : 0;
-    if (ops[0].n <= 256) return;
+    if (ops[0].n <= 256) return 0.0;
     const double n = (double)ops[0].n, both = (double)ops[0].rows + (count == 2 ? (double)ops[1].rows : 0.0);
     const int forms0 = ops[0].by_col ? FORMS : 1, forms1 = count == 2 && ops[1].by_col ? FORMS : 1;
     double least = -1.0;
@@ -987,15 +1130,66 @@ static void choose_columns(const SplitIn* ops, int count, int k, int* per)
             for (int q = 0; q < count; ++q) per[q] = ops[q].by_col ? columns_of[f[q]] : 0;
         }
     }
+    return least;
+}
+
+static CutOp make_cut(const SplitIn& i, int k, uint16_t* keys)
+{
+    CutOp o{};
+    o.X = i.X;
+    o.ld = i.ld;
+    o.rows = i.rows;
+    o.n = i.n;
+    o.S = i.S;
+    o.e = i.e;
+    o.trailer = reinterpret_cast<int32_t*>(i.S + ozl::trailer_offset(i.rows, i.n, k));
+    o.keys = keys;
+    o.slice_stride = ozl::slice_bytes(i.rows, i.n);
+    o.KT = (int)(ozl::inner_padded(i.n) / ozl::TILE_K);
+    o.by_col = i.by_col;
+    o.groups = (int)((i.rows + cut_vectors(i.by_col) - 1) / cut_vectors(i.by_col));
+    o.pieces = (int)((ozl::inner_padded(i.n) + cut_inner(i.by_col) - 1) / cut_inner(i.by_col));
+    return o;
+}
+
+// Both operands in two launches (k_cut_maxima, k_cut_split), where that is estimated to take less than `us`: 11 us and 8 bytes per
+// ps while the operands are still in the memory-side cache for the second, else 3.8 (whole calls, one launch or the cut columns'
+// four and two, k = 8: 47 x 11948 x 48 58.4 and 31.4, 256 x 8192 x 256 63.6 and 48.9, 600 x 20000 x 200 203 and 185, 75 x 2212 x 512 30.2 and
+// 29.1, 500 x 1024 x 500 23.2 and 26.1; k = 4: 100 x 262144 x 100 488 and 370, 1000 x 2000 x 1000 35.2 and 40.6).
+static bool cut_pays(const SplitIn* ops, int count, int k, double us, size_t room)
+{
+    if (count != 2 || ops[0].n < 1024) return false;
+    double vectors = 0.0;
+    size_t keys = 0;
+    for (int q = 0; q < 2; ++q) {
+        const CutOp o = make_cut(ops[q], k, nullptr);
+        if ((int64_t)o.groups * o.pieces >= ((int64_t)1 << 22)) return false;
+        keys += 2 * (size_t)o.pieces * (size_t)o.rows;
+        vectors += (double)o.rows;
+    }
+    if (keys > room) return false;
+    const double bytes = vectors * (double)ops[0].n * (16 + k), near = bytes < 160e6 ? bytes : 160e6;
+    return 11.0 + near / 8e6 + (bytes - near) / 3.8e6 + 1.5 < us;
 }
 
 hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,
-                        int also_zero_count)
+                        int also_zero_count, void* room, size_t room_bytes)
 {
     SplitOp op[2]{};
     int used = 0, per[2] = {0, 0};
     bool columns = false;
-    choose_columns(ops, count, k, per);
+    const double whole_us = choose_columns(ops, count, k, per);
+    if (room && cut_pays(ops, count, k, whole_us, room_bytes)) {
+        const CutOp a = make_cut(ops[0], k, static_cast<uint16_t*>(room));
+        const CutOp b = make_cut(ops[1], k, a.keys + (int64_t)a.pieces * a.rows);
+        const dim3 grid((unsigned)(a.groups * a.pieces + b.groups * b.pieces)), block(64 * CUT_WAVES);
+        hipLaunchKernelGGL(k_cut_maxima, grid, block, 0, st, a, b);
+        if (split_mode != 0)
+            hipLaunchKernelGGL(k_cut_split<true>, grid, block, 0, st, a, b, k, beta, also_zero, also_zero_count);
+        else
+            hipLaunchKernelGGL(k_cut_split<false>, grid, block, 0, st, a, b, k, beta, also_zero, also_zero_count);
+        return hipGetLastError();
+    }
     for (int q = 0; q < count; ++q) {
         if (ops[q].by_col && per[q] == 0) {
             const hipError_t e = launch_split_cols_cut(ops[q], k, beta, split_mode, st);
