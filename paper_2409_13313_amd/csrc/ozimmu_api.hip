@@ -1038,7 +1038,10 @@ int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, co
     hipError_t e = mark(0);
     if (e != hipSuccess) return OZIMMU_ERR_HIP;
     const int offset = (split_mode == OZIMMU_SPLIT_NEAREST && accumulate_mode != OZIMMU_ACCUM_WIDE) ? rn_offset(beta) : 0;
-    if (per_slice) {
+    if (per_slice && n <= ozk::PER_SLICE_MAX_INNER) {
+        const ozk::SplitIn ops[2] = {{A, lda, m, n, 0, 0, SA, eA}, {B, ldb, p, n, 1, 0, SB, eB}};
+        e = ozk::launch_split_per_slice(ops, k, beta, st);
+    } else if (per_slice) {
         e = ozk::launch_split_A_per_slice(m, n, A, lda, k, beta, SA, eA, remA, st);
         if (e != hipSuccess) return OZIMMU_ERR_HIP;
         e = ozk::launch_split_B_per_slice(n, p, B, ldb, k, beta, SB, eB, remB, st);

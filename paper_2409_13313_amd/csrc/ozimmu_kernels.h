@@ -28,6 +28,9 @@ hipError_t launch_split_A_per_slice(int64_t m, int64_t n, const double* A, int64
                                     int32_t* eA, double* rem, hipStream_t st);
 hipError_t launch_split_B_per_slice(int64_t n, int64_t p, const double* B, int64_t ldb, int k, int beta, int8_t* SB,
                                     int32_t* eB, double* rem, hipStream_t st);
+// Both operands in one launch, no scratch (k_split_ps); n <= PER_SLICE_MAX_INNER.
+constexpr int PER_SLICE_MAX_INNER = 8192;
+hipError_t launch_split_per_slice(const SplitIn* ops, int k, int beta, hipStream_t st);
 hipError_t launch_export(int64_t rows, int64_t n, int k, const int8_t* packed, int8_t* out, hipStream_t st);
 
 constexpr int QUEUE_ROUND_TILES = 256;  // tiles per round of the queue schedule (see GemmArgs::queue_sets)

@@ -796,6 +796,87 @@ __global__ __launch_bounds__(256) void k_split_A_ps(int64_t m, int64_t n, const 
 }
 
 // ---------------------------------------------------------------------------
+// Algorithm 5, vectors that stay in the registers of a workgroup of 8 waves: both operands in one launch, read once.
+//
+// A workgroup has one row, or 4 columns, 16 U elements a thread (up to 2048 U inner positions); the remainders stay where they
+// are from slice to slice, only their maximum goes through LDS.  Bound by HBM for large operands (8 + k bytes an element; the
+// kernels above and below move 16 k), by k barriers for small ones.  Whole calls, k + 4 launches and this one: 176 x 38 x 702, k = 9 74 and
+// 24 us, 2006 x 768 x 615, k = 8 168 and 113, 3892^3, k = 12 4.4 and 3.7 ms.  (U = 4 spills 39 registers: 5376^3, k = 8, 6.3 ms either way.)
+// ---------------------------------------------------------------------------
+constexpr int PS_COLS = 4;
+struct PsOp {
+    const double* X;
+    int64_t ld, rows, n;
+    int8_t* S;
+    int32_t* e;
+    int32_t* trailer;
+    int64_t slice_stride;
+    int KT, by_col, blocks;
+};
+
+template <int U>
+__global__ __launch_bounds__(512) void k_split_ps(PsOp a, PsOp b, int k, int beta)
+{
+    __shared__ double red[2][8][PS_COLS];
+    const bool second = (int)blockIdx.x >= a.blocks;
+    const PsOp o = second ? b : a;
+    const int block = second ? (int)blockIdx.x - a.blocks : (int)blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (block == 0 && t == 0) o.trailer[0] = 0;  // slices with a scale each are stored without offset
+    const int v = o.by_col ? lane % PS_COLS : 0;
+    const int64_t R = (int64_t)block * (o.by_col ? PS_COLS : 1) + v;
+    const bool ok = R < o.rows;
+    const int64_t at = ok ? R : o.rows - 1, end = (int64_t)o.KT * TILE_K;
+    const global_f64 x = (global_f64)o.X + (o.by_col ? at : at * o.ld);
+    const int64_t pitch = o.by_col ? o.ld : 1;
+    // positions of quad q (4 consecutive ones)
+    auto place = [&](int q) -> int64_t {
+        if (o.by_col) return (int64_t)(q / 4) * 2048 + w * 256 + (lane / PS_COLS) * 16 + (q % 4) * 4;
+        return (int64_t)q * 2048 + w * 256 + lane * 4;
+    };
+    double y[4 * U][4], mx = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4 * U; ++q) {
+        const int64_t l = place(q);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            y[q][j] = 0.0;
+            if (l + j < o.n) y[q][j] = x[(l + j) * pitch];
+            mx = fmax(mx, fabs(y[q][j]));
+        }
+    }
+    for (int s = 0; s < k; ++s) {
+        // (two places for the maxima in turn: one barrier a slice)
+        if (!o.by_col) {
+            mx = fmax(mx, __shfl_xor(mx, 1, 64));
+            mx = fmax(mx, __shfl_xor(mx, 2, 64));
+        }
+#pragma unroll
+        for (int off = PS_COLS; off < 64; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+        if (lane < PS_COLS) red[s & 1][w][lane] = mx;
+        __syncthreads();
+        for (int z = 0; z < 8; ++z) mx = fmax(mx, red[s & 1][z][v]);
+        const int e = exponent_of<false>(mx), sc = beta - 1 - e;
+        if (ok && w == 0 && (o.by_col ? lane < PS_COLS : lane == 0)) o.e[(int64_t)s * o.rows + R] = e;
+        mx = 0.0;
+        int8_t* out = o.S + s * o.slice_stride;
+#pragma unroll
+        for (int q = 0; q < 4 * U; ++q) {
+            uint32_t word = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double ys = ldexp(y[q][j], sc), d = __builtin_rint(ys);
+                word |= ((uint32_t)(int)d & 0xffu) << (8 * j);
+                y[q][j] = ldexp(ys - d, -sc);
+                mx = fmax(mx, fabs(y[q][j]));
+            }
+            const int64_t l = place(q);
+            if (ok && l < end) *reinterpret_cast<uint32_t*>(out + packed_offset(R, l, o.KT)) = word;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Algorithm 5, B: one launch per slice (the column maxima of the remainder need
 // a grid-wide reduction between slices).  Tiling and write-out as in k_split_B;
 // src is B for the first slice and the remainder buffer (pitch p) afterwards.
@@ -1289,6 +1370,33 @@ hipError_t launch_split_A_per_slice(int64_t m, int64_t n, const double* A, int64
     else
         hipLaunchKernelGGL((k_split_A_ps<false>), grid, block, 0, st, m, n, A, lda, k, beta, SA, eA, rem, trailer, Npad,
                            stride);
+    return hipGetLastError();
+}
+
+hipError_t launch_split_per_slice(const SplitIn* ops, int k, int beta, hipStream_t st)
+{
+    PsOp op[2]{};
+    for (int q = 0; q < 2; ++q) {
+        const SplitIn& i = ops[q];
+        op[q].X = i.X;
+        op[q].ld = i.ld;
+        op[q].rows = i.rows;
+        op[q].n = i.n;
+        op[q].S = i.S;
+        op[q].e = i.e;
+        op[q].trailer = reinterpret_cast<int32_t*>(i.S + ozl::trailer_offset(i.rows, i.n, k));
+        op[q].slice_stride = ozl::slice_bytes(i.rows, i.n);
+        op[q].KT = (int)(ozl::inner_padded(i.n) / ozl::TILE_K);
+        op[q].by_col = i.by_col;
+        op[q].blocks = (int)(i.by_col ? (i.rows + PS_COLS - 1) / PS_COLS : i.rows);
+    }
+    const dim3 grid((unsigned)(op[0].blocks + op[1].blocks)), block(512);
+    if (op[0].n <= 2048)
+        hipLaunchKernelGGL(k_split_ps<1>, grid, block, 0, st, op[0], op[1], k, beta);
+    else if (op[0].n <= 4096)
+        hipLaunchKernelGGL(k_split_ps<2>, grid, block, 0, st, op[0], op[1], k, beta);
+    else
+        hipLaunchKernelGGL(k_split_ps<4>, grid, block, 0, st, op[0], op[1], k, beta);
     return hipGetLastError();
 }
 

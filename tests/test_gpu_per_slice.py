@@ -101,3 +101,19 @@ def test_mode_errors_and_workspace_size(oz):
     A, B = inputs.phi_pair(300, 520, 270, 0.5, seed=74)
     with pytest.raises(oz.OzimmuError):
         oz.dgemm_variant(dev(A), dev(B), 8, "per_slice", "per_pair", workspace=small)
+
+
+# operands that stay in a workgroup's registers: edges of the 2048, 4096 and 8192 inner positions, of 4 columns and of the inner tiles
+@pytest.mark.parametrize("m,n,p,k", [(1, 1, 1, 3), (3, 63, 5, 8), (9, 2047, 4, 7), (6, 2048, 7, 13), (5, 2049, 9, 14), (4, 4096, 5, 6), (5, 4097, 3, 6), (2, 8191, 3, 5),
+                                     (3, 8192, 2, 9), (2, 8193, 5, 4), (130, 257, 70, 16)])
+def test_split_in_one_launch(oz, m, n, p, k):
+    A, B = inputs.phi_pair(m, n, p, 4.0, seed=75)
+    A[m - 1, n - 1], B[n - 1, p - 1] = 2.0 ** 30, -0.75
+    if m > 2 and p > 2:
+        A[1], B[:, 1] = 0.0, 0.0
+        A[2], B[:, 2] = 2.0, -1.0          # nothing left after the first slice
+    a = torch.full((m, n + 1), float("nan"), dtype=torch.float64, device="cuda")[:, :n]
+    b = torch.full((n, p + 3), float("nan"), dtype=torch.float64, device="cuda")[:, :p]
+    a.copy_(dev(A)), b.copy_(dev(B))
+    got = oz.dgemm_variant(a, b, k, "per_slice", "per_pair").cpu().numpy()
+    assert np.array_equal(got, oracle.dgemm_per_slice(A, B, k))
