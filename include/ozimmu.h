@@ -83,7 +83,8 @@ size_t ozimmu_slices_bytes(int64_t rows, int64_t n, int k);
  * tiles one per chunk and tile, at most 4096 = 1 GiB; for larger outputs what the queue schedule takes,
  * min(ceil(tiles / 256), 3) x chunks x min(tiles, 256) blocks and a block of counters -- 1.5 GiB at k = 8 with one chunk
  * per group, more where the inner dimension makes the chunks shorter than the groups); host.  Not monotone in k (the per-chunk blocks
- * are only counted while they stay within those limits). */
+ * are only counted while they stay within those limits).  At least 128 blocks for outputs of up to 16 tiles and n >= 1024, whose
+ * inner dimension may be cut among workgroups. */
 size_t ozimmu_workspace_bytes(int64_t m, int64_t n, int64_t p, int k);
 
 /* The least ozimmu_dgemm accepts (one block per output tile, at most 128): with less than
@@ -136,9 +137,11 @@ enum { OZIMMU_SPLIT_NEAREST = 0, OZIMMU_SPLIT_BITMASK = 1, OZIMMU_SPLIT_NEAREST_
 enum { OZIMMU_ACCUM_GROUPED = 0, OZIMMU_ACCUM_PER_PAIR = 1, OZIMMU_ACCUM_WIDE = 2 };
 /* How the schedule is run; OR one of these into accumulate_mode (default: the library chooses).  The result
  * does not depend on it, bit for bit.  Without a flag, for 3 to 16 slices with one scale per row and column, the
- * library usually takes a way that has no flag: all chunk sums of a tile (32 x 32 to 128 x 128 outputs) grow side by
+ * library usually takes a way that has no flag: small outputs of at most 256 inner positions in one launch that uses no
+ * workspace; else all chunk sums of a tile (32 x 32 to 128 x 128 outputs) grow side by
  * side in registers while the inner dimension is walked once, and D is written once.  It needs no blocks, so any workspace
- * that is accepted will do.  The ways below serve the rest - other slice counts, a scale per slice, schedules of so
+ * that is accepted will do (with blocks, few tiles of a long inner dimension are cut along it).  A scale per slice takes
+ * it too, up to 13 slices.  The ways below serve the rest - other slice counts, schedules of so
  * many chunks (long inner dimensions) that the tiles would become too small, few tiles of a long inner dimension, whose
  * operands would be waited for - and whoever asks for them.
  *   OZIMMU_SCHEDULE_ONE_LAUNCH   the whole schedule in one persistent kernel with the FP64 accumulation

@@ -233,7 +233,8 @@ struct Finish {
 // of at most r consecutive s), into D.  Five ways to run it, with bit-identical results (details where each is
 // decided below):
 //  * resident: one launch, all chunk sums of a tile side by side in registers, D written once -- the default where its
-//    estimate is the lowest (nearly everywhere at 3 to 16 slices and at most 16 chunks);
+//    estimate is the lowest (nearly everywhere at 3 to 16 slices and at most 16 chunks); few tiles of a long inner dimension
+//    cut along it, a second launch adding the parts up, where the workspace has room for their sums;
 //  * the queue: one launch whose work items are the (chunk, tile) pairs, an INT32 block per item, the tile's chunks
 //    added up by the workgroup that completes it -- the default for outputs of more tiles than compute units (and
 //    from QUEUE_MIN_TILES tiles on where the chunk-parallel way has no room) when the workspace holds the blocks;

@@ -1,7 +1,7 @@
 // Steps (iii) and (iv) of the scheme on the gfx950 matrix cores, one chunk after the other.
 //
 // (Most calls take k_resident, ozimmu_resident.hip, which keeps all chunks of a tile in registers.  What is here serves
-// slice counts outside 3 .. 16, slices with one scale each, schedules of so many chunks that k_resident's tiles would be
+// slice counts outside 3 .. 16 (13 with one scale each), schedules of so many chunks that k_resident's tiles would be
 // too small - 4096 x 65536 x 4096, k = 10, 30 chunks: the queue 39.7 ms, k_resident 40.3 to 42.3 -, the forced schedules
 // and the phase-level entry points.)
 //
