@@ -144,6 +144,14 @@ def _matrix(t: torch.Tensor) -> Tuple[int, int, int]:
     return rows, cols, ld if rows > 1 else max(cols, ld, 1)
 
 
+def _output(D: torch.Tensor, m: int, p: int) -> int:
+    """Leading dimension of a caller's output, which has to hold m x p elements."""
+    rows, cols, ldd = _matrix(D)
+    if rows < m or cols < p:
+        raise ValueError(f"output of {rows} x {cols} for a product of {m} x {p}")
+    return ldd
+
+
 def status_string(status: int) -> str:
     return _lib.ozimmu_status_string(status).decode()
 
@@ -190,7 +198,7 @@ def dgemm(A: torch.Tensor, B: torch.Tensor, k: int, D: Optional[torch.Tensor] = 
     if D is None:
         D, ldd = A.new_empty((m, p)), max(p, 1)
     else:
-        ldd = _matrix(D)[2]
+        ldd = _output(D, m, p)
     if workspace is None:
         workspace = alloc_workspace(m, n, p, k, A.device)
     status = _lib.ozimmu_dgemm(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), ldd, k,
@@ -205,11 +213,13 @@ def dgemm_profiled(A: torch.Tensor, B: torch.Tensor, k: int, D: torch.Tensor, wo
     """dgemm that records three torch.cuda.Event objects (start, after split,
     end) on the current stream; the events must have been recorded once before
     so that their HIP handles exist."""
-    _dev(A, torch.float64), _dev(B, torch.float64), _dev(D, torch.float64)
-    m, n = A.shape
-    p = B.shape[1]
+    m, n, lda = _matrix(A)
+    n2, p, ldb = _matrix(B)
+    if n2 < n:
+        raise ValueError("B has fewer rows than A has columns")
+    ldd = _output(D, m, p)
     handles = (_vp * 3)(*[_vp(ev.cuda_event) if ev is not None else _vp(None) for ev in events])
-    _check(_lib.ozimmu_dgemm_profiled(m, n, p, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), D.data_ptr(), _ld(D), k,
+    _check(_lib.ozimmu_dgemm_profiled(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), ldd, k,
                                       workspace.data_ptr(), workspace.numel(), _stream(), handles))
     return D
 
@@ -229,9 +239,10 @@ def dgemm_variant(A: torch.Tensor, B: torch.Tensor, k: int, split: str = "rn", a
         raise ValueError("inner dimensions differ")
     if D is None:
         D = A.new_empty((m, p))
+    ldd = _output(D, m, p)
     if workspace is None:
         workspace = alloc_workspace(m, n, p, k, A.device, split)
-    _check(_lib.ozimmu_dgemm_variant(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), _ld(D), k,
+    _check(_lib.ozimmu_dgemm_variant(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), ldd, k,
                                      SPLIT_MODES[split], ACCUMULATE_MODES[accumulate] | SCHEDULES[schedule],
                                      workspace.data_ptr(),
                                      workspace.numel(), _stream()))
@@ -249,16 +260,16 @@ def resident_tile(n: int, k: int, accumulate: str, tile: int) -> Optional[Tuple[
 def dgemm_resident(A: torch.Tensor, B: torch.Tensor, k: int, tile: int, split: str = "rn", accumulate: str = "grouped",
                    D: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """dgemm_variant with all chunk sums in registers and the given tile (debug / test helper)."""
-    _dev(A, torch.float64), _dev(B, torch.float64)
-    m, n = A.shape
-    n2, p = B.shape
+    m, n, lda = _matrix(A)
+    n2, p, ldb = _matrix(B)
     if n != n2:
         raise ValueError("inner dimensions differ")
     if D is None:
-        D = torch.empty((m, p), dtype=torch.float64, device=A.device)
+        D = A.new_empty((m, p))
+    ldd = _output(D, m, p)
     if workspace is None:
         workspace = alloc_workspace(m, n, p, k, A.device, split)
-    _check(_lib.ozimmu_dgemm_resident(m, n, p, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), D.data_ptr(), _ld(D), k,
+    _check(_lib.ozimmu_dgemm_resident(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), ldd, k,
                                       SPLIT_MODES[split], ACCUMULATE_MODES[accumulate], tile, workspace.data_ptr(),
                                       workspace.numel(), _stream()))
     return D
