@@ -112,10 +112,14 @@ def _check(status: int) -> None:
 
 # The current stream's handle without a Stream object around it, and every tensor looked at once: a call of a small product takes
 # as long on the host as on the GPU (64^3: 12.9 us a call, of which 6.4 the library and its launches, 2.8 the Stream object).
-_current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+# (A torch built without a GPU has neither; the functions of the host do without.)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream() -> int:
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_current_device())
 
 

@@ -1,4 +1,8 @@
 """What the Python binding refuses before anything reaches the library (no GPU: tensors and library are stand-ins)."""
+import os
+import subprocess
+import sys
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -65,3 +69,14 @@ def test_an_output_of_the_size_or_larger_is_taken_with_its_leading_dimension(oz,
         CALLS[call](oz, A, B, D, ws)
         (_, args), = oz._lib.calls
         assert args[:3] == (20, 30, 40) and args[4] == 31 and args[6] == 40 and args[8] == ldd
+
+
+def test_the_functions_of_the_host_need_no_torch_with_a_gpu():
+    code = ("import torch\n"
+            "for name in ('_cuda_getDevice', '_cuda_getCurrentRawStream'):\n"
+            "    if hasattr(torch._C, name): delattr(torch._C, name)\n"
+            "from paper_2409_13313_amd import ozimmu\n"
+            "assert ozimmu.params(1024) == (7, 128) and ozimmu.num_chunks(1024, 8) == 8\n")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    pr = subprocess.run([sys.executable, "-c", code], cwd=root, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert pr.returncode == 0, pr.stdout
