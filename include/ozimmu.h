@@ -297,6 +297,32 @@ int ozimmu_dgemm_resident(int64_t m, int64_t n, int64_t p,
                           double *D, int64_t ldd, int k, int split_mode, int accumulate_mode, int tile,
                           void *workspace, size_t workspace_bytes, void *stream);
 
+/* The same with the inner dimension of every tile cut into `parts` (1 .. 64, at least two steps of 64 each) whose sums a second
+ * launch adds up: parts > 1 for the tiles that the library cuts and as far as the workspace has room for the sums
+ * (OZIMMU_ERR_WORKSPACE else); and, with parts == 1, for OZIMMU_SPLIT_NEAREST_PER_SLICE.  OZIMMU_ERR_SLICES where there is no such
+ * kernel.  Debug / test helper. */
+int ozimmu_dgemm_tile(int64_t m, int64_t n, int64_t p,
+                      const double *A, int64_t lda, const double *B, int64_t ldb,
+                      double *D, int64_t ldd, int k, int split_mode, int accumulate_mode, int tile, int parts,
+                      void *workspace, size_t workspace_bytes, void *stream);
+
+/* What ozimmu_dgemm_variant (no schedule flag) does with a call by itself, in a workspace of that many bytes on a device of num_cu
+ * compute units.  Host, pure; sizes of at least 1.  (An output that overlaps an operand keeps a call from OZIMMU_WAY_SMALL.)
+ * Debug / test helper. */
+enum { OZIMMU_WAY_SMALL = 0,          /* the whole call in one launch */
+       OZIMMU_WAY_RESIDENT = 1,       /* all chunk sums of a tile in registers: `tile`; parts > 1: cut along the inner dimension */
+       OZIMMU_WAY_QUEUE = 2, OZIMMU_WAY_CHUNK_PARALLEL = 3, OZIMMU_WAY_SPLIT_INNER = 4, OZIMMU_WAY_ONE_LAUNCH = 5 };
+enum { OZIMMU_SPLIT_WAY_NONE = 0,     /* part of the one launch */
+       OZIMMU_SPLIT_WAY_WHOLE = 1,    /* workgroups own whole vectors */
+       OZIMMU_SPLIT_WAY_CUT = 2,      /* two launches along the inner dimension */
+       OZIMMU_SPLIT_WAY_PASSES = 3 }; /* one scale per slice of vectors too long for registers: a pass per slice */
+typedef struct {
+    int way, tile, parts, split_way;
+    int merge_rows;                   /* rows of D that begin inside a memory line are merged in L2 */
+} ozimmu_choice;
+int ozimmu_choose(int64_t m, int64_t n, int64_t p, int k, int split_mode, int accumulate_mode, size_t workspace_bytes,
+                  int num_cu, ozimmu_choice *out);
+
 /* Unpack a packed slice stack into the canonical order out[s][row][l]
  * (int8, k x rows x n, dense): for A that is A''_s[i][l]; for B it is
  * B''_s[l][j] stored at out[s][j][l].  Debug / test helper. */

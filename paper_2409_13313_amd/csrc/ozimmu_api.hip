@@ -90,7 +90,7 @@ int64_t r_of_mode(int64_t n, int accumulate_mode)
 
 int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, const double* B, int64_t ldb,
                double* D, int64_t ldd, int k, int split_mode, int accumulate_mode, void* workspace,
-               size_t workspace_bytes, void* stream, void* const* events, int resident_tile = -1);
+               size_t workspace_bytes, void* stream, void* const* events, int resident_tile = -1, int parts = 1);
 
 // The split-inner way of running the schedule (see run_schedule) works on at most this many 256 x 256 tiles
 // at a time: outputs that small as a whole, or the last, partly filled round of tiles of a larger output
@@ -229,86 +229,28 @@ struct Finish {
     int64_t ldco;
 };
 
-// Steps (iii) + (iv) (+ (v), see Finish) for the whole schedule of Algorithm 6 (groups g = 2..k+1 ascending, chunks
-// of at most r consecutive s), into D.  Five ways to run it, with bit-identical results (details where each is
-// decided below):
-//  * resident: one launch, all chunk sums of a tile side by side in registers, D written once -- the default where its
-//    estimate is the lowest (nearly everywhere at 3 to 16 slices and at most 16 chunks); few tiles of a long inner dimension
-//    cut along it, a second launch adding the parts up, where the workspace has room for their sums;
-//  * the queue: one launch whose work items are the (chunk, tile) pairs, an INT32 block per item, the tile's chunks
-//    added up by the workgroup that completes it -- the default for outputs of more tiles than compute units (and
-//    from QUEUE_MIN_TILES tiles on where the chunk-parallel way has no room) when the workspace holds the blocks;
-//  * one persistent launch with the accumulation fused into the GEMM epilogue (mode 1, or 2 for per-slice
-//    scales): one workgroup per compute unit takes tile after tile, all chunks of a tile in turn -- needs no
-//    blocks;
-//  * chunk-parallel, for outputs of few tiles or the last, partly filled round after a persistent launch: one
-//    launch whose work items are (chunk, inner part, tile), a block per chunk and tile, then one accumulation
-//    kernel over those tiles;
-//  * split-inner, for the same tiles when there is room for one block per tile only: per chunk, the chunk GEMM
-//    with its inner range cut into Z parts on Z workgroups per tile, which add their partial sums to zeroed
-//    per-tile INT32 blocks with integer atomics, then the accumulation kernel over those tiles, which also clears
-//    the blocks again.
-// schedule: 0 = choose, or one of the OZIMMU_SCHEDULE_* flags (honoured when possible).  resident_tile >= 0: the resident
-// way with that tile (the caller has checked that there is one).
-int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t* SB, const int32_t* eA,
-                 const int32_t* eB, int k, int64_t r, bool per_slice, int schedule, double* D, int64_t ldd,
-                 const Finish& fin, int32_t* partial, int64_t partial_capacity, void* scratch, int num_cu, hipStream_t st,
-                 bool sync_clean = false, int resident_tile = -1)
+// How steps (iii) to (v) are run.
+struct Way {
+    enum Kind { RESIDENT, QUEUE, TILES } kind = TILES;
+    int tile = -1, parts = 1;        // RESIDENT: which tile; workgroups that share its inner dimension
+    int64_t sets = 0;                // QUEUE
+    int64_t cp_tail = 0, tail = 0;   // TILES: the last cp_tail tiles go the chunk-parallel way, or the last `tail` the split-inner
+    int cp_z = 1, Z = 1;             // way, cut in cp_z / Z; the others to the persistent launch
+};
+
+// The choice among the ways that run_schedule lists.  A function of the sizes, the room for blocks (`capacity`, of BLOCK_BYTES; with one
+// scale per slice no way that needs any is taken: they know one exponent per row and column) and the number of compute units only: no GPU is asked, so tests check it without one.
+Way choose_way(int64_t m, int64_t n, int64_t p, int k, int r_eff, bool per_slice, int schedule, int64_t capacity, int num_cu)
 {
-    // sync_clean: the caller has already zeroed the soft-barrier counters in `scratch` (the first GEMM launch
-    // then need not; later ones of the same call find them used and do)
-    auto take_clean = [&]() -> int {
-        const int c = sync_clean ? 1 : 0;
-        sync_clean = false;
-        return c;
-    };
-    const int beta = beta_of(n);
-    const int r_eff = (int)(r < k ? r : k);
     const int KT = (int)(ozl::inner_padded(n) / ozl::TILE_K);
     const int64_t T = output_tiles(m, p);
     const int64_t w = chunks_of(k, r_eff);
-
-    auto launch_resident = [&](int variant, int parts = 1) -> int {
-        const ozk::GemmArgs g = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
-        ozk::ResidentArgs a{};
-        a.SA = g.SA;
-        a.SB = g.SB;
-        a.PA = g.PA;
-        a.PB = g.PB;
-        a.pstrideA = g.pstrideA;
-        a.pstrideB = g.pstrideB;
-        a.cA = g.cA;
-        a.cB = g.cB;
-        a.strideA = g.strideA;
-        a.strideB = g.strideB;
-        a.KT = KT;
-        a.steps = (int)((n + ozl::TILE_K - 1) / ozl::TILE_K);
-        a.m = m;
-        a.p = p;
-        a.D = D;
-        a.ldd = ldd;
-        a.eA = eA;
-        a.eB = eB;
-        a.beta = beta;
-        a.finish = fin.on ? 1 : 0;
-        a.alpha = fin.alpha;
-        a.cbeta = fin.cbeta;
-        a.Cout = fin.Cout;
-        a.ldco = fin.ldco;
-        a.per_slice = per_slice ? 1 : 0;
-        a.parts = parts;
-        a.blocks = partial;
-        double* const out = fin.on ? fin.Cout : D;
-        a.keep = (reinterpret_cast<uintptr_t>(out) % 64 != 0 || (fin.on ? fin.ldco : ldd) % 8 != 0) && ozr::merge_rows(k, n);
-        const hipError_t e = ozk::launch_resident(a, k, r_eff, variant, st);
-        if (e != hipSuccess || parts == 1) return hip_status(e);
-        const ozr::Config c = ozr::config_for(k, r_eff, variant);
-        const ozk::AddPartsArgs add = {partial, k,      r_eff,     beta,     parts, c.ta, c.tb,
-                                       m,       p,      eA,        eB,       a.finish, fin.alpha, fin.cbeta,
-                                       out,     fin.on ? fin.ldco : ldd};
-        return hip_status(ozk::launch_add_parts(add, st));
+    Way way;
+    auto queue_way = [&](int64_t sets) {
+        way.kind = Way::QUEUE;
+        way.sets = sets;
+        return way;
     };
-    if (resident_tile >= 0) return launch_resident(resident_tile);
 
     // The queue, for the tiles [0, tiles) of the band order: one launch whose work items are all
     // (chunk, tile) pairs, handed out round by round (256 tiles) through a counter; an item leaves its INT32 sums
@@ -318,59 +260,25 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     // and chunk instead of 16, and no workgroup ever waits for another (measured 3 to 4 % faster at 16384^3,
     // 2 % at 8192^3, k = 8).  queue_sets: how many sets fit (0: the way cannot be used for that many tiles).
     auto queue_sets = [&](int64_t tiles) -> int64_t {
-        if (per_slice || !partial || tiles < 1 || tiles * w >= ((int64_t)1 << 30)) return 0;
+        if (per_slice || tiles < 1 || tiles * w >= ((int64_t)1 << 30)) return 0;
         const int64_t stride = tiles < ozk::QUEUE_ROUND_TILES ? tiles : ozk::QUEUE_ROUND_TILES;
         if (w * stride * BLOCK_BYTES >= ((int64_t)1 << 31)) return 0;  // 32-bit byte offsets inside a set of blocks
         const int64_t rounds = (tiles + ozk::QUEUE_ROUND_TILES - 1) / ozk::QUEUE_ROUND_TILES;
         const int64_t counter_blocks = (4 * (tiles + rounds + 2 + QUEUE_XCD_WORDS) + BLOCK_BYTES - 1) / BLOCK_BYTES;
         int64_t sets = rounds < QUEUE_SETS ? rounds : QUEUE_SETS;
-        while (sets > 1 && sets * w * stride + counter_blocks > partial_capacity) --sets;
-        if (sets * w * stride + counter_blocks > partial_capacity) return 0;
+        while (sets > 1 && sets * w * stride + counter_blocks > capacity) --sets;
+        if (sets * w * stride + counter_blocks > capacity) return 0;
         return (sets >= 2 || rounds == 1) ? sets : 0;
-    };
-    auto launch_queue = [&](int64_t tiles, int64_t sets) -> int {
-        const int64_t stride = tiles < ozk::QUEUE_ROUND_TILES ? tiles : ozk::QUEUE_ROUND_TILES;
-        const int64_t rounds = (tiles + ozk::QUEUE_ROUND_TILES - 1) / ozk::QUEUE_ROUND_TILES;
-        int32_t* const ctr = partial + sets * w * stride * (BLOCK_BYTES / 4);
-        // counters: one per tile, one per round, the flag; then, 8-byte aligned, the per-XCD ticket batches
-        const int64_t xq_at = (tiles + rounds + 2) & ~(int64_t)1;
-        hipError_t e = ozk::launch_fill_zero_i32(xq_at + QUEUE_XCD_WORDS, ctr, st);
-        if (e != hipSuccess) return OZIMMU_ERR_HIP;
-        ozk::GemmArgs a = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
-        a.tile_count = (int)tiles;
-        a.C = partial;
-        a.zsplit = 1;
-        a.nchunks = (int)w;
-        a.queue_sets = (int)sets;
-        a.queue_stride = (int)stride;
-        const int64_t TM = ozl::rows_padded(m) / ozl::TILE_R, TP = ozl::rows_padded(p) / ozl::TILE_R;
-        a.queue_block_rounds = (tiles == T && TM % 16 == 0 && TP % 16 == 0) ? 1 : 0;
-        a.done = reinterpret_cast<unsigned*>(ctr);
-        // batches of 32 tickets per XCD when every compute unit of the 8-XCD chip this is written for has a workgroup
-        a.xq = (tiles >= num_cu && num_cu == 256) ? reinterpret_cast<unsigned*>(ctr) + xq_at : nullptr;
-        a.D = D;
-        a.ldd = ldd;
-        a.eA = eA;
-        a.eB = eB;
-        a.finish = fin.on ? 1 : 0;
-        a.alpha = fin.alpha;
-        a.cbeta = fin.cbeta;
-        a.Cout = fin.Cout;
-        a.ldco = fin.ldco;
-        a.spin_limit = 0;  // the items of a team are different chunks: nothing to line up
-        a.grid_spin_limit = 0;
-        a.sync_zeroed = take_clean();
-        return hip_status(ozk::launch_gemm(a, 3, st));
     };
     // An output of one round of tiles whose blocks fit goes the chunk-parallel way rather than through the queue: every
     // compute unit gets items from the first moment, and the one accumulation kernel at the end costs less than the
     // queue's ramp (k = 8, chunk-parallel against queue: 2560^3, 100 tiles, 0.53 against 0.58 ms; 3072^3 0.87 against
     // 0.92; 4096^3, 256 tiles, 1.87 against 1.89; 5120^3, 400 tiles, with the queue for the full round only: 3.60
     // against 3.43).
-    const bool one_round_fits = !per_slice && partial && T <= num_cu && T * w <= CHUNK_PARALLEL_MAX_BLOCKS &&
-                                T * w <= partial_capacity;
+    const bool one_round_fits = !per_slice && T <= num_cu && T * w <= CHUNK_PARALLEL_MAX_BLOCKS &&
+                                T * w <= capacity;
     const int64_t sets_all = queue_sets(T);
-    if (schedule == OZIMMU_SCHEDULE_QUEUE && sets_all > 0) return launch_queue(T, sets_all);
+    if (schedule == OZIMMU_SCHEDULE_QUEUE && sets_all > 0) return queue_way(sets_all);
 
     // Chunk-parallel, for outputs of few tiles, or the tiles of a partly filled last round (`cand`, the last ones in band
     // order): ONE launch whose work items are (chunk, inner part, tile), every chunk writing (or, when cut,
@@ -381,7 +289,7 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     int64_t cp_tail = 0;  // tiles that go this way
     int cp_z = 1;
     double cp_us = 0.0;
-    if (!per_slice && partial && cand >= 1 && cand * w <= CHUNK_PARALLEL_MAX_BLOCKS && cand * w <= partial_capacity &&
+    if (!per_slice && cand >= 1 && cand * w <= CHUNK_PARALLEL_MAX_BLOCKS && cand * w <= capacity &&
         schedule != OZIMMU_SCHEDULE_ONE_LAUNCH && schedule != OZIMMU_SCHEDULE_SPLIT_INNER) {
         // (measured on MI355X: a stage 0.58 us; prologue + epilogue of an item 12 us, 19 us when the epilogue adds
         // with atomics; clearing the blocks 5 us + 0.065 us per block; the accumulation kernel 15 us + 0.058 us
@@ -423,7 +331,7 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
     int64_t tail = 0;
     int Z = 1;
     double tail_us = 0.0;
-    if (!per_slice && partial && cp_tail == 0 && !queue_pays && schedule != OZIMMU_SCHEDULE_ONE_LAUNCH &&
+    if (!per_slice && cp_tail == 0 && !queue_pays && schedule != OZIMMU_SCHEDULE_ONE_LAUNCH &&
         schedule != OZIMMU_SCHEDULE_CHUNK_PARALLEL) {
         const int64_t ncu = num_cu;
         const int64_t zmax = KT / 4;  // every part gets at least one group of 4 stages of the shortest chunk
@@ -490,8 +398,8 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
             if (us < 16.0) continue;
             const ozr::Config c = ozr::config_for(k, r_eff, v);
             const int64_t tiles = ((m + 32 * c.ta - 1) / (32 * c.ta)) * ((p + 32 * c.tb - 1) / (32 * c.tb));
-            const int64_t room = partial ? partial_capacity * BLOCK_BYTES : 0, steps = (n + ozl::TILE_K - 1) / ozl::TILE_K;
-            for (int z = 2; ozr::may_cut(v, c) && z <= 64 && tiles * z <= (int64_t)num_cu * c.waves && 2 * z <= steps &&
+            const int64_t room = capacity * BLOCK_BYTES, steps = (n + ozl::TILE_K - 1) / ozl::TILE_K;
+            for (int z = 2; !per_slice && ozr::may_cut(v, c) && z <= 64 && tiles * z <= (int64_t)num_cu * c.waves && 2 * z <= steps &&
                             ozr::sums_bytes(k, r_eff, c, tiles * z) <= room;
                  z += z < 4 ? 1 : z / 2) {
                 const double cut_us = ozr::estimate_us(k, r_eff, v, m, n, p, num_cu, z);
@@ -502,9 +410,142 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
                 }
             }
         }
-        if (variant >= 0) return launch_resident(variant, parts);
+        if (variant >= 0) {
+            way.kind = Way::RESIDENT;
+            way.tile = variant;
+            way.parts = parts;
+            return way;
+        }
     }
-    if (queue_pays) return launch_queue(T, sets_all);
+    if (queue_pays) return queue_way(sets_all);
+    way.cp_tail = cp_tail;
+    way.cp_z = cp_z;
+    way.tail = tail;
+    way.Z = Z;
+    return way;
+}
+
+// Steps (iii) + (iv) (+ (v), see Finish) for the whole schedule of Algorithm 6 (groups g = 2..k+1 ascending, chunks
+// of at most r consecutive s), into D.  Five ways to run it, with bit-identical results (which one: see
+// choose_way):
+//  * resident: one launch, all chunk sums of a tile side by side in registers, D written once -- the default where its
+//    estimate is the lowest (nearly everywhere at 3 to 16 slices and at most 16 chunks); few tiles of a long inner dimension
+//    cut along it, a second launch adding the parts up, where the workspace has room for their sums;
+//  * the queue: one launch whose work items are the (chunk, tile) pairs, an INT32 block per item, the tile's chunks
+//    added up by the workgroup that completes it -- the default for outputs of more tiles than compute units (and
+//    from QUEUE_MIN_TILES tiles on where the chunk-parallel way has no room) when the workspace holds the blocks;
+//  * one persistent launch with the accumulation fused into the GEMM epilogue (mode 1, or 2 for per-slice
+//    scales): one workgroup per compute unit takes tile after tile, all chunks of a tile in turn -- needs no
+//    blocks;
+//  * chunk-parallel, for outputs of few tiles or the last, partly filled round after a persistent launch: one
+//    launch whose work items are (chunk, inner part, tile), a block per chunk and tile, then one accumulation
+//    kernel over those tiles;
+//  * split-inner, for the same tiles when there is room for one block per tile only: per chunk, the chunk GEMM
+//    with its inner range cut into Z parts on Z workgroups per tile, which add their partial sums to zeroed
+//    per-tile INT32 blocks with integer atomics, then the accumulation kernel over those tiles, which also clears
+//    the blocks again.
+// schedule: 0 = choose, or one of the OZIMMU_SCHEDULE_* flags (honoured when possible).  resident_tile >= 0: the resident
+// way with that tile, cut in `parts` (the caller has checked that there is one, and the room for its sums).
+int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t* SB, const int32_t* eA,
+                 const int32_t* eB, int k, int64_t r, bool per_slice, int schedule, double* D, int64_t ldd,
+                 const Finish& fin, int32_t* partial, int64_t partial_capacity, void* scratch, int num_cu, hipStream_t st,
+                 bool sync_clean = false, int resident_tile = -1, int parts = 1)
+{
+    // sync_clean: the caller has already zeroed the soft-barrier counters in `scratch` (the first GEMM launch
+    // then need not; later ones of the same call find them used and do)
+    auto take_clean = [&]() -> int {
+        const int c = sync_clean ? 1 : 0;
+        sync_clean = false;
+        return c;
+    };
+    const int beta = beta_of(n);
+    const int r_eff = (int)(r < k ? r : k);
+    const int KT = (int)(ozl::inner_padded(n) / ozl::TILE_K);
+    const int64_t T = output_tiles(m, p);
+    const int64_t w = chunks_of(k, r_eff);
+
+    auto launch_resident = [&](int variant, int z) -> int {
+        const ozk::GemmArgs g = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
+        ozk::ResidentArgs a{};
+        a.SA = g.SA;
+        a.SB = g.SB;
+        a.PA = g.PA;
+        a.PB = g.PB;
+        a.pstrideA = g.pstrideA;
+        a.pstrideB = g.pstrideB;
+        a.cA = g.cA;
+        a.cB = g.cB;
+        a.strideA = g.strideA;
+        a.strideB = g.strideB;
+        a.KT = KT;
+        a.steps = (int)((n + ozl::TILE_K - 1) / ozl::TILE_K);
+        a.m = m;
+        a.p = p;
+        a.D = D;
+        a.ldd = ldd;
+        a.eA = eA;
+        a.eB = eB;
+        a.beta = beta;
+        a.finish = fin.on ? 1 : 0;
+        a.alpha = fin.alpha;
+        a.cbeta = fin.cbeta;
+        a.Cout = fin.Cout;
+        a.ldco = fin.ldco;
+        a.per_slice = per_slice ? 1 : 0;
+        a.parts = z;
+        a.blocks = partial;
+        double* const out = fin.on ? fin.Cout : D;
+        a.keep = (reinterpret_cast<uintptr_t>(out) % 64 != 0 || (fin.on ? fin.ldco : ldd) % 8 != 0) && ozr::merge_rows(k, n);
+        const hipError_t e = ozk::launch_resident(a, k, r_eff, variant, st);
+        if (e != hipSuccess || z == 1) return hip_status(e);
+        const ozr::Config c = ozr::config_for(k, r_eff, variant);
+        const ozk::AddPartsArgs add = {partial, k,      r_eff,     beta,     z, c.ta, c.tb,
+                                       m,       p,      eA,        eB,       a.finish, fin.alpha, fin.cbeta,
+                                       out,     fin.on ? fin.ldco : ldd};
+        return hip_status(ozk::launch_add_parts(add, st));
+    };
+    if (resident_tile >= 0) return launch_resident(resident_tile, parts);
+
+    const Way way = choose_way(m, n, p, k, r_eff, per_slice, schedule, partial ? partial_capacity : 0, num_cu);
+    if (way.kind == Way::RESIDENT) return launch_resident(way.tile, way.parts);
+
+    auto launch_queue = [&](int64_t tiles, int64_t sets) -> int {
+        const int64_t stride = tiles < ozk::QUEUE_ROUND_TILES ? tiles : ozk::QUEUE_ROUND_TILES;
+        const int64_t rounds = (tiles + ozk::QUEUE_ROUND_TILES - 1) / ozk::QUEUE_ROUND_TILES;
+        int32_t* const ctr = partial + sets * w * stride * (BLOCK_BYTES / 4);
+        // counters: one per tile, one per round, the flag; then, 8-byte aligned, the per-XCD ticket batches
+        const int64_t xq_at = (tiles + rounds + 2) & ~(int64_t)1;
+        hipError_t e = ozk::launch_fill_zero_i32(xq_at + QUEUE_XCD_WORDS, ctr, st);
+        if (e != hipSuccess) return OZIMMU_ERR_HIP;
+        ozk::GemmArgs a = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
+        a.tile_count = (int)tiles;
+        a.C = partial;
+        a.zsplit = 1;
+        a.nchunks = (int)w;
+        a.queue_sets = (int)sets;
+        a.queue_stride = (int)stride;
+        const int64_t TM = ozl::rows_padded(m) / ozl::TILE_R, TP = ozl::rows_padded(p) / ozl::TILE_R;
+        a.queue_block_rounds = (tiles == T && TM % 16 == 0 && TP % 16 == 0) ? 1 : 0;
+        a.done = reinterpret_cast<unsigned*>(ctr);
+        // batches of 32 tickets per XCD when every compute unit of the 8-XCD chip this is written for has a workgroup
+        a.xq = (tiles >= num_cu && num_cu == 256) ? reinterpret_cast<unsigned*>(ctr) + xq_at : nullptr;
+        a.D = D;
+        a.ldd = ldd;
+        a.eA = eA;
+        a.eB = eB;
+        a.finish = fin.on ? 1 : 0;
+        a.alpha = fin.alpha;
+        a.cbeta = fin.cbeta;
+        a.Cout = fin.Cout;
+        a.ldco = fin.ldco;
+        a.spin_limit = 0;  // the items of a team are different chunks: nothing to line up
+        a.grid_spin_limit = 0;
+        a.sync_zeroed = take_clean();
+        return hip_status(ozk::launch_gemm(a, 3, st));
+    };
+    if (way.kind == Way::QUEUE) return launch_queue(T, way.sets);
+    const int64_t tail = way.tail, cp_tail = way.cp_tail;
+    const int Z = way.Z, cp_z = way.cp_z;
 
     if (T - tail - cp_tail > 0) {
         ozk::GemmArgs a = make_args(m, n, p, SA, k, SB, k, 2, k + 1, r_eff, 0, 0, scratch, num_cu);
@@ -610,12 +651,16 @@ inline bool overlap(const double* x, int64_t rows, int64_t cols, int64_t ldx, co
 // One round of its workgroups, two to a compute unit where LDS holds their slices (us a call in a graph, two launches and one, k = 8:
 // 64^3 9.6 and 5.6, 128^3 10.1 and 6.5, 256^3 11.5 and 8.7, 320 x 256 x 320, 400 workgroups, 12.2 and 11.2, 400 x 256 x 400, 625, 12.4 and
 // 16.1; 512 x 64 x 512, 1024, 10.1 and 10.7; k = 14: 256^3 16.3 and 12.2).
+inline bool small_sizes(int64_t m, int64_t n, int64_t p, int k, int64_t r, int num_cu)
+{
+    if (n > ozk::SMALL_MAX_INNER || k < ozk::SMALL_MIN_K || k > ozk::SMALL_MAX_K || r < k) return false;
+    const int64_t room = 2 * (2 * k * ((n + 63) / 64) * 1024 + 2048) <= 160 * 1024 ? 2 : 1;
+    return ((m + 15) / 16) * ((p + 15) / 16) <= room * num_cu;
+}
 inline bool small_way(const ozk::SmallArgs& a, int k, int64_t r, int num_cu)
 {
-    if (a.n > ozk::SMALL_MAX_INNER || k < ozk::SMALL_MIN_K || k > ozk::SMALL_MAX_K || r < k) return false;
     const ozk::SmallArgs::Op &A = a.op[0], &B = a.op[1];
-    const int64_t room = 2 * (2 * k * a.steps * 1024 + 2048) <= 160 * 1024 ? 2 : 1;
-    if (((A.rows + 15) / 16) * ((B.rows + 15) / 16) > room * num_cu) return false;
+    if (!small_sizes(A.rows, a.n, B.rows, k, r, num_cu)) return false;
     // the operands are read while the output is written
     const int64_t size = (A.rows - 1) * a.ldo + B.rows;
     return !overlap(A.X, A.by_col ? a.n : A.rows, A.by_col ? A.rows : a.n, A.ld, a.out, size) &&
@@ -932,6 +977,88 @@ int ozimmu_dgemm_resident(int64_t m, int64_t n, int64_t p, const double* A, int6
                       nullptr, tile);
 }
 
+// blocks behind the slice stacks in a workspace of that many bytes
+static int64_t block_capacity(int64_t m, int64_t n, int64_t p, int k, size_t workspace_bytes)
+{
+    const size_t before = (size_t)(align256(OZIMMU_SCRATCH_BYTES) + align256(4 * m) + align256(4 * p)) +
+                          ozimmu_slices_bytes(m, n, k) + ozimmu_slices_bytes(p, n, k);
+    return workspace_bytes < before ? 0 : (int64_t)((workspace_bytes - before) / BLOCK_BYTES);
+}
+
+int ozimmu_dgemm_tile(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, const double* B, int64_t ldb,
+                      double* D, int64_t ldd, int k, int split_mode, int accumulate_mode, int tile, int parts,
+                      void* workspace, size_t workspace_bytes, void* stream)
+{
+    const bool per_slice = split_mode == OZIMMU_SPLIT_NEAREST_PER_SLICE;
+    if (!per_slice) {
+        if (parts == 1)
+            return ozimmu_dgemm_resident(m, n, p, A, lda, B, ldb, D, ldd, k, split_mode, accumulate_mode, tile, workspace,
+                                         workspace_bytes, stream);
+        if (split_mode != OZIMMU_SPLIT_NEAREST && split_mode != OZIMMU_SPLIT_BITMASK) return OZIMMU_ERR_SLICES;
+        if (accumulate_mode == OZIMMU_ACCUM_WIDE && split_mode != OZIMMU_SPLIT_NEAREST) return OZIMMU_ERR_SLICES;
+    } else if (accumulate_mode != OZIMMU_ACCUM_PER_PAIR || parts != 1) {
+        return OZIMMU_ERR_SLICES;
+    }
+    int rows = 0, cols = 0;
+    const int st = ozimmu_resident_tile(n, k, accumulate_mode, tile, &rows, &cols);
+    if (st != OZIMMU_OK) return st;
+    if (m < 0 || p < 0 || m > MAX_OUTER || p > MAX_OUTER || !ozr::in_range(m, n, p, rows, cols)) return OZIMMU_ERR_DIM;
+    if (per_slice) {
+        if (!ozr::per_slice_tile(k, tile)) return OZIMMU_ERR_SLICES;
+    } else {
+        const int r = (int)(r_of_mode(n, accumulate_mode) < k ? r_of_mode(n, accumulate_mode) : k);
+        const ozr::Config c = ozr::config_for(k, r, tile);
+        const int64_t tiles = ((m + rows - 1) / rows) * ((p + cols - 1) / cols);
+        if (!ozr::may_cut(tile, c) || parts < 1 || parts > 64 || 2 * (int64_t)parts > (n + ozl::TILE_K - 1) / ozl::TILE_K)
+            return OZIMMU_ERR_SLICES;
+        if (tiles * parts > ((int64_t)1 << 18)) return OZIMMU_ERR_DIM;  // (grids of k_cut and k_add_parts)
+        if (ozr::sums_bytes(k, r, c, tiles * parts) > block_capacity(m, n, p, k, workspace_bytes) * BLOCK_BYTES)
+            return OZIMMU_ERR_WORKSPACE;
+    }
+    return dgemm_impl(m, n, p, A, lda, B, ldb, D, ldd, k, split_mode, accumulate_mode, workspace, workspace_bytes, stream,
+                      nullptr, tile, parts);
+}
+
+int ozimmu_choose(int64_t m, int64_t n, int64_t p, int k, int split_mode, int accumulate_mode, size_t workspace_bytes, int num_cu,
+                  ozimmu_choice* out)
+{
+    if (m < 1 || n < 1 || p < 1 || m > MAX_OUTER || p > MAX_OUTER || n > MAX_INNER) return OZIMMU_ERR_DIM;
+    if (k < 1 || k > OZIMMU_MAX_SLICES || num_cu < 1) return OZIMMU_ERR_SLICES;
+    if (split_mode < OZIMMU_SPLIT_NEAREST || split_mode > OZIMMU_SPLIT_NEAREST_PER_SLICE ||
+        accumulate_mode < OZIMMU_ACCUM_GROUPED || accumulate_mode > OZIMMU_ACCUM_WIDE)
+        return OZIMMU_ERR_SLICES;
+    if (!out) return OZIMMU_ERR_NULL;
+    const bool per_slice = split_mode == OZIMMU_SPLIT_NEAREST_PER_SLICE;
+    const int64_t r = r_of_mode(n, accumulate_mode);
+    *out = ozimmu_choice{OZIMMU_WAY_ONE_LAUNCH, -1, 1, OZIMMU_SPLIT_WAY_WHOLE, 0};
+    if (split_mode == OZIMMU_SPLIT_NEAREST && small_sizes(m, n, p, k, r, num_cu)) {
+        out->way = OZIMMU_WAY_SMALL;
+        out->split_way = OZIMMU_SPLIT_WAY_NONE;
+        return OZIMMU_OK;
+    }
+    const int64_t capacity = block_capacity(m, n, p, k, workspace_bytes);
+    if (per_slice) {
+        out->split_way = n <= ozk::PER_SLICE_MAX_INNER ? OZIMMU_SPLIT_WAY_WHOLE : OZIMMU_SPLIT_WAY_PASSES;
+    } else if (short_product(m, n, p, k)) {
+        const ozk::SplitIn ops[2] = {{nullptr, n, m, n, 0, 0, nullptr, nullptr}, {nullptr, p, p, n, 1, 0, nullptr, nullptr}};
+        if (ozk::split_is_cut(ops, 2, k, (size_t)(capacity * BLOCK_BYTES))) out->split_way = OZIMMU_SPLIT_WAY_CUT;
+    }
+    const Way way = choose_way(m, n, p, k, (int)(r < k ? r : k), per_slice, 0, capacity, num_cu);
+    if (way.kind == Way::RESIDENT) {
+        out->way = OZIMMU_WAY_RESIDENT;
+        out->tile = way.tile;
+        out->parts = way.parts;
+        out->merge_rows = ozr::merge_rows(k, n) ? 1 : 0;
+    } else if (way.kind == Way::QUEUE) {
+        out->way = OZIMMU_WAY_QUEUE;
+    } else if (way.cp_tail > 0) {
+        out->way = OZIMMU_WAY_CHUNK_PARALLEL;
+    } else if (way.tail > 0) {
+        out->way = OZIMMU_WAY_SPLIT_INNER;
+    }
+    return OZIMMU_OK;
+}
+
 int ozimmu_split_A_variant(int64_t m, int64_t n, const double* A, int64_t lda, int k, int split_mode, int8_t* SA,
                            int32_t* eA, void* stream)
 {
@@ -988,7 +1115,7 @@ namespace {
 
 int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, const double* B, int64_t ldb,
                double* D, int64_t ldd, int k, int split_mode, int accumulate_mode, void* workspace,
-               size_t workspace_bytes, void* stream, void* const* events, int resident_tile)
+               size_t workspace_bytes, void* stream, void* const* events, int resident_tile, int parts)
 {
     if (m < 0 || n < 0 || p < 0 || m > MAX_OUTER || p > MAX_OUTER || n > MAX_INNER) return OZIMMU_ERR_DIM;
     if (lda < n || ldb < p || ldd < p || lda > MAX_LD || ldb > MAX_LD || ldd > MAX_LD) return OZIMMU_ERR_DIM;
@@ -1065,7 +1192,7 @@ int dgemm_impl(int64_t m, int64_t n, int64_t p, const double* A, int64_t lda, co
         capacity = (int64_t)((static_cast<char*>(workspace) + workspace_bytes - reinterpret_cast<char*>(partial)) /
                              BLOCK_BYTES);
     const int rc = run_schedule(m, n, p, SA, SB, eA, eB, k, r, per_slice, schedule, D, ldd, no_finish, partial,
-                                capacity, scratch, ds.num_cu, st, !per_slice, resident_tile);
+                                capacity, scratch, ds.num_cu, st, !per_slice, resident_tile, parts);
     if (rc != OZIMMU_OK) return rc;
     return hip_status(mark(2));
 }

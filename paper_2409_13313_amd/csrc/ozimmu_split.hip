@@ -1253,6 +1253,12 @@ static bool cut_pays(const SplitIn* ops, int count, int k, double us, size_t roo
     return 11.0 + near / 8e6 + (bytes - near) / 3.8e6 + 1.5 < us;
 }
 
+bool split_is_cut(const SplitIn* ops, int count, int k, size_t room_bytes)
+{
+    int per[2] = {0, 0};
+    return cut_pays(ops, count, k, choose_columns(ops, count, k, per), room_bytes);
+}
+
 hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,
                         int also_zero_count, void* room, size_t room_bytes)
 {

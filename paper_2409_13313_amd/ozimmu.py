@@ -81,6 +81,17 @@ _lib.ozimmu_resident_tile.argtypes = [_i64, _int, _int, _int, ctypes.POINTER(_in
 _lib.ozimmu_resident_tile.restype = _int
 _lib.ozimmu_dgemm_resident.argtypes = [_i64, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _i64, _int, _int, _int, _int, _vp, _sz, _vp]
 _lib.ozimmu_dgemm_resident.restype = _int
+_lib.ozimmu_dgemm_tile.argtypes = [_i64, _i64, _i64, _vp, _i64, _vp, _i64, _vp, _i64, _int, _int, _int, _int, _int, _vp, _sz, _vp]
+_lib.ozimmu_dgemm_tile.restype = _int
+
+
+class Choice(ctypes.Structure):
+    """What the library does with a call by itself (see ozimmu_choose in the header)."""
+    _fields_ = [(name, _int) for name in ("way", "tile", "parts", "split_way", "merge_rows")]
+
+
+_lib.ozimmu_choose.argtypes = [_i64, _i64, _i64, _int, _int, _int, _sz, _int, ctypes.POINTER(Choice)]
+_lib.ozimmu_choose.restype = _int
 _lib.ozimmu_export_slices.argtypes = [_i64, _i64, _int, _vp, _vp, _vp]
 _lib.ozimmu_export_slices.restype = _int
 
@@ -90,12 +101,14 @@ EXPORTS = ["ozimmu_status_string", "ozimmu_params", "ozimmu_num_chunks", "ozimmu
            "ozimmu_accumulate", "ozimmu_gemm_group_accumulate", "ozimmu_export_slices",
            "ozimmu_workspace_bytes_variant", "ozimmu_remainder_bytes", "ozimmu_split_A_per_slice",
            "ozimmu_split_B_per_slice", "ozimmu_init", "ozimmu_dgemm_static", "ozimmu_workspace_bytes_min",
-           "ozimmu_resident_tile", "ozimmu_dgemm_resident"]
+           "ozimmu_resident_tile", "ozimmu_dgemm_resident", "ozimmu_dgemm_tile", "ozimmu_choose"]
 
 
 SPLIT_MODES = {"rn": 0, "bitmask": 1, "per_slice": 2}
 ACCUMULATE_MODES = {"grouped": 0, "per_pair": 1, "wide": 2}
 RESIDENT_TILES = 7
+WAYS = ["small", "resident", "queue", "chunk_parallel", "split_inner", "one_launch"]
+SPLIT_WAYS = ["none", "whole", "cut", "passes"]
 SCHEDULES = {"auto": 0, "one_launch": 0x100, "split_inner": 0x200, "chunk_parallel": 0x400, "queue": 0x800}
 
 
@@ -277,6 +290,35 @@ def dgemm_resident(A: torch.Tensor, B: torch.Tensor, k: int, tile: int, split: s
                                       SPLIT_MODES[split], ACCUMULATE_MODES[accumulate], tile, workspace.data_ptr(),
                                       workspace.numel(), _stream()))
     return D
+
+
+def dgemm_tile(A: torch.Tensor, B: torch.Tensor, k: int, tile: int, parts: int = 1, split: str = "rn",
+               accumulate: str = "grouped", D: Optional[torch.Tensor] = None,
+               workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    """dgemm_resident with the inner dimension of the tiles cut into `parts`, or with one scale per slice (debug / test helper)."""
+    m, n, lda = _matrix(A)
+    n2, p, ldb = _matrix(B)
+    if n != n2:
+        raise ValueError("inner dimensions differ")
+    if D is None:
+        D = A.new_empty((m, p))
+    ldd = _output(D, m, p)
+    if workspace is None:
+        workspace = alloc_workspace(m, n, p, k, A.device, split)
+    _check(_lib.ozimmu_dgemm_tile(m, n, p, A.data_ptr(), lda, B.data_ptr(), ldb, D.data_ptr(), ldd, k, SPLIT_MODES[split],
+                                  ACCUMULATE_MODES[accumulate], tile, parts, workspace.data_ptr(), workspace.numel(), _stream()))
+    return D
+
+
+def choose(m: int, n: int, p: int, k: int, split: str = "rn", accumulate: str = "grouped",
+           workspace_bytes: Optional[int] = None, num_cu: int = 256) -> Choice:
+    """What dgemm_variant does with a call by itself, in alloc_workspace's workspace unless another size is given (host; debug / test
+    helper).  WAYS and SPLIT_WAYS name the values."""
+    if workspace_bytes is None:
+        workspace_bytes = int(_lib.ozimmu_workspace_bytes_variant(m, n, p, k, SPLIT_MODES[split]))
+    out = Choice()
+    _check(_lib.ozimmu_choose(m, n, p, k, SPLIT_MODES[split], ACCUMULATE_MODES[accumulate], workspace_bytes, num_cu, ctypes.byref(out)))
+    return out
 
 
 def gemm_ex(transA: bool, transB: bool, alpha: float, A: torch.Tensor, B: torch.Tensor, beta: float,

@@ -89,6 +89,35 @@ int main()
     EXPECT(ozimmu_dgemm_resident(4, inner_max, 4, fd, inner_max, fd, 4, fd, 4, 8, 0, 1, 0, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
     EXPECT(ozimmu_dgemm_resident(4, 4, 4, fd, 3, fd, 4, fd, 4, 8, 0, 0, 0, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
     EXPECT(ozimmu_dgemm_resident(4, 4, 4, fd, 4, fd, 4, fd, 4, 8, 0, 0, 0, fake, 16, nullptr), OZIMMU_ERR_WORKSPACE);
+    // forced parts: one scale per slice is never cut, parts of less than two steps, tiles that are not cut, room for the sums
+    EXPECT(ozimmu_dgemm_tile(4, 4096, 4, fd, 4096, fd, 4, fd, 4, 8, 2, 1, 0, 2, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_dgemm_tile(4, 4096, 4, fd, 4096, fd, 4, fd, 4, 8, 2, 0, 5, 1, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_dgemm_tile(4, 4096, 4, fd, 4096, fd, 4, fd, 4, 8, 0, 0, 5, 33, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_dgemm_tile(4, 4096, 4, fd, 4096, fd, 4, fd, 4, 8, 0, 0, 5, 0, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_dgemm_tile(4, 4096, 4, fd, 4096, fd, 4, fd, 4, 8, 0, 0, 0, 2, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_dgemm_tile(4, 4096, 4, fd, 4096, fd, 4, fd, 4, 8, 1, OZIMMU_ACCUM_WIDE, 5, 2, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_dgemm_tile(4, 4096, 4, fd, 4096, fd, 4, fd, 4, 8, 0, 0, 5, 2, fake, 16, nullptr), OZIMMU_ERR_WORKSPACE);
+    EXPECT(ozimmu_dgemm_tile(200000, 4096, 400, fd, 4096, fd, 400, fd, 400, 8, 0, 0, 5, 2, fake, 1 << 30, nullptr), OZIMMU_ERR_WORKSPACE);
+    EXPECT(ozimmu_dgemm_tile(top, 4096, 400, fd, 4096, fd, 400, fd, 400, 8, 0, 0, 5, 2, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
+    EXPECT(ozimmu_dgemm_tile(4, 4, 4, fd, 4, fd, 4, fd, 4, 2, 0, 0, 0, 1, fake, 1 << 30, nullptr), OZIMMU_ERR_SLICES);
+    // the choice, over the admissible range
+    ozimmu_choice choice;
+    for (int64_t m : sizes)
+        for (int64_t p : sizes)
+            for (int64_t n : {(int64_t)0, (int64_t)1, (int64_t)300, (int64_t)20000, inner_max})
+                for (int k = 1; k <= OZIMMU_MAX_SLICES; ++k)
+                    for (int mode = 0; mode < 3; ++mode)
+                        for (size_t bytes : {(size_t)0, ozimmu_workspace_bytes_min(m, n, p, k), ozimmu_workspace_bytes(m, n, p, k)}) {
+                            const int accumulate = mode == 2 ? OZIMMU_ACCUM_PER_PAIR : OZIMMU_ACCUM_GROUPED;
+                            const int st = ozimmu_choose(m, n, p, k, mode, accumulate, bytes, 256, &choice);
+                            EXPECT(st, m && n && p ? OZIMMU_OK : OZIMMU_ERR_DIM);
+                            if (st != OZIMMU_OK) continue;
+                            EXPECT(choice.way == OZIMMU_WAY_RESIDENT ? choice.tile >= 0 && choice.parts >= 1 : choice.tile == -1, 1);
+                            EXPECT(choice.parts > 1 && (mode == 2 || 2 * choice.parts > (n + 63) / 64), 0);
+                        }
+    EXPECT(ozimmu_choose(4, 4, 4, 8, 0, 0, 0, 256, nullptr), OZIMMU_ERR_NULL);
+    EXPECT(ozimmu_choose(4, 4, 4, 8, 3, 0, 0, 256, &choice), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_choose(4, 4, 4, 8, 0, 0, 0, 0, &choice), OZIMMU_ERR_SLICES);
     EXPECT(ozimmu_gemm_ex(0, 0, 4, 4, 4, 1.0, fd, 3, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
     EXPECT(ozimmu_gemm_ex(1, 0, 5, 4, 4, 1.0, fd, 4, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
     EXPECT(ozimmu_gemm_ex(0, 1, 4, 5, 4, 1.0, fd, 5, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
