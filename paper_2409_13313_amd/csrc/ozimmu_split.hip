@@ -796,14 +796,16 @@ __global__ __launch_bounds__(256) void k_split_A_ps(int64_t m, int64_t n, const 
 }
 
 // ---------------------------------------------------------------------------
-// Algorithm 5, vectors that stay in the registers of a workgroup of 8 waves: both operands in one launch, read once.
+// Algorithm 5, vectors that stay in the registers of a workgroup: both operands in one launch, read once.
 //
-// A workgroup has one row, or 4 columns, 16 U elements a thread (up to 2048 U inner positions); the remainders stay where they
-// are from slice to slice, only their maximum goes through LDS.  Bound by HBM for large operands (8 + k bytes an element; the
-// kernels above and below move 16 k), by k barriers for small ones.  Whole calls, k + 4 launches and this one: 176 x 38 x 702, k = 9 74 and
-// 24 us, 2006 x 768 x 615, k = 8 168 and 113, 3892^3, k = 12 4.4 and 3.7 ms.  (U = 4 spills 39 registers: 5376^3, k = 8, 6.3 ms either way.)
+// A workgroup of THREADS has V vectors, rows or columns, 16 U elements a thread: 16 U THREADS / V inner positions.  The remainders
+// stay where they are from slice to slice; only their maximum travels, between lanes and, where a vector is on several waves,
+// through LDS.  V by the length (see launch_split_per_slice): elements past the end cost as much as real ones, so short vectors share a
+// workgroup (a wave skips a quad or chunk that lies past the padding).  Bound by HBM for large operands (8 + k bytes an element; the
+// kernels above and below move 16 k), by k reductions for small ones.
+// Whole calls, us, k + 4 launches; one launch with a row to each workgroup of 512 threads whatever its length; and this: 176 x 38 x 702,
+// k = 9, 74, 23.1, 15.3; 2006 x 768 x 615, k = 8, 168, 109, 72; 3892^3, k = 12, 4400, 3690, 3470; 100000 x 50 x 10, k = 6, 1215, 1682, 72.
 // ---------------------------------------------------------------------------
-constexpr int PS_COLS = 4;
 struct PsOp {
     const double* X;
     int64_t ld, rows, n;
@@ -814,66 +816,110 @@ struct PsOp {
     int KT, by_col, blocks;
 };
 
-template <int U>
-__global__ __launch_bounds__(512) void k_split_ps(PsOp a, PsOp b, int k, int beta)
+// BY_COL: vector t % V, a thread has U chunks of 16 consecutive positions; else vector t / (threads of a vector), U times 4 quads,
+// neighbouring threads beside each other.
+template <int THREADS, int U, int V, bool BY_COL>
+__device__ inline void split_ps(const PsOp& o, int block, int k, int beta, double (*red)[THREADS / 64][64])
 {
-    __shared__ double red[2][8][PS_COLS];
+    constexpr int TPV = THREADS / V;                       // threads of a vector
+    constexpr int LANES = BY_COL ? 64 / (V < 64 ? V : 64) : TPV < 64 ? TPV : 64;   // of a vector in a wave
+    constexpr int WAVES = BY_COL ? THREADS / 64 : TPV / LANES;                     // that a vector is on
+    constexpr int FIRST = BY_COL ? V : 1;                  // distance of a vector's lanes
+    constexpr int GROUP = BY_COL ? 4 : 2;
+    static_assert(V <= 64 && TPV * V == THREADS, "");
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int v = BY_COL ? t % V : t / TPV, tv = BY_COL ? t / V : t % TPV;
+    const int64_t R = (int64_t)block * V + v;
+    const bool ok = R < o.rows;
+    const int64_t at = ok ? R : o.rows - 1;                // (vectors past the edge read along, their results are not stored)
+    const int n = (int)o.n, end = o.KT * TILE_K;
+    // position of quad q (4 consecutive elements)
+    auto place = [&](int q) -> int { return BY_COL ? (q / 4) * (TPV * 16) + tv * 16 + (q % 4) * 4 : q * (TPV * 4) + tv * 4; };
+    double y[4 * U][4], mx = 0.0;
+    if constexpr (BY_COL) {
+        const global_f64 x = (global_f64)o.X + at;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            global_f64 p = x + (int64_t)place(4 * u) * o.ld;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                y[4 * u + i / 4][i % 4] = 0.0;
+                if (place(4 * u) + i < n) y[4 * u + i / 4][i % 4] = *p;
+                p += o.ld;
+                asm volatile("" : "+v"(p));                // (one running pointer: see split_cols)
+            }
+        }
+    } else {
+        const global_f64 x = (global_f64)o.X + at * o.ld;
+#pragma unroll
+        for (int q = 0; q < 4 * U; ++q) {
+            const int l = place(q), l0 = q * (TPV * 4) + (WAVES > 1 ? w % WAVES * 256 : 0);  // (the wave's first: uniform)
+            if (l0 + 4 * LANES <= n) {
+                const f64x2_a8 a = *(global_f64x2)(x + l), b = *(global_f64x2)(x + l + 2);
+                y[q][0] = a.x, y[q][1] = a.y, y[q][2] = b.x, y[q][3] = b.y;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    y[q][j] = 0.0;
+                    if (l + j < n) y[q][j] = x[l + j];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4 * U; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mx = fmax(mx, fabs(y[q][j]));
+    for (int s = 0; s < k; ++s) {
+#pragma unroll
+        for (int off = FIRST; off < FIRST * LANES; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+        if constexpr (WAVES > 1) {
+            // (two places for the maxima in turn: one barrier a slice)
+            constexpr int SLOTS = BY_COL ? V : 1;
+            if (lane < SLOTS) red[s & 1][w][lane] = mx;
+            __syncthreads();
+            const int w0 = BY_COL ? 0 : w / WAVES * WAVES;
+#pragma unroll
+            for (int z = 0; z < WAVES; ++z) mx = fmax(mx, red[s & 1][w0 + z][BY_COL ? v : 0]);
+        }
+        const int e = exponent_of<false>(mx), sc = beta - 1 - e;
+        if (ok && tv == 0) o.e[(int64_t)s * o.rows + R] = e;
+        mx = 0.0;
+        int8_t* out = o.S + s * o.slice_stride;
+        // (under one condition GROUP quads: each by itself they would wait for each other's latencies)
+#pragma unroll
+        for (int q0 = 0; q0 < 4 * U; q0 += GROUP) {
+            uint32_t word[GROUP] = {};
+            if (place(q0) < n) {
+#pragma unroll
+                for (int g = 0; g < GROUP; ++g)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const double ys = ldexp(y[q0 + g][j], sc), d = __builtin_rint(ys);
+                        word[g] |= ((uint32_t)(int)d & 0xffu) << (8 * j);
+                        y[q0 + g][j] = ldexp(ys - d, -sc);
+                        mx = fmax(mx, fabs(y[q0 + g][j]));
+                    }
+            }
+#pragma unroll
+            for (int g = 0; g < GROUP; ++g)
+                if (ok && place(q0 + g) < end) *reinterpret_cast<uint32_t*>(out + packed_offset(R, place(q0 + g), o.KT)) = word[g];
+        }
+    }
+}
+
+template <int THREADS, int U, int V>
+__global__ __launch_bounds__(THREADS) void k_split_ps(PsOp a, PsOp b, int k, int beta)
+{
+    __shared__ double red[2][THREADS / 64][64];
     const bool second = (int)blockIdx.x >= a.blocks;
     const PsOp o = second ? b : a;
     const int block = second ? (int)blockIdx.x - a.blocks : (int)blockIdx.x;
-    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
-    if (block == 0 && t == 0) o.trailer[0] = 0;  // slices with a scale each are stored without offset
-    const int v = o.by_col ? lane % PS_COLS : 0;
-    const int64_t R = (int64_t)block * (o.by_col ? PS_COLS : 1) + v;
-    const bool ok = R < o.rows;
-    const int64_t at = ok ? R : o.rows - 1, end = (int64_t)o.KT * TILE_K;
-    const global_f64 x = (global_f64)o.X + (o.by_col ? at : at * o.ld);
-    const int64_t pitch = o.by_col ? o.ld : 1;
-    // positions of quad q (4 consecutive ones)
-    auto place = [&](int q) -> int64_t {
-        if (o.by_col) return (int64_t)(q / 4) * 2048 + w * 256 + (lane / PS_COLS) * 16 + (q % 4) * 4;
-        return (int64_t)q * 2048 + w * 256 + lane * 4;
-    };
-    double y[4 * U][4], mx = 0.0;
-#pragma unroll
-    for (int q = 0; q < 4 * U; ++q) {
-        const int64_t l = place(q);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            y[q][j] = 0.0;
-            if (l + j < o.n) y[q][j] = x[(l + j) * pitch];
-            mx = fmax(mx, fabs(y[q][j]));
-        }
-    }
-    for (int s = 0; s < k; ++s) {
-        // (two places for the maxima in turn: one barrier a slice)
-        if (!o.by_col) {
-            mx = fmax(mx, __shfl_xor(mx, 1, 64));
-            mx = fmax(mx, __shfl_xor(mx, 2, 64));
-        }
-#pragma unroll
-        for (int off = PS_COLS; off < 64; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
-        if (lane < PS_COLS) red[s & 1][w][lane] = mx;
-        __syncthreads();
-        for (int z = 0; z < 8; ++z) mx = fmax(mx, red[s & 1][z][v]);
-        const int e = exponent_of<false>(mx), sc = beta - 1 - e;
-        if (ok && w == 0 && (o.by_col ? lane < PS_COLS : lane == 0)) o.e[(int64_t)s * o.rows + R] = e;
-        mx = 0.0;
-        int8_t* out = o.S + s * o.slice_stride;
-#pragma unroll
-        for (int q = 0; q < 4 * U; ++q) {
-            uint32_t word = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double ys = ldexp(y[q][j], sc), d = __builtin_rint(ys);
-                word |= ((uint32_t)(int)d & 0xffu) << (8 * j);
-                y[q][j] = ldexp(ys - d, -sc);
-                mx = fmax(mx, fabs(y[q][j]));
-            }
-            const int64_t l = place(q);
-            if (ok && l < end) *reinterpret_cast<uint32_t*>(out + packed_offset(R, l, o.KT)) = word;
-        }
-    }
+    if (block == 0 && threadIdx.x == 0) o.trailer[0] = 0;  // slices with a scale each are stored without offset
+    if (o.by_col)
+        split_ps<THREADS, U, V, true>(o, block, k, beta, red);
+    else
+        split_ps<THREADS, U, V, false>(o, block, k, beta, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -1379,7 +1425,8 @@ hipError_t launch_split_A_per_slice(int64_t m, int64_t n, const double* A, int64
     return hipGetLastError();
 }
 
-hipError_t launch_split_per_slice(const SplitIn* ops, int k, int beta, hipStream_t st)
+template <int THREADS, int U, int V>
+static hipError_t launch_split_ps(const SplitIn* ops, int k, int beta, hipStream_t st)
 {
     PsOp op[2]{};
     for (int q = 0; q < 2; ++q) {
@@ -1394,16 +1441,25 @@ hipError_t launch_split_per_slice(const SplitIn* ops, int k, int beta, hipStream
         op[q].slice_stride = ozl::slice_bytes(i.rows, i.n);
         op[q].KT = (int)(ozl::inner_padded(i.n) / ozl::TILE_K);
         op[q].by_col = i.by_col;
-        op[q].blocks = (int)(i.by_col ? (i.rows + PS_COLS - 1) / PS_COLS : i.rows);
+        op[q].blocks = (int)((i.rows + V - 1) / V);
     }
-    const dim3 grid((unsigned)(op[0].blocks + op[1].blocks)), block(512);
-    if (op[0].n <= 2048)
-        hipLaunchKernelGGL(k_split_ps<1>, grid, block, 0, st, op[0], op[1], k, beta);
-    else if (op[0].n <= 4096)
-        hipLaunchKernelGGL(k_split_ps<2>, grid, block, 0, st, op[0], op[1], k, beta);
-    else
-        hipLaunchKernelGGL(k_split_ps<4>, grid, block, 0, st, op[0], op[1], k, beta);
+    hipLaunchKernelGGL((k_split_ps<THREADS, U, V>), dim3((unsigned)(op[0].blocks + op[1].blocks)), dim3(THREADS), 0, st, op[0], op[1],
+                       k, beta);
     return hipGetLastError();
+}
+hipError_t launch_split_per_slice(const SplitIn* ops, int k, int beta, hipStream_t st)
+{
+    // As many vectors to a workgroup as the padding of the slices (to 256 positions, stored too) allows; from 2048 positions on that
+    // would be 32 elements a thread, which few vectors, a compute unit to each workgroup, have to wait for: 30 x 4008 x 10,
+    // k = 10, 57.5 us, with two vectors to a workgroup 52.2; 200 x 3000 x 200, k = 8, 40.3 and 39.4.  (Two columns are 16 bytes of a
+    // memory line at a time: 30 x 4000 x 300, k = 5, 37.3 and 39.7.)
+    const int64_t n = ozl::inner_padded(ops[0].n);
+    if (n <= 256) return launch_split_ps<256, 1, 16>(ops, k, beta, st);
+    if (n <= 512) return launch_split_ps<512, 1, 16>(ops, k, beta, st);
+    if (n <= 2048) return launch_split_ps<512, 1, 4>(ops, k, beta, st);
+    if (n <= 4096 && ops[0].rows <= 256 && ops[1].rows <= 256) return launch_split_ps<512, 1, 2>(ops, k, beta, st);
+    if (n <= 4096) return launch_split_ps<512, 2, 4>(ops, k, beta, st);
+    return launch_split_ps<1024, 2, 4>(ops, k, beta, st);
 }
 
 hipError_t launch_split_B_per_slice(int64_t n, int64_t p, const double* B, int64_t ldb, int k, int beta, int8_t* SB,

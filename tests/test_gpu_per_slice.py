@@ -103,8 +103,11 @@ def test_mode_errors_and_workspace_size(oz):
         oz.dgemm_variant(dev(A), dev(B), 8, "per_slice", "per_pair", workspace=small)
 
 
-# operands that stay in a workgroup's registers: edges of the 2048, 4096 and 8192 inner positions, of 4 columns and of the inner tiles
-@pytest.mark.parametrize("m,n,p,k", [(1, 1, 1, 3), (3, 63, 5, 8), (9, 2047, 4, 7), (6, 2048, 7, 13), (5, 2049, 9, 14), (4, 4096, 5, 6), (5, 4097, 3, 6), (2, 8191, 3, 5),
+# operands that stay in a workgroup's registers: edges of the 256, 512, 2048, 4096 and 8192 inner positions, of 16, 4 and 2 vectors to a
+# workgroup and of the inner tiles
+@pytest.mark.parametrize("m,n,p,k", [(17, 256, 33, 4), (16, 257, 15, 14), (33, 512, 16, 5), (15, 513, 31, 15), (2, 2304, 257, 3),
+                                     (257, 3000, 5, 4), (1, 2049, 1, 16), (3, 4095, 256, 3), (4099, 3, 2, 14), (5, 70, 5003, 3),
+                                     (1, 1, 1, 3), (3, 63, 5, 8), (9, 2047, 4, 7), (6, 2048, 7, 13), (5, 2049, 9, 14), (4, 4096, 5, 6), (5, 4097, 3, 6), (2, 8191, 3, 5),
                                      (3, 8192, 2, 9), (2, 8193, 5, 4), (130, 257, 70, 16)])
 def test_split_in_one_launch(oz, m, n, p, k):
     A, B = inputs.phi_pair(m, n, p, 4.0, seed=75)
