@@ -72,8 +72,7 @@ constexpr Config config_for(int k, int r, int variant)
     if (k < MIN_K || k > MAX_K || (r < k && r != 8 && r != 4 && r != 2 && r != 1)) return Config{0, 0, 1, 1};
     return config(k, r < k ? r : k, variant);
 }
-// Tiles for slices with one scale each (r = 1): k_extended only where there is no other (with a third way to add its sums up the
-// compiler reads some of them before the wait states behind the loop).
+// Tiles for slices with one scale each (r = 1; k_per_slice): k_extended's only where there is no other.
 constexpr bool per_slice_tile(int k, int variant) { return variant != EXTENDED || config(k, 1, 0).ta == 0; }
 // grid size; 32-bit operand offsets
 constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)

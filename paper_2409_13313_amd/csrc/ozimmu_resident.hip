@@ -204,10 +204,16 @@ struct Plan {
     }
 };
 
-// A workgroup's tile.  IN_PLACE: k_extended (see the head).  CUT: k_cut, a part of a tile's inner dimension.
-template <class P, bool IN_PLACE, bool CUT>
+// What becomes of a tile's sums: added up into D with one exponent per row and column, or (r = 1) per row, column and slice; or left in
+// memory as the sums of a part of the inner dimension.  Kernels of their own, each with one of them: an end that a call does not take
+// costs it all the same (the second in the kernels of the first: 3 to 5 % of whole calls of short inner dimensions, 140388 x 4 x 8,
+// k = 9, one addition per pair, 215.5 and 224 us; the third: spilled chunk sums).
+enum class End { COMMON, PER_SLICE, PART };
+// A workgroup's tile.  IN_PLACE: k_extended (see the head).
+template <class P, bool IN_PLACE, End END>
 __device__ __attribute__((always_inline)) inline void run_tile(const ozk::ResidentArgs& a)
 {
+    constexpr bool CUT = END == End::PART, PER_SLICE = END == End::PER_SLICE;
     static constexpr P plan{};
     constexpr int K = P::k, R = P::r, TA = P::ta, TB = P::tb, D = P::depth;
     constexpr int L = P::L, W = P::W, NF = P::NF, NI = P::NI;
@@ -519,18 +525,17 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     }
     // One scale per slice (Algorithm 5; a chunk is then one pair): the exponents of all slices of the tile's rows, then columns,
     // take the place of the operands.
-    constexpr bool PER_SLICE = R == 1 && ozr::per_slice_tile(K, IN_PLACE ? ozr::EXTENDED : 0);
     int* const slice_exp = reinterpret_cast<int*>(lds);
-    if constexpr (PER_SLICE)
-        if (a.per_slice) {
-            __syncthreads();
-            for (int x = t; x < K * (RA + RB); x += 256) {
-                const int s = x / (RA + RB), y = x - s * (RA + RB);
-                const int64_t at = y < RA ? (int64_t)row0 + y : (int64_t)col0 + (y - RA), end = y < RA ? a.m : a.p;
-                slice_exp[x] = at < end ? (y < RA ? a.eA : a.eB)[s * end + at] : 0;
-            }
-            __syncthreads();
+    if constexpr (PER_SLICE) {
+        static_assert(R == 1, "");
+        __syncthreads();
+        for (int x = t; x < K * (RA + RB); x += 256) {
+            const int s = x / (RA + RB), y = x - s * (RA + RB);
+            const int64_t at = y < RA ? (int64_t)row0 + y : (int64_t)col0 + (y - RA), end = y < RA ? a.m : a.p;
+            slice_exp[x] = at < end ? (y < RA ? a.eA : a.eB)[s * end + at] : 0;
         }
+        __syncthreads();
+    }
 
     // Steps (iv) and (v): per element the chunk sums in schedule order, one rounded addition each.  Register r of tile
     // (i, j) in lane l: row 4 (l / 16) + r, column l % 16.
@@ -564,7 +569,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     const bool scaled = __ballot(plain_range) == ~0ull;
     // Four 16 x 16 tiles at a time: sixteen independent chains of additions per lane keep the FP64 unit busy.
     // KEEP: stores that stay in L2 until its lines are whole (see ozr::merge_rows) instead of streaming past it.
-    auto finish_tile = [&](auto SCALED, auto KEEP, auto PER_SLICE) __attribute__((always_inline)) {
+    auto finish_tile = [&](auto SCALED, auto KEEP) __attribute__((always_inline)) {
         constexpr int TT = TA * TB, BATCH = TT < 4 ? TT : 4;
         const double step = ldexp(1.0, -a.beta);
         static_for<(TT + BATCH - 1) / BATCH>([&](auto Q) __attribute__((always_inline)) {
@@ -594,7 +599,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
                         const double v = (double)acc[c][i][j][r];
                         if constexpr (decltype(SCALED)::value) {
                             d[x][r] = c == 0 ? v : __builtin_fma(v, scale, d[x][r]);
-                        } else if constexpr (decltype(PER_SLICE)::value) {
+                        } else if constexpr (PER_SLICE) {
                             const int es = slice_exp[(s - 1) * (RA + RB) + wm * (16 * TA) + 16 * i + 4 * lq + r];
                             const int et = slice_exp[(g - s - 1) * (RA + RB) + RA + wn * (16 * TB) + 16 * j + lc];
                             const double term = ldexp(v, es + et + 2 - 2 * a.beta);
@@ -633,36 +638,38 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     constexpr std::false_type no{};
     constexpr std::true_type yes{};
     if constexpr (PER_SLICE)
-        if (a.per_slice) {
-            finish_tile(no, yes, yes);
-            return;
-        }
-    if (!scaled)
-        finish_tile(no, no, no);
+        finish_tile(no, yes);
+    else if (!scaled)
+        finish_tile(no, no);
     else if (a.keep)
-        finish_tile(yes, yes, no);
+        finish_tile(yes, yes);
     else
-        finish_tile(yes, no, no);
+        finish_tile(yes, no);
 }
 
 template <int K, int R, int TA, int TB, int D, int WAVES>
 __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, R, TA, TB, D>, false, false>(a);
+    run_tile<Plan<K, R, TA, TB, D>, false, End::COMMON>(a);
 }
 // Few tiles of a long inner dimension would leave most of the chip idle: each is cut among a.parts workgroups, whose INT32 sums
-// k_add_parts (ozimmu_gemm.hip) adds up.  A kernel of its own: with both ends in one the compiler spills chunk sums.  What bounds it
-// is the latency of a step and of the sums' way (whole calls, k = 8: 47 x 11948 x 48 119 -> 62 us, 43 of it the split; 256 x 8192 x 256
+// k_add_parts (ozimmu_gemm.hip) adds up.  What bounds it is the latency of a step and of the sums' way (whole calls, k = 8: 47 x 11948 x 48 119 -> 62 us, 43 of it the split; 256 x 8192 x 256
 // 83 -> 63; 67 x 25614 x 69, k = 4, 148 -> 96).
 template <int K, int R, int TA, int TB, int D, int WAVES>
 __global__ __launch_bounds__(256, WAVES) void k_cut(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, R, TA, TB, D>, false, true>(a);
+    run_tile<Plan<K, R, TA, TB, D>, false, End::PART>(a);
 }
 template <int K, int R, int TA, int TB, int D>
 __global__ __launch_bounds__(256, 1) void k_extended(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, R, TA, TB, D>, true, false>(a);
+    run_tile<Plan<K, R, TA, TB, D>, true, End::COMMON>(a);
+}
+// One scale per slice: k_resident or k_extended with the exponents of every slice.
+template <int K, int TA, int TB, int D, int WAVES, bool IN_PLACE>
+__global__ __launch_bounds__(256, WAVES) void k_per_slice(ozk::ResidentArgs a)
+{
+    run_tile<Plan<K, 1, TA, TB, D>, IN_PLACE, End::PER_SLICE>(a);
 }
 
 template <int K, int R, int V>
@@ -679,22 +686,25 @@ hipError_t launch(const ozk::ResidentArgs& a_in, hipStream_t st)
         const unsigned tiles = (unsigned)a.TM * (unsigned)a.TP;
         constexpr int smem = ozr::lds_bytes(K, c);
         static_assert(smem <= 160 * 1024, "LDS of a compute unit");
-        const void* kernel;
+        // [0]: whole tiles, one exponent per row and column; then, where there is one, the kernel for a scale per slice, for parts
+        const void* kernels[3] = {};
         if constexpr (V == ozr::EXTENDED)
-            kernel = reinterpret_cast<const void*>(&k_extended<K, R, c.ta, c.tb, c.depth>);
+            kernels[0] = reinterpret_cast<const void*>(&k_extended<K, R, c.ta, c.tb, c.depth>);
         else
-            kernel = reinterpret_cast<const void*>(&k_resident<K, R, c.ta, c.tb, c.depth, c.waves>);
-        if constexpr (ozr::may_cut(V, c)) {
-            const void* cut = reinterpret_cast<const void*>(&k_cut<K, R, c.ta, c.tb, c.depth, c.waves>);
-            if (a.setup) {
-                const hipError_t e = hipFuncSetAttribute(cut, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+            kernels[0] = reinterpret_cast<const void*>(&k_resident<K, R, c.ta, c.tb, c.depth, c.waves>);
+        if constexpr (R == 1 && ozr::per_slice_tile(K, V))
+            kernels[1] = reinterpret_cast<const void*>(&k_per_slice<K, c.ta, c.tb, c.depth, c.waves, V == ozr::EXTENDED>);
+        if constexpr (ozr::may_cut(V, c))
+            kernels[2] = reinterpret_cast<const void*>(&k_cut<K, R, c.ta, c.tb, c.depth, c.waves>);
+        if (a.setup) {
+            for (const void* kernel : kernels) {
+                const hipError_t e = kernel ? hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem) : hipSuccess;
                 if (e != hipSuccess) return e;
             }
-            if (a.parts > 1) kernel = cut;
-        } else if (a.parts > 1) {
-            return hipErrorInvalidValue;
+            return hipSuccess;
         }
-        if (a.setup) return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        const void* const kernel = kernels[a.parts > 1 ? 2 : a.per_slice ? 1 : 0];
+        if (!kernel || (a.parts > 1 && a.per_slice)) return hipErrorInvalidValue;
         void* args[] = {&a};
         return hipLaunchKernel(kernel, dim3(a.parts > 1 ? tiles * (unsigned)a.parts : tiles), dim3(256), args, smem, st);
     }

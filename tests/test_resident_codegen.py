@@ -53,6 +53,11 @@ def test_every_instance(tmp_path):
                     assert by_hand or "vmcnt" not in code, (what, line)
                     assert not re.search(r"v_accvgpr|scratch_|buffer_", code), (what, line)
             assert m0 >= k, what
+            # one exponent per row and column is all that this kernel adds its sums up with: term by term (an ldexp for every
+            # sum), or scaled (one for every element of a tile).  A third way, whoever takes it, costs every call
+            w = sum((g - 1 + r - 1) // r for g in range(2, k + 2))
+            ldexps = sum("v_ldexp_f64" in line for line in lines)
+            assert ldexps <= 4 * ta * tb * (w + 2) + 8, (what, ldexps)
             at = text.index(".name:           " + name)
             about = text[text.rindex("- .agpr_count", 0, at):text.find("- .agpr_count", at)]
             for key in ("private_segment_fixed_size", "vgpr_spill_count", "sgpr_spill_count"):
