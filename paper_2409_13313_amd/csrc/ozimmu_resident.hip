@@ -210,7 +210,7 @@ struct Plan {
 // k = 9, one addition per pair, 215.5 and 224 us; the third: spilled chunk sums).
 enum class End { COMMON, PER_SLICE, PART };
 // A workgroup's tile.  IN_PLACE: k_extended (see the head).
-template <class P, bool IN_PLACE, End END>
+template <class P, int WAVES, bool IN_PLACE, End END>
 __device__ __attribute__((always_inline)) inline void run_tile(const ozk::ResidentArgs& a)
 {
     constexpr bool CUT = END == End::PART, PER_SLICE = END == End::PER_SLICE;
@@ -568,8 +568,12 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     const bool plain_range = emin + 2 - a.beta * (K + 1) >= -1022 && emax + 2 - 2 * a.beta + 40 <= 1023;
     const bool scaled = __ballot(plain_range) == ~0ull;
     // Four 16 x 16 tiles at a time: sixteen independent chains of additions per lane keep the FP64 unit busy.
-    // KEEP: stores that stay in L2 until its lines are whole (see ozr::merge_rows) instead of streaming past it.
-    auto finish_tile = [&](auto SCALED, auto KEEP) __attribute__((always_inline)) {
+    // Stores stay in L2 until its lines are whole (see ozr::merge_rows) or stream past it.  Where the registers allow it, that is asked around
+    // every four stores: two whole ends, one for each, are 2 to 10 % of calls of short inner dimensions (554 x 5 x 20266, k = 10,
+    // 96.0 and 94.9 us; 2947 x 1 x 756, k = 12, one addition per pair, 76.3 and 73.0).  Elsewhere it spills sums, and asked around
+    // every store it costs more than it saves (4096 x 256 x 4096, k = 9, per pair, 329 and 344 us).
+    enum { STREAMED, KEPT, ASK };
+    auto finish_tile = [&](auto SCALED, auto STORE) __attribute__((always_inline)) {
         constexpr int TT = TA * TB, BATCH = TT < 4 ? TT : 4;
         const double step = ldexp(1.0, -a.beta);
         static_for<(TT + BATCH - 1) / BATCH>([&](auto Q) __attribute__((always_inline)) {
@@ -616,41 +620,69 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
                 const int i = (first + x) % TA, j = (first + x) / TA;
                 const int64_t col = (int64_t)col0 + wn * (16 * TB) + 16 * j + lc;
                 const int64_t row = (int64_t)row0 + wm * (16 * TA) + 16 * i + 4 * lq;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
+                auto finish = [&](int r) __attribute__((always_inline)) {
                     if constexpr (decltype(SCALED)::value) d[x][r] = ldexp(d[x][r], ea[i][r] + eb[j] + 2 - 2 * a.beta);
                     if (a.finish) {
                         d[x][r] = a.alpha * d[x][r];
                         if (with_c) d[x][r] = d[x][r] + a.cbeta * cold[x][r];
                     }
-                    if (col < a.p && row + r < a.m) {
-                        double* const out = obase + (row + r) * opitch + col;
-                        if constexpr (decltype(KEEP)::value)
-                            *out = d[x][r];
-                        else
-                            __builtin_nontemporal_store(d[x][r], out);
+                };
+                if constexpr (decltype(STORE)::value == ASK) {
+                    auto store = [&](auto KEEP) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (col < a.p && row + r < a.m) {
+                                double* const out = obase + (row + r) * opitch + col;
+                                if constexpr (decltype(KEEP)::value)
+                                    *out = d[x][r];
+                                else
+                                    __builtin_nontemporal_store(d[x][r], out);
+                            }
+                    };
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) finish(r);
+                    // (the comments in asm keep the compiler from making one ordinary store of two)
+                    if (a.keep) {
+                        store(std::true_type{});
+                    } else {
+                        asm volatile("; streamed");
+                        store(std::false_type{});
+                        asm volatile("; streamed");
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        finish(r);
+                        if (col < a.p && row + r < a.m) {
+                            double* const out = obase + (row + r) * opitch + col;
+                            if constexpr (decltype(STORE)::value == KEPT)
+                                *out = d[x][r];
+                            else
+                                __builtin_nontemporal_store(d[x][r], out);
+                        }
                     }
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    constexpr std::false_type no{};
-    constexpr std::true_type yes{};
+    constexpr bool ROOM = W * TA * TB < (WAVES == 1 ? 60 : 32);
+    constexpr std::integral_constant<int, ROOM ? ASK : STREAMED> asked{};
+    constexpr std::integral_constant<int, ROOM ? ASK : KEPT> kept{};
     if constexpr (PER_SLICE)
-        finish_tile(no, yes);
+        finish_tile(std::false_type{}, kept);
     else if (!scaled)
-        finish_tile(no, no);
-    else if (a.keep)
-        finish_tile(yes, yes);
-    else
-        finish_tile(yes, no);
+        finish_tile(std::false_type{}, asked);
+    else if (ROOM || !a.keep)
+        finish_tile(std::true_type{}, asked);
+    else if constexpr (!ROOM)
+        finish_tile(std::true_type{}, kept);
 }
 
 template <int K, int R, int TA, int TB, int D, int WAVES>
 __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, R, TA, TB, D>, false, End::COMMON>(a);
+    run_tile<Plan<K, R, TA, TB, D>, WAVES, false, End::COMMON>(a);
 }
 // Few tiles of a long inner dimension would leave most of the chip idle: each is cut among a.parts workgroups, whose INT32 sums
 // k_add_parts (ozimmu_gemm.hip) adds up.  What bounds it is the latency of a step and of the sums' way (whole calls, k = 8: 47 x 11948 x 48 119 -> 62 us, 43 of it the split; 256 x 8192 x 256
@@ -658,18 +690,18 @@ __global__ __launch_bounds__(256, WAVES) void k_resident(ozk::ResidentArgs a)
 template <int K, int R, int TA, int TB, int D, int WAVES>
 __global__ __launch_bounds__(256, WAVES) void k_cut(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, R, TA, TB, D>, false, End::PART>(a);
+    run_tile<Plan<K, R, TA, TB, D>, WAVES, false, End::PART>(a);
 }
 template <int K, int R, int TA, int TB, int D>
 __global__ __launch_bounds__(256, 1) void k_extended(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, R, TA, TB, D>, true, End::COMMON>(a);
+    run_tile<Plan<K, R, TA, TB, D>, 1, true, End::COMMON>(a);
 }
 // One scale per slice: k_resident or k_extended with the exponents of every slice.
 template <int K, int TA, int TB, int D, int WAVES, bool IN_PLACE>
 __global__ __launch_bounds__(256, WAVES) void k_per_slice(ozk::ResidentArgs a)
 {
-    run_tile<Plan<K, 1, TA, TB, D>, IN_PLACE, End::PER_SLICE>(a);
+    run_tile<Plan<K, 1, TA, TB, D>, WAVES, IN_PLACE, End::PER_SLICE>(a);
 }
 
 template <int K, int R, int V>

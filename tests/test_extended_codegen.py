@@ -16,7 +16,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "paper_2409_13313_amd", "csrc", "ozimmu_resident.hip")
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
-INSTANCE = re.compile(r"^(_ZN12_GLOBAL__N_110k_extendedILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)EEEv\w+):(.*?)s_endpgm", re.S | re.M)
+INSTANCE = re.compile(r"^(_ZN12_GLOBAL__N_110k_extendedILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)EEEv\w+):(.*?)^\.Lfunc_end", re.S | re.M)
 INSTANCES = 38
 
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
