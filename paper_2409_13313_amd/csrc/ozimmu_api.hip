@@ -495,7 +495,8 @@ int run_schedule(int64_t m, int64_t n, int64_t p, const int8_t* SA, const int8_t
         a.parts = z;
         a.blocks = partial;
         double* const out = fin.on ? fin.Cout : D;
-        a.keep = (reinterpret_cast<uintptr_t>(out) % 64 != 0 || (fin.on ? fin.ldco : ldd) % 8 != 0) && ozr::merge_rows(k, n);
+        a.keep = (reinterpret_cast<uintptr_t>(out) % 64 != 0 || (fin.on ? fin.ldco : ldd) % 8 != 0) &&
+                 ozr::merge_rows(k, m, n, p, ozr::estimate_us(k, r_eff, variant, m, n, p, num_cu));
         const hipError_t e = ozk::launch_resident(a, k, r_eff, variant, st);
         if (e != hipSuccess || z == 1) return hip_status(e);
         const ozr::Config c = ozr::config_for(k, r_eff, variant);
@@ -1048,7 +1049,8 @@ int ozimmu_choose(int64_t m, int64_t n, int64_t p, int k, int split_mode, int ac
         out->way = OZIMMU_WAY_RESIDENT;
         out->tile = way.tile;
         out->parts = way.parts;
-        out->merge_rows = ozr::merge_rows(k, n) ? 1 : 0;
+        const double us = ozr::estimate_us(k, (int)(r < k ? r : k), way.tile, m, n, p, num_cu);
+        out->merge_rows = way.parts == 1 && ozr::merge_rows(k, m, n, p, us) ? 1 : 0;
     } else if (way.kind == Way::QUEUE) {
         out->way = OZIMMU_WAY_QUEUE;
     } else if (way.cp_tail > 0) {

@@ -86,7 +86,21 @@ constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
 // 3439 x 62 x 3552 into rows of 3553, k = 6, 74 -> 49, 2633 x 83 x 5709, k = 8, 113 -> 87.  Where the output is a small part of the work,
 // what that evicts costs as much (pairs times inner steps at 3000 x 3003: 576, k = 8, n = 1024, 238.5 -> 234.4 us; 672,
 // k = 6, n = 2048, 286.8 -> 276.5; 1152, k = 8, n = 2048, 443.8 -> 447.6; 1248, k = 12, n = 1024, 450 -> 454).
-constexpr bool merge_rows(int k, int64_t n) { return (int64_t)k * (k + 1) / 2 * ((n + 63) / 64) <= 700; }
+//
+// What stays in L2 stays in the memory-side cache behind it too.  Where output, operands and slices (all of their padding is
+// written) exceed its 256 MB, the operands of the next call and the slices of this one are evicted for it: 97567 x 95 x 106, k = 7, 148 us
+// streamed and 158 kept; 68693 x 119 x 285, k = 8, 183 and 191; 280 x 3 x 77204, k = 12, 185 and 195.  It then pays only where the
+// merging in memory, at 1.35 bytes per ps, is what the kernel waits for: 249 x 3 x 117287, k = 9, 301 and 262 us; 471 x 14 x
+// 57084, k = 5, one addition per pair, 154 and 148; 374 x 114 x 84687, k = 4, per pair, with 78 MB of operands to evict, 210 and 167.
+// us: the kernel's estimate.
+constexpr bool may_merge_rows(int k, int64_t n) { return (int64_t)k * (k + 1) / 2 * ((n + 63) / 64) <= 700; }
+inline bool merge_rows(int k, int64_t m, int64_t n, int64_t p, double us)
+{
+    if (!may_merge_rows(k, n)) return false;
+    const double out = 8.0 * (double)m * (double)p, vectors = (double)m + (double)p, operands = 8.0 * vectors * (double)n;
+    const double slices = vectors * (double)ozl::inner_padded(n) * k;
+    return out + operands + slices <= 256e6 || out / 1.35e6 >= us * (operands > out / 8.0 ? 1.2 : 0.95);
+}
 
 // Tiles whose inner dimension may be cut among workgroups (k_cut): the smallest, which leave the fewest sums to exchange (at 15
 // shapes of 41 to 1000 rows and columns one of these two was the best or within 4 % of it).
@@ -140,7 +154,7 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     const double fetched = 0.5 * kib / mfmas;                                 // KiB fetched from LDS per MFMA and wave
     // (rows of D that begin inside a piece of 64 bytes leave pieces to be merged, in memory: 4224 x 4608 x 1611, k = 4, 128 x 128
     // tiles 296 us, 1608 columns 280)
-    const double odd_us = p % 8 == 0 || merge_rows(k, n) ? 0.0 : c.ta * c.tb == 16 ? 0.6 : variant == EXTENDED ? 0.3 : 0.0;
+    const double odd_us = p % 8 == 0 || may_merge_rows(k, n) ? 0.0 : c.ta * c.tb == 16 ? 0.6 : variant == EXTENDED ? 0.3 : 0.0;
     // (k_extended has more start values to form and more sums to add up: 448 x 359 x 4480, k = 7, one addition per pair, 32 x 96
     // 39 us behind the split, three rounds of 5.4 us of steps)
     const double round_us = 4.0 + (variant == EXTENDED ? 2.0 + 0.08 * c.ta * c.tb : 0.0) + (0.4 + odd_us) * c.ta * c.tb;

@@ -20,3 +20,13 @@ def test_one_scale_per_slice_is_never_cut_whatever_the_room(oz, m, n, p, k):
     # (the sums of cut tiles are added up with one exponent per row and column)
     assert oz.choose(m, n, p, k, "per_slice", "per_pair", workspace_bytes=1 << 34).parts == 1
     assert oz.choose(m, n, p, 3, "rn", "grouped", workspace_bytes=1 << 34).parts > 1
+
+
+# (measured with rows of D that begin inside a memory line, kept in L2 and streamed past it, us)
+@pytest.mark.parametrize("m,n,p,k,accumulate,kept,streamed", [
+    (1011, 34, 20402, 3, "grouped", 55.6, 131.9), (3440, 31, 6195, 5, "grouped", 65.7, 129.8), (554, 5, 20266, 10, "grouped", 94.9, 104.5),
+    (249, 3, 117287, 9, "grouped", 261.8, 300.7), (374, 114, 84687, 4, "per_pair", 167.5, 209.5), (169, 1, 120809, 6, "grouped", 120.7, 153.9),
+    (97567, 95, 106, 7, "grouped", 158.4, 147.8), (68693, 119, 285, 8, "grouped", 191.3, 183.0), (280, 3, 77204, 12, "grouped", 195.2, 184.6),
+    (88, 24, 135175, 9, "grouped", 154.8, 147.6), (133562, 2, 213, 6, "per_pair", 303.1, 291.8), (129710, 145, 65, 3, "per_pair", 138.4, 129.4)])
+def test_rows_are_kept_in_the_cache_where_that_is_faster(oz, m, n, p, k, accumulate, kept, streamed):
+    assert oz.choose(m, n, p, k, "rn", accumulate).merge_rows == (kept < streamed)
