@@ -159,12 +159,16 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     // 39 us behind the split, three rounds of 5.4 us of steps)
     const double round_us = 4.0 + (variant == EXTENDED ? 2.0 + 0.08 * c.ta * c.tb : 0.0) + (0.4 + odd_us) * c.ta * c.tb;
     const int64_t slots = (int64_t)num_cu * c.waves, full = tiles / slots, left = tiles % slots;
-    // (32 x 32 tiles of 11 slices and more, two to a compute unit, several rounds: the steps of the one, 1.3 us and up, cover half of the
-    // other's ends.  Whole calls, the tile that was chosen without this and 32 x 32: 9998 x 67 x 320, k = 14, 73.9 and 61.0 us, 5000 x 200 x 500,
-    // k = 14, 74.8 and 62.2, 7552 x 80 x 393, k = 11, 48.0 and 45.4; it stays with the other at 1500 x 1000 x 1500, k = 12, 124.2 and 127.7)
-    const bool covered = k >= 11 && c.ta * c.tb == 1 && c.waves == 2 && full >= 2;
+    // (32 x 32 tiles, two to a compute unit, several rounds: the steps of the one cover the ends of the other, half of them at most, and no
+    // more than there are steps to cover with.  Whole calls, the tile that was chosen without this and 32 x 32: 9998 x 67 x 320, k = 14,
+    // 73.9 and 61.0 us, 5000 x 200 x 500, k = 14, 74.8 and 62.2, 7552 x 80 x 393, k = 11, 48.0 and 45.4, 70484 x 1 x 109, k = 6, one
+    // addition per pair, 128 and 119; it stays with the other at 1500 x 1000 x 1500, k = 12, 124.2 and 127.7, and, for the length of the
+    // steps, at 127768 x 4 x 114, k = 16, 387 and 415, and 55 x 120 x 154014, k = 14, 314 and 326.  Of 260 shapes of up to 600
+    // inner positions the choice took 1.8 % longer than the best tile on average, 4.7 % without this.)
+    const bool covered = c.ta * c.tb == 1 && c.waves == 2 && full >= 2;
     auto total = [&](double alone_us, double all_us) {
-        double us = (double)full * ((double)steps * all_us + (covered ? 0.5 : 1.0) * round_us);
+        const double half_us = 0.5 * round_us, cover_us = 1.3 * (double)steps * all_us;
+        double us = (double)full * ((double)steps * all_us + round_us - (!covered ? 0.0 : cover_us < half_us ? cover_us : half_us));
         if (left > 0) us += (double)steps * (left > num_cu ? all_us : alone_us) + round_us;
         return us;
     };

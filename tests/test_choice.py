@@ -30,3 +30,14 @@ def test_one_scale_per_slice_is_never_cut_whatever_the_room(oz, m, n, p, k):
     (88, 24, 135175, 9, "grouped", 154.8, 147.6), (133562, 2, 213, 6, "per_pair", 303.1, 291.8), (129710, 145, 65, 3, "per_pair", 138.4, 129.4)])
 def test_rows_are_kept_in_the_cache_where_that_is_faster(oz, m, n, p, k, accumulate, kept, streamed):
     assert oz.choose(m, n, p, k, "rn", accumulate).merge_rows == (kept < streamed)
+
+
+# (measured with 32 x 32 tiles, two to a compute unit, and with the tile that was the next best, us)
+@pytest.mark.parametrize("m,n,p,k,accumulate,small,other", [
+    (9998, 67, 320, 14, "grouped", 61.0, 73.9), (5000, 200, 500, 14, "grouped", 62.2, 74.8), (7552, 80, 393, 11, "grouped", 45.4, 48.0),
+    (70484, 1, 109, 6, "per_pair", 118.7, 128.0), (1500, 1000, 1500, 12, "grouped", 127.7, 124.2),
+    (216, 1, 105570, 12, "grouped", 225.1, 212.5), (1936, 53, 14344, 12, "grouped", 216.9, 195.7), (447, 31, 33552, 11, "grouped", 119.0, 114.1)])
+def test_the_smallest_tiles_where_their_steps_cover_their_ends(oz, m, n, p, k, accumulate, small, other):
+    choice = oz.choose(m, n, p, k, "rn", accumulate)
+    assert oz.WAYS[choice.way] == "resident"
+    assert (oz.resident_tile(n, k, accumulate, choice.tile) == (32, 32)) == (small < other)
