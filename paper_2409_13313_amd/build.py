@@ -1,9 +1,13 @@
 """Build the HIP library (gfx950 only) in-tree: csrc/*.hip -> libozimmu.so."""
 from __future__ import annotations
 
+import glob
+import importlib.util
 import os
+import shutil
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -18,8 +22,18 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=o
          "-Wno-unused-command-line-argument"]
 
 
+def _codegen():
+    """codegen.py, without the package (whose import needs the library)"""
+    spec = importlib.util.spec_from_file_location("ozimmu_codegen", os.path.join(HERE, "codegen.py"))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
 def build(verbose: bool = False) -> str:
-    """Compile every source and link the shared library; always recompiles."""
+    """Compile every source and link the shared library; always recompiles.  The assembly of the kernels whose asm statements the
+    compiler does not look into (codegen.py) is checked on the way: no library comes of code that fails."""
+    codegen = _codegen()
     objs = [os.path.join(CSRC, src.replace(".hip", ".o")) for src in SOURCES]
     core = os.path.join(CSRC, "ozimmu_gemm_core.o")
     resident = [os.path.join(CSRC, f"ozimmu_resident_k{k}.o") for k in RESIDENT_KS]
@@ -28,15 +42,24 @@ def build(verbose: bool = False) -> str:
 
     def compile_one(job):
         src, defs, obj = job
-        cmd = ["hipcc", *FLAGS, *defs, "-c", os.path.join(CSRC, src), "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        pr = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-        out = "\n".join(l for l in pr.stdout.splitlines() if "packed-fp32-ops" not in l)
-        if pr.returncode != 0:
-            raise RuntimeError(f"hipcc failed: {' '.join(cmd)}\n{out}")
-        if verbose and out.strip():
-            print(out)
+        with tempfile.TemporaryDirectory() as tmp:
+            # (the assembly that becomes the object is kept beside it for a look)
+            made = os.path.join(tmp, os.path.basename(obj))
+            cmd = ["hipcc", *FLAGS, *defs, *(["--save-temps=obj"] if defs else []), "-c", os.path.join(CSRC, src), "-o", made]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            pr = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+            out = "\n".join(l for l in pr.stdout.splitlines() if "packed-fp32-ops" not in l)
+            if pr.returncode != 0:
+                raise RuntimeError(f"hipcc failed: {' '.join(cmd)}\n{out}")
+            if verbose and out.strip():
+                print(out)
+            if defs:
+                text, = (open(f).read() for f in glob.glob(os.path.join(tmp, "*gfx950*.s")))
+                seen = codegen.check_resident(text, int(defs[0].split("=")[1]))
+                if not all(seen[kind] for kind in ("k_resident", "k_cut")):
+                    raise RuntimeError(f"{defs[0]}: kernels missing from the assembly: {seen}")
+            shutil.copyfile(made, obj)
 
     with ThreadPoolExecutor(max_workers=8) as pool:
         list(pool.map(compile_one, jobs))

@@ -10,3 +10,23 @@ if ROOT not in sys.path:
 
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs an MI355X (runs the HIP library through its C ABI)")
+
+
+@pytest.fixture(scope="session")
+def resident_assembly(tmp_path_factory):
+    """Assembly of the kernels with resident chunk sums by slice count, compiled once for all the tests that look at it."""
+    import subprocess
+    from concurrent.futures import ThreadPoolExecutor
+    from paper_2409_13313_amd import build
+    tmp = tmp_path_factory.mktemp("assembly")
+
+    def assembly(k):
+        out = str(tmp / f"k{k}.s")
+        pr = subprocess.run(["hipcc", *build.FLAGS, f"-DOZ_RES_K={k}", "--cuda-device-only", "-S",
+                             os.path.join(build.CSRC, "ozimmu_resident.hip"), "-o", out],
+                            stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert pr.returncode == 0, pr.stdout[-3000:]
+        return open(out).read()
+
+    with ThreadPoolExecutor(8) as pool:
+        return dict(zip(build.RESIDENT_KS, pool.map(assembly, build.RESIDENT_KS)))

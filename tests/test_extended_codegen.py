@@ -4,18 +4,11 @@ Its matrix instructions are asm statements: the compiler neither knows that they
 states between one and a reader of its result.  So nothing but the MFMAs may touch a chunk sum before the wait states behind the loop: no
 spill, no move between the register files and no copy of a register that an MFMA of the loop has written.  And what
 test_resident_codegen checks of k_resident: nothing but the copies' own set-ups names M0, no `vmcnt` wait in the loop but the hand-written ones."""
-import os
 import re
 import shutil
-import subprocess
-from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = os.path.join(ROOT, "paper_2409_13313_amd", "csrc", "ozimmu_resident.hip")
-FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=off",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 INSTANCE = re.compile(r"^(_ZN12_GLOBAL__N_110k_extendedILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)EEEv\w+):(.*?)^\.Lfunc_end", re.S | re.M)
 INSTANCES = 38
 
@@ -31,18 +24,9 @@ def registers(operand):
     return {n + (1000 if m.group(1) == "a" else 0) for n in range(lo, hi + 1)}
 
 
-def assembly(out, k):
-    pr = subprocess.run(["hipcc", *FLAGS, f"-DOZ_RES_K={k}", "--cuda-device-only", "-S", SRC, "-o", out],
-                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    assert pr.returncode == 0, pr.stdout[-3000:]
-    return open(out).read()
-
-
-def test_every_instance(tmp_path):
-    with ThreadPoolExecutor(8) as pool:
-        texts = list(pool.map(lambda k: assembly(str(tmp_path / f"k{k}.s"), k), range(3, 17)))
+def test_every_instance(resident_assembly):
     seen = 0
-    for text in texts:
+    for text in resident_assembly.values():
         for m in INSTANCE.finditer(text):
             name, (k, r, ta, tb, depth) = m.group(1), map(int, m.groups()[1:6])
             what = (k, r, 32 * ta, 32 * tb)

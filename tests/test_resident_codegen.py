@@ -4,35 +4,19 @@ Its copies into LDS are inline assembly that the compiler does not follow: M0 ho
 `s_waitcnt vmcnt(N)` count the copies in flight.  The first copy of a slice sets M0
 and the others rely on it, so nothing else in the whole kernel may name it; and the loop holds neither spills (whose reloads
 bring waits of their own) nor moves to and from accumulation registers nor a `vmcnt` wait of the compiler's."""
-import os
 import re
 import shutil
-import subprocess
-from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = os.path.join(ROOT, "paper_2409_13313_amd", "csrc", "ozimmu_resident.hip")
-FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=off",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 INSTANCE = re.compile(r"^(_ZN12_GLOBAL__N_110k_residentILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)EEEv\w+):(.*?)^\.Lfunc_end", re.S | re.M)
 
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
 
 
-def assembly(out, k):
-    pr = subprocess.run(["hipcc", *FLAGS, f"-DOZ_RES_K={k}", "--cuda-device-only", "-S", SRC, "-o", out],
-                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    assert pr.returncode == 0, pr.stdout[-3000:]
-    return open(out).read()
-
-
-def test_every_instance(tmp_path):
-    with ThreadPoolExecutor(8) as pool:
-        texts = list(pool.map(lambda k: assembly(str(tmp_path / f"k{k}.s"), k), range(3, 17)))
+def test_every_instance(resident_assembly):
     seen = 0
-    for text in texts:
+    for text in resident_assembly.values():
         for m in INSTANCE.finditer(text):
             name, (k, r, ta, tb, depth, waves) = m.group(1), map(int, m.groups()[1:7])
             what = (k, r, 32 * ta, 32 * tb)
