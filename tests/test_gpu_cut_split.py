@@ -35,6 +35,7 @@ def test_cut_split(oz, m, n, p, k):
     if m > 3 and p > 3:
         A[1], B[:, 2] = 0.0, 0.0
     want = oracle.dgemm(A, B, k)
+    assert oz.SPLIT_WAYS[oz.choose(m, n, p, k).split_way] == "cut"
     ws = oz.alloc_workspace(m, n, p, k)
     ws.fill_(0xA7)
     assert np.array_equal(oz.dgemm(padded(A, 1), padded(B, 3), k, workspace=ws).cpu().numpy(), want)

@@ -13,10 +13,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m,n,p,k,split,accumulate", [
     (1023, 130, 1025, 11, "bitmask", "per_pair"), (33, 250, 31, 12, "rn", "per_pair"), (1, 64, 1, 13, "bitmask", "per_pair"),
-    (2047, 257, 2049, 9, "bitmask", "per_pair"), (4095, 320, 4097, 5, "rn", "grouped"), (2049, 1000, 2047, 9, "rn", "grouped"),
-    (2047, 510, 2176, 10, "rn", "grouped"), (700, 33000, 2050, 10, "rn", "grouped")])
+    (2047, 257, 2049, 9, "bitmask", "per_pair"), (2047, 3000, 4088, 5, "rn", "grouped"), (4090, 500, 4088, 9, "rn", "grouped"),
+    (4090, 500, 4088, 10, "rn", "grouped"), (4097, 4100, 4088, 6, "rn", "grouped"), (700, 33000, 2050, 10, "rn", "grouped")])
 def test_library_choice(m, n, p, k, split, accumulate):
     from paper_2409_13313_amd import ozimmu as oz
+    choice = oz.choose(m, n, p, k, split, accumulate)
+    assert oz.WAYS[choice.way] == "resident" and choice.tile == oz.RESIDENT_TILES - 1 and choice.parts == 1
     A, B = inputs.phi_pair(m, n, p, 1.0, seed=301)
     dA, dB = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
     ref = oz.dgemm_variant(dA, dB, k, split, accumulate, schedule="one_launch")

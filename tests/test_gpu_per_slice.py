@@ -61,15 +61,35 @@ def test_per_slice_split_of_strided_operands(oz):
     assert np.array_equal(oz.export_slices(90, 131, 6, SB).cpu().numpy().transpose(0, 2, 1), wantb)
 
 
+# by the library's choice (up to 13 slices k_per_slice), with every tile of that forced, and by the persistent launch, which takes the rest
 @pytest.mark.parametrize("m,n,p,k,phi", [(300, 520, 270, 9, 2.0), (257, 5, 513, 7, 4.0), (40, 3, 30, 12, 1.0),
-                                         (130, 65536, 70, 6, 1.0)])
+                                         (130, 65536, 70, 6, 1.0), (293, 130, 261, 14, 1.0)])
 def test_ozimmu_rn_matches_oracle_bit_for_bit(oz, m, n, p, k, phi):
     A, B = inputs.phi_pair(m, n, p, phi, seed=72)
+    dA, dB = dev(A), dev(B)
     want = oracle.dgemm_per_slice(A, B, k)
-    got = oz.dgemm_variant(dev(A), dev(B), k, "per_slice", "per_pair").cpu().numpy()
-    assert np.isfinite(got).all()
-    assert (np.abs(got - want) <= 2 * np.spacing(np.abs(want))).all()
-    assert np.array_equal(got, want)
+    assert oz.WAYS[oz.choose(m, n, p, k, "per_slice", "per_pair").way] == ("resident" if k <= 13 else "one_launch")
+    for schedule in ("auto", "one_launch"):
+        got = oz.dgemm_variant(dA, dB, k, "per_slice", "per_pair", schedule=schedule).cpu().numpy()
+        assert np.isfinite(got).all()
+        assert (np.abs(got - want) <= 2 * np.spacing(np.abs(want))).all()
+        assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("k", range(3, 14))
+def test_every_tile_of_k_per_slice(oz, k):
+    m, p, tiles = 293, 261, 0
+    for n in (64, 129, 250):
+        A, B = inputs.phi_pair(m, n, p, 2.0, seed=76)
+        dA, dB, want = dev(A), dev(B), oracle.dgemm_per_slice(A, B, k)
+        for tile in range(oz.RESIDENT_TILES):
+            if oz.resident_tile(n, k, "per_pair", tile) is None or (tile == oz.RESIDENT_TILES - 1 and k <= 10):
+                continue
+            D = torch.full((m, p + 1), float("nan"), dtype=torch.float64, device="cuda")
+            oz.dgemm_tile(dA, dB, k, tile, 1, "per_slice", "per_pair", D=D[:, :p])
+            assert np.array_equal(D[:, :p].cpu().numpy(), want) and bool(torch.isnan(D[:, p]).all()), (n, tile)
+            tiles += 1
+    assert tiles >= 3
 
 
 def test_phase_calls_reproduce_the_fused_path(oz):

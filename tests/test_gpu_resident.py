@@ -28,11 +28,16 @@ def dev(x):
 @pytest.mark.parametrize("k", range(3, 17))
 @pytest.mark.parametrize("m,n,p", [(1, 1, 1), (31, 63, 33), (65, 64, 63), (129, 65, 97), (64, 129, 257), (257, 300, 128)])
 def test_tile_and_step_edges_match_the_oracle_bit_for_bit(oz, m, n, p, k):
+    # (forced: by its own choice the library takes most of these in one launch with the split, k_small)
     A, B = inputs.phi_pair(m, n, p, 1.0, seed=201)
-    D = torch.full((m, p + 1), float("nan"), dtype=torch.float64, device="cuda")
-    oz.dgemm(dev(A), dev(B), k, D=D[:, :p])
-    got = D.cpu().numpy()
-    assert np.array_equal(got[:, :p], oracle.dgemm(A, B, k)) and np.isnan(got[:, p]).all()
+    dA, dB, want = dev(A), dev(B), oracle.dgemm(A, B, k)
+    for tile in range(oz.RESIDENT_TILES):
+        if oz.resident_tile(n, k, "grouped", tile) is None:
+            continue
+        D = torch.full((m, p + 1), float("nan"), dtype=torch.float64, device="cuda")
+        oz.dgemm_resident(dA, dB, k, tile, D=D[:, :p])
+        got = D.cpu().numpy()
+        assert np.array_equal(got[:, :p], want) and np.isnan(got[:, p]).all(), tile
 
 
 # Chunk lengths r by the inner dimensions and the accumulate mode that give them; inner dimensions of one step, an odd and an
@@ -97,7 +102,9 @@ def test_larger_outputs_match_the_persistent_launch_and_sampled_oracle_entries(o
 @pytest.mark.parametrize("k", [4, 8, 9, 13])
 @pytest.mark.parametrize("alpha,beta", [(-1.5, 0.0), (0.75, -0.25)])
 def test_step_v_on_ragged_tiles(oz, k, alpha, beta):
-    m, n, p = 333, 190, 277
+    m, n, p = 333, 290, 277          # (up to 256 inner positions k_small takes it)
+    choice = oz.choose(m, n, p, k)
+    assert oz.WAYS[choice.way] == "resident" and choice.parts == 1
     A, B = inputs.phi_pair(m, n, p, 1.0, seed=203)
     C0 = np.random.Generator(np.random.PCG64(204)).standard_normal((m, p))
     C = torch.full((m, p + 3), -7.0, dtype=torch.float64, device="cuda")
@@ -113,13 +120,18 @@ def test_scales_at_the_ends_of_the_exponent_range(oz, shift):
     # the sums stay below 2^1024): some tiles hold terms (or results) that are
     # subnormal or close to overflow and are summed term by term, the others take the scaled sum; same bits as the
     # persistent launch, which always sums term by term
-    m, n, p, k = 200, 130, 300, 8
+    # (forced, every tile, k_extended's among them: by its own choice the library takes a call of this size in one launch with the
+    # split, k_small, which sums term by term too)
+    m, n, p, k = 200, 130, 300, 9
     A, B = inputs.phi_pair(m, n, p, 0.5, seed=205)
     rng = np.random.Generator(np.random.PCG64(206))
     A = np.ldexp(A, (shift + rng.integers(-10, 11, size=(m, 1))).astype(np.int32))
     B = np.ldexp(B, (shift + rng.integers(-10, 11, size=(1, p))).astype(np.int32))
     dA, dB = dev(A), dev(B)
     ref = oz.dgemm_variant(dA, dB, k, schedule="one_launch")
-    got = oz.dgemm(dA, dB, k)
     assert bool(torch.isfinite(ref).all())
-    assert torch.equal(got, ref)
+    tiles = [t for t in range(oz.RESIDENT_TILES) if oz.resident_tile(n, k, "grouped", t) is not None]
+    assert oz.RESIDENT_TILES - 1 in tiles and len(tiles) >= 5
+    for tile in tiles:
+        assert torch.equal(oz.dgemm_resident(dA, dB, k, tile), ref), tile
+    assert torch.equal(oz.dgemm(dA, dB, k), ref)

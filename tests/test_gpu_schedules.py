@@ -293,17 +293,27 @@ def test_default_schedule_of_a_large_output_with_the_comparison_variants(oz, spl
     assert np.array_equal(got[torch.from_numpy(I).cuda()][:, torch.from_numpy(J).cuda()].cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("m,n,p,k,resident", [
-    (256, 256, 256, 8, True), (1024, 1024, 1024, 9, True), (1024, 16384, 1024, 8, True), (2000, 500, 3000, 14, True),
-    (62, 39895, 62, 6, False), (748, 15315, 748, 5, False), (615, 31277, 496, 7, False), (327, 45742, 521, 4, False),
-    (493, 16563, 2750, 4, False), (2779, 23124, 355, 4, False)])
-def test_which_way_the_library_chooses(oz, m, n, p, k, resident):
-    # long inner dimensions of few tiles: a step of k_resident is then bound by the latency of its operands, and the way whose
-    # work items cut the inner dimension is 1.2 to 1.9 times as fast (products alone)
+@pytest.mark.parametrize("m,n,p,k,way,cut", [
+    (256, 256, 256, 8, "small", False), (300, 300, 300, 8, "resident", False), (1024, 1024, 1024, 9, "resident", False),
+    (1024, 16384, 1024, 8, "resident", False), (2000, 500, 3000, 14, "resident", False), (62, 39895, 62, 6, "resident", True),
+    (748, 15315, 748, 5, "chunk_parallel", False), (615, 31277, 496, 7, "chunk_parallel", False),
+    (327, 45742, 521, 4, "resident", True), (493, 16563, 2750, 4, "chunk_parallel", False),
+    (2779, 23124, 355, 4, "chunk_parallel", False)])
+def test_which_way_the_library_chooses(oz, m, n, p, k, way, cut):
+    # long inner dimensions of few tiles: a step of k_resident is then bound by the latency of its operands, and the ways whose
+    # work items cut the inner dimension are 1.2 to 1.9 times as fast (products alone)
+    choice = oz.choose(m, n, p, k)
+    assert oz.WAYS[choice.way] == way and (choice.parts > 1) == cut
     A, B = inputs.phi_pair(m, n, p, 1.0, seed=103)
     dA, dB = dev(A), dev(B)
     ws = oz.alloc_workspace(m, n, p, k)
     ws.fill_(0x5A)
     D = oz.dgemm(dA, dB, k, workspace=ws)
-    assert bool((blocks_of(ws, oz, m, n, p, k) == 0x5A).all()) == resident
+    if way == "small":               # (nothing of the workspace is used)
+        assert bool((ws == 0x5A).all())
+    elif way == "resident" and not cut and oz.SPLIT_WAYS[choice.split_way] != "cut":
+        assert bool((blocks_of(ws, oz, m, n, p, k) == 0x5A).all())
+    else:                            # (sums behind the maxima of the split, where it has any: two bytes per vector and piece of 512)
+        keys = 2 * (m + p) * -(-n // 512) if oz.SPLIT_WAYS[choice.split_way] == "cut" else 0
+        assert not bool((blocks_of(ws, oz, m, n, p, k)[keys:] == 0x5A).all())
     assert torch.equal(D, oz.dgemm_variant(dA, dB, k, "rn", "grouped", schedule="one_launch"))

@@ -41,6 +41,7 @@ def operands(m, n, p, seed):
                                      (16, 256, 16, 15), (256, 256, 256, 8), (257, 256, 255, 8), (16, 257, 16, 8)])
 @pytest.mark.parametrize("pad,shift", [(0, 0), (3, 1)])
 def test_dgemm(oz, m, n, p, k, pad, shift):
+    assert (oz.WAYS[oz.choose(m, n, p, k).way] == "small") == (n <= 256)
     A, B = operands(m, n, p, 501)
     want = oracle.dgemm(A, B, k)
     D = view(np.zeros((m, p)), 2)
