@@ -112,15 +112,15 @@ inline int64_t sums_bytes(int k, int r, const Config& c, int64_t tiles)
 }
 // z_groups of k_add_parts: threads that share the parts of an element
 constexpr int z_groups(int parts) { return parts > 8 ? 16 : 4; }
-// What writing and adding the sums takes.  Every chunk costs a store in k_cut and a load and an addition in k_add_parts, one after the other,
-// and once more for every further turn of the parts (fitted to 2400 timings of 260 shapes.  With the turns alone and a larger constant,
-// tiles of many chunks were cut that were faster whole: 8 x 2054 x 8, k = 10, one addition per pair, 31.2 us whole, 45.2 in four
-// parts; 33 x 3385 x 232 44.6 and 53.9; 44 x 1909 x 1, k = 7, 19.3 and 23.3 with its split).
+// What writing and adding the sums takes: every chunk costs a store in k_cut and a load and an addition in k_add_parts, one after the other
+// (fitted to 8000 timings of 720 shapes of 500 to 60000 inner positions: four that are cut are slower than whole, by 2 to 6 %.  With
+// the turns of the loop alone and a larger constant 24 were: 8 x 2054 x 8, k = 10, one addition per pair, 31.2 us whole, 45.2 in
+// four parts; 33 x 3385 x 232 44.6 and 53.9; 44 x 1909 x 1, k = 7, 19.3 and 23.3 with its split).
 inline double add_parts_us(int k, int r, const Config& c, int64_t tiles, int parts)
 {
-    const int zg = z_groups(parts), batch = zg == 4 ? 8 : 4, turns = (parts + zg - 1) / zg, w = num_chunks(k, r < k ? r : k);
-    const double trips = (double)turns * ((w + batch - 1) / batch);
-    return 2.5 + 1.0 * trips + w * (0.33 + 0.15 * (zg == 4 ? turns - 1 : turns)) + (double)sums_bytes(k, r, c, tiles) / 2.5e6;
+    const int zg = z_groups(parts), batch = zg == 4 ? 8 : 4, w = num_chunks(k, r < k ? r : k);
+    const double trips = (double)((parts + zg - 1) / zg) * ((w + batch - 1) / batch);
+    return 2.5 + 1.0 * trips + 0.3 * w + (double)sums_bytes(k, r, c, tiles) / 2.5e6;
 }
 
 // Estimate of the kernel's time in microseconds on a chip of num_cu compute units; -1 where it cannot run.

@@ -47,6 +47,6 @@ def test_the_smallest_tiles_where_their_steps_cover_their_ends(oz, m, n, p, k, a
 @pytest.mark.parametrize("m,n,p,k,accumulate,whole,cut", [
     (8, 2054, 8, 10, "per_pair", 31.2, 45.2), (2, 2465, 19, 8, "per_pair", 27.7, 35.2), (33, 3385, 232, 10, "per_pair", 44.6, 53.9),
     (103, 3720, 8, 9, "per_pair", 40.1, 45.2), (297, 4429, 88, 10, "per_pair", 56.4, 60.7), (21, 2761, 6, 6, "per_pair", 24.6, 27.4),
-    (3, 1951, 56, 7, "grouped", 22.4, 23.6), (9, 6694, 26, 3, "grouped", 35.4, 20.4)])
+    (477, 4256, 8, 10, "per_pair", 54.7, 58.7), (9, 6694, 26, 3, "grouped", 35.4, 20.4)])
 def test_tiles_are_cut_where_that_is_faster(oz, m, n, p, k, accumulate, whole, cut):
     assert (oz.choose(m, n, p, k, "rn", accumulate).parts > 1) == (cut < whole)
