@@ -1279,24 +1279,32 @@ static CutOp make_cut(const SplitIn& i, int k, uint16_t* keys)
     return o;
 }
 
-// Both operands in two launches (k_cut_maxima, k_cut_split), where that is estimated to take less than `us`: 11 us and 8 bytes per
+// Both operands in two launches (k_cut_maxima, k_cut_split), where that is estimated to take less than `us`: 12.5 us (0.4 more for
+// each slice less than six: `us` is then too large by that) and 8 bytes per
 // ps while the operands are still in the memory-side cache for the second, else 3.8 (whole calls, one launch or the cut columns'
 // four and two, k = 8: 47 x 11948 x 48 58.4 and 31.4, 256 x 8192 x 256 63.6 and 48.9, 600 x 20000 x 200 203 and 185, 75 x 2212 x 512 30.2 and
-// 29.1, 500 x 1024 x 500 23.2 and 26.1; k = 4: 100 x 262144 x 100 488 and 370, 1000 x 2000 x 1000 35.2 and 40.6).
+// 29.1, 500 x 1024 x 500 23.2 and 26.1; k = 4: 100 x 262144 x 100 488 and 370, 1000 x 2000 x 1000 35.2 and 40.6).  Not for many columns of
+// moderate length: whole ones fill the chip then, and read what does not fit their registers again from near by (12 x 1982 x
+// 3483, k = 8, 47.7 and 61.2, 8 x 2369 x 4391, k = 3, 55.2 and 66.4, 31 x 4960 x 3851, k = 1, 96.0 and 126.5; 12 x 17700 x 942, k = 14, 246 and
+// 212), and from 2048 positions on, a workgroup's registers full with one row (37 x 2031 x 130, k = 8, 21.7 and 23.7, 22 x 2240 x 170,
+// k = 13, 38.4 and 35.4).  Of 488 shapes of many columns or of few vectors this takes 0.3 % longer than the faster of the two on average, without
+// the exception 1.0 %.
 static bool cut_pays(const SplitIn* ops, int count, int k, double us, size_t room)
 {
-    if (count != 2 || ops[0].n < 1024) return false;
+    if (count != 2 || ops[0].n < 2048) return false;
     double vectors = 0.0;
+    int64_t columns = 0;
     size_t keys = 0;
     for (int q = 0; q < 2; ++q) {
         const CutOp o = make_cut(ops[q], k, nullptr);
         if ((int64_t)o.groups * o.pieces >= ((int64_t)1 << 22)) return false;
         keys += 2 * (size_t)o.pieces * (size_t)o.rows;
         vectors += (double)o.rows;
+        columns += o.by_col ? o.rows : 0;
     }
-    if (keys > room) return false;
+    if (keys > room || (columns > 1300 && ops[0].n <= 14500)) return false;
     const double bytes = vectors * (double)ops[0].n * (16 + k), near = bytes < 160e6 ? bytes : 160e6;
-    return 11.0 + near / 8e6 + (bytes - near) / 3.8e6 + 1.5 < us;
+    return 12.5 + (k < 6 ? 0.4 * (6 - k) : 0.0) + near / 8e6 + (bytes - near) / 3.8e6 < us;
 }
 
 bool split_is_cut(const SplitIn* ops, int count, int k, size_t room_bytes)

@@ -50,3 +50,13 @@ def test_the_smallest_tiles_where_their_steps_cover_their_ends(oz, m, n, p, k, a
     (477, 4256, 8, 10, "per_pair", 54.7, 58.7), (9, 6694, 26, 3, "grouped", 35.4, 20.4)])
 def test_tiles_are_cut_where_that_is_faster(oz, m, n, p, k, accumulate, whole, cut):
     assert (oz.choose(m, n, p, k, "rn", accumulate).parts > 1) == (cut < whole)
+
+
+# (measured in one launch, or the launches of cut columns, and in two along the inner dimension, us, whole calls)
+@pytest.mark.parametrize("m,n,p,k,whole,cut", [
+    (12, 1982, 3483, 8, 47.7, 61.2), (8, 2369, 4391, 3, 55.2, 66.4), (5, 2756, 1415, 3, 31.6, 37.1), (58, 1583, 4548, 7, 60.6, 66.8),
+    (14, 1992, 4768, 9, 69.6, 76.1), (1, 1306, 2569, 12, 43.6, 46.6), (31, 1624, 1920, 6, 26.0, 32.5),
+    (47, 11948, 48, 8, 58.4, 31.4), (256, 8192, 256, 8, 63.6, 48.9), (12, 17700, 942, 14, 245.5, 212.0), (1, 13311, 545, 13, 112.8, 93.0), (27, 6332, 560, 3, 30.4, 25.7), (13, 10255, 295, 4, 48.9, 34.4),
+    (142, 11505, 66, 8, 67.1, 39.5), (37, 2031, 130, 8, 21.7, 23.7), (22, 2240, 170, 13, 38.4, 35.4), (7, 2613, 2, 3, 15.3, 19.8), (500, 1024, 500, 8, 23.2, 26.1)])
+def test_vectors_are_split_along_the_inner_dimension_where_that_is_faster(oz, m, n, p, k, whole, cut):
+    assert (oz.SPLIT_WAYS[oz.choose(m, n, p, k).split_way] == "cut") == (cut < whole)
