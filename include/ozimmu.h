@@ -58,7 +58,7 @@ const char *ozimmu_status_string(int status);
  * ozimmu_dgemm_static.  Every entry point that launches the chunk GEMM does this by itself on its first
  * call on a device; the set-up calls are not legal inside a HIP stream capture, so call ozimmu_init (or
  * any such entry point) once per device BEFORE capturing a graph that contains library calls.  Host;
- * idempotent; thread-safe; about 37 ms the first time on a device.  Returns OZIMMU_OK or OZIMMU_ERR_HIP. */
+ * idempotent; thread-safe; about 42 ms the first time on a device.  Returns OZIMMU_OK or OZIMMU_ERR_HIP. */
 int ozimmu_init(void);
 
 /* beta = min(7, floor((31 - log2 n)/2))   [Section 2, the bound n 2^(2 beta) <= 2^31]  and
