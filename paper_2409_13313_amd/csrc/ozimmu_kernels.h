@@ -7,6 +7,13 @@
 
 namespace ozk {
 
+// A launch's own status: reported here, it is not left behind for the next call that asks the runtime for its last error.
+inline hipError_t launch_status(hipError_t e)
+{
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 // Steps (i) and (ii): exponents and slices of one or two operands (in one launch where that pays).  split_mode 0: round to
 // nearest, ceil exponent (Algorithm 8); 1: bit-mask digits, floor exponent (Algorithm 3).
 struct SplitIn {

@@ -738,7 +738,7 @@ hipError_t launch(const ozk::ResidentArgs& a_in, hipStream_t st)
         const void* const kernel = kernels[a.parts > 1 ? 2 : a.per_slice ? 1 : 0];
         if (!kernel || (a.parts > 1 && a.per_slice)) return hipErrorInvalidValue;
         void* args[] = {&a};
-        return hipLaunchKernel(kernel, dim3(a.parts > 1 ? tiles * (unsigned)a.parts : tiles), dim3(256), args, smem, st);
+        return ozk::launch_status(hipLaunchKernel(kernel, dim3(a.parts > 1 ? tiles * (unsigned)a.parts : tiles), dim3(256), args, smem, st));
     }
 }
 

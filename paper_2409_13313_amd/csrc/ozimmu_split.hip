@@ -1500,7 +1500,7 @@ static hipError_t launch_small_k(const SmallArgs* a, int k, hipStream_t st)
         if (!a) return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * K * 4 * 1024);
         void* args[] = {const_cast<SmallArgs*>(a)};
         const dim3 grid((unsigned)((a->op[1].rows + 15) / 16), (unsigned)((a->op[0].rows + 15) / 16));
-        return hipLaunchKernel(kernel, grid, dim3(256), args, 2 * K * a->steps * 1024, st);
+        return ozk::launch_status(hipLaunchKernel(kernel, grid, dim3(256), args, 2 * K * a->steps * 1024, st));
     }
     return hipErrorInvalidValue;
 }
