@@ -159,6 +159,23 @@ __device__ inline uint32_t with_offset(uint32_t w, uint32_t c4, int* sum)
     return w;
 }
 
+// Slices are written through L2.  Left there they are written back when the kernel ends, before the product may start: 2 to 6 us in
+// which nothing runs (start of the product after the last workgroup of the split, left in L2 and written through: 777 x 1001 x 513, k = 7,
+// 6.3 and 1.1 us, a call 30.2 and 26.9; 512^3, k = 8, 3.6 and 1.8, 16.2 and 14.0; 1024^3, k = 9, 4.4 and 0.9, 45.2 and 42.7).  They stay in the
+// memory-side cache, which non-temporal stores would not do (the product then takes 4 us longer at 777 x 1001 x 513).
+__device__ __attribute__((always_inline)) inline void store_slices(int8_t* out, uint32_t v)
+{
+    __hip_atomic_store(reinterpret_cast<uint32_t*>(out), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __attribute__((always_inline)) inline void store_slices(int8_t* out, uint32_t x, uint32_t y, uint32_t z, uint32_t w)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = {x, y, z, w};
+    // (one store: as two of 8 bytes each memory line would be written twice.  The wait state is what a store of more than 8 bytes asks for
+    // before its registers are written again)
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(out), "v"(v) : "memory");
+}
+
 template <bool MASK>
 __device__ inline int exponent_of(double mx)
 {
@@ -234,7 +251,7 @@ __device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int be
             for (int u = 0; u < U; ++u) {
                 if (b * per_batch + u * nw + w < groups) {
                     const uint32_t v = with_offset(digits4<MASK>(y[u], sig, step), c4, &sum);
-                    if (ok) *reinterpret_cast<uint32_t*>(out + (int64_t)u * nw * (TPW * TILE_BYTES)) = v;
+                    if (ok) store_slices(out + (int64_t)u * nw * (TPW * TILE_BYTES), v);
                 }
             }
             out += o.slice_stride;
@@ -333,7 +350,7 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
                     v.y = with_offset(digits4<MASK>(y[u] + 4, sig, step), c4, &sum);
                     v.z = with_offset(digits4<MASK>(y[u] + 8, sig, step), c4, &sum);
                     v.w = with_offset(digits4<MASK>(y[u] + 12, sig, step), c4, &sum);
-                    if (ok) *reinterpret_cast<uint4*>(out + (int64_t)u * nw * (TPW * TILE_BYTES)) = v;
+                    if (ok) store_slices(out + (int64_t)u * nw * (TPW * TILE_BYTES), v.x, v.y, v.z, v.w);
                 }
             }
             out += o.slice_stride;
@@ -483,12 +500,12 @@ __global__ __launch_bounds__(64 * CUT_WAVES) void k_cut_split(CutOp a, CutOp b, 
         for (int u = 0; u < 4; ++u) v[u] = digits4<MASK>(y[u], sig, step);
         if (ok) {
             if (o.by_col) {
-                if (l0 < (int64_t)o.KT * TILE_K) *reinterpret_cast<uint4*>(out) = make_uint4(v[0], v[1], v[2], v[3]);
+                if (l0 < (int64_t)o.KT * TILE_K) store_slices(out, v[0], v[1], v[2], v[3]);
             } else {
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
                     if (l0 + u * (CUT_WAVES * 64) < (int64_t)o.KT * TILE_K)
-                        *reinterpret_cast<uint32_t*>(out + (int64_t)u * CUT_WAVES * TILE_BYTES) = v[u];
+                        store_slices(out + (int64_t)u * CUT_WAVES * TILE_BYTES, v[u]);
             }
         }
         out += o.slice_stride;
@@ -695,7 +712,7 @@ __global__ __launch_bounds__(256) void k_split_B(int64_t n, int64_t p, const dou
                     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
                     const u32x4 vv = {v.x, v.y, v.z, v.w};
                     if constexpr (KEEP)
-                        *reinterpret_cast<u32x4*>(dst) = vv;
+                        store_slices(dst, v.x, v.y, v.z, v.w);
                     else
                         __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(dst));
                 }
@@ -903,7 +920,14 @@ __device__ inline void split_ps(const PsOp& o, int block, int k, int beta, doubl
             }
 #pragma unroll
             for (int g = 0; g < GROUP; ++g)
-                if (ok && place(q0 + g) < end) *reinterpret_cast<uint32_t*>(out + packed_offset(R, place(q0 + g), o.KT)) = word[g];
+                if (ok && place(q0 + g) < end) {
+                    // (through L2, see store_slices, but for 700 x 8000 x 900, k = 8, where that is 258 -> 278 us: 700 x 500 x 900 40.4 -> 37.1)
+                    int8_t* const at = out + packed_offset(R, place(q0 + g), o.KT);
+                    if constexpr (U == 1 && V >= 4)
+                        store_slices(at, word[g]);
+                    else
+                        *reinterpret_cast<uint32_t*>(at) = word[g];
+                }
         }
     }
 }
