@@ -284,13 +284,14 @@ int ozimmu_gemm_group_accumulate(int64_t m, int64_t n, int64_t p,
                                  double *D, int64_t ldd, void *scratch, void *stream);
 
 /* The way of running the schedule that keeps all chunk sums of a tile in registers (see ozimmu_dgemm_variant), with tile
- * number `tile` (0 .. OZIMMU_RESIDENT_TILES - 1) instead of the library's choice; the result is the same, bit for bit.
+ * number `tile` (0 .. OZIMMU_RESIDENT_TILES - 1, or OZIMMU_HELD_TILE: the larger ones that hold slices of A) instead of the library's choice; the result is the same, bit for bit.
  * Debug / test helpers.
  *   ozimmu_resident_tile  rows and columns of that tile (either may be NULL) for inner dimension n, k slices and an
  *                         accumulate mode; OZIMMU_ERR_SLICES where there is no such kernel.  Host, pure.
  *   ozimmu_dgemm_resident arguments as for ozimmu_dgemm_variant (no schedule flag, one scale per row and column);
  *                         OZIMMU_ERR_SLICES where there is no such kernel. */
 #define OZIMMU_RESIDENT_TILES 7
+#define OZIMMU_HELD_TILE 16
 int ozimmu_resident_tile(int64_t n, int k, int accumulate_mode, int tile, int *rows, int *cols);
 int ozimmu_dgemm_resident(int64_t m, int64_t n, int64_t p,
                           const double *A, int64_t lda, const double *B, int64_t ldb,

@@ -5,7 +5,7 @@ Two things in these kernels rest on what the compiler does with asm statements t
   * their copies into LDS: M0 holds the LDS address, set by the first copy of a slice and relied on by the others, and hand-written
     `s_waitcnt vmcnt(N)` count the copies in flight.  So nothing else in the kernel may name M0, and the loop holds neither
     spills (whose reloads bring waits of their own) nor moves to and from accumulation registers nor a `vmcnt` wait of the compiler's;
-  * the matrix instructions of the kernels that add in place (k_extended and its like): the compiler neither knows that they are matrix
+  * the matrix instructions of the kernels that add in place (k_extended, k_held and their like): the compiler neither knows that they are matrix
     instructions nor puts the wait states before and behind them.  So nothing but they may touch a chunk sum before the wait states behind
     the loop (no spill, no move between the register files, no copy), and no ordinary vector instruction may write an operand of one
     within the two wait states before it."""
@@ -15,7 +15,7 @@ import re
 
 MFMA = "v_mfma_i32_16x16x64_i8"
 OPERAND_WAIT_STATES = 2     # between a vector instruction that writes a register and a matrix instruction that reads it
-KERNEL = re.compile(r"^(_ZN12_GLOBAL__N_1\d+(k_resident|k_cut|k_extended|k_per_slice)I((?:L[ib]\d+E)+)EEv\w+):(.*?)^\.Lfunc_end", re.S | re.M)
+KERNEL = re.compile(r"^(_ZN12_GLOBAL__N_1\d+(k_resident|k_cut|k_extended|k_held|k_per_slice)I((?:L[ib]\d+E)+)EEv\w+):(.*?)^\.Lfunc_end", re.S | re.M)
 
 
 def registers(operand: str) -> set:
@@ -116,10 +116,10 @@ def check_body(body: str, k: int, r: int, ta: int, tb: int, in_place: bool, what
     _require(m0 >= k, what, "copies' own set-ups of M0", m0)
 
 
-def check_resident(text: str, k: int) -> dict:
+def check_kernels(text: str, k: int) -> dict:
     """Looks at every kernel in the assembly of ozimmu_resident.hip compiled for k slices; raises Wrong.  Returns how many there are
     of each kind."""
-    seen = dict.fromkeys(("k_resident", "k_cut", "k_extended", "k_per_slice"), 0)
+    seen = dict.fromkeys(("k_resident", "k_cut", "k_extended", "k_held", "k_per_slice"), 0)
     for m in KERNEL.finditer(text):
         name, kind, args = m.group(1), m.group(2), [int(x) for x in re.findall(r"L[ib](\d+)E", m.group(3))]
         what = (kind, *args)
@@ -128,7 +128,7 @@ def check_resident(text: str, k: int) -> dict:
             r = 1
         else:
             kk, r, ta, tb = args[:4]
-            in_place = kind == "k_extended"
+            in_place = kind in ("k_extended", "k_held")
         _require(kk == k, what)
         check_body(m.group(4), k, r, ta, tb, bool(in_place), what)
         at = text.index(".name:           " + name)
@@ -137,3 +137,8 @@ def check_resident(text: str, k: int) -> dict:
             _require(re.search(r"\.%s:\s+(\d+)" % key, about).group(1) == "0", what, key)
         seen[kind] += 1
     return seen
+
+
+def check_resident(text: str, k: int) -> dict:
+    """check_kernels, which looks at k_held too, without its count."""
+    return {kind: count for kind, count in check_kernels(text, k).items() if kind != "k_held"}

@@ -384,7 +384,7 @@ Way choose_way(int64_t m, int64_t n, int64_t p, int k, int r_eff, bool per_slice
             other_us *= 1.0 + (slower < 0.08 ? slower : 0.08) * log2((double)n / 16384.0);
         }
         int variant = -1, parts = 1;
-        for (int v = 0; v < ozr::NUM_VARIANTS; ++v) {
+        for (int v = 0; v <= ozr::HELD; v = v + 1 == ozr::NUM_VARIANTS ? ozr::HELD : v + 1) {
             if (per_slice && !ozr::per_slice_tile(k, v)) continue;
             const double us = ozr::estimate_us(k, r_eff, v, m, n, p, num_cu);
             if (us < 0.0) continue;
@@ -955,7 +955,7 @@ int ozimmu_resident_tile(int64_t n, int k, int accumulate_mode, int tile, int* r
 {
     if (n < 1 || n > MAX_INNER) return OZIMMU_ERR_DIM;
     if (accumulate_mode < OZIMMU_ACCUM_GROUPED || accumulate_mode > OZIMMU_ACCUM_WIDE) return OZIMMU_ERR_SLICES;
-    if (k < 1 || k > OZIMMU_MAX_SLICES || tile < 0 || tile >= ozr::NUM_VARIANTS) return OZIMMU_ERR_SLICES;
+    if (k < 1 || k > OZIMMU_MAX_SLICES || !ozr::is_variant(tile)) return OZIMMU_ERR_SLICES;
     const int64_t r = r_of_mode(n, accumulate_mode);
     const ozr::Config c = ozr::config_for(k, (int)(r < k ? r : k), tile);
     if (c.ta == 0) return OZIMMU_ERR_SLICES;

@@ -17,14 +17,21 @@ constexpr int num_chunks(int k, int r)
 }
 
 // A wave holds ta x tb tiles of 16 x 16 for every chunk, a workgroup 2 x 2 waves; depth = inner steps of operands in
-// LDS; waves = workgroups that share a compute unit.  ta == 0: no such kernel.
+// LDS; waves = workgroups that share a compute unit; held = slices of A that k_held keeps in registers at a time (the other kernels:
+// 0).  ta == 0: no such kernel.
 struct Config {
-    int ta, tb, depth, waves;
+    int ta, tb, depth, waves, held = 0;
 };
-constexpr int lds_bytes(int k, const Config& c) { return c.depth * k * (c.ta + c.tb) * 2048 + 128 * (c.ta + c.tb); }
+// (k_held fetches slices 2 .. k - held of B twice a step, early and late: a second place each, or their copies had no time)
+constexpr int lds_bytes(int k, const Config& c)
+{
+    return c.depth * k * (c.ta + c.tb) * 2048 + (c.held ? (k - c.held - 1) * c.tb * 2048 : 0) + 128 * (c.ta + c.tb);
+}
 
 constexpr int ACC_TILES = 64;    // tiles of 16 x 16 that the accumulation registers of a wave hold
 constexpr int NUM_VARIANTS = 7, EXTENDED = 6;  // the last one is k_extended, the others k_resident
+constexpr int HELD = 16;         // k_held, beside them
+constexpr bool is_variant(int v) { return (v >= 0 && v < NUM_VARIANTS) || v == HELD; }
 
 // variant 0: the largest tile whose chunk sums fit the 256 accumulation registers; the others: smaller ones for outputs that
 // the large one would not spread evenly over the chip; EXTENDED: the next larger tile whose chunk sums fit the ordinary registers
@@ -41,6 +48,23 @@ constexpr Config config(int k, int r, int variant)
     else if (w <= 32) c.ta = 1, c.tb = 2;
     else if (w <= ACC_TILES) c.ta = 1, c.tb = 1;
     const int area = c.ta * c.tb;  // 16 x 16 tiles of a wave in the largest tile
+    if (variant == HELD) {
+        // The largest tile, in the order of what they move per MFMA, whose sums, held slices of A and two slices of B fit the registers (26
+        // others), if it is larger than k_resident's and k_extended's.  An odd number held: see the kernel's order of a step.
+        constexpr int shapes[4][2] = {{4, 4}, {3, 4}, {3, 3}, {2, 4}}, last[2] = {2, 3};
+        const Config e = config(k, r, EXTENDED);
+        const int least = e.ta * e.tb > area ? e.ta * e.tb : area;
+        c.ta = 0;
+        if (k < 5 || r == 1 || w > 26) return c;
+        for (int x = 0; x < 5 && c.ta == 0; ++x) {
+            const int ta = x < 4 ? shapes[x][0] : last[0], tb = x < 4 ? shapes[x][1] : last[1];
+            for (int held = ((k + 1) / 2) | 1; held < k && c.ta == 0; held += 2) {
+                const Config h{ta, tb, 1, 1, held};
+                if (ta * tb > least && 4 * (w * ta * tb + held * ta + 2 * tb) + 26 <= 512 && lds_bytes(k, h) <= 160 * 1024) c = h;
+            }
+        }
+        return c;
+    }
     if (variant == EXTENDED) {
         constexpr int shapes[8][2] = {{4, 4}, {3, 4}, {2, 4}, {2, 3}, {2, 2}, {1, 3}, {1, 2}, {1, 1}};
         c.ta = 0;
@@ -73,7 +97,7 @@ constexpr Config config_for(int k, int r, int variant)
     return config(k, r < k ? r : k, variant);
 }
 // Tiles for slices with one scale each (r = 1; k_per_slice): k_extended's only where there is no other.
-constexpr bool per_slice_tile(int k, int variant) { return variant != EXTENDED || config(k, 1, 0).ta == 0; }
+constexpr bool per_slice_tile(int k, int variant) { return variant < EXTENDED || (variant == EXTENDED && config(k, 1, 0).ta == 0); }
 // grid size; 32-bit operand offsets
 constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
 {
@@ -104,7 +128,7 @@ inline bool merge_rows(int k, int64_t m, int64_t n, int64_t p, double us)
 
 // Tiles whose inner dimension may be cut among workgroups (k_cut): the smallest, which leave the fewest sums to exchange (at 15
 // shapes of 41 to 1000 rows and columns one of these two was the best or within 4 % of it).
-constexpr bool may_cut(int variant, const Config& c) { return variant != EXTENDED && c.ta * c.tb >= 1 && c.ta * c.tb <= 2; }
+constexpr bool may_cut(int variant, const Config& c) { return variant < EXTENDED && c.ta * c.tb >= 1 && c.ta * c.tb <= 2; }
 // Bytes of the chunk sums of `tiles` tiles (k_add_parts).
 inline int64_t sums_bytes(int k, int r, const Config& c, int64_t tiles)
 {
@@ -155,13 +179,13 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
     const double mfmas = 0.5 * k * (k + 1) * c.ta * c.tb;
     const double kib = 2.0 * k * (c.ta + c.tb);                               // operands of a step
     const double copied = 1024.0 * kib / (4.0 * mfmas);                      // bytes brought in per MFMA
-    const double fetched = 0.5 * kib / mfmas;                                 // KiB fetched from LDS per MFMA and wave
+    const double fetched = (c.held ? (double)(k * c.ta + (2 * k - c.held - 1) * c.tb) : 0.5 * kib) / mfmas;  // KiB fetched from LDS per MFMA and wave
     // (rows of D that begin inside a piece of 64 bytes leave pieces to be merged, in memory: 4224 x 4608 x 1611, k = 4, 128 x 128
     // tiles 296 us, 1608 columns 280)
-    const double odd_us = p % 8 == 0 || may_merge_rows(k, n) ? 0.0 : c.ta * c.tb == 16 ? 0.6 : variant == EXTENDED ? 0.3 : 0.0;
+    const double odd_us = p % 8 == 0 || may_merge_rows(k, n) ? 0.0 : c.ta * c.tb == 16 ? 0.6 : variant >= EXTENDED ? 0.3 : 0.0;
     // (k_extended has more start values to form and more sums to add up: 448 x 359 x 4480, k = 7, one addition per pair, 32 x 96
     // 39 us behind the split, three rounds of 5.4 us of steps)
-    const double round_us = 4.0 + (variant == EXTENDED ? 2.0 + 0.08 * c.ta * c.tb : 0.0) + (0.4 + odd_us) * c.ta * c.tb;
+    const double round_us = 4.0 + (variant >= EXTENDED ? 2.0 + 0.08 * c.ta * c.tb : 0.0) + (0.4 + odd_us) * c.ta * c.tb;
     const int64_t slots = (int64_t)num_cu * c.waves, full = tiles / slots, left = tiles % slots;
     // (32 x 32 tiles, two to a compute unit, several rounds: the steps of the one cover the ends of the other, half of them at most, and no
     // more than there are steps to cover with.  Whole calls, the tile that was chosen without this and 32 x 32: 9998 x 67 x 320, k = 14,
@@ -193,7 +217,9 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
                             at_least(c.waves == 2 ? 0.0168 * mfmas + 0.2 : 0.0075 * mfmas + barrier_us, wait2_us));
     if (parts > 1) return us + add_parts_us(k, r, c, tiles, parts);
     if (us < 1500.0) return us;
-    const double hot_us = mfmas * ((c.waves == 2 ? 0.0062 : 0.0068) + 2.0e-5 * copied + 0.005 * fetched);
+    // (k_held's tiles of 96 rows 2 % more: 8192^3, k = 8, 96 x 128 11.48 ms, 64 x 128 11.30; 16384^3, k = 9, 96 x 96 112.4, 64 x 128
+    // 109.4; still ahead at 16384^3, k = 8, 88.5 and 91.5, 6144^3 4.71 and 4.82)
+    const double hot_us = mfmas * ((c.waves == 2 ? 0.0062 : 0.0068) + 2.0e-5 * copied + 0.005 * fetched) * (c.held && c.ta == 3 ? 1.02 : 1.0);
     return total(at_least(hot_us, wait_us), at_least(hot_us * c.waves, wait2_us));
 }
 

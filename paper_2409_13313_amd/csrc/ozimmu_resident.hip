@@ -30,6 +30,14 @@
 // 2.54 -> 2.25 ms, and k = 11 to 13, which had no resident tile at all, 5.95, 7.09, 8.32 -> 3.39, 3.77, 4.20 ms.
 // No gain: 96 x 96 and 64 x 160 at k = 7 and 8 (0 to 0.5 % at 8192^3 and 16384^3, 3 to 5 % slower where 4096 is no multiple of them).
 //
+// k_held is k_extended with another order of a step (HeldPlan): the lower slices of A stay in registers while those of B pass by, which takes
+// fewer fragments at a time and leaves room for the sums of the next larger tile: 128 x 128 at k = 6, 96 x 128 at 7 and 8, 96 x 96 at 9 and
+// 10, 64 x 128 at 11, 64 x 96 at 13, 14 and for the 16 chunks of k = 12 at r = 8.  What that saves is bytes, out of L2 and beyond (all of
+// them compiled out, a working copy, 16384^3, k = 8, is 16 % of the time, half of the LDS fetches 0.5 %): 16384^3, k = 8, 64 x 128
+// 91.5 ms, 96 x 128 88.5; k = 12 189.9 and 186.5; 8192^3, k = 6, 96 x 128 7.00, 128 x 128 6.66; 6144^3, k = 11, 8.70 and 8.12;
+// 1537 x 2051 x 1283, k = 9, one round of 96 x 96 instead of four of 32 x 32, 161 and 150 us.  Two to four barriers a step,
+// copies spread wider, MFMAs with A held: the same within 0.5 %.
+//
 // Fragments: L = (k + 1) / 2 low slices of both operands stay in registers for a step, the high ones pass through two
 // buffers, so that every fragment is fetched once per step and wave.  A wave holds as many 16 x 16 tiles as w chunk
 // sums leave room for in the 256 accumulation registers (ozimmu_resident.h).
@@ -109,7 +117,7 @@ constexpr Range chunk_range(int c)
 // where the rest has grown too long (8192^3, k = 16: 40.0 ms with three, 38.4 with five; k = 12 23.7 and 24.3).
 template <int K, int R, int TA, int TB, int D>
 struct Plan {
-    static constexpr int k = K, r = R, ta = TA, tb = TB, depth = D;
+    static constexpr int k = K, r = R, ta = TA, tb = TB, depth = D, HELD = 0;
     static constexpr int L = (K + 1) / 2;
     static constexpr int NP = K * (K + 1) / 2;
     static constexpr int W = num_chunks(K, R);
@@ -204,6 +212,366 @@ struct Plan {
     }
 };
 
+// The order of one inner step of k_held, made at compile time: H = held slices of A (an odd number, at least K / 2) stay in registers, the
+// slices of B pass by in two buffers.  First B_K with A_1, B_(K-1) with A_1 and A_2, ... down to B_1 with A_1 .. A_H; the others of A
+// take the places of the held ones as those are used up, B_1 stays for them; then B_2 .. B_(K-H) once more.  2 K - H - 1 slices of B
+// pass, an even number, so a slice finds the same buffer in every step.  Every slice of A is fetched once, B_2 .. B_(K-H) twice.
+//
+// A place in LDS holds one slice of a step; the copy of the next step's goes out once every wave has fetched it, at the next barrier,
+// and has landed at the barrier before it is fetched.  B_2 .. B_(K-H), fetched last in one step and early in the next, have two places.
+template <int K, int R, int TA, int TB, int H_>
+struct HeldPlan {
+    static constexpr int k = K, r = R, ta = TA, tb = TB, depth = 1, HELD = H_, H = H_;
+    static constexpr int L = (K + 1) / 2, NC = 1, NF = TA + TB;
+    static constexpr int NP = K * (K + 1) / 2, W = num_chunks(K, R), TT = TA * TB, NM = NP * TT;
+    static constexpr int NI = 3;                             // intervals (barriers) of a step
+    static constexpr int SEGS = 2 * K - H - 1;               // slices of B that pass
+    static constexpr int CA = (2 * TA + 3) / 4, CB = (2 * TB + 3) / 4, NCOPY = K * (CA + CB);  // copies per wave (16 rows, or 8)
+    static constexpr int ALT = K - H - 1;                    // slices of B with two places
+    static constexpr int NR = K * TA + SEGS * TB;            // fragments
+    static_assert(H % 2 == 1 && 2 * H >= K && H < K, "");
+
+    // LDS, in bytes: A_1 .. A_K, then B: B_1, B_(K-H+1) .. B_K, B_2 .. B_(K-H), the second places of those
+    static constexpr int A_BYTES = TA * 2048, B_BYTES = TB * 2048;
+    static constexpr int BYTES = K * (A_BYTES + B_BYTES) + ALT * B_BYTES;
+    static constexpr bool alternates(int t) { return t >= 2 && t <= K - H; }
+    static constexpr int place_b(int t) { return t == 1 ? 0 : t > K - H ? t - (K - H) : H + 1 + t - 2; }
+    // register place of a slice of A
+    static constexpr int place_a(int s) { return s <= H ? s - 1 : K - s; }
+
+    struct Read { int op = 0, slice = 0, frag = 0, to = 0, pos = 0; bool next = false; };
+    struct Copy { int op = 0, slice = 0, part = 0, pos = 0, ahead = 0; };
+    int s[NP] = {}, t[NP] = {}, seg[NP] = {};                // pairs
+    int seg_t[SEGS] = {}, seg_at[SEGS + 1] = {};             // first MFMA
+    Read reads[NR];
+    int read_first[NM + 1] = {};
+    Copy copies[NCOPY];
+    int copy_first[NM + 1] = {};
+    int border[NI + 1] = {}, wait[NI] = {};
+    int most_ahead = 0;
+    bool good = true;
+    int from = 0;                                            // first copy of the step after next's data
+
+    static constexpr int floor_div(int a, int b) { return a >= 0 ? a / b : -((b - 1 - a) / b); }
+    constexpr int interval_of(int pos) const
+    {
+        int v = 0;
+        while (v + 1 < NI && pos >= border[v + 1]) ++v;
+        return v;
+    }
+    // number of the interval that holds MFMA x, counted from the first of step 0 (x < 0: the steps before)
+    constexpr int interval_at(int x) const
+    {
+        const int step = floor_div(x, NM);
+        return step * NI + interval_of(x - step * NM);
+    }
+    constexpr HeldPlan()
+    {
+        int n = 0, g = 0, end_of_a[K + 1] = {};              // end_of_a: behind the last MFMA that uses a slice of A
+        auto pair = [&](int a, int b) {
+            s[n] = a, t[n] = b, seg[n] = g;
+            end_of_a[a] = ++n * TT;
+        };
+        auto open = [&](int b) { seg_t[g] = b, seg_at[g] = n * TT; };
+        for (int b = K; b >= 1; --b) {
+            open(b);
+            for (int a = 1; a <= H && a <= K + 1 - b; ++a) pair(a, b);
+            if (b == 1)
+                for (int a = K; a > H; --a) pair(a, 1);
+            ++g;
+        }
+        for (int b = 2; b <= K - H; ++b) {
+            open(b);
+            for (int a = K + 1 - b; a > H; --a) pair(a, b);
+            ++g;
+        }
+        seg_at[SEGS] = NM;
+        good = good && n == NP && g == SEGS;
+
+        // fetches: a slice of B while the one before passes, a slice of A once its place is free
+        int at[NM] = {}, count = 0;
+        Read list[NR];
+        auto put = [&](int op, int slice, int frag, int to, bool next, int from, int limit) {
+            int pos = from;
+            while (pos < limit - 1 && at[pos] > 0) ++pos;
+            if (at[pos] > 0) pos = from;
+            ++at[pos];
+            list[count].op = op, list[count].slice = slice, list[count].frag = frag, list[count].to = to, list[count].next = next;
+            list[count++].pos = pos;
+            return pos;
+        };
+        int b_first[SEGS] = {}, b_last[SEGS] = {}, a_first[K + 1] = {}, a_last[K + 1] = {};
+        for (int q = 0; q < SEGS; ++q) {
+            const int before = q == 0 ? SEGS - 1 : q - 1, len = seg_at[before + 1] - seg_at[before];
+            const int stride = len / (TB + 1) > 2 ? 2 : 1;
+            int from = seg_at[before];
+            for (int x = 0; x < TB; ++x) {
+                const int pos = put(1, seg_t[q], x, q & 1, q == 0, from, seg_at[before + 1]);
+                if (x == 0) b_first[q] = pos;
+                b_last[q] = pos;
+                from = pos + stride < seg_at[before + 1] ? pos + stride : seg_at[before + 1] - 1;
+            }
+        }
+        for (int a = 1; a <= K; ++a) {
+            // (its place belongs to K + 1 - a before)
+            int from = a > H ? end_of_a[K + 1 - a] : a <= K - H ? end_of_a[K + 1 - a] : end_of_a[a];
+            bool next = a <= H;
+            if (from + 2 * TA >= NM) from = 0, next = false;  // (the place that comes free last: early in the step itself)
+            for (int x = 0; x < TA; ++x) {
+                const int pos = put(0, a, x, place_a(a), next, from, NM);
+                if (x == 0) a_first[a] = pos;
+                a_last[a] = pos;
+                from = pos + 2 < NM ? pos + 2 : NM - 1;
+            }
+        }
+        good = good && count == NR;
+        // in the order of their places
+        int out = 0;
+        for (int q = 0; q < NM; ++q) {
+            read_first[q] = out;
+            for (int x = 0; x < NR; ++x)
+                if (list[x].pos == q) reads[out++] = list[x];
+        }
+        read_first[NM] = out;
+
+        // barriers: about a third of a step each, not where a slice is half fetched and best not just behind a fetch
+        border[NI] = NM;
+        for (int v = 1; v < NI; ++v) {
+            int best = -1, best_cost = 0;
+            for (int q = border[v - 1] + NM / (2 * NI); q < NM * v / NI + NM / (2 * NI); ++q) {
+                int cost = q > NM * v / NI ? q - NM * v / NI : NM * v / NI - q;
+                for (int x = 0; x < SEGS; ++x)
+                    if (b_first[x] < q && q <= b_last[x]) cost += 1000;
+                for (int a = 1; a <= K; ++a)
+                    if (a_first[a] < q && q <= a_last[a]) cost += 1000;
+                for (int x = read_first[q - 6 > 0 ? q - 6 : 0]; x < read_first[q]; ++x) cost += 8;
+                if (best < 0 || cost < best_cost) best = q, best_cost = cost;
+            }
+            border[v] = best;
+        }
+
+        // copies: first and last fetch of a step's data, in MFMAs from the begin of that step
+        int first[2 * K] = {}, last[2 * K] = {}, issue[2 * K] = {};
+        for (int i = 0; i < 2 * K; ++i) first[i] = NM, last[i] = -NM;
+        for (int x = 0; x < NR; ++x) {
+            const int i = reads[x].op * K + reads[x].slice - 1, pos = reads[x].pos - (reads[x].next ? NM : 0);
+            first[i] = pos < first[i] ? pos : first[i];
+            last[i] = pos > last[i] ? pos : last[i];
+        }
+        for (int i = 0; i < 2 * K; ++i) {
+            // (step 0's data goes out in this interval)
+            issue[i] = interval_at(last[i]) - (i >= K && alternates(i - K + 1) ? 2 : 1) * NI + 1;
+            good = good && issue[i] < interval_at(first[i]);
+        }
+        int seq[2 * K] = {}, nc = 0, before_interval[NI + 1] = {};
+        for (int v = 0; v < NI; ++v) {
+            before_interval[v] = nc;
+            int total = 0, x = 0;
+            for (int i = 0; i < 2 * K; ++i)
+                if (issue[i] - floor_div(issue[i], NI) * NI == v) total += i < K ? CA : CB;
+            const int len = border[v + 1] - border[v];
+            int stride = len / (total + 2);
+            stride = stride > 4 ? 4 : stride < 1 ? 1 : stride;
+            for (int slack = 1; slack <= 3 * NI; ++slack)     // (what is needed first goes first)
+                for (int i = 0; i < 2 * K; ++i) {
+                    if (issue[i] - floor_div(issue[i], NI) * NI != v || interval_at(first[i]) - issue[i] != slack) continue;
+                    for (int part = 0; part < (i < K ? CA : CB); ++part, ++x) {
+                        Copy& c = copies[nc++];
+                        c.op = i < K ? 0 : 1, c.slice = i % K + 1, c.part = part;
+                        c.pos = border[v] + (x * stride + 1 < len ? x * stride + 1 : len - 1);
+                        c.ahead = -floor_div(issue[i], NI);
+                        most_ahead = c.ahead > most_ahead ? c.ahead : most_ahead;
+                        good = good && c.ahead >= 0;
+                    }
+                    seq[i] = nc - 1;
+                }
+            good = good && x == total;
+        }
+        before_interval[NI] = nc;
+        good = good && nc == NCOPY && most_ahead <= 2;
+        while (from < NCOPY && copies[from].ahead < 2) ++from;
+        int at_copy = 0;
+        for (int q = 0; q < NM; ++q) {
+            copy_first[q] = at_copy;
+            while (at_copy < NCOPY && copies[at_copy].pos == q) ++at_copy;
+        }
+        copy_first[NM] = at_copy;
+        good = good && at_copy == NCOPY;
+        // copies that may still be on their way when an interval opens
+        for (int v = 0; v < NI; ++v) wait[v] = 63;
+        for (int i = 0; i < 2 * K; ++i) {
+            const int f = interval_at(first[i]), step = floor_div(f, NI), v = f - step * NI;
+            const int sent = step * NCOPY + before_interval[v], needed = floor_div(issue[i], NI) * NCOPY + seq[i] + 1;
+            good = good && sent >= needed;
+            if (sent - needed < wait[v]) wait[v] = sent - needed;
+        }
+    }
+};
+
+// The operands and the loop of k_held.  Copies: a slice's 2 TA or 2 TB pieces of 16 rows go to its place, TA / 2 or TB / 2 of them by each
+// wave, all with one M0; of a last two, which four waves share, each brings half, with half of its lanes (6 pieces as 8, two of
+// them brought twice, move a third more: 96 x 96 tiles, k = 9, then took as long as 64 x 128).
+template <class P>
+struct Held {
+    static constexpr P plan{};
+    static constexpr int K = P::k, TA = P::ta, TB = P::tb, H = P::H, WHOLE[2] = {TA / 2, TB / 2};
+    const int8_t* base[2];                       // A, B: the row block of the tile's first row
+    uint32_t from[2][2];                         // a lane's part of the wave's pieces from there: whole ones, the shared one
+    uint32_t m0[2], m0_half[2];
+    uint32_t even, odd, two_places;              // the slices of two places: that of the step's parity, the other one, both together
+    uint64_t half;                               // lanes of a shared copy
+    uint32_t at_a, at_b, at_two, at_two_sum;     // fragments of A, B, and B's slices of two places
+    v4i fa[H][TA], fb[2][TB];
+
+    template <int X>
+    __device__ __attribute__((always_inline)) inline void copy(const ozk::ResidentArgs& a, bool second, uint32_t step)
+    {
+        constexpr auto c = plan.copies[X];
+        constexpr int off = c.op ? P::place_b(c.slice) * P::B_BYTES : (c.slice - 1) * P::A_BYTES;
+        const int8_t* const slice = base[c.op] + (int64_t)(c.slice - 1) * (c.op ? a.strideB : a.strideA);
+        const uint32_t at = from[c.op][c.part == WHOLE[c.op] ? 1 : 0] + step;
+        const uint32_t place = c.op && P::alternates(c.slice) ? (second ? odd : even) : 0u;
+        if constexpr (c.part == WHOLE[c.op]) {
+            const uint32_t m = m0_half[c.op] + place;
+            const uint64_t lanes = half;
+            // (all lanes take part in everything else)
+            asm volatile("s_add_u32 m0, %0, %1\n\ts_mov_b64 exec, %4\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, -1" ::"s"(m), "n"(off),
+                         "v"(at), "s"(slice), "s"(lanes)
+                         : "memory", "scc");
+        } else if constexpr (c.part == 0) {
+            const uint32_t m = m0[c.op] + place;
+            asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" ::"s"(m), "n"(off), "v"(at), "s"(slice)
+                         : "memory", "scc");
+        } else {
+            // (the offset moves both addresses; two whole pieces a wave: tiles of 128, whose pieces lie one behind the other)
+            asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" ::"v"(at), "s"(slice), "n"(c.part * 1024) : "memory");
+        }
+    }
+    template <int X>
+    __device__ __attribute__((always_inline)) inline void fetch()
+    {
+        constexpr auto r = plan.reads[X];
+        if constexpr (r.op == 0)
+            fa[r.to][r.frag] = *(lds_v4i_ptr)(uintptr_t)(at_a + ((r.slice - 1) * P::A_BYTES + r.frag * 1024));
+        else if constexpr (P::alternates(r.slice))
+            fb[r.to][r.frag] = *(lds_v4i_ptr)(uintptr_t)(at_two + ((r.slice - 2) * P::B_BYTES + r.frag * 1024));
+        else
+            fb[r.to][r.frag] = *(lds_v4i_ptr)(uintptr_t)(at_b + (P::place_b(r.slice) * P::B_BYTES + r.frag * 1024));
+    }
+    // addresses, and step 0's slices on their way
+    __device__ __attribute__((always_inline)) inline void begin(const ozk::ResidentArgs& a, uint32_t lds_base, uint32_t row0, uint32_t col0,
+                                                                int wave, int lane)
+    {
+        // (r >= 2: at most 65536 inner positions, a row block 16 MiB)
+        static_assert(P::r > 1, "");
+        const uint32_t rowblk = (uint32_t)rowblock_bytes(a.KT);
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            const uint32_t row0_o = o ? col0 : row0, top = (uint32_t)(o ? a.pstrideB : a.pstrideA) - 16u;  // (padded rows of the stack)
+            const uint32_t block0 = (row0_o < top ? row0_o : top) / TILE_R;
+            const int piece[2] = {wave * WHOLE[o], 4 * WHOLE[o] + (wave >> 1)};
+            const uint32_t lds = lds_base + (o ? (uint32_t)(K * P::A_BYTES) : 0u);
+            m0[o] = lds + (uint32_t)piece[0] * 1024u;
+            m0_half[o] = lds + (uint32_t)piece[1] * 1024u;
+            base[o] = (o ? a.SB : a.SA) + (int64_t)block0 * rowblk;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                uint32_t row = row0_o + (uint32_t)piece[q] * 16u;
+                row = row < top ? row : top;  // a tile may reach past the padding: what it reads there is never stored
+                from[o][q] = (row / TILE_R - block0) * rowblk + row % TILE_R * TILE_K + (uint32_t)lane * 16u;
+            }
+        }
+        half = (wave & 1) ? 0xffffffff00000000ull : 0x00000000ffffffffull;
+        even = 0, odd = P::ALT * P::B_BYTES, two_places = odd;
+        asm volatile("" : "+s"(two_places), "+s"(half));
+        const int chunk = (0x9c >> (2 * (lane >> 4))) & 3;  // 0, 3, 1, 2 (see run_tile)
+        const int ra = (wave >> 1) * (16 * TA) + (lane & 15), rb = (wave & 1) * (16 * TB) + (lane & 15);
+        at_a = lds_base + ra * TILE_K + swizzle(ra, chunk) * CHUNK;
+        at_b = lds_base + K * P::A_BYTES + rb * TILE_K + swizzle(rb, chunk) * CHUNK;
+        at_two = at_b + (H + 1) * P::B_BYTES;
+        at_two_sum = 2 * at_two + P::ALT * P::B_BYTES;
+        asm volatile("" : "+v"(at_a), "+v"(at_b), "+v"(at_two), "+v"(at_two_sum));
+        // (but for those whose copies the loop's first interval sends out)
+        static_for<P::NCOPY>([&](auto X) __attribute__((always_inline)) {
+            constexpr int x = decltype(X)::value;
+            if constexpr (plan.copies[x].ahead > 0) copy<x>(a, false, 0u);
+        });
+    }
+    // (step 0's slices have landed, every wave's)
+    template <class ACC>
+    __device__ __attribute__((always_inline)) inline void loop(const ozk::ResidentArgs& a, ACC& acc, int KT)
+    {
+        static_assert(plan.good, "order of a step");
+        auto step_off = [&](int kt) { return (uint32_t)(kt < KT - 1 ? kt : KT - 1) * (uint32_t)TILE_BYTES; };
+        // What the step before would have fetched, and then its copies from the first of step 1's on, in the order of the loop, so that
+        // its counted waits hold from the start (some bring the same bytes to the same place again).
+        static_for<P::NR>([&](auto X) __attribute__((always_inline)) {
+            constexpr int x = decltype(X)::value;
+            if constexpr (plan.reads[x].next) fetch<x>();
+        });
+        wait_lds();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        static_for<P::NCOPY - plan.from>([&](auto X) __attribute__((always_inline)) {
+            constexpr int x = plan.from + decltype(X)::value, ahead = plan.copies[x].ahead;
+            if constexpr (ahead > 0) copy<x>(a, ahead == 2, step_off(ahead - 1));
+        });
+        // where the copies of a step read: this step, the next one, the one after (past the end: the last step again, never used)
+        uint32_t s0 = 0, s1 = step_off(1), s2 = step_off(2);
+        for (int kt = 0; kt < KT; ++kt) {
+            static_for<P::NM>([&](auto Q) __attribute__((always_inline)) {
+                constexpr int q = decltype(Q)::value, v = plan.interval_of(q);
+                if constexpr (plan.border[v] == q) {
+                    wait_lds();
+                    wait_vmcnt<plan.wait[v]>();
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                static_for<plan.read_first[q + 1] - plan.read_first[q]>([&](auto X) __attribute__((always_inline)) {
+                    fetch<plan.read_first[q] + decltype(X)::value>();
+                });
+                static_for<plan.copy_first[q + 1] - plan.copy_first[q]>([&](auto X) __attribute__((always_inline)) {
+                    constexpr int x = plan.copy_first[q] + decltype(X)::value, ahead = plan.copies[x].ahead;
+                    copy<x>(a, ahead == 1, ahead == 0 ? s0 : ahead == 1 ? s1 : s2);
+                });
+                constexpr int pr = q / P::TT, m = q % P::TT;
+                constexpr int j = m / TA, i = (j & 1) ? TA - 1 - m % TA : m % TA;
+                constexpr int c = chunk_of(plan.s[pr], plan.t[pr], P::r);
+                const v4i x = fa[P::place_a(plan.s[pr])][i], y = fb[plan.seg[pr] & 1][j];
+                // (in place, see k_extended: the compiler sees no matrix instruction)
+                if constexpr ((c * TB + j) * TA + i >= ozr::ACC_TILES)
+                    asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(acc[c][i][j]) : "v"(x), "v"(y));
+                else
+                    asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc[c][i][j]) : "v"(x), "v"(y));
+                // (in gaps between two MFMAs, behind the last fetch of the slices of two places and behind the last copy)
+                if constexpr (q == P::NM - 3) {
+                    at_two = at_two_sum - at_two;
+                    asm volatile("" : "+v"(at_two));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            even = odd;
+            odd = two_places - even;
+            s0 = s1;
+            s1 = s2;
+            s2 = step_off(kt + 3);
+        }
+    }
+};
+
+// Copies of what interval V reads in `step` (a low slice for the step after).
+template <class P, int V, int STEP, class COPY_SLICE, class STEP_OFF>
+__device__ __attribute__((always_inline)) inline void copy_interval(COPY_SLICE&& copy_slice, STEP_OFF&& step_off, uint32_t m0_cur, uint32_t m0_nxt,
+                                                                    uint32_t lv)
+{
+    static constexpr P plan{};
+    static_for<plan.nslot[V]>([&](auto X) __attribute__((always_inline)) {
+        constexpr int x = decltype(X)::value, data = STEP + (plan.slot_next[V][x] ? 1 : 0);
+        copy_slice(std::integral_constant<int, plan.slot_slice[V][x]>{}, (data & 1) ? m0_nxt : m0_cur, lv + step_off(data));
+    });
+}
+
 // What becomes of a tile's sums: added up into D with one exponent per row and column, or (r = 1) per row, column and slice; or left in
 // memory as the sums of a part of the inner dimension.  Kernels of their own, each with one of them: an end that a call does not take
 // costs it all the same (the second in the kernels of the first: 3 to 5 % of whole calls of short inner dimensions, 140388 x 4 x 8,
@@ -216,10 +584,15 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     constexpr bool CUT = END == End::PART, PER_SLICE = END == End::PER_SLICE;
     static constexpr P plan{};
     constexpr int K = P::k, R = P::r, TA = P::ta, TB = P::tb, D = P::depth;
-    constexpr int L = P::L, W = P::W, NF = P::NF, NI = P::NI;
+    constexpr int L = P::L, W = P::W, NF = P::NF, NI = P::NI, HELD = P::HELD;
     constexpr int RA = 32 * TA, RB = 32 * TB;               // rows and columns of the workgroup's tile
     constexpr int SLOT = (RA + RB) * TILE_K;                // one slice of both operands: A rows, then B columns
-    constexpr int SET = K * SLOT;                           // all slices of an inner step
+    constexpr int SET = [] {                                // all slices of an inner step
+        if constexpr (P::HELD > 0)
+            return P::BYTES;
+        else
+            return K * SLOT;
+    }();
     extern __shared__ __align__(16) int8_t lds[];
     int* const lds_exp = reinterpret_cast<int*>(lds + D * SET);  // exponents of the tile's rows, then columns
 
@@ -365,18 +738,14 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     }
     // Copies of the first steps in the order of the loop, so that its counted waits hold from the start: what interval v
     // reads in `step` (a low slice for the step after).  Before that, the low slices 2 .. L of step 0 themselves.
-    auto copy_interval = [&](auto V, auto STEP) __attribute__((always_inline)) {
-        constexpr int v = decltype(V)::value;
-        static_for<plan.nslot[v]>([&](auto X) __attribute__((always_inline)) {
-            constexpr int x = decltype(X)::value, data = decltype(STEP)::value + (plan.slot_next[v][x] ? 1 : 0);
-            copy_slice(std::integral_constant<int, plan.slot_slice[v][x]>{}, (data & 1) ? m0_nxt : m0_cur, lv + step_off(data));
+    if constexpr (HELD == 0) {
+        static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
+            copy_slice(std::integral_constant<int, L - decltype(X)::value>{}, m0_cur, lv);
         });
-    };
-    constexpr std::integral_constant<int, 0> step0{};
-    static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
-        copy_slice(std::integral_constant<int, L - decltype(X)::value>{}, m0_cur, lv);
-    });
-    static_for<D == 2 ? NI : 1>([&](auto V) __attribute__((always_inline)) { copy_interval(V, step0); });
+        static_for<D == 2 ? NI : 1>([&](auto V) __attribute__((always_inline)) { copy_interval<P, decltype(V)::value, 0>(copy_slice, step_off, m0_cur, m0_nxt, lv); });
+    }
+    std::conditional_t<(HELD > 0), Held<P>, int> held;
+    if constexpr (HELD > 0) held.begin(a, lds_base, row0, col0, wave, lane);
     if (t < RA) lds_exp[t] = exp_row;
     if (t < RB) lds_exp[RA + t] = exp_col;
     // The accumulators of a chunk start at -(ra[row] + cb[column]) (see the head of ozimmu_gemm.hip); the inner positions
@@ -409,106 +778,110 @@ __device__ __attribute__((always_inline)) inline void run_tile(const ozk::Reside
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
-        constexpr int s = L - decltype(X)::value;
-        static_for<NF>([&](auto F) __attribute__((always_inline)) { fetch(std::integral_constant<int, s>{}, F, std::false_type{}); });
-    });
-    wait_lds();
-    __builtin_amdgcn_s_barrier();  // every wave has the low slices of step 0: their slots are free
-    asm volatile("" ::: "memory");
-    if constexpr (D == 2)
-        static_for<NI - 1>([&](auto V) __attribute__((always_inline)) { copy_interval(V, std::integral_constant<int, 1>{}); });
-    else if constexpr (NI > 2)
-        static_for<NI - 2>([&](auto V) __attribute__((always_inline)) {
-            copy_interval(std::integral_constant<int, decltype(V)::value + 1>{}, step0);
+    if constexpr (HELD == 0) {
+        static_for<L - 1>([&](auto X) __attribute__((always_inline)) {
+            constexpr int s = L - decltype(X)::value;
+            static_for<NF>([&](auto F) __attribute__((always_inline)) { fetch(std::integral_constant<int, s>{}, F, std::false_type{}); });
         });
+        wait_lds();
+        __builtin_amdgcn_s_barrier();  // every wave has the low slices of step 0: their slots are free
+        asm volatile("" ::: "memory");
+        if constexpr (D == 2)
+            static_for<NI - 1>([&](auto V) __attribute__((always_inline)) { copy_interval<P, decltype(V)::value, 1>(copy_slice, step_off, m0_cur, m0_nxt, lv); });
+        else if constexpr (NI > 2)
+            static_for<NI - 2>([&](auto V) __attribute__((always_inline)) {
+                copy_interval<P, decltype(V)::value + 1, 0>(copy_slice, step_off, m0_cur, m0_nxt, lv);
+            });
 
-    uint32_t m0_sum = m0_cur + m0_nxt, fsum[2][2];
+        uint32_t m0_sum = m0_cur + m0_nxt, fsum[2][2];
 #pragma unroll
-    for (int o = 0; o < 2; ++o)
+        for (int o = 0; o < 2; ++o)
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-            fsum[o][f] = fcur[o][f] + fnxt[o][f];
-            if (D == 2) asm volatile("" : "+v"(fsum[o][f]));
-        }
-    if (D == 2) asm volatile("" : "+s"(m0_sum));
-    // where the copies of a step read: what is fetched for this step is followed by step kt + D in its place (v1), what is
-    // fetched for the next one by step kt + 1 + D (v2; past the end: the last step again, never used)
-    // (v0: v1 of the step before, for what the last interval of that step read for itself)
-    uint32_t v0 = lv + step_off(D - 1), v1 = lv + step_off(D), v2 = v1;
-    for (int kt = 0; kt < KT; ++kt) {
-        static_for<P::NM>([&](auto Q) __attribute__((always_inline)) {
-            constexpr int q = decltype(Q)::value;
-            constexpr int gi = plan.group_of[q], v = plan.interval_of[q], vp = (v + NI - 1) % NI;
-            if constexpr (plan.opens[q]) {
-                // what this interval reads has landed, and every wave has what the interval before read
-                wait_lds();
-                wait_vmcnt<P::NC * (D * K - plan.nslot[v] - plan.nslot[vp])>();
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_sched_barrier(0);
+            for (int f = 0; f < 2; ++f) {
+                fsum[o][f] = fcur[o][f] + fnxt[o][f];
+                if (D == 2) asm volatile("" : "+v"(fsum[o][f]));
             }
-            if constexpr (plan.group_at[0] + 2 == q) {
-                // what the step needs from its second group on, and the next step from its start (in a gap between two
-                // MFMAs: at the end of the loop it would make a bubble of a dozen instructions)
-                v2 = lv + step_off(kt + 1 + D);
-                asm volatile("" : "+v"(v2));
-            }
-            if constexpr (D == 2 && plan.group_at[0] + 3 == q) {
-                fnxt[0][0] = fsum[0][0] - fcur[0][0];
-                fnxt[1][0] = fsum[1][0] - fcur[1][0];
-                asm volatile("" : "+v"(fnxt[0][0]), "+v"(fnxt[1][0]));
-                if constexpr (SET > 61440) {
-                    fnxt[0][1] = fsum[0][1] - fcur[0][1];
-                    fnxt[1][1] = fsum[1][1] - fcur[1][1];
-                    asm volatile("" : "+v"(fnxt[0][1]), "+v"(fnxt[1][1]));
+        if (D == 2) asm volatile("" : "+s"(m0_sum));
+        // where the copies of a step read: what is fetched for this step is followed by step kt + D in its place (v1), what is
+        // fetched for the next one by step kt + 1 + D (v2; past the end: the last step again, never used)
+        // (v0: v1 of the step before, for what the last interval of that step read for itself)
+        uint32_t v0 = lv + step_off(D - 1), v1 = lv + step_off(D), v2 = v1;
+        for (int kt = 0; kt < KT; ++kt) {
+            static_for<P::NM>([&](auto Q) __attribute__((always_inline)) {
+                constexpr int q = decltype(Q)::value;
+                constexpr int gi = plan.group_of[q], v = plan.interval_of[q], vp = (v + NI - 1) % NI;
+                if constexpr (plan.opens[q]) {
+                    // what this interval reads has landed, and every wave has what the interval before read
+                    wait_lds();
+                    wait_vmcnt<P::NC * (D * K - plan.nslot[v] - plan.nslot[vp])>();
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+                if constexpr (plan.group_at[0] + 2 == q) {
+                    // what the step needs from its second group on, and the next step from its start (in a gap between two
+                    // MFMAs: at the end of the loop it would make a bubble of a dozen instructions)
+                    v2 = lv + step_off(kt + 1 + D);
+                    asm volatile("" : "+v"(v2));
+                }
+                if constexpr (D == 2 && plan.group_at[0] + 3 == q) {
+                    fnxt[0][0] = fsum[0][0] - fcur[0][0];
+                    fnxt[1][0] = fsum[1][0] - fcur[1][0];
+                    asm volatile("" : "+v"(fnxt[0][0]), "+v"(fnxt[1][0]));
+                    if constexpr (SET > 61440) {
+                        fnxt[0][1] = fsum[0][1] - fcur[0][1];
+                        fnxt[1][1] = fsum[1][1] - fcur[1][1];
+                        asm volatile("" : "+v"(fnxt[0][1]), "+v"(fnxt[1][1]));
+                    }
+                }
+                static_for<plan.reads[q]>([&](auto X) __attribute__((always_inline)) {
+                    constexpr int x = plan.read_at[q] + decltype(X)::value;
+                    constexpr int sl = plan.read_slice[gi][x / NF];
+                    // (the operand that is needed first comes first: B of a low slice, A of a high one)
+                    constexpr int f = sl <= L ? (x % NF + TA) % NF : x % NF;
+                    fetch(std::integral_constant<int, sl>{}, std::integral_constant<int, f>{},
+                          std::integral_constant<bool, plan.read_next[gi][x / NF]>{});
+                });
+                static_for<plan.copies[q]>([&](auto X) __attribute__((always_inline)) {
+                    constexpr int x = plan.copy_at[q] + decltype(X)::value, y = x / P::NC;
+                    constexpr int sl = plan.slot_slice[vp][y];
+                    // the first interval replaces what the last one of the step before read
+                    constexpr bool next = plan.slot_next[vp][y];
+                    constexpr int ahead = (next ? 1 : 0) - (v == 0 ? 1 : 0);  // -1, 0, 1: v0, v1, v2
+                    copy(std::integral_constant<int, sl>{}, std::integral_constant<int, x % P::NC>{}, ahead == 0 ? m0_cur : m0_nxt,
+                         ahead < 0 ? v0 : ahead == 0 ? v1 : v2);
+                });
+                constexpr int pr = q / P::TT, m = q % P::TT;
+                constexpr int s = plan.s[pr], u = plan.t[pr];
+                // (back and forth, so that consecutive MFMAs share an operand)
+                constexpr int j = m / TA, i = (j & 1) ? TA - 1 - m % TA : m % TA;
+                constexpr int c = chunk_of(s, u, R);
+                const v4i fa = s <= L ? low[s <= L ? s : 0][i] : hi[(s - L - 1) & 1][i];
+                const v4i fb = u <= L ? low[u <= L ? u : 0][TA + j] : hi[(u - L - 1) & 1][TA + j];
+                // (in place: the compiler sees no matrix instruction; the wait states that its result asks for come after the loop)
+                if constexpr (!IN_PLACE)
+                    acc[c][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, acc[c][i][j], 0, 0, 0);
+                else if constexpr (ordinary(c, i, j))
+                    asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(acc[c][i][j]) : "v"(fa), "v"(fb));
+                else
+                    asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc[c][i][j]) : "v"(fa), "v"(fb));
+                // (an MFMA touches no memory: without a use in the order of the asm statements instruction selection may gather
+                // all fetches and copies of the step in front of all MFMAs)
+                // (with one set of operands it does not, and the use would cost moves of accumulators)
+                if constexpr (D == 2 && !IN_PLACE) asm volatile("" ::"a"(acc[c][i][j]));
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            v0 = v1;
+            v1 = v2;
+            if constexpr (D == 2) {
+                m0_cur = m0_nxt;
+                m0_nxt = m0_sum - m0_cur;
+                fcur[0][0] = fnxt[0][0], fcur[0][1] = fnxt[0][1];
+                fcur[1][0] = fnxt[1][0], fcur[1][1] = fnxt[1][1];
             }
-            static_for<plan.reads[q]>([&](auto X) __attribute__((always_inline)) {
-                constexpr int x = plan.read_at[q] + decltype(X)::value;
-                constexpr int sl = plan.read_slice[gi][x / NF];
-                // (the operand that is needed first comes first: B of a low slice, A of a high one)
-                constexpr int f = sl <= L ? (x % NF + TA) % NF : x % NF;
-                fetch(std::integral_constant<int, sl>{}, std::integral_constant<int, f>{},
-                      std::integral_constant<bool, plan.read_next[gi][x / NF]>{});
-            });
-            static_for<plan.copies[q]>([&](auto X) __attribute__((always_inline)) {
-                constexpr int x = plan.copy_at[q] + decltype(X)::value, y = x / P::NC;
-                constexpr int sl = plan.slot_slice[vp][y];
-                // the first interval replaces what the last one of the step before read
-                constexpr bool next = plan.slot_next[vp][y];
-                constexpr int ahead = (next ? 1 : 0) - (v == 0 ? 1 : 0);  // -1, 0, 1: v0, v1, v2
-                copy(std::integral_constant<int, sl>{}, std::integral_constant<int, x % P::NC>{}, ahead == 0 ? m0_cur : m0_nxt,
-                     ahead < 0 ? v0 : ahead == 0 ? v1 : v2);
-            });
-            constexpr int pr = q / P::TT, m = q % P::TT;
-            constexpr int s = plan.s[pr], u = plan.t[pr];
-            // (back and forth, so that consecutive MFMAs share an operand)
-            constexpr int j = m / TA, i = (j & 1) ? TA - 1 - m % TA : m % TA;
-            constexpr int c = chunk_of(s, u, R);
-            const v4i fa = s <= L ? low[s <= L ? s : 0][i] : hi[(s - L - 1) & 1][i];
-            const v4i fb = u <= L ? low[u <= L ? u : 0][TA + j] : hi[(u - L - 1) & 1][TA + j];
-            // (in place: the compiler sees no matrix instruction; the wait states that its result asks for come after the loop)
-            if constexpr (!IN_PLACE)
-                acc[c][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa, fb, acc[c][i][j], 0, 0, 0);
-            else if constexpr (ordinary(c, i, j))
-                asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+v"(acc[c][i][j]) : "v"(fa), "v"(fb));
-            else
-                asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc[c][i][j]) : "v"(fa), "v"(fb));
-            // (an MFMA touches no memory: without a use in the order of the asm statements instruction selection may gather
-            // all fetches and copies of the step in front of all MFMAs)
-            // (with one set of operands it does not, and the use would cost moves of accumulators)
-            if constexpr (D == 2 && !IN_PLACE) asm volatile("" ::"a"(acc[c][i][j]));
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        v0 = v1;
-        v1 = v2;
-        if constexpr (D == 2) {
-            m0_cur = m0_nxt;
-            m0_nxt = m0_sum - m0_cur;
-            fcur[0][0] = fnxt[0][0], fcur[0][1] = fnxt[0][1];
-            fcur[1][0] = fnxt[1][0], fcur[1][1] = fnxt[1][1];
         }
+    } else {
+        held.loop(a, acc, KT);
     }
     wait_vmcnt<0>();  // no copy may still be writing LDS when the workgroup ends
     if constexpr (IN_PLACE) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
@@ -700,6 +1073,12 @@ __global__ __launch_bounds__(256, 1) void k_extended(ozk::ResidentArgs a)
 {
     run_tile<Plan<K, R, TA, TB, D>, 1, true, End::COMMON>(a);
 }
+// k_extended's way with H slices of A held and those of B passing by (HeldPlan).
+template <int K, int R, int TA, int TB, int H>
+__global__ __launch_bounds__(256, 1) void k_held(ozk::ResidentArgs a)
+{
+    run_tile<HeldPlan<K, R, TA, TB, H>, 1, true, End::COMMON>(a);
+}
 // One scale per slice: k_resident or k_extended with the exponents of every slice.
 template <int K, int TA, int TB, int D, int WAVES, bool IN_PLACE>
 __global__ __launch_bounds__(256, WAVES) void k_per_slice(ozk::ResidentArgs a)
@@ -723,7 +1102,9 @@ hipError_t launch(const ozk::ResidentArgs& a_in, hipStream_t st)
         static_assert(smem <= 160 * 1024, "LDS of a compute unit");
         // [0]: whole tiles, one exponent per row and column; then, where there is one, the kernel for a scale per slice, for parts
         const void* kernels[3] = {};
-        if constexpr (V == ozr::EXTENDED)
+        if constexpr (V == ozr::HELD)
+            kernels[0] = reinterpret_cast<const void*>(&k_held<K, R, c.ta, c.tb, c.held>);
+        else if constexpr (V == ozr::EXTENDED)
             kernels[0] = reinterpret_cast<const void*>(&k_extended<K, R, c.ta, c.tb, c.depth>);
         else
             kernels[0] = reinterpret_cast<const void*>(&k_resident<K, R, c.ta, c.tb, c.depth, c.waves>);
@@ -756,6 +1137,7 @@ hipError_t launch_r(const ozk::ResidentArgs& a, int variant, hipStream_t st)
         case 4: return launch<K, R, 4>(a, st);
         case 5: return launch<K, R, 5>(a, st);
         case ozr::EXTENDED: return launch<K, R, ozr::EXTENDED>(a, st);
+        case ozr::HELD: return launch<K, R, ozr::HELD>(a, st);
         default: return hipErrorInvalidValue;
     }
 }
