@@ -316,6 +316,7 @@ enum { OZIMMU_WAY_SMALL = 0,          /* the whole call in one launch */
 enum { OZIMMU_SPLIT_WAY_NONE = 0,     /* part of the one launch */
        OZIMMU_SPLIT_WAY_WHOLE = 1,    /* workgroups own whole vectors */
        OZIMMU_SPLIT_WAY_CUT = 2,      /* two launches along the inner dimension */
+       OZIMMU_SPLIT_WAY_CUT_COLUMNS = 4, /* columns in two launches along the inner dimension, rows whole */
        OZIMMU_SPLIT_WAY_PASSES = 3 }; /* one scale per slice of vectors too long for registers: a pass per slice */
 typedef struct {
     int way, tile, parts, split_way;

@@ -1040,9 +1040,10 @@ int ozimmu_choose(int64_t m, int64_t n, int64_t p, int k, int split_mode, int ac
     const int64_t capacity = block_capacity(m, n, p, k, workspace_bytes);
     if (per_slice) {
         out->split_way = n <= ozk::PER_SLICE_MAX_INNER ? OZIMMU_SPLIT_WAY_WHOLE : OZIMMU_SPLIT_WAY_PASSES;
-    } else if (short_product(m, n, p, k)) {
+    } else {
         const ozk::SplitIn ops[2] = {{nullptr, n, m, n, 0, 0, nullptr, nullptr}, {nullptr, p, p, n, 1, 0, nullptr, nullptr}};
-        if (ozk::split_is_cut(ops, 2, k, (size_t)(capacity * BLOCK_BYTES))) out->split_way = OZIMMU_SPLIT_WAY_CUT;
+        const int cut = ozk::split_cut(ops, 2, k, (size_t)(capacity * BLOCK_BYTES), short_product(m, n, p, k));
+        if (cut) out->split_way = cut == 1 ? OZIMMU_SPLIT_WAY_CUT : OZIMMU_SPLIT_WAY_CUT_COLUMNS;
     }
     const Way way = choose_way(m, n, p, k, (int)(r < k ? r : k), per_slice, 0, capacity, num_cu);
     if (way.kind == Way::RESIDENT) {

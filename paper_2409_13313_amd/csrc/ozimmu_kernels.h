@@ -29,8 +29,8 @@ struct SplitIn {
 // their offsets then (where the product that follows is so short that the offsets do not matter); nullptr: none
 hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st,
                         uint32_t* also_zero = nullptr, int also_zero_count = 0, void* room = nullptr, size_t room_bytes = 0);
-// whether two operands go through `room` of that many bytes
-bool split_is_cut(const SplitIn* ops, int count, int k, size_t room_bytes);
+// 1: two operands go through `room` of that many bytes (the product is short); 2: their columns are cut along the inner dimension; 0: neither
+int split_cut(const SplitIn* ops, int count, int k, size_t room_bytes, bool short_product);
 // Algorithm 5: round-to-nearest slices with one scale per slice.  e holds k arrays of exponents (slice-major);
 // rem is scratch for the remainders: m x inner_padded(n) doubles for A, n x p doubles for B.
 hipError_t launch_split_A_per_slice(int64_t m, int64_t n, const double* A, int64_t lda, int k, int beta, int8_t* SA,

@@ -379,6 +379,9 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
 // to collect.  (That costs clock in long products, and is used where the product is short: launch_split.)
 // A piece: 8 waves of 64 positions of 16 columns, or 8 waves of 4 x 64 positions of 4 rows.
 // ---------------------------------------------------------------------------
+// Marks a column entry of eB that still holds the key of the column maximum rather than the exponent decoded
+// from it (k_split_B and k_cut_columns decode on the fly and store the exponents): exponents are small, keys carry this bit.
+constexpr uint32_t RAW_KEY_TAG = 0x40000000u;
 constexpr int CUT_COLS = 16, CUT_ROWS = 4, CUT_WAVES = 8;
 __host__ __device__ inline int cut_vectors(int by_col) { return by_col ? CUT_COLS : CUT_ROWS; }
 __host__ __device__ inline int cut_inner(int by_col) { return by_col ? CUT_WAVES * 64 : CUT_WAVES * 256; }
@@ -448,11 +451,10 @@ __device__ inline T cut_max(T v, bool by_col, T (*red)[16])
     return v;
 }
 
-__global__ __launch_bounds__(64 * CUT_WAVES) void k_cut_maxima(CutOp a, CutOp b)
+// TAGGED: merged into the exponents' place, which holds RAW_KEY_TAG
+template <bool TAGGED>
+__device__ inline void cut_maxima(const CutOp& o, int block, double (*red)[16])
 {
-    __shared__ double red[CUT_WAVES][16];
-    const int first = a.groups * a.pieces, second = (int)blockIdx.x >= first, block = (int)blockIdx.x - (second ? first : 0);
-    const CutOp o = second ? b : a;
     const int group = block % o.groups, piece = block / o.groups, lane = threadIdx.x & 63;
     double y[4][4], mx = 0.0;
     cut_load(o, group, piece, y);
@@ -460,8 +462,21 @@ __global__ __launch_bounds__(64 * CUT_WAVES) void k_cut_maxima(CutOp a, CutOp b)
     for (int i = 0; i < 16; ++i) mx = fmax(mx, fabs(y[i / 4][i % 4]));
     mx = cut_max(mx, o.by_col, red);
     const int64_t R = (int64_t)group * cut_vectors(o.by_col) + (o.by_col ? lane & 15 : lane >> 4);
-    if (threadIdx.x < 64 && (o.by_col ? lane < 16 : (lane & 15) == 0) && R < o.rows)
-        o.keys[piece * o.rows + R] = (uint16_t)exp_key(abs_bits(mx));
+    if (threadIdx.x < 64 && (o.by_col ? lane < 16 : (lane & 15) == 0) && R < o.rows) {
+        const uint32_t key = exp_key(abs_bits(mx));
+        if constexpr (TAGGED) {
+            if (key) atomicMax(reinterpret_cast<uint32_t*>(o.e) + R, RAW_KEY_TAG | key);
+        } else {
+            o.keys[piece * o.rows + R] = (uint16_t)key;
+        }
+    }
+}
+__global__ __launch_bounds__(64 * CUT_WAVES) void k_cut_maxima(CutOp a, CutOp b)
+{
+    __shared__ double red[CUT_WAVES][16];
+    const int first = a.groups * a.pieces, second = (int)blockIdx.x >= first;
+    const CutOp o = second ? b : a;
+    cut_maxima<false>(o, (int)blockIdx.x - (second ? first : 0), red);
 }
 
 template <bool MASK>
@@ -558,15 +573,105 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : DBR == 32 ? 4 : 2
 }
 
 // ---------------------------------------------------------------------------
+// Columns of a long inner dimension cut along it, with their offsets.
+//
+// A workgroup that owns 4 to 16 whole columns walks them twice, and what it takes is not memory alone: the digits of 8 columns of 16384 are
+// 55 us of vector instructions of a compute unit.  Where whole columns leave compute units idle at the end, they are cut into
+// pieces: behind a fill of maxima and sums, k_split_and_maxima splits the operand taken by rows, if there is one, and takes the maxima of
+// the pieces of columns on the side; k_cut_columns splits the pieces.  (1024 x 16384 x 1024, k = 8: split
+// 174 -> 138 us, 671 MB in all.)
+// ---------------------------------------------------------------------------
+struct ColumnsOp : CutOp {
+    int32_t* P;           // prefix sums
+    int64_t Rpad;
+    int c;                // offset
+};
+template <int DBR, int ROWS, bool MASK>
+__global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : 2) void k_split_and_maxima(SplitOp a, ColumnsOp b, ColumnsOp c, int k, int beta,
+                                                                                         uint32_t* zero, int zero_count)
+{
+    __shared__ double red[SPLIT_WAVES][16];
+    __shared__ int lsum[OZIMMU_MAX_SLICES_DEV][16];
+    const int t = threadIdx.x;
+    if (blockIdx.x == 0 && t < zero_count) zero[t] = 0u;
+    int block = (int)blockIdx.x;
+    if (block < a.blocks) {
+        if (block == 0 && t == 0) a.trailer[0] = a.c;
+        block = (block >> 5) * 32 + (block & 7) * 4 + ((block >> 3) & 3);  // (see k_split_both)
+        if ((int64_t)block * ROWS < a.rows) split_rows<DBR, ROWS, MASK>(a, block, k, beta, red, lsum);
+        return;
+    }
+    block -= a.blocks;
+    const int first = b.groups * b.pieces, second = block >= first;
+    const ColumnsOp o = second ? c : b;
+    block -= second ? first : 0;
+    if (block == 0 && t == 0) o.trailer[0] = o.c;
+    cut_maxima<true>(o, block, red);
+}
+
+template <bool MASK>
+__global__ __launch_bounds__(64 * CUT_WAVES) void k_cut_columns(ColumnsOp b, ColumnsOp c, int k, int beta)
+{
+    __shared__ int lsum[OZIMMU_MAX_SLICES_DEV][16];
+    const int first = b.groups * b.pieces, second = (int)blockIdx.x >= first, block = (int)blockIdx.x - (second ? first : 0);
+    const ColumnsOp o = second ? c : b;
+    const int group = block % o.groups, piece = block / o.groups;
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+    double y[4][4];
+    cut_load(o, group, piece, y);
+    const int64_t R = (int64_t)group * CUT_COLS + (lane & 15);
+    const bool ok = R < o.rows;
+    for (int i = t; i < k * 16; i += 64 * CUT_WAVES) lsum[i / 16][i % 16] = 0;
+    // (the tagged key of the column's maximum, or already the exponent that the first piece's workgroup puts in its place: see k_split_B)
+    int e = 0;
+    if (ok) {
+        const uint32_t v = __hip_atomic_load(reinterpret_cast<uint32_t*>(o.e) + R, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        e = (v & 0xc0000000u) == RAW_KEY_TAG ? key_to_exp<MASK>(v - RAW_KEY_TAG) : (int)v;
+        if (piece == 0 && w == 0 && lane < 16)
+            __hip_atomic_store(reinterpret_cast<uint32_t*>(o.e) + R, (uint32_t)e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const int sc = beta - 1 - e;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y[i / 4][i % 4] = ldexp(y[i / 4][i % 4], sc);
+    const double inv_step = ldexp(1.0, -beta), step = (double)(1 << beta);
+    const uint32_t c4 = (uint32_t)o.c * 0x01010101u;
+    double sig = 6755399441055744.0;
+    const int64_t l0 = (int64_t)piece * cut_inner(1) + w * 64 + (lane >> 4) * 16;
+    const bool inside = l0 < (int64_t)o.KT * TILE_K;
+    int8_t* out = o.S + packed_offset(R, l0, o.KT);
+    for (int s = 0; s < k; ++s) {
+        uint32_t v[4];
+        int sum = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = with_offset(digits4<MASK>(y[u], sig, step), c4, &sum);
+        if (ok && inside) store_slices(out, v[0], v[1], v[2], v[3]);
+        out += o.slice_stride;
+        sig *= inv_step;
+        sum = inside ? sum : 0;
+        sum += __shfl_xor(sum, 16, 64);
+        sum += __shfl_xor(sum, 32, 64);
+        if (lane < 16) atomicAdd(&lsum[s][lane], sum);
+    }
+    if (o.c == 0) return;  // (nobody asks for the sums)
+    __syncthreads();
+    // integers: their order does not matter
+    for (int i = t; i < k * 16; i += 64 * CUT_WAVES) {
+        const int s = i / 16;
+        const int64_t col = (int64_t)group * CUT_COLS + i % 16;
+        int run = 0;
+        for (int q = 0; q <= s; ++q) run += lsum[q][i % 16];
+        if (col < o.rows) atomicAdd(&o.P[(int64_t)s * o.Rpad + col], run);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // B, pass 1: column maxima.  A workgroup covers 64 columns x LCH inner rows;
 // lane = column, so each wave reads 512 contiguous bytes per inner row.  The
 // per-column maximum is merged into keys[] with a 32-bit atomic max (order
 // free, hence deterministic).
 // ---------------------------------------------------------------------------
 constexpr int LCH = 512;  // rows of B per workgroup of the column-maximum kernel (fewer for small B)
-// Marks a column entry of eB that still holds the key of the column maximum rather than the exponent decoded
-// from it (k_split_B decodes on the fly and stores the exponents): exponents are small, keys carry this bit.
-constexpr uint32_t RAW_KEY_TAG = 0x40000000u;
 
 __global__ __launch_bounds__(256) void k_colmax_B(int64_t n, int64_t p, const double* __restrict__ B, int64_t ldb,
                                                   uint32_t* __restrict__ keys, int lch, uint32_t tag)
@@ -1331,10 +1436,77 @@ static bool cut_pays(const SplitIn* ops, int count, int k, double us, size_t roo
     return 12.5 + (k < 6 ? 0.4 * (6 - k) : 0.0) + near / 8e6 + (bytes - near) / 3.8e6 < us;
 }
 
-bool split_is_cut(const SplitIn* ops, int count, int k, size_t room_bytes)
+// The columns of a call cut (k_split_and_maxima, k_cut_columns), where that is estimated to take less than `us` by a sixth:
+// 12 us, rows as in choose_columns at 5.5 bytes per ps, 16 + k / 2 bytes an element of columns at 4.5 (whole calls, without and with,
+// k = 8: 1024 x 16384 x 1024 522 and 491 us, 523 x 31110 x 815 737 and 668, 256 x 145408 x 512 1364 and 1184; k = 4, A transposed, 256 x 58880 x
+// 1152 719 and 523; left whole: 1024^3 39.5 and 44.0, 3000 x 2900 x 3100 613 and 631, 14 x 16060 x 3607, k = 12, 510 and 550, 16384^3,
+// k = 3, 18.55 and 18.79 ms.  Of 190 shapes of 2000 to 200000 inner positions it takes what is 4.4 % faster on average where the best choice
+// would be 5.3 %, and four that are 1 to 3 % slower).
+static bool cut_columns_pay(const SplitIn* ops, int count, int k, double us)
+{
+    if (count != 2 || ops[0].n < 2048) return false;
+    const double n = (double)ops[0].n;
+    double cut_us = 12.0;
+    int64_t columns = 0;
+    for (int q = 0; q < 2; ++q) {
+        const double vectors = (double)ops[q].rows;
+        if (!ops[q].by_col) {
+            const double all_us = n * vectors * (n > 16384.0 ? 16 + k : 8 + k) / 5.5e6, row_us = n * (16 + k) * (n > 8192.0 ? 2 : 1) / 25e3;
+            cut_us += all_us > row_us ? all_us : row_us;
+            continue;
+        }
+        const CutOp o = make_cut(ops[q], k, nullptr);
+        if ((int64_t)o.groups * o.pieces >= ((int64_t)1 << 22)) return false;
+        cut_us += n * vectors * (16.0 + 0.5 * k) / 4.5e6;
+        columns += ops[q].rows;
+    }
+    return columns > 0 && columns <= 2400 && cut_us < 0.84 * us;
+}
+
+static hipError_t launch_cut_columns(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,
+                                     int also_zero_count)
+{
+    SplitOp rows{};
+    ColumnsOp columns[2]{};
+    int n_columns = 0;
+    for (int q = 0; q < count; ++q) {
+        if (!ops[q].by_col) {
+            rows = make_op(ops[q], k);
+            continue;
+        }
+        ColumnsOp& o = columns[n_columns++];
+        static_cast<CutOp&>(o) = make_cut(ops[q], k, nullptr);
+        o.P = reinterpret_cast<int32_t*>(ops[q].S + ozl::sums_offset(o.rows, o.n, k));
+        o.Rpad = ozl::rows_padded(o.rows);
+        o.c = ops[q].offset;
+        const int64_t sums = (int64_t)k * o.Rpad, most = sums > o.rows ? sums : o.rows;
+        hipLaunchKernelGGL(k_fill2_u32, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, st, o.rows, reinterpret_cast<uint32_t*>(o.e),
+                           RAW_KEY_TAG, sums, reinterpret_cast<uint32_t*>(o.P), 0u);
+    }
+    const bool wide = rows.n > 8192;
+    if (rows.rows > 0) {
+        rows.per = 2;
+        rows.blocks = (int)(((rows.rows + rows.per - 1) / rows.per + 31) / 32 * 32);
+    }
+    const unsigned pieces = (unsigned)(columns[0].groups * columns[0].pieces + columns[1].groups * columns[1].pieces);
+    auto launch = [&](auto first, auto second) {
+        hipLaunchKernelGGL(first, dim3((unsigned)rows.blocks + pieces), dim3(64 * SPLIT_WAVES), 0, st, rows, columns[0], columns[1], k, beta,
+                           also_zero, also_zero_count);
+        hipLaunchKernelGGL(second, dim3(pieces), dim3(64 * CUT_WAVES), 0, st, columns[0], columns[1], k, beta);
+    };
+    if (split_mode != 0)
+        wide ? launch(k_split_and_maxima<64, 2, true>, k_cut_columns<true>) : launch(k_split_and_maxima<16, 2, true>, k_cut_columns<true>);
+    else
+        wide ? launch(k_split_and_maxima<64, 2, false>, k_cut_columns<false>) : launch(k_split_and_maxima<16, 2, false>, k_cut_columns<false>);
+    return hipGetLastError();
+}
+
+int split_cut(const SplitIn* ops, int count, int k, size_t room_bytes, bool short_product)
 {
     int per[2] = {0, 0};
-    return cut_pays(ops, count, k, choose_columns(ops, count, k, per), room_bytes);
+    const double us = choose_columns(ops, count, k, per);
+    if (short_product && cut_pays(ops, count, k, us, room_bytes)) return 1;
+    return cut_columns_pay(ops, count, k, us) ? 2 : 0;
 }
 
 hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,
@@ -1355,6 +1527,7 @@ hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int spli
             hipLaunchKernelGGL(k_cut_split<false>, grid, block, 0, st, a, b, k, beta, also_zero, also_zero_count);
         return hipGetLastError();
     }
+    if (cut_columns_pay(ops, count, k, whole_us)) return launch_cut_columns(ops, count, k, beta, split_mode, st, also_zero, also_zero_count);
     for (int q = 0; q < count; ++q) {
         if (ops[q].by_col && per[q] == 0) {
             const hipError_t e = launch_split_cols_cut(ops[q], k, beta, split_mode, st);

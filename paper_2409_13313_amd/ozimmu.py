@@ -109,7 +109,7 @@ ACCUMULATE_MODES = {"grouped": 0, "per_pair": 1, "wide": 2}
 RESIDENT_TILES = 7
 HELD_TILE = 16                  # beside them: k_held's
 WAYS = ["small", "resident", "queue", "chunk_parallel", "split_inner", "one_launch"]
-SPLIT_WAYS = ["none", "whole", "cut", "passes"]
+SPLIT_WAYS = ["none", "whole", "cut", "passes", "cut_columns"]
 SCHEDULES = {"auto": 0, "one_launch": 0x100, "split_inner": 0x200, "chunk_parallel": 0x400, "queue": 0x800}
 
 
