@@ -1124,7 +1124,7 @@ __global__ __launch_bounds__(256) void k_split_B_ps(int64_t n, int64_t p, const 
 // swizzle, signed digits without offset), each wave multiplies one inner step of 64 into its k chunk sums (r >= k there: a chunk is a
 // group), and the sums of the waves meet in LDS, where each thread adds up one element.  Every vector is split again
 // by all the tiles in its row or column; what it saves is what such a call consists of: a launch and the wait between two
-// dependent ones (k = 8: 64^3 9.6 us for two launches, 5.6 for this one, 256^3 11.5 and 8.7).  What bounds it is one latency after the other:
+// dependent ones (k = 8: 64^3 9.6 us for two launches, 5.2 for this one, 256^3 11.5 and 7.1).  What bounds it is one latency after the other:
 // operands, maxima, digits (a thread makes those of 32 elements), fragments, sums.
 // ---------------------------------------------------------------------------
 template <int K>
@@ -1221,20 +1221,23 @@ __global__ __launch_bounds__(256) void k_small(ozk::SmallArgs a)
 #pragma unroll
             for (int s = 0; s <= g; ++s) acc[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(f[0][s], f[1][g - s], acc[g], 0, 0, 0);
     }
-    __syncthreads();  // every wave has its fragments: their place takes the sums
-    if (w < steps)
+    __syncthreads();  // every wave has its fragments: their place takes the sums (zeros past the last step)
 #pragma unroll
-        for (int g = 0; g < K; ++g) *reinterpret_cast<v4i*>(lds + (w * K + g) * 1024 + lane * 16) = acc[g];
+    for (int g = 0; g < K; ++g) *reinterpret_cast<v4i*>(lds + (w * K + g) * 1024 + lane * 16) = acc[g];
     __syncthreads();
-    // register w of the accumulators: row 4 (lane / 16) + w, column lane % 16
-    const int i = 4 * (lane >> 4) + w, j = lane & 15;
+    // Thread t adds up integer t of every sum: register t % 4 of lane t / 4, row 4 (lane / 16) + register, column lane % 16.  Always four
+    // waves' sums, all of them on their way at once (a loop over the steps waited for one after the other: 256^3, k = 8, 1.7 us of 8.4).
+    const int i = 4 * w + (t & 3), j = lane >> 2;
     const int e = lds_exp[0][i] + lds_exp[1][j] + 2;
+    int v[4][K];
+#pragma unroll
+    for (int z = 0; z < 4; ++z)
+#pragma unroll
+        for (int g = 0; g < K; ++g) v[z][g] = *reinterpret_cast<const int*>(lds + (z * K + g) * 1024 + 4 * t);
     double d = 0.0;
 #pragma unroll
     for (int g = 0; g < K; ++g) {
-        int v = 0;
-        for (int z = 0; z < steps; ++z) v += *reinterpret_cast<const int*>(lds + (z * K + g) * 1024 + lane * 16 + 4 * w);
-        const double term = ldexp((double)v, e - a.beta * (g + 2));
+        const double term = ldexp((double)(v[0][g] + v[1][g] + (v[2][g] + v[3][g])), e - a.beta * (g + 2));
         d = g == 0 ? term : d + term;
     }
     if (row0 + i < a.op[0].rows && col0 + j < a.op[1].rows) {
@@ -1697,7 +1700,8 @@ static hipError_t launch_small_k(const SmallArgs* a, int k, hipStream_t st)
         if (!a) return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * K * 4 * 1024);
         void* args[] = {const_cast<SmallArgs*>(a)};
         const dim3 grid((unsigned)((a->op[1].rows + 15) / 16), (unsigned)((a->op[0].rows + 15) / 16));
-        return ozk::launch_status(hipLaunchKernel(kernel, grid, dim3(256), args, 2 * K * a->steps * 1024, st));
+        // (the operands' slices, then the sums of four waves)
+        return ozk::launch_status(hipLaunchKernel(kernel, grid, dim3(256), args, (a->steps > 2 ? 2 * a->steps : 4) * K * 1024, st));
     }
     return hipErrorInvalidValue;
 }
