@@ -65,6 +65,68 @@ __device__ inline uint64_t wave_max_u64(uint64_t v)
     return v;
 }
 
+// Sums and maxima over lanes without the way through LDS that a shuffle takes (four to six of those one after the other for every slice:
+// 100000 x 100 x 64, k = 6, 114 -> 102 us a call, 300^3, k = 8, 12.6 -> 11.8, 777 x 1001 x 513, k = 7, 26.3 -> 25.5, 1024^3, k = 12, 59.7 -> 58.3).
+// moved: inside 16 lanes; swapped: the halves of 32 or of 64.
+template <int CTRL>
+__device__ inline int moved(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ inline double moved(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)moved<CTRL>((int)(uint32_t)b), hi = (uint32_t)moved<CTRL>((int)(uint32_t)(b >> 32));
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+struct Sum {
+    __device__ int operator()(int a, int b) const { return a + b; }
+};
+struct Max {
+    __device__ double operator()(double a, double b) const { return fmax(a, b); }
+};
+// v of a lane with the one 16 or 32 lanes away
+template <int BY, class OP>
+__device__ inline int swapped(int v, OP op)
+{
+    const auto r = BY == 16 ? __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false)
+                            : __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    return op((int)r[0], (int)r[1]);
+}
+template <int BY, class OP>
+__device__ inline double swapped(double v, OP op)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const unsigned l = (unsigned)b, h = (unsigned)(b >> 32);
+    const auto lo = BY == 16 ? __builtin_amdgcn_permlane16_swap(l, l, false, false) : __builtin_amdgcn_permlane32_swap(l, l, false, false);
+    const auto hi = BY == 16 ? __builtin_amdgcn_permlane16_swap(h, h, false, false) : __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    return op(__longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])), __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1])));
+}
+// over groups of LANES (16, 32 or 64) neighbours
+template <int LANES, class T, class OP>
+__device__ inline T over_neighbours(T v, OP op)
+{
+    static_assert(LANES >= 16, "");
+    v = op(v, moved<0xb1>(v));   // lane ^ 1
+    v = op(v, moved<0x4e>(v));   // lane ^ 2
+    v = op(v, moved<0x141>(v));  // mirrored in 8: the other four
+    v = op(v, moved<0x140>(v));  // mirrored in 16: the other eight
+    if (LANES >= 32) v = swapped<16>(v, op);
+    if (LANES >= 64) v = swapped<32>(v, op);
+    return v;
+}
+// over the lanes of the same number modulo FIRST (4, 8 or 16)
+template <int FIRST, class T, class OP>
+__device__ inline T over_strided(T v, OP op)
+{
+    static_assert(FIRST >= 4, "");
+    if (FIRST <= 8) v = op(v, moved<0x128>(v));  // rotated by 8 in 16
+    if (FIRST <= 4) v = op(v, moved<0x124>(v));  // by 4
+    v = swapped<16>(v, op);
+    return swapped<32>(v, op);
+}
+
 // One slice of 4 consecutive inner elements: digits of y[], remainders updated in place, the 4 stored
 // bytes (digit + c, c = the stack's offset) packed into a dword.  Returns the dword; *sum receives the sum
 // of the 4 stored bytes.  Inner padding (l >= n) enters as y = 0 like a real zero and is stored as c.
@@ -226,8 +288,7 @@ __device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int be
 #pragma unroll
             for (int j = 0; j < 4; ++j) mx = fmax(mx, fabs(y[u][j]));
     }
-#pragma unroll
-    for (int off = LPR / 2; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+    mx = over_neighbours<LPR>(mx, Max{});
     if (lane % LPR == 0) red[w][lane / LPR] = mx;
     for (int i = t; i < k * ROWS; i += blockDim.x) lsum[i / ROWS][i % ROWS] = 0;
     __syncthreads();
@@ -256,8 +317,7 @@ __device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int be
             }
             out += o.slice_stride;
             sig *= inv_step;
-#pragma unroll
-            for (int off = LPR / 2; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+            sum = over_neighbours<LPR>(sum, Sum{});
             if (lane % LPR == 0) atomicAdd(&lsum[s][lane / LPR], sum);
         }
     }
@@ -321,8 +381,7 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
 #pragma unroll
             for (int i = 0; i < 16; ++i) mx = fmax(mx, fabs(y[u][i]));
     }
-#pragma unroll
-    for (int off = COLS; off < 64; off <<= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+    mx = over_strided<COLS>(mx, Max{});
     if (lane < COLS) red[w][lane] = mx;
     for (int i = t; i < k * COLS; i += blockDim.x) lsum[i / COLS][i % COLS] = 0;
     __syncthreads();
@@ -355,8 +414,7 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
             }
             out += o.slice_stride;
             sig *= inv_step;
-#pragma unroll
-            for (int off = COLS; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+            sum = over_strided<COLS>(sum, Sum{});
             if (lane < COLS) atomicAdd(&lsum[s][lane], sum);
         }
     }
@@ -649,8 +707,7 @@ __global__ __launch_bounds__(64 * CUT_WAVES) void k_cut_columns(ColumnsOp b, Col
         out += o.slice_stride;
         sig *= inv_step;
         sum = inside ? sum : 0;
-        sum += __shfl_xor(sum, 16, 64);
-        sum += __shfl_xor(sum, 32, 64);
+        sum = over_strided<16>(sum, Sum{});
         if (lane < 16) atomicAdd(&lsum[s][lane], sum);
     }
     if (o.c == 0) return;  // (nobody asks for the sums)
@@ -1172,12 +1229,10 @@ __global__ __launch_bounds__(256) void k_small(ozk::SmallArgs a)
 #pragma unroll
             for (int i = 0; i < 4; ++i) mx[o] = fmax(mx[o], fabs(y[o][j][i]));
         if (a.op[o].by_col) {
-            mx[o] = fmax(mx[o], __shfl_xor(mx[o], 16, 64));
-            mx[o] = fmax(mx[o], __shfl_xor(mx[o], 32, 64));
+            mx[o] = over_strided<16>(mx[o], Max{});
             if (lane < 16) red[o][w][lane] = mx[o];
         } else {
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) mx[o] = fmax(mx[o], __shfl_xor(mx[o], off, 64));
+            mx[o] = over_neighbours<16>(mx[o], Max{});
         }
     }
     __syncthreads();
