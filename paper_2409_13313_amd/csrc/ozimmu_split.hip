@@ -259,9 +259,9 @@ __device__ __attribute__((always_inline)) inline void store_slices(int8_t* out, 
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const u32x4 v = {x, y, z, w};
-    // (one store: as two of 8 bytes each memory line would be written twice.  The wait state is what a store of more than 8 bytes asks for
-    // before its registers are written again)
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(out), "v"(v) : "memory");
+    // (one store: as two of 8 bytes each memory line would be written twice.  Behind a store of more than 8 bytes a vector instruction may
+    // write its registers again from the third wait state on; the compiler, which sees no store here, would not keep that distance)
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(out), "v"(v) : "memory");
 }
 
 template <bool MASK>
