@@ -1030,7 +1030,7 @@ __device__ inline void split_ps(const PsOp& o, int block, int k, int beta, doubl
     constexpr int LANES = BY_COL ? 64 / (V < 64 ? V : 64) : TPV < 64 ? TPV : 64;   // of a vector in a wave
     constexpr int WAVES = BY_COL ? THREADS / 64 : TPV / LANES;                     // that a vector is on
     constexpr int FIRST = BY_COL ? V : 1;                  // distance of a vector's lanes
-    constexpr int GROUP = BY_COL ? 4 : 2;
+    constexpr int GROUP = BY_COL ? 4 : 2;                  // quads at a time: a column's chunk of 16 bytes
     static_assert(V <= 64 && TPV * V == THREADS, "");
     const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int v = BY_COL ? t % V : t / TPV, tv = BY_COL ? t / V : t % TPV;
@@ -1106,16 +1106,16 @@ __device__ inline void split_ps(const PsOp& o, int block, int k, int beta, doubl
                         mx = fmax(mx, fabs(y[q0 + g][j]));
                     }
             }
+            // (Through L2, see store_slices.  A chunk of a column in one store: in four of 4 bytes each goes through by itself.  Four, one and left in
+            // L2, whole calls: 36 x 1885 x 5453, k = 8, 172.3, 114.9 and 116.7 us, 303 x 380 x 10162, k = 6, 86.2, 71.0 and 74.0;
+            // one and left in L2: 700 x 500 x 900, k = 8, 36.9 and 40.9, 700 x 8000 x 900 256.7 and 261.5.)
+            if constexpr (BY_COL) {
+                if (ok && place(q0) < end) store_slices(out + packed_offset(R, place(q0), o.KT), word[0], word[1], word[2], word[3]);
+            } else {
 #pragma unroll
-            for (int g = 0; g < GROUP; ++g)
-                if (ok && place(q0 + g) < end) {
-                    // (through L2, see store_slices, but for 700 x 8000 x 900, k = 8, where that is 258 -> 278 us: 700 x 500 x 900 40.4 -> 37.1)
-                    int8_t* const at = out + packed_offset(R, place(q0 + g), o.KT);
-                    if constexpr (U == 1 && V >= 4)
-                        store_slices(at, word[g]);
-                    else
-                        *reinterpret_cast<uint32_t*>(at) = word[g];
-                }
+                for (int g = 0; g < GROUP; ++g)
+                    if (ok && place(q0 + g) < end) store_slices(out + packed_offset(R, place(q0 + g), o.KT), word[g]);
+            }
         }
     }
 }

@@ -55,3 +55,15 @@ def test_wide_stores_by_hand_bring_their_wait_states(assembly):
                 if sum(wait_states(y) for y in code[i + 1:]) < 2:
                     short.append(code)
     assert seen > 0 and not short, (seen, short[:1], len(short))
+
+
+def test_columns_of_one_scale_per_slice_go_out_in_whole_chunks(assembly):
+    # Slices are written through L2, each store by itself: a column's 16 consecutive bytes in stores of 4 would go through as four pieces.
+    seen = 0
+    for m in re.finditer(r"^(_Z\S*k_split_psILi\d+ELi(\d+)ELi\d+EE\S*):(.*?)^\.Lfunc_end", assembly, re.S | re.M):
+        seen += 1
+        through = re.findall(r"\t(global_store_\w+) .* sc1", m.group(3))
+        u = int(m.group(2))                              # chunks a thread holds of a column, four quads of a row instead
+        assert through.count("global_store_dwordx4") >= u and through.count("global_store_dword") <= 4 * u, (m.group(1), through)
+        assert set(through) == {"global_store_dwordx4", "global_store_dword"}, (m.group(1), through)
+    assert seen == 6
