@@ -388,6 +388,9 @@ Way choose_way(int64_t m, int64_t n, int64_t p, int k, int r_eff, bool per_slice
             if (per_slice && !ozr::per_slice_tile(k, v)) continue;
             const double us = ozr::estimate_us(k, r_eff, v, m, n, p, num_cu);
             if (us < 0.0) continue;
+            if (v == ozr::HELD && variant >= 0 && parts == 1 &&
+                us + ozr::held_lead_us(k, r_eff, variant, us, m, n, p, num_cu) >= other_us)
+                continue;
             if (us < other_us) {
                 other_us = us;
                 variant = v;
