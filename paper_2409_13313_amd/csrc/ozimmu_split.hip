@@ -1522,12 +1522,17 @@ static bool cut_pays(const SplitIn* ops, int count, int k, double us, size_t roo
     return 12.5 + (k < 6 ? 0.4 * (6 - k) : 0.0) + near / 8e6 + (bytes - near) / 3.8e6 < us;
 }
 
-// The columns of a call cut (k_split_and_maxima, k_cut_columns), where that is estimated to take less than `us` by a sixth:
+// The columns of a call cut (k_split_and_maxima, k_cut_columns), where that is estimated to take clearly less than `us`:
 // 12 us, rows as in choose_columns at 5.5 bytes per ps, 16 + k / 2 bytes an element of columns at 4.5 (whole calls, without and with,
-// k = 8: 1024 x 16384 x 1024 522 and 491 us, 523 x 31110 x 815 737 and 668, 256 x 145408 x 512 1364 and 1184; k = 4, A transposed, 256 x 58880 x
+// k = 8: 1024 x 16384 x 1024 535 and 505 us, 523 x 31110 x 815 737 and 673, 256 x 145408 x 512 1364 and 1184; k = 4, A transposed, 256 x 58880 x
 // 1152 719 and 523; left whole: 1024^3 39.5 and 44.0, 3000 x 2900 x 3100 613 and 631, 14 x 16060 x 3607, k = 12, 510 and 550, 16384^3,
-// k = 3, 18.55 and 18.79 ms.  Of 190 shapes of 2000 to 200000 inner positions it takes what is 4.4 % faster on average where the best choice
-// would be 5.3 %, and four that are 1 to 3 % slower).
+// k = 3, 18.55 and 18.79 ms).
+// 17 to 300 columns of 8192 and more, whose whole ones walk far longer than the rows beside them, have to be ahead by a sixth
+// (640 x 14848 x 256, k = 8, 141 and 129 us, 909 x 14947 x 85, k = 4, 88 and 72), others by 20 us and an eighth: whole columns of
+// moderate length then fill the chip, and `us` is up to 30 us too long (11 x 7698 x 2231, k = 5, 93 and 118 us, 10 x 5261 x 2140, k = 4, 58 and
+// 73, 704 x 13298 x 1524, k = 5, 331 and 362, 1045 x 8580 x 8, k = 4, 45.6 and 52.2).  Of 629 shapes of 2000 to 200000 positions for which it is estimated
+// at less than 0.84 `us` this takes 289, of which five are slower by more than 2 %, and is 2.1 % faster on average over all 629 where the best choice
+// would be 2.7 %; with the sixth alone 120 were, by up to 26 %, and the average 1.3 %.
 static bool cut_columns_pay(const SplitIn* ops, int count, int k, double us)
 {
     if (count != 2 || ops[0].n < 2048) return false;
@@ -1546,7 +1551,8 @@ static bool cut_columns_pay(const SplitIn* ops, int count, int k, double us)
         cut_us += n * vectors * (16.0 + 0.5 * k) / 4.5e6;
         columns += ops[q].rows;
     }
-    return columns > 0 && columns <= 2400 && cut_us < 0.84 * us;
+    if (columns < 1 || columns > 2400) return false;
+    return columns > 16 && columns <= 300 && ops[0].n >= 8192 ? cut_us < 0.84 * us : cut_us + 20.0 < 0.88 * us;
 }
 
 static hipError_t launch_cut_columns(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,

@@ -70,3 +70,15 @@ def test_vectors_are_split_along_the_inner_dimension_where_that_is_faster(oz, m,
     (2105, 2105, 2105, 13, 508.5, 581.1), (759, 8816, 1462, 11, 554.4, 653.0), (2788, 16786, 2762, 5, 1499.2, 1746.3), (2000, 600, 2000, 6, 52.6, 51.2), (1537, 2051, 1283, 9, 149.0, 157.3), (1424, 1424, 1424, 9, 107.7, 113.2), (6981, 1090, 895, 7, 160.5, 181.0)])
 def test_slices_of_a_are_held_where_that_is_faster(oz, m, n, p, k, held, other):
     assert (oz.choose(m, n, p, k).tile == oz.HELD_TILE) == (held < other)
+
+
+# (measured with whole columns, or the cut of many launches, and with columns cut along the inner dimension beside rows, us, whole calls)
+@pytest.mark.parametrize("m,n,p,k,accumulate,whole,cut", [
+    (11, 7698, 2231, 5, "grouped", 92.8, 117.5), (10, 5261, 2140, 4, "grouped", 58.1, 72.9), (704, 13298, 1524, 5, "grouped", 330.1, 361.3),
+    (1045, 8580, 8, 4, "grouped", 45.1, 51.7), (8, 9356, 2100, 4, "per_pair", 99.1, 124.3), (754, 5777, 2091, 6, "per_pair", 219.0, 235.5),
+    (352, 4636, 1844, 11, "grouped", 182.5, 192.1), (736, 9172, 1735, 7, "grouped", 313.8, 329.5), (701, 16385, 1513, 5, "grouped", 395.8, 421.7),
+    (640, 14848, 256, 8, "grouped", 141.0, 128.8), (909, 14947, 85, 4, "grouped", 88.5, 72.3), (523, 31111, 815, 8, "grouped", 736.8, 672.6),
+    (1024, 16384, 1024, 8, "grouped", 535.4, 505.2), (448, 57799, 128, 14, "wide", 643.7, 515.3), (33, 56249, 2084, 9, "grouped", 1141.5, 980.5),
+    (28, 12427, 2068, 14, "grouped", 338.2, 292.4), (57, 156679, 812, 14, "grouped", 1863.8, 1582.4), (232, 56640, 1927, 9, "grouped", 1567.2, 1554.4)])
+def test_columns_are_cut_beside_rows_where_that_is_faster(oz, m, n, p, k, accumulate, whole, cut):
+    assert (oz.SPLIT_WAYS[oz.choose(m, n, p, k, "rn", accumulate).split_way] == "cut_columns") == (cut < whole)
