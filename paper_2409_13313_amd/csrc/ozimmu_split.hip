@@ -251,14 +251,24 @@ __device__ inline uint32_t with_offset(uint32_t w, uint32_t c4, int* sum)
 // which nothing runs (start of the product after the last workgroup of the split, left in L2 and written through: 777 x 1001 x 513, k = 7,
 // 6.3 and 1.1 us, a call 30.2 and 26.9; 512^3, k = 8, 3.6 and 1.8, 16.2 and 14.0; 1024^3, k = 9, 4.4 and 0.9, 45.2 and 42.7).  They stay in the
 // memory-side cache, which non-temporal stores would not do (the product then takes 4 us longer at 777 x 1001 x 513).
+// NEAR: left there, for the few vectors whose workgroups and the product's only tile run on one XCD (see launch_split).
+template <bool NEAR = false>
 __device__ __attribute__((always_inline)) inline void store_slices(int8_t* out, uint32_t v)
 {
-    __hip_atomic_store(reinterpret_cast<uint32_t*>(out), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (NEAR)
+        *reinterpret_cast<uint32_t*>(out) = v;
+    else
+        __hip_atomic_store(reinterpret_cast<uint32_t*>(out), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+template <bool NEAR = false>
 __device__ __attribute__((always_inline)) inline void store_slices(int8_t* out, uint32_t x, uint32_t y, uint32_t z, uint32_t w)
 {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const u32x4 v = {x, y, z, w};
+    if constexpr (NEAR) {
+        *reinterpret_cast<u32x4*>(out) = v;
+        return;
+    }
     // (one store: as two of 8 bytes each memory line would be written twice.  Behind a store of more than 8 bytes a vector instruction may
     // write its registers again from the third wait state on; the compiler, which sees no store here, would not keep that distance)
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(out), "v"(v) : "memory");
@@ -270,7 +280,7 @@ __device__ inline int exponent_of(double mx)
     return key_to_exp<MASK>(exp_key(abs_bits(mx)));
 }
 
-template <int DB, int ROWS, bool MASK>
+template <int DB, int ROWS, bool MASK, bool NEAR = false>
 __device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int beta, double (*red)[16], int (*lsum)[16])
 {
     constexpr int LPR = 64 / ROWS;        // lanes of a row
@@ -338,7 +348,7 @@ __device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int be
             for (int u = 0; u < U; ++u) {
                 if (b * per_batch + u * nw + w < groups) {
                     const uint32_t v = with_offset(digits4<MASK>(y[u], sig, step), c4, &sum);
-                    if (ok) store_slices(out + (int64_t)u * nw * (TPW * TILE_BYTES), v);
+                    if (ok) store_slices<NEAR>(out + (int64_t)u * nw * (TPW * TILE_BYTES), v);
                 }
             }
             out += o.slice_stride;
@@ -357,7 +367,7 @@ __device__ inline void split_rows(const SplitOp& o, int64_t block, int k, int be
     }
 }
 
-template <int DB, int COLS, bool MASK>
+template <int DB, int COLS, bool MASK, bool NEAR>
 __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int beta, double (*red)[16], int (*lsum)[16])
 {
     constexpr int TPW = 16 / COLS;        // inner tiles of 64 a wave covers at a time
@@ -435,7 +445,7 @@ __device__ inline void split_cols(const SplitOp& o, int64_t block, int k, int be
                     v.y = with_offset(digits4<MASK>(y[u] + 4, sig, step), c4, &sum);
                     v.z = with_offset(digits4<MASK>(y[u] + 8, sig, step), c4, &sum);
                     v.w = with_offset(digits4<MASK>(y[u] + 12, sig, step), c4, &sum);
-                    if (ok) store_slices(out + (int64_t)u * nw * (TPW * TILE_BYTES), v.x, v.y, v.z, v.w);
+                    if (ok) store_slices<NEAR>(out + (int64_t)u * nw * (TPW * TILE_BYTES), v.x, v.y, v.z, v.w);
                 }
             }
             out += o.slice_stride;
@@ -616,7 +626,7 @@ constexpr int SPLIT_WAVES = 8;
 // DBR: elements of a row a thread holds (columns: 16); COLS: the launch may have columns.  Vectors per workgroup are each
 // operand's own: both sides of a product may be columns (A transposed), one of many vectors and one of few.
 // (With 64 elements a thread one kernel for both numbers of rows would spill: ROWS is fixed there.)
-template <int DBR, int ROWS, bool COLS, bool MASK>
+template <int DBR, int ROWS, bool COLS, bool MASK, bool NEAR = false>
 __global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : DBR == 32 ? 4 : 2) void k_split_both(SplitOp a, SplitOp b, int k, int beta, uint32_t* zero, int zero_count)
 {
     __shared__ double red[SPLIT_WAVES][16];
@@ -637,21 +647,21 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES, DBR == 16 ? 6 : DBR == 32 ? 4 : 2
     if ((int64_t)block * o.per >= o.rows) return;
     if (COLS && o.by_col) {
         if (o.per == 16)
-            split_cols<16, 16, MASK>(o, block, k, beta, red, lsum);
+            split_cols<16, 16, MASK, NEAR>(o, block, k, beta, red, lsum);
         else if (o.per == 8)
-            split_cols<16, 8, MASK>(o, block, k, beta, red, lsum);
+            split_cols<16, 8, MASK, NEAR>(o, block, k, beta, red, lsum);
         else
-            split_cols<16, 4, MASK>(o, block, k, beta, red, lsum);
+            split_cols<16, 4, MASK, NEAR>(o, block, k, beta, red, lsum);
     } else {
         if constexpr (ROWS > 0) {
-            split_rows<DBR, ROWS, MASK>(o, block, k, beta, red, lsum);
+            split_rows<DBR, ROWS, MASK, NEAR>(o, block, k, beta, red, lsum);
         } else {
             if (DBR == 16 && o.per == 4)
-                split_rows<DBR, 4, MASK>(o, block, k, beta, red, lsum);
+                split_rows<DBR, 4, MASK, NEAR>(o, block, k, beta, red, lsum);
             else if (o.per == 2)
-                split_rows<DBR, 2, MASK>(o, block, k, beta, red, lsum);
+                split_rows<DBR, 2, MASK, NEAR>(o, block, k, beta, red, lsum);
             else
-                split_rows<DBR, 1, MASK>(o, block, k, beta, red, lsum);
+                split_rows<DBR, 1, MASK, NEAR>(o, block, k, beta, red, lsum);
         }
     }
 }
@@ -1688,7 +1698,17 @@ hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int spli
         hipLaunchKernelGGL(kernel, grid, block, 0, st, op[0], op[1], k, beta, also_zero, also_zero_count);
     };
     const bool mask = split_mode != 0;
-    if (columns && dbr == 16)
+    // The first four workgroups of an operand run on XCD 0 (see k_split_both), and so does the product's only tile, which finds slices left in that L2
+    // near by.  Written through it waits for them: 11 x 1176 x 9, k = 5, 11.9 and 13.4 us a call, 5 x 772 x 7, k = 11, 17.2 and 19.4, 3 x
+    // 2304 x 6, k = 3, 14.1 and 16.6; also where four more hold rows, 24 x 1722 x 16, k = 3, 11.9 and 13.4 (of 116 random calls of so few vectors 56
+    // were slower written through by more than 2 %, up to 15 %, two faster; more columns, 4 x 640 x 32, k = 12, 18.0 and 17.7).
+    auto beside_the_tile = [](const SplitOp& o) { return o.rows <= (o.by_col ? 4 : 8) * o.per; };
+    const bool near = used == 2 && dbr == 16 && beside_the_tile(op[0]) && beside_the_tile(op[1]);
+    if (near && columns)
+        mask ? launch(k_split_both<16, 0, true, true, true>) : launch(k_split_both<16, 0, true, false, true>);
+    else if (near)
+        mask ? launch(k_split_both<16, 0, false, true, true>) : launch(k_split_both<16, 0, false, false, true>);
+    else if (columns && dbr == 16)
         mask ? launch(k_split_both<16, 0, true, true>) : launch(k_split_both<16, 0, true, false>);
     else if (columns && dbr == 65)
         mask ? launch(k_split_both<64, 1, true, true>) : launch(k_split_both<64, 1, true, false>);
