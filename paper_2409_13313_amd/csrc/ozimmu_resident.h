@@ -217,28 +217,29 @@ inline double estimate_us(int k, int r, int variant, int64_t m, int64_t n, int64
                             at_least(c.waves == 2 ? 0.0168 * mfmas + 0.2 : 0.0075 * mfmas + barrier_us, wait2_us));
     if (parts > 1) return us + add_parts_us(k, r, c, tiles, parts);
     if (us < 1500.0) return us;
-    // (k_held's tiles of 96 rows 2 % more: 8192^3, k = 8, 96 x 128 11.48 ms, 64 x 128 11.30; 16384^3, k = 9, 96 x 96 112.4, 64 x 128
-    // 109.4; still ahead at 16384^3, k = 8, 88.5 and 91.5, 6144^3 4.71 and 4.82)
+    // (k_held's tiles of 96 rows 2 % more: in turn, 8192^3, k = 8, 96 x 128 11.58 ms, 64 x 128 11.42; 16384^3, k = 9, 96 x 96 114.2, 64 x 128
+    // 111.2; still ahead at 16384^3, k = 8, 89.5 and 90.9, 6144^3 4.76 and 4.90)
     const double hot_us = mfmas * ((c.waves == 2 ? 0.0062 : 0.0068) + 2.0e-5 * copied + 0.005 * fetched) * (c.held && c.ta == 3 ? 1.02 : 1.0);
     return total(at_least(hot_us, wait_us), at_least(hot_us * c.waves, wait2_us));
 }
 
 // What k_held, estimated to take `us`, has to be ahead of the best other tile by to be taken instead.  The estimates know one workgroup's
 // steps and ends after one another.  Two that share a compute unit cover each other's ends, by all that the steps of one last, 5 us a
-// round at most (estimated less measured lead, us a round: 1 or 2 steps 1.5, 3 and 4 2.7, 5 to 8 4.0, 9 to 40 4.7).  32 x 32
-// tiles, two to a unit, are estimated 3 % too long besides, and k_extended's ends are like k_held's own, the two level within 1 %.
+// round at most (estimated less measured lead, us a round: 1 or 2 steps 1.5, 3 and 4 2.7, 5 to 8 4.0, 9 to 40 4.7), and their estimates run
+// 6 % too long besides, 2 us at least; 32 x 32 tiles' 3 % more.  k_extended's ends are like k_held's own, the two level within 1 %, and
+// the others' estimates within half a percent.
 // (Whole calls with k_held and without: 8532 x 421 x 5453, k = 8, 613 and 532 us, 780 x 6178 x 1346, k = 14, 579 and 519,
-// 1409 x 65 x 805, k = 13, 26.4 and 22.9; still taken: 2017 x 193 x 824, k = 11, 34.3 and 39.5, 1537 x 2051 x 1283, k = 9, 149.0 and 157.3,
-// 2705^3, k = 13, 1066 and 1211.  Of 1053 random shapes of up to 40000 inner positions where it was estimated to be the fastest 193 were slower with it by
-// more than 1 %, up to 16 %, and the average gained 2.7 %; with this it is taken at 838, 32 of them slower, up to 5 %, where runs differ
-// by 3 %, and the average gains 3.5 %.)
+// 1409 x 65 x 805, k = 13, 26.4 and 22.9, 2944 x 5595 x 3896, k = 7, A and B transposed, 1267 and 1189, 647 x 4 x 6747, k = 9, 47.7 and 43.7; still taken:
+// 2017 x 193 x 824, k = 11, 34.3 and 39.5, 1537 x 2051 x 1283, k = 9, 149.0 and 157.3, 2705^3, k = 13, 1066 and 1211.  Of 500 random
+// shapes for which it led by more than the first of these 33 were slower with it by more than 2 %, up to 9 %, and the average gained 4.0 %; with all of them it
+// is taken at 444, twelve of them slower by more than 2 %, up to 7 %, and the average over the 500 is the same within 0.1 %.)
 inline double held_lead_us(int k, int r, int other, double us, int64_t m, int64_t n, int64_t p, int num_cu)
 {
     const Config h = config_for(k, r, HELD), o = config_for(k, r, other);
-    if (o.waves < 2) return other == EXTENDED ? 0.01 * us : 0.0;
+    if (o.waves < 2) return (other == EXTENDED ? 0.01 : 0.005) * us;
     const int64_t tiles = ((m + 32 * h.ta - 1) / (32 * h.ta)) * ((p + 32 * h.tb - 1) / (32 * h.tb));
     const double cover_us = 1.0 + 0.7 * (double)((n + 63) / 64), rounds = (double)((tiles + num_cu - 1) / num_cu);
-    return rounds * (cover_us < 5.0 ? cover_us : 5.0) + (o.ta * o.tb == 1 ? 0.03 * us : 0.0);
+    return rounds * (cover_us < 5.0 ? cover_us : 5.0) + (0.06 * us > 2.0 ? 0.06 * us : 2.0) + (o.ta * o.tb == 1 ? 0.03 * us : 0.0);
 }
 
 // Which tile workgroup b takes.  Workgroup b runs on XCD b % 8, and 256 consecutive workgroups run at about the same

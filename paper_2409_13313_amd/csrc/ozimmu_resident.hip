@@ -28,14 +28,15 @@
 // k = 9 and 10, 1.84 -> 1.75 and 2.16 -> 2.06 ms at 4096^3, 14.5 -> 13.9 ms at 8192^3, k = 9.  One addition per slice pair, whose k (k + 1) / 2 sums
 // leave small tiles only and whose bound is the way of the operands through LDS, gains most: 4096^3, k = 9, 32 x 64 instead of 32 x 32,
 // 2.54 -> 2.25 ms, and k = 11 to 13, which had no resident tile at all, 5.95, 7.09, 8.32 -> 3.39, 3.77, 4.20 ms.
-// No gain: 96 x 96 and 64 x 160 at k = 7 and 8 (0 to 0.5 % at 8192^3 and 16384^3, 3 to 5 % slower where 4096 is no multiple of them).
+// No gain in k_extended's order: 96 x 96 and 64 x 160 at k = 7 and 8 (0 to 0.5 % at 8192^3 and 16384^3, 3 to 5 % slower where 4096 is no multiple of them).
 //
 // k_held is k_extended with another order of a step (HeldPlan): the lower slices of A stay in registers while those of B pass by, which takes
 // fewer fragments at a time and leaves room for the sums of the next larger tile: 128 x 128 at k = 6, 96 x 128 at 7 and 8, 96 x 96 at 9 and
 // 10, 64 x 128 at 11, 64 x 96 at 13, 14 and for the 16 chunks of k = 12 at r = 8.  What that saves is bytes, out of L2 and beyond (all of
-// them compiled out, a working copy, 16384^3, k = 8, is 16 % of the time, half of the LDS fetches 0.5 %): 16384^3, k = 8, 64 x 128
-// 91.5 ms, 96 x 128 88.5; k = 12 189.9 and 186.5; 8192^3, k = 6, 96 x 128 7.00, 128 x 128 6.66; 6144^3, k = 11, 8.70 and 8.12;
-// 1537 x 2051 x 1283, k = 9, one round of 96 x 96 instead of four of 32 x 32, 161 and 150 us.  Two to four barriers a step,
+// them compiled out, a working copy, 16384^3, k = 8, is 16 % of the time, half of the LDS fetches 0.5 %).  Whole calls, the two in turn: 8192^3,
+// k = 6, 96 x 128 7.04 ms, 128 x 128 6.70; k = 11, 64 x 96 20.8 and 64 x 128 19.5; 12288^3, k = 8, 64 x 128 38.0, 96 x 128 36.9; 6144^3 4.90
+// and 4.76.  At 16384^3, where the power budget sets the clock, little is left of it: k = 8 90.2 and 88.7, k = 12 191.0 and 187.2, where runs differ by 1 %.
+// 1537 x 2051 x 1283, k = 9, one round of 96 x 96 instead of four of 32 x 32, 157 and 149 us.  Two to four barriers a step,
 // copies spread wider, MFMAs with A held: the same within 0.5 %.
 //
 // Fragments: L = (k + 1) / 2 low slices of both operands stay in registers for a step, the high ones pass through two

@@ -1700,8 +1700,9 @@ hipError_t launch_split(const SplitIn* ops, int count, int k, int beta, int spli
     const bool mask = split_mode != 0;
     // The first four workgroups of an operand run on XCD 0 (see k_split_both), and so does the product's only tile, which finds slices left in that L2
     // near by.  Written through it waits for them: 11 x 1176 x 9, k = 5, 11.9 and 13.4 us a call, 5 x 772 x 7, k = 11, 17.2 and 19.4, 3 x
-    // 2304 x 6, k = 3, 14.1 and 16.6; also where four more hold rows, 24 x 1722 x 16, k = 3, 11.9 and 13.4 (of 116 random calls of so few vectors 56
-    // were slower written through by more than 2 %, up to 15 %, two faster; more columns, 4 x 640 x 32, k = 12, 18.0 and 17.7).
+    // 2304 x 6, k = 3, 14.1 and 16.6 (300 random calls of up to 16 x 16 outputs: 6.5 % slower on average, up to 22 %).  Also where the next four hold
+    // rows (300 calls of 17 to 32 x 1 to 16: 0.8 % on average, up to 25 %, eight gain, 2.3 % at most); not with more columns (4 x 640 x 32,
+    // k = 12, 18.0 and 17.7).
     auto beside_the_tile = [](const SplitOp& o) { return o.rows <= (o.by_col ? 4 : 8) * o.per; };
     const bool near = used == 2 && dbr == 16 && beside_the_tile(op[0]) && beside_the_tile(op[1]);
     if (near && columns)

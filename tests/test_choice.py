@@ -67,7 +67,10 @@ def test_vectors_are_split_along_the_inner_dimension_where_that_is_faster(oz, m,
     (8532, 421, 5453, 8, 612.9, 531.7), (7595, 240, 357, 8, 43.8, 38.3), (1701, 159, 3116, 11, 80.3, 71.5), (1081, 70, 5947, 10, 67.0, 59.7),
     (1409, 65, 805, 13, 26.4, 22.9), (215, 203, 5345, 13, 40.2, 34.8), (780, 6178, 1346, 14, 579.3, 518.8), (2446, 6611, 444, 14, 646.4, 581.1),
     (2017, 193, 824, 11, 34.3, 39.5), (1387, 59, 1565, 9, 22.5, 26.4), (1621, 114, 4056, 9, 56.9, 64.9), (804, 386, 5432, 13, 130.8, 150.5),
-    (2105, 2105, 2105, 13, 508.5, 581.1), (759, 8816, 1462, 11, 554.4, 653.0), (2788, 16786, 2762, 5, 1499.2, 1746.3), (2000, 600, 2000, 6, 52.6, 51.2), (1537, 2051, 1283, 9, 149.0, 157.3), (1424, 1424, 1424, 9, 107.7, 113.2), (6981, 1090, 895, 7, 160.5, 181.0)])
+    (2105, 2105, 2105, 13, 508.5, 581.1), (759, 8816, 1462, 11, 554.4, 653.0), (2788, 16786, 2762, 5, 1499.2, 1746.3), (2000, 600, 2000, 6, 52.6, 51.2), (1537, 2051, 1283, 9, 149.0, 157.3), (1424, 1424, 1424, 9, 107.7, 113.2), (6981, 1090, 895, 7, 160.5, 181.0),
+    (4708, 5, 409, 10, 26.0, 24.0), (3136, 1631, 2097, 10, 436.8, 415.5), (2462, 7133, 2808, 6, 828.7, 795.7), (2541, 712, 2488, 10, 205.6, 197.6),
+    (801, 2368, 10172, 7, 493.6, 480.8), (8192, 8192, 8192, 6, 6701.7, 7039.9), (8192, 8192, 8192, 8, 11580.0, 11420.0),
+    (6144, 6144, 6144, 11, 8316.0, 8774.0), (6144, 6144, 6144, 8, 4761.0, 4897.0), (16384, 16384, 16384, 9, 114243.0, 111196.0)])
 def test_slices_of_a_are_held_where_that_is_faster(oz, m, n, p, k, held, other):
     assert (oz.choose(m, n, p, k).tile == oz.HELD_TILE) == (held < other)
 
