@@ -116,7 +116,21 @@ def check_body(body: str, k: int, r: int, ta: int, tb: int, in_place: bool, what
     _require(m0 >= k, what, "copies' own set-ups of M0", m0)
 
 
-def check_kernels(text: str, k: int) -> dict:
+def check_lanes(body: str, ta: int, tb: int, what: tuple) -> None:
+    """k_held's pieces that four waves share: half of the lanes are off for one copy, and on again in the same asm statement."""
+    halves = 0
+    for statement in re.findall(r"#ASMSTART(.*?)#ASMEND", body, re.S):
+        code = [c for c in (line.split(";")[0].strip() for line in statement.split("\n")) if c]
+        off = [i for i, c in enumerate(code) if re.match(r"s_\w+ exec\b", c)]
+        if not off:
+            continue
+        _require(len(off) == 2 and off[1] == off[0] + 2 and code[off[0]].startswith("s_mov_b64 exec, s[")
+                 and code[off[0] + 1].startswith("global_load_lds_dwordx4") and code[off[1]] == "s_mov_b64 exec, -1", what, code)
+        halves += 1
+    _require((halves > 0) == (ta % 2 == 1 or tb % 2 == 1), what, "copies with half of the lanes", halves)
+
+
+def check_resident(text: str, k: int) -> dict:
     """Looks at every kernel in the assembly of ozimmu_resident.hip compiled for k slices; raises Wrong.  Returns how many there are
     of each kind."""
     seen = dict.fromkeys(("k_resident", "k_cut", "k_extended", "k_held", "k_per_slice"), 0)
@@ -131,14 +145,11 @@ def check_kernels(text: str, k: int) -> dict:
             in_place = kind in ("k_extended", "k_held")
         _require(kk == k, what)
         check_body(m.group(4), k, r, ta, tb, bool(in_place), what)
+        if kind == "k_held":
+            check_lanes(m.group(4), ta, tb, what)
         at = text.index(".name:           " + name)
         about = text[text.rindex("- .agpr_count", 0, at):text.find("- .agpr_count", at)]
         for key in ("private_segment_fixed_size", "vgpr_spill_count", "sgpr_spill_count"):
             _require(re.search(r"\.%s:\s+(\d+)" % key, about).group(1) == "0", what, key)
         seen[kind] += 1
     return seen
-
-
-def check_resident(text: str, k: int) -> dict:
-    """check_kernels, which looks at k_held too, without its count."""
-    return {kind: count for kind, count in check_kernels(text, k).items() if kind != "k_held"}
