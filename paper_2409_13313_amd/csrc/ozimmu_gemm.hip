@@ -1403,7 +1403,7 @@ hipError_t setup_gemm_kernels()
     for (int k = ozr::MIN_K; k <= ozr::MAX_K; ++k)
         for (int r : {1, 2, 4, 8, k}) {
             if (r > k) continue;
-            for (int variant = 0; variant <= ozr::HELD; variant = variant + 1 == ozr::NUM_VARIANTS ? ozr::HELD : variant + 1) {
+            for (int variant = 0; ozr::is_variant(variant); variant = ozr::next_variant(variant)) {
                 e = launch_resident(ra, k, r, variant, nullptr);
                 if (e != hipSuccess) return e;
             }

@@ -32,6 +32,8 @@ constexpr int ACC_TILES = 64;    // tiles of 16 x 16 that the accumulation regis
 constexpr int NUM_VARIANTS = 7, EXTENDED = 6;  // the last one is k_extended, the others k_resident
 constexpr int HELD = 16;         // k_held, beside them
 constexpr bool is_variant(int v) { return (v >= 0 && v < NUM_VARIANTS) || v == HELD; }
+// for (int v = 0; is_variant(v); v = next_variant(v)): all of them, k_held last
+constexpr int next_variant(int v) { return v + 1 == NUM_VARIANTS ? HELD : v + 1; }
 
 // variant 0: the largest tile whose chunk sums fit the 256 accumulation registers; the others: smaller ones for outputs that
 // the large one would not spread evenly over the chip; EXTENDED: the next larger tile whose chunk sums fit the ordinary registers
@@ -98,10 +100,13 @@ constexpr Config config_for(int k, int r, int variant)
 }
 // Tiles for slices with one scale each (r = 1; k_per_slice): k_extended's only where there is no other.
 constexpr bool per_slice_tile(int k, int variant) { return variant < EXTENDED || (variant == EXTENDED && config(k, 1, 0).ta == 0); }
-// grid size; 32-bit operand offsets
+// grid size; 32-bit operand offsets: a tile's rows lie in two row blocks at most, and an offset from the first one's begin is less than both
+// of them (k_held; the others' are from a copy's own rows)
+constexpr int64_t MAX_STEPS = ((int64_t)1 << 17) - 1;
+static_assert(2 * (MAX_STEPS + 1) * ozl::TILE_BYTES + 2 * ozl::ROWPAD <= ((int64_t)1 << 32) && (MAX_STEPS + 1) % (ozl::KPAD / ozl::TILE_K) == 0, "");
 constexpr bool in_range(int64_t m, int64_t n, int64_t p, int rows, int cols)
 {
-    return ((m + rows - 1) / rows) * ((p + cols - 1) / cols) < ((int64_t)1 << 23) && (n + 63) / 64 < ((int64_t)1 << 17);
+    return ((m + rows - 1) / rows) * ((p + cols - 1) / cols) < ((int64_t)1 << 23) && (n + 63) / 64 <= MAX_STEPS;
 }
 
 // Rows of the output that do not begin on 64 bytes leave pieces of lines at every tile's edge.  Streamed past L2 (non-temporal

@@ -463,8 +463,8 @@ struct Held {
     __device__ __attribute__((always_inline)) inline void begin(const ozk::ResidentArgs& a, uint32_t lds_base, uint32_t row0, uint32_t col0,
                                                                 int wave, int lane)
     {
-        // (r >= 2: at most 65536 inner positions, a row block 16 MiB)
-        static_assert(P::r > 1, "");
+        // (at most MAX_STEPS steps: a row block is 2 GiB at most, and a tile has rows in two)
+        static_assert(32 * (TA > TB ? TA : TB) <= TILE_R, "");
         const uint32_t rowblk = (uint32_t)rowblock_bytes(a.KT);
 #pragma unroll
         for (int o = 0; o < 2; ++o) {
