@@ -316,14 +316,19 @@ enum { OZIMMU_WAY_SMALL = 0,          /* the whole call in one launch */
 enum { OZIMMU_SPLIT_WAY_NONE = 0,     /* part of the one launch */
        OZIMMU_SPLIT_WAY_WHOLE = 1,    /* workgroups own whole vectors */
        OZIMMU_SPLIT_WAY_CUT = 2,      /* two launches along the inner dimension */
-       OZIMMU_SPLIT_WAY_CUT_COLUMNS = 4, /* columns in two launches along the inner dimension, rows whole */
-       OZIMMU_SPLIT_WAY_PASSES = 3 }; /* one scale per slice of vectors too long for registers: a pass per slice */
+       OZIMMU_SPLIT_WAY_PASSES = 3,   /* one scale per slice of vectors too long for registers: a pass per slice */
+       OZIMMU_SPLIT_WAY_CUT_COLUMNS = 4 }; /* columns in two launches along the inner dimension, rows whole */
 typedef struct {
-    int way, tile, parts, split_way;
+    int way, tile, parts, split_way;  /* tile: 0 .. OZIMMU_RESIDENT_TILES - 1 or OZIMMU_HELD_TILE; -1 where way is not OZIMMU_WAY_RESIDENT */
     int merge_rows;                   /* rows of D that begin inside a memory line are merged in L2 */
 } ozimmu_choice;
 int ozimmu_choose(int64_t m, int64_t n, int64_t p, int k, int split_mode, int accumulate_mode, size_t workspace_bytes,
                   int num_cu, ozimmu_choice *out);
+
+/* How a call with one scale per row and column splits op(A) and op(B) (OZIMMU_SPLIT_WAY_*, or a negative status) in a workspace of that
+ * many bytes: ozimmu_choose's split_way for operands that may be transposed (see ozimmu_gemm_ex).  Host, pure; sizes of at least 1.
+ * Debug / test helper. */
+int ozimmu_split_way(int transA, int transB, int64_t m, int64_t n, int64_t p, int k, size_t workspace_bytes);
 
 /* Unpack a packed slice stack into the canonical order out[s][row][l]
  * (int8, k x rows x n, dense): for A that is A''_s[i][l]; for B it is

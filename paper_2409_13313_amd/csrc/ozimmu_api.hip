@@ -384,7 +384,7 @@ Way choose_way(int64_t m, int64_t n, int64_t p, int k, int r_eff, bool per_slice
             other_us *= 1.0 + (slower < 0.08 ? slower : 0.08) * log2((double)n / 16384.0);
         }
         int variant = -1, parts = 1;
-        for (int v = 0; v <= ozr::HELD; v = v + 1 == ozr::NUM_VARIANTS ? ozr::HELD : v + 1) {
+        for (int v = 0; ozr::is_variant(v); v = ozr::next_variant(v)) {
             if (per_slice && !ozr::per_slice_tile(k, v)) continue;
             const double us = ozr::estimate_us(k, r_eff, v, m, n, p, num_cu);
             if (us < 0.0) continue;
@@ -1023,6 +1023,19 @@ int ozimmu_dgemm_tile(int64_t m, int64_t n, int64_t p, const double* A, int64_t 
                       nullptr, tile, parts);
 }
 
+int ozimmu_split_way(int transA, int transB, int64_t m, int64_t n, int64_t p, int k, size_t workspace_bytes)
+{
+    if (m < 1 || n < 1 || p < 1 || m > MAX_OUTER || p > MAX_OUTER || n > MAX_INNER) return OZIMMU_ERR_DIM;
+    if (k < 1 || k > OZIMMU_MAX_SLICES) return OZIMMU_ERR_SLICES;
+    const ozk::SplitIn ops[2] = {{nullptr, n, m, n, transA != 0, 0, nullptr, nullptr}, {nullptr, p, p, n, transB == 0, 0, nullptr, nullptr}};
+    const int64_t capacity = block_capacity(m, n, p, k, workspace_bytes);
+    switch (ozk::split_cut(ops, 2, k, (size_t)(capacity * BLOCK_BYTES), short_product(m, n, p, k))) {
+        case 1: return OZIMMU_SPLIT_WAY_CUT;
+        case 2: return OZIMMU_SPLIT_WAY_CUT_COLUMNS;
+        default: return OZIMMU_SPLIT_WAY_WHOLE;
+    }
+}
+
 int ozimmu_choose(int64_t m, int64_t n, int64_t p, int k, int split_mode, int accumulate_mode, size_t workspace_bytes, int num_cu,
                   ozimmu_choice* out)
 {
@@ -1044,9 +1057,7 @@ int ozimmu_choose(int64_t m, int64_t n, int64_t p, int k, int split_mode, int ac
     if (per_slice) {
         out->split_way = n <= ozk::PER_SLICE_MAX_INNER ? OZIMMU_SPLIT_WAY_WHOLE : OZIMMU_SPLIT_WAY_PASSES;
     } else {
-        const ozk::SplitIn ops[2] = {{nullptr, n, m, n, 0, 0, nullptr, nullptr}, {nullptr, p, p, n, 1, 0, nullptr, nullptr}};
-        const int cut = ozk::split_cut(ops, 2, k, (size_t)(capacity * BLOCK_BYTES), short_product(m, n, p, k));
-        if (cut) out->split_way = cut == 1 ? OZIMMU_SPLIT_WAY_CUT : OZIMMU_SPLIT_WAY_CUT_COLUMNS;
+        out->split_way = ozimmu_split_way(0, 0, m, n, p, k, workspace_bytes);
     }
     const Way way = choose_way(m, n, p, k, (int)(r < k ? r : k), per_slice, 0, capacity, num_cu);
     if (way.kind == Way::RESIDENT) {

@@ -92,6 +92,8 @@ class Choice(ctypes.Structure):
 
 _lib.ozimmu_choose.argtypes = [_i64, _i64, _i64, _int, _int, _int, _sz, _int, ctypes.POINTER(Choice)]
 _lib.ozimmu_choose.restype = _int
+_lib.ozimmu_split_way.argtypes = [_int, _int, _i64, _i64, _i64, _int, _sz]
+_lib.ozimmu_split_way.restype = _int
 _lib.ozimmu_export_slices.argtypes = [_i64, _i64, _int, _vp, _vp, _vp]
 _lib.ozimmu_export_slices.restype = _int
 
@@ -101,7 +103,7 @@ EXPORTS = ["ozimmu_status_string", "ozimmu_params", "ozimmu_num_chunks", "ozimmu
            "ozimmu_accumulate", "ozimmu_gemm_group_accumulate", "ozimmu_export_slices",
            "ozimmu_workspace_bytes_variant", "ozimmu_remainder_bytes", "ozimmu_split_A_per_slice",
            "ozimmu_split_B_per_slice", "ozimmu_init", "ozimmu_dgemm_static", "ozimmu_workspace_bytes_min",
-           "ozimmu_resident_tile", "ozimmu_dgemm_resident", "ozimmu_dgemm_tile", "ozimmu_choose"]
+           "ozimmu_resident_tile", "ozimmu_dgemm_resident", "ozimmu_dgemm_tile", "ozimmu_choose", "ozimmu_split_way"]
 
 
 SPLIT_MODES = {"rn": 0, "bitmask": 1, "per_slice": 2}
@@ -320,6 +322,14 @@ def choose(m: int, n: int, p: int, k: int, split: str = "rn", accumulate: str = 
     out = Choice()
     _check(_lib.ozimmu_choose(m, n, p, k, SPLIT_MODES[split], ACCUMULATE_MODES[accumulate], workspace_bytes, num_cu, ctypes.byref(out)))
     return out
+
+
+def split_way(transA: bool, transB: bool, m: int, n: int, p: int, k: int, workspace_bytes: int) -> str:
+    """How gemm_ex splits its operands in a workspace of that many bytes, by name (host; debug / test helper)."""
+    way = _lib.ozimmu_split_way(int(transA), int(transB), m, n, p, k, workspace_bytes)
+    if way < 0:
+        raise OzimmuError(way)
+    return SPLIT_WAYS[way]
 
 
 def gemm_ex(transA: bool, transB: bool, alpha: float, A: torch.Tensor, B: torch.Tensor, beta: float,

@@ -111,6 +111,11 @@ int main()
                             const int accumulate = mode == 2 ? OZIMMU_ACCUM_PER_PAIR : OZIMMU_ACCUM_GROUPED;
                             const int st = ozimmu_choose(m, n, p, k, mode, accumulate, bytes, 256, &choice);
                             EXPECT(st, m && n && p ? OZIMMU_OK : OZIMMU_ERR_DIM);
+                            for (int trans = 0; trans < 4; ++trans) {
+                                const int split = ozimmu_split_way(trans & 1, trans >> 1, m, n, p, k, bytes);
+                                EXPECT(m && n && p ? split >= OZIMMU_SPLIT_WAY_WHOLE : split == OZIMMU_ERR_DIM, 1);
+                                if (trans == 0 && st == OZIMMU_OK && mode < 2 && choice.way != OZIMMU_WAY_SMALL) EXPECT(split, choice.split_way);
+                            }
                             if (st != OZIMMU_OK) continue;
                             EXPECT(choice.way == OZIMMU_WAY_RESIDENT ? choice.tile >= 0 && choice.parts >= 1 : choice.tile == -1, 1);
                             EXPECT(choice.parts > 1 && (mode == 2 || 2 * choice.parts > (n + 63) / 64), 0);
@@ -118,6 +123,7 @@ int main()
     EXPECT(ozimmu_choose(4, 4, 4, 8, 0, 0, 0, 256, nullptr), OZIMMU_ERR_NULL);
     EXPECT(ozimmu_choose(4, 4, 4, 8, 3, 0, 0, 256, &choice), OZIMMU_ERR_SLICES);
     EXPECT(ozimmu_choose(4, 4, 4, 8, 0, 0, 0, 0, &choice), OZIMMU_ERR_SLICES);
+    EXPECT(ozimmu_split_way(0, 0, 4, 4, 4, 0, 0), OZIMMU_ERR_SLICES);
     EXPECT(ozimmu_gemm_ex(0, 0, 4, 4, 4, 1.0, fd, 3, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
     EXPECT(ozimmu_gemm_ex(1, 0, 5, 4, 4, 1.0, fd, 4, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);
     EXPECT(ozimmu_gemm_ex(0, 1, 4, 5, 4, 1.0, fd, 5, fd, 4, 0.0, fd, 4, 8, fake, 1 << 30, nullptr), OZIMMU_ERR_DIM);

@@ -54,6 +54,7 @@ def test_two_operands_of_columns_and_a_graph(oz):
     oz.gemm_ex(False, True, 1.0, dA, dB.t().contiguous(), 0.0, ref, k)
     C = torch.zeros((m, p), dtype=torch.float64, device="cuda")
     ws = torch.empty(oz.workspace_bytes(m, n, p, k) + (64 << 20), dtype=torch.uint8, device="cuda")
+    assert oz.split_way(True, False, m, n, p, k, ws.numel()) == "cut_columns" and oz.split_way(False, True, m, n, p, k, ws.numel()) != "cut_columns"
     oz.gemm_ex(True, False, 1.0, At, dB, 0.0, C, k, workspace=ws)
     assert torch.equal(C, ref)
     check_corners(C, A, B, k, "rn")
