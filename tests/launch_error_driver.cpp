@@ -9,6 +9,9 @@ extern "C" hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, h
 {
     return last_error = hipErrorLaunchOutOfResources;
 }
+// (what a launch in triple brackets goes through first; without a GPU the runtime's own fail before they come to it)
+extern "C" hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+extern "C" hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
 extern "C" hipError_t hipGetLastError(void)
 {
     const hipError_t e = last_error;
@@ -43,6 +46,22 @@ int main()
     a.parts = 1;
     a.per_slice = 1;
     expect("launch_resident, one scale per slice", ozk::launch_resident(a, 5, 1, 5, nullptr));
+    // the split: whole vectors, the same of a few, both operands in two launches, columns cut beside rows and columns alone (several launches)
+    const struct { int64_t m, n, p; int a_by_col, room, way; } splits[] = {{300, 600, 300, 0, 0, 0}, {4, 600, 4, 0, 0, 0},
+                                                                           {47, 11948, 48, 0, 1, 1}, {523, 31111, 815, 0, 0, 2}, {256, 40001, 700, 1, 0, 2}};
+    for (const auto& s : splits)
+        for (int mode = 0; mode < 2; ++mode) {
+            ozk::SplitIn ops[2] = {};                   // (nothing is dereferenced: the launches fail)
+            ops[0].rows = s.m, ops[0].ld = s.a_by_col ? s.m : s.n, ops[0].by_col = s.a_by_col;
+            ops[1].rows = ops[1].ld = s.p, ops[1].by_col = 1;
+            ops[0].n = ops[1].n = s.n;
+            static char room[1 << 20];
+            if (ozk::split_cut(ops, 2, 8, s.room ? sizeof(room) : 0, s.room != 0) != s.way) {
+                std::printf("split of %d x %d x %d: another way\n", (int)s.m, (int)s.n, (int)s.p);
+                ++failures;
+            }
+            expect("launch_split", ozk::launch_split(ops, 2, 8, 7, mode, nullptr, nullptr, 0, s.room ? room : nullptr, s.room ? sizeof(room) : 0));
+        }
     if (!failures) std::printf("launch error driver ok\n");
     return failures != 0;
 }
