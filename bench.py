@@ -24,7 +24,7 @@ PEAK_HBM_GBS = 8000.0
 # Bytes per launch of the GEMM kernel at the L2 / fabric boundary, from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE
 # runs of this script, each scaled by the same counter on a plain copy (profiles/gemm_16384_k8_traffic.md).
 # Counters cannot be read from inside this process: the figure exists for the shapes profiled, else null.
-MEASURED_TRAFFIC_BYTES = {(16384, 16384, 16384, 8): 143.4e9 + 2.15e9}
+MEASURED_TRAFFIC_BYTES = {(16384, 16384, 16384, 8): {"k_held": 143.95e9 + 2.15e9, "k_resident": 143.4e9 + 2.15e9}}
 
 
 def log(*a):
@@ -149,7 +149,19 @@ def main() -> int:
     flops = 2.0 * m * n * p
     value = flops / (wall_ms * 1e-3) / 1e12
     int_ops = flops * pairs
-    resident = 3 <= k <= 16 and n <= 2 ** 15   # (longer inner dimensions have more chunks than fit the registers)
+    # the kernel that the library runs the products with, by its own choice
+    choice = ozimmu.choose(m, n, p, k)
+    resident = ozimmu.WAYS[choice.way] == "resident"
+    if resident:
+        kernel = ("k_cut" if choice.parts > 1 else "k_held" if choice.tile == ozimmu.HELD_TILE else
+                  "k_extended" if choice.tile == ozimmu.RESIDENT_TILES - 1 else "k_resident")
+        rows, cols = ozimmu.resident_tile(n, k, "grouped", choice.tile)
+        what = (f"{kernel}, {rows} x {cols} outputs a workgroup (INT8 MFMA kernel: all chunk sums of a tile grow in registers while "
+                "the inner dimension is walked once, then are added up in FP64; one launch per step)")
+    else:
+        kernel = "k_small" if ozimmu.WAYS[choice.way] == "small" else "k_gemm"
+        what = f"{kernel} (way of the schedule: {ozimmu.WAYS[choice.way]})"
+    traffic = MEASURED_TRAFFIC_BYTES.get((m, n, p, k), {}).get(kernel)
     gemm_tops = int_ops / (gemm_ms * 1e-3) / 1e12
     split_bytes = 8.0 * (m * n + n * p) + float(k) * (m * n + n * p)
     log(f"k={k}: {wall_ms:.2f} ms/step  -> {value:.1f} TFLOP/s effective; split {split_ms:.2f} ms "
@@ -175,8 +187,7 @@ def main() -> int:
         "phases_ms": {"split_A_and_B": round(split_ms, 4), "chunk_gemm_with_fused_accumulation": round(gemm_ms, 4)},
         "int8_mfma_utilisation_pct": round(100.0 * gemm_tops / PEAK_INT8_TOPS, 2),
         "roofline": {
-            "kernel": "k_resident (INT8 MFMA kernel: all chunk sums of a tile grow in registers while the inner dimension is "
-                      "walked once, then are added up in FP64; one launch per step; shapes of very many chunks: k_gemm<3,4>)",
+            "kernel": what,
             "bound": "mfma",
             "achieved": round(gemm_tops, 2),
             "peak": PEAK_INT8_TOPS,
@@ -185,10 +196,10 @@ def main() -> int:
             "launches_per_step": 1,
             "avg_launch_ms": round(gemm_ms, 4),
             "ops_per_launch": int_ops,
-            "traffic": MEASURED_TRAFFIC_BYTES.get((m, n, p, k)),
+            "traffic": traffic,
             "traffic_note": ("FETCH_SIZE + WRITE_SIZE of one launch, rocprofv3 --pmc, copy-calibrated "
-                             "(profiles/gemm_16384_k8_traffic.md)" if (m, n, p, k) in MEASURED_TRAFFIC_BYTES else
-                             "null: no rocprofv3 --pmc run of this shape is on file (hardware counters cannot be "
+                             "(profiles/gemm_16384_k8_traffic.md)" if traffic is not None else
+                             "null: no rocprofv3 --pmc run of this shape and kernel is on file (hardware counters cannot be "
                              "read from inside the benchmark process)"),
             # every slice read once where all chunks of a tile stay in registers, else anew for every slice pair
             "algorithmic_bytes": float(k if resident else pairs) * (m * n + n * p) + 8.0 * m * p,
