@@ -653,8 +653,9 @@ inline bool overlap(const double* x, int64_t rows, int64_t cols, int64_t ldx, co
     return x0 < y0 + 8 * (uintptr_t)ysize && y0 < x0 + 8 * (uintptr_t)((rows - 1) * ldx + cols);
 }
 // One round of its workgroups, two to a compute unit where LDS holds their slices (us a call in a graph, two launches and one, k = 8:
-// 64^3 9.6 and 5.6, 128^3 10.1 and 6.5, 256^3 11.5 and 8.7, 320 x 256 x 320, 400 workgroups, 12.2 and 11.2, 400 x 256 x 400, 625, 12.4 and
-// 16.1; 512 x 64 x 512, 1024, 10.1 and 10.7; k = 14: 256^3 16.3 and 12.2).
+// 64^3 8.9 and 5.2, 128^3 9.6 and 5.7, 256^3 10.6 and 7.2, 320 x 256 x 320, 400 workgroups, 10.7 and 9.3, 352 x 256 x 352, 484, 10.7 and 9.6;
+// k = 14: 256^3 14.2 and 9.4; at 70 sizes of up to 420 x 256 x 700 never slower in one.  Beyond, before either way was shortened by about a fifth: 400 x 256 x
+// 400, 625, 12.4 and 16.1; 512 x 64 x 512, 1024, 10.1 and 10.7).
 inline bool small_sizes(int64_t m, int64_t n, int64_t p, int k, int64_t r, int num_cu)
 {
     if (n > ozk::SMALL_MAX_INNER || k < ozk::SMALL_MIN_K || k > ozk::SMALL_MAX_K || r < k) return false;

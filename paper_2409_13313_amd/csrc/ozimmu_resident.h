@@ -38,7 +38,7 @@ constexpr int next_variant(int v) { return v + 1 == NUM_VARIANTS ? HELD : v + 1;
 // variant 0: the largest tile whose chunk sums fit the 256 accumulation registers; the others: smaller ones for outputs that
 // the large one would not spread evenly over the chip; EXTENDED: the next larger tile whose chunk sums fit the ordinary registers
 // too, beside fragments (those of the low slices and of two high ones) and about 24 more.  Shapes in the order of what they move per MFMA;
-// others that fit (96 x 96, 64 x 160, 32 x 128) were no faster.
+// others that fit (96 x 96, 64 x 160, 32 x 128) were no faster in k_extended.
 constexpr Config config(int k, int r, int variant)
 {
     const int w = num_chunks(k, r);

@@ -32,8 +32,9 @@
 //
 // k_held is k_extended with another order of a step (HeldPlan): the lower slices of A stay in registers while those of B pass by, which takes
 // fewer fragments at a time and leaves room for the sums of the next larger tile: 128 x 128 at k = 6, 96 x 128 at 7 and 8, 96 x 96 at 9 and
-// 10, 64 x 128 at 11, 64 x 96 at 13, 14 and for the 16 chunks of k = 12 at r = 8.  What that saves is bytes, out of L2 and beyond (all of
-// them compiled out, a working copy, 16384^3, k = 8, is 16 % of the time, half of the LDS fetches 0.5 %).  Whole calls, the two in turn: 8192^3,
+// 10, 64 x 128 at 11, 64 x 96 at 13, 14 and for the 16 chunks of k = 12 at r = 8.  What that saves is bytes that the compute units bring in (all of
+// them compiled out, a working copy, 16384^3, k = 8, is 16 % of the time, half of the LDS fetches 0.5 %).  From beyond L2, the other tile and k_held's: 8192^3,
+// k = 6, 12.4 and 9.7 GB, k = 11 38.7 and 28.5, 12288^3, k = 8, 58 and 51, 16384^3, k = 12, 530 to 590 and 374, but k = 8 138 to 143 and 143.  Whole calls, the two in turn: 8192^3,
 // k = 6, 96 x 128 7.04 ms, 128 x 128 6.70; k = 11, 64 x 96 20.8 and 64 x 128 19.5; 12288^3, k = 8, 64 x 128 38.0, 96 x 128 36.9; 6144^3 4.90
 // and 4.76.  At 16384^3, where the power budget sets the clock, little is left of it: k = 8 90.2 and 88.7, k = 12 191.0 and 187.2, where runs differ by 1 %.
 // 1537 x 2051 x 1283, k = 9, one round of 96 x 96 instead of four of 32 x 32, 157 and 149 us.  Two to four barriers a step,

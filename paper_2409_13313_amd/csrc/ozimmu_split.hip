@@ -1217,7 +1217,7 @@ __global__ __launch_bounds__(256) void k_split_B_ps(int64_t n, int64_t p, const 
 // swizzle, signed digits without offset), each wave multiplies one inner step of 64 into its k chunk sums (r >= k there: a chunk is a
 // group), and the sums of the waves meet in LDS, where each thread adds up one element.  Every vector is split again
 // by all the tiles in its row or column; what it saves is what such a call consists of: a launch and the wait between two
-// dependent ones (k = 8: 64^3 9.6 us for two launches, 5.2 for this one, 256^3 11.5 and 7.1).  What bounds it is one latency after the other:
+// dependent ones (k = 8, in a graph: 64^3 8.9 us for two launches, 5.2 for this one, 256^3 10.6 and 7.2).  What bounds it is one latency after the other:
 // operands, maxima, digits (a thread makes those of 32 elements), fragments, sums.
 // ---------------------------------------------------------------------------
 template <int K>
