@@ -17,7 +17,6 @@ SOURCES = ["ozimmu_api.hip", "ozimmu_split.hip", "ozimmu_gemm.hip"]
 # ozimmu_resident.hip holds kernels specialised for a slice count: one compilation per count, all of them linked into
 # the object of the chunk GEMM (whoever links that object gets every way to run the schedule)
 RESIDENT_KS = range(3, 17)
-HELD_KS = range(5, 15)          # those with tiles that hold slices of A
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
@@ -57,9 +56,8 @@ def build(verbose: bool = False) -> str:
                 print(out)
             if defs:
                 text, = (open(f).read() for f in glob.glob(os.path.join(tmp, "*gfx950*.s")))
-                k = int(defs[0].split("=")[1])
-                seen = codegen.check_resident(text, k)
-                if not all(seen[kind] for kind in ("k_resident", "k_cut", *(("k_held",) if k in HELD_KS else ()))):
+                seen = codegen.check_resident(text, int(defs[0].split("=")[1]))
+                if not all(seen[kind] for kind in ("k_resident", "k_cut")):
                     raise RuntimeError(f"{defs[0]}: kernels missing from the assembly: {seen}")
             shutil.copyfile(made, obj)
 

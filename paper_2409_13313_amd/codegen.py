@@ -14,6 +14,7 @@ from __future__ import annotations
 import re
 
 MFMA = "v_mfma_i32_16x16x64_i8"
+HELD_KS = range(5, 15)      # slice counts with tiles that hold slices of A (k_held)
 OPERAND_WAIT_STATES = 2     # between a vector instruction that writes a register and a matrix instruction that reads it
 KERNEL = re.compile(r"^(_ZN12_GLOBAL__N_1\d+(k_resident|k_cut|k_extended|k_held|k_per_slice)I((?:L[ib]\d+E)+)EEv\w+):(.*?)^\.Lfunc_end", re.S | re.M)
 
@@ -130,9 +131,9 @@ def check_lanes(body: str, ta: int, tb: int, what: tuple) -> None:
     _require((halves > 0) == (ta % 2 == 1 or tb % 2 == 1), what, "copies with half of the lanes", halves)
 
 
-def check_resident(text: str, k: int) -> dict:
-    """Looks at every kernel in the assembly of ozimmu_resident.hip compiled for k slices; raises Wrong.  Returns how many there are
-    of each kind."""
+def check_kernels(text: str, k: int) -> dict:
+    """Looks at every kernel in the assembly of ozimmu_resident.hip compiled for k slices; raises Wrong, also where a kind that has to be
+    there is missing.  Returns how many there are of each kind."""
     seen = dict.fromkeys(("k_resident", "k_cut", "k_extended", "k_held", "k_per_slice"), 0)
     for m in KERNEL.finditer(text):
         name, kind, args = m.group(1), m.group(2), [int(x) for x in re.findall(r"L[ib](\d+)E", m.group(3))]
@@ -152,4 +153,12 @@ def check_resident(text: str, k: int) -> dict:
         for key in ("private_segment_fixed_size", "vgpr_spill_count", "sgpr_spill_count"):
             _require(re.search(r"\.%s:\s+(\d+)" % key, about).group(1) == "0", what, key)
         seen[kind] += 1
+    # (one that KERNEL no longer matches would be linked without a look)
+    for kind in ("k_resident", "k_cut", *(("k_held",) if k in HELD_KS else ())):
+        _require(seen[kind] > 0, k, "no", kind, "in the assembly")
     return seen
+
+
+def check_resident(text: str, k: int) -> dict:
+    """check_kernels, which looks at k_held too, with the counts of the others."""
+    return {kind: count for kind, count in check_kernels(text, k).items() if kind != "k_held"}

@@ -10,15 +10,14 @@ from paper_2409_13313_amd import build, codegen
 
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
 IN_PLACE = "k_extendedILi12ELi12E"
-HELD = "k_heldILi12E"
 
 
 def test_every_instance(resident_assembly):
-    total = dict.fromkeys(("k_resident", "k_cut", "k_extended", "k_held", "k_per_slice"), 0)
+    total = dict.fromkeys(("k_resident", "k_cut", "k_extended", "k_per_slice"), 0)
     for k, text in resident_assembly.items():
         for kind, count in codegen.check_resident(text, k).items():
             total[kind] += count
-    assert total == {"k_resident": 196, "k_cut": 100, "k_extended": 38, "k_held": 20, "k_per_slice": 26}
+    assert total == {"k_resident": 196, "k_cut": 100, "k_extended": 38, "k_per_slice": 26}
 
 
 def kernel_lines(text, part):
@@ -53,11 +52,6 @@ MISTAKES = {
     "a move between register files": ("k_resident", lambda lines, at: lines.insert(at[4], "\tv_accvgpr_read_b32 v0, a0")),
     "a spill in the loop": ("k_cut", lambda lines, at: lines.insert(at[4], "\tscratch_load_dword v0, off, off")),
     "a wait of the compiler's": ("k_per_slice", lambda lines, at: lines.insert(at[4] - 1, "\ts_waitcnt vmcnt(0)")),
-    "k_held: a chunk sum is copied in the loop": (HELD, lambda lines, at: lines.insert(at[5] + 1, f"\tv_mov_b32_e32 v0, {first(operands(lines[at[3]])[0])}")),
-    "k_held: no wait states": (HELD, lambda lines, at: lines.__setitem__(slice(at[-1], len(lines)), [x.replace("s_nop 15", "s_nop 0") for x in lines[at[-1]:]])),
-    "k_held: a fragment is written right before the instruction that reads it": (HELD, lambda lines, at: lines.insert(at[7] - 1, f"\tv_mov_b32_e32 {first(operands(lines[at[7]])[1])}, v0")),
-    "k_held: another user of M0": (HELD, lambda lines, at: lines.insert(at[0] - 40, "\ts_mov_b32 m0, s0")),
-    "k_held: lanes stay off": (HELD, lambda lines, at: lines.remove(next(x for x in lines if x.strip() == "s_mov_b64 exec, -1"))),
     "another user of M0": ("k_cut", lambda lines, at: lines.insert(at[0] - 40, "\ts_mov_b32 m0, s0")),
 }
 
