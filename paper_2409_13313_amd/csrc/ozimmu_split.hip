@@ -1543,15 +1543,20 @@ static bool cut_pays(const SplitIn* ops, int count, int k, double us, size_t roo
 // 73, 704 x 13298 x 1524, k = 5, 331 and 362, 1045 x 8580 x 8, k = 4, 45.6 and 52.2).  Of 629 shapes of 2000 to 200000 positions for which it is estimated
 // at less than 0.84 `us` this takes 289, of which five are slower by more than 2 %, and is 2.1 % faster on average over all 629 where the best choice
 // would be 2.7 %; with the sixth alone 120 were, by up to 26 %, and the average 1.3 %.
+// From 12 slices on beside 256 rows and more the sixth is enough again: the error of `us` is small beside all that is written (1300 x 8190 x 901,
+// k = 20, whole 2001 us, cut 1971, 488 x 7153 x 1075, k = 17, 653 and 615, 1500 x 9579 x 308, k = 17, 999 and 1024; 28 shapes that the twenty us had
+// left whole, cut: 1.0 % faster on average, one slower by more than 1 %.  With fewer rows 44 x 5720 x 1762, k = 16, 144 and 164, with fewer slices 325 x
+// 7969 x 1875, k = 6, 171 and 191).
 static bool cut_columns_pay(const SplitIn* ops, int count, int k, double us)
 {
     if (count != 2 || ops[0].n < 2048) return false;
     const double n = (double)ops[0].n;
     double cut_us = 12.0;
-    int64_t columns = 0;
+    int64_t columns = 0, rows = 0;
     for (int q = 0; q < 2; ++q) {
         const double vectors = (double)ops[q].rows;
         if (!ops[q].by_col) {
+            rows += ops[q].rows;
             const double all_us = n * vectors * (n > 16384.0 ? 16 + k : 8 + k) / 5.5e6, row_us = n * (16 + k) * (n > 8192.0 ? 2 : 1) / 25e3;
             cut_us += all_us > row_us ? all_us : row_us;
             continue;
@@ -1562,7 +1567,8 @@ static bool cut_columns_pay(const SplitIn* ops, int count, int k, double us)
         columns += ops[q].rows;
     }
     if (columns < 1 || columns > 2400) return false;
-    return columns > 16 && columns <= 300 && ops[0].n >= 8192 ? cut_us < 0.84 * us : cut_us + 20.0 < 0.88 * us;
+    const bool by_a_sixth = (columns > 16 && columns <= 300 && ops[0].n >= 8192) || (k >= 12 && rows >= 256);
+    return by_a_sixth ? cut_us < 0.84 * us : cut_us + 20.0 < 0.88 * us;
 }
 
 static hipError_t launch_cut_columns(const SplitIn* ops, int count, int k, int beta, int split_mode, hipStream_t st, uint32_t* also_zero,

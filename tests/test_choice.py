@@ -82,6 +82,14 @@ def test_slices_of_a_are_held_where_that_is_faster(oz, m, n, p, k, held, other):
     (352, 4636, 1844, 11, "grouped", 182.5, 192.1), (736, 9172, 1735, 7, "grouped", 313.8, 329.5), (701, 16385, 1513, 5, "grouped", 395.8, 421.7),
     (640, 14848, 256, 8, "grouped", 141.0, 128.8), (909, 14947, 85, 4, "grouped", 88.5, 72.3), (523, 31111, 815, 8, "grouped", 736.8, 672.6),
     (1024, 16384, 1024, 8, "grouped", 535.4, 505.2), (448, 57799, 128, 14, "wide", 643.7, 515.3), (33, 56249, 2084, 9, "grouped", 1141.5, 980.5),
+    (1300, 8190, 901, 20, "grouped", 2001.4, 1971.4), (488, 7153, 1075, 17, "grouped", 652.8, 615.1), (44, 5720, 1762, 16, "grouped", 144.4, 164.0), (325, 7969, 1875, 6, "grouped", 171.4, 191.1),
     (28, 12427, 2068, 14, "grouped", 338.2, 292.4), (57, 156679, 812, 14, "grouped", 1863.8, 1582.4), (232, 56640, 1927, 9, "grouped", 1567.2, 1554.4)])
 def test_columns_are_cut_beside_rows_where_that_is_faster(oz, m, n, p, k, accumulate, whole, cut):
     assert (oz.SPLIT_WAYS[oz.choose(m, n, p, k, "rn", accumulate).split_way] == "cut_columns") == (cut < whole)
+
+
+def test_two_operands_of_columns_are_cut_beside_each_other(oz):
+    # (what the GPU test of that kernel calls, in its workspace; with A by rows and B transposed there is nothing to cut)
+    m, n, p, k = 256, 40001, 700, 8
+    room = oz.workspace_bytes(m, n, p, k) + (64 << 20)
+    assert oz.split_way(True, False, m, n, p, k, room) == "cut_columns" and oz.split_way(False, True, m, n, p, k, room) != "cut_columns"
